@@ -301,7 +301,7 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     }
     if (gemm_glu_supported(dt, M, F, h, ws + p.xn, w.wg, w.wu)) {
         TLT_RUN(ctx, s, ctx->in_draft ? CLS_GEMM_DRAFT : CLS_GEMM, 4.0 * M * F * h,
-                ((double)M * h + 2.0 * F * h + (double)M * F) * e, gemm_glu(s, M, F, h, ws + p.xn, w.wg, w.wu, ws + p.act));
+                ((double)M * h + 2.0 * F * h + (double)M * F) * e, gemm_glu(s, dt, M, F, h, ws + p.xn, w.wg, w.wu, ws + p.act));
     } else {
         if ((rc = run_gemm(ctx, s, OUT_T, M, F, h, ws + p.xn, w.wg, ws + p.g))) return rc;
         if ((rc = run_gemm(ctx, s, OUT_T, M, F, h, ws + p.xn, w.wu, ws + p.u))) return rc;
@@ -913,7 +913,7 @@ int tlt_attention(void* stream, int dtype, int B, int n, int n_q_heads, int n_kv
 int tlt_gemm_glu(void* stream, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
     if (M < 1 || N < 1 || K < 1 || !A || !Wg || !Wu || !act) return TLT_EINVAL;
     if (!gemm_glu_supported(TLT_BF16, M, N, K, A, Wg, Wu) || ((uintptr_t)act & 7) != 0) return TLT_ENOTIMPL;   // (8-byte stores)
-    return gemm_glu((hipStream_t)stream, M, N, K, A, Wg, Wu, act) == hipSuccess ? TLT_OK : TLT_EHIP;
+    return gemm_glu((hipStream_t)stream, TLT_BF16, M, N, K, A, Wg, Wu, act) == hipSuccess ? TLT_OK : TLT_EHIP;
 }
 
 int tlt_gemm_argmax(void* stream, int M, int N, int K, const void* A, const void* W, void* ws, size_t ws_bytes,

@@ -4,14 +4,18 @@
 // the provisional rows seq_len[b] + j whose bit j is set in the row's mask (ancestors-or-self of a
 // tree node; a causal prefix for chains).
 //
-// impl 0 ("wave-per-row"): one wavefront per (row, query head); lanes own keys for the score pass
-//   and head dimensions for the value pass; online softmax across 64-key tiles.  Any dtype, any
-//   head_dim that is a multiple of 64 up to 256.  Used for fp32 mode and as a cross-check.
+// impl 0 ("wave-per-row"): one workgroup of four wavefronts per (row, query head), each wave taking every fourth tile
+//   of 64 keys; lanes own keys for the score pass and head dimensions for the value pass; online softmax across a wave's
+//   tiles, the waves merged at the end.  Any dtype, any head_dim that is a multiple of 64 up to 256.  Used for fp32
+//   mode and as a cross-check.  Bound by load latency: keys are read in 16-byte pieces, the values of 16 keys at a time
+//   (4 heads of 64, 130 keys: 40 us with one wave and 4-byte loads, one after the other -> 14).
 // impl 1 ("MFMA split-KV"): the bf16 / head_dim 128 production kernel, described further down.
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace tlt {
+
+constexpr int kRowWaves = 4;   // waves of impl 0's workgroup (64 * kRowWaves covers the largest head_dim)
 
 __device__ __forceinline__ bool region_visible(const Rows& rows, int r, int i, int j) {
     if (j >= rows.n_region) return false;
@@ -21,12 +25,12 @@ __device__ __forceinline__ bool region_visible(const Rows& rows, int r, int i, i
 }
 
 template <typename T>
-__global__ __launch_bounds__(64) void attn_wave_per_row_k(Rows rows, KVLayer kv, const T* __restrict__ qkv,
-                                                          T* __restrict__ out, int n_q_heads, float scale) {
-    __shared__ float q_s[256];
-    __shared__ float p_s[64];
-    __shared__ int64_t base_s[64];
-    const int lane = threadIdx.x;
+__global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows, KVLayer kv, const T* __restrict__ qkv,
+                                                                      T* __restrict__ out, int n_q_heads, float scale) {
+    constexpr int VEC = 16 / sizeof(T), kU = 16;
+    __shared__ __align__(16) float q_s[256];
+    __shared__ float o_s[kRowWaves][256], m_s[kRowWaves], l_s[kRowWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
     const int r = b * rows.n + i;
     const int d = kv.d;
@@ -34,18 +38,18 @@ __global__ __launch_bounds__(64) void attn_wave_per_row_k(Rows rows, KVLayer kv,
     const int qkv_dim = (n_q_heads + 2 * kv.n_kv) * d;
     T* o = out + ((int64_t)r * n_q_heads + hq) * d;
     if (rows.n_valid && i >= rows.n_valid[b]) {
-        for (int c = lane; c < d; c += 64) o[c] = from_float<T>(0.f);
+        if ((int)threadIdx.x < d) o[threadIdx.x] = from_float<T>(0.f);
         return;
     }
     const int ctx = kv.seq_len[b];
     const int total = ctx + rows.n_region;
-    for (int c = lane; c < d; c += 64) q_s[c] = to_float(qkv[(int64_t)r * qkv_dim + hq * d + c]) * scale;
+    if ((int)threadIdx.x < d) q_s[threadIdx.x] = to_float(qkv[(int64_t)r * qkv_dim + hq * d + threadIdx.x]) * scale;
     __syncthreads();
     const T* kc = (const T*)kv.k;
     const T* vc = (const T*)kv.v;
     float m = -INFINITY, l = 0.f;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    for (int t0 = 0; t0 < total; t0 += 64) {
+    for (int t0 = 64 * wave; t0 < total; t0 += 64 * kRowWaves) {
         const int key = t0 + lane;
         bool vis = key < total && (key < ctx || region_visible(rows, r, i, key - ctx));
         PageRef pr;
@@ -53,42 +57,63 @@ __global__ __launch_bounds__(64) void attn_wave_per_row_k(Rows rows, KVLayer kv,
         if (vis && locate(kv.block_table, kv.max_pages, kv.n_pages, kv.page_size, b, key, pr))
             base = ((pr.page * kv.n_kv + kh) * kv.page_size + pr.row) * d;
         vis = base >= 0;
-        float s = -INFINITY;
-        if (vis) {
-            s = 0.f;
-            for (int c = 0; c < d; ++c) s = fmaf(q_s[c], to_float(kc[base + c]), s);
+        if (!vis) base = 0;   // (row 0 of the pool: its weight below is zero)
+        float s = 0.f;
+        const T* kp = kc + base;
+#pragma unroll 8
+        for (int c = 0; c < d; c += VEC) {
+            T kk[VEC];
+            *(uint4*)kk = *(const uint4*)(kp + c);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) s = fmaf(q_s[c + e], to_float(kk[e]), s);
         }
-        float tm = wave_max(s);
-        float m_new = fmaxf(m, tm);
+        if (!vis) s = -INFINITY;
+        const float m_new = fmaxf(m, wave_max(s));
         if (m_new == -INFINITY) continue;  // nothing visible so far (uniform across the wave)
-        float corr = expf(m - m_new);      // exp(-inf) = 0 on the first visible tile
-        float p = vis ? expf(s - m_new) : 0.f;
+        const float corr = expf(m - m_new);      // exp(-inf) = 0 on the first visible tile
+        const float p = vis ? expf(s - m_new) : 0.f;
         l = l * corr + wave_sum(p);
         m = m_new;
-        __syncthreads();
-        p_s[lane] = p;
-        base_s[lane] = base;
-        __syncthreads();
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] *= corr;
         const int nk = min(64, total - t0);
-        for (int k = 0; k < nk; ++k) {
-            float pk = p_s[k];
-            if (pk == 0.f) continue;
-            int64_t bk = base_s[k];
+        for (int k0 = 0; k0 < nk; k0 += kU) {   // (kU keys' loads in flight; keys past nk have weight zero and read row 0)
+            float pk[kU], vv[kU][4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                int c = lane + 64 * t;
-                if (c < d) acc[t] = fmaf(pk, to_float(vc[bk + c]), acc[t]);
+            for (int u = 0; u < kU; ++u) {
+                pk[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), k0 + u));
+                const int64_t bk = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, k0 + u) |
+                                   (int64_t)__builtin_amdgcn_readlane((int)(base >> 32), k0 + u) << 32;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) vv[u][t] = lane + 64 * t < d ? to_float(vc[bk + lane + 64 * t]) : 0.f;
             }
+#pragma unroll
+            for (int u = 0; u < kU; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[t] = pk[u] != 0.f ? fmaf(pk[u], vv[u][t], acc[t]) : acc[t];
         }
     }
-    float inv = l > 0.f ? 1.0f / l : 0.f;
+    // the waves' partial results, merged in wave order
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        int c = lane + 64 * t;
-        if (c < d) o[c] = from_float<T>(acc[t] * inv);
+    for (int t = 0; t < 4; ++t)
+        if (lane + 64 * t < d) o_s[wave][lane + 64 * t] = acc[t];
+    if (lane == 0) {
+        m_s[wave] = m;
+        l_s[wave] = l;
     }
+    __syncthreads();
+    if ((int)threadIdx.x >= d) return;
+    float mm = m_s[0];
+#pragma unroll
+    for (int w = 1; w < kRowWaves; ++w) mm = fmaxf(mm, m_s[w]);
+    float ll = 0.f, a = 0.f;
+#pragma unroll
+    for (int w = 0; w < kRowWaves; ++w) {
+        const float f = m_s[w] == -INFINITY ? 0.f : expf(m_s[w] - mm);
+        ll += f * l_s[w];
+        a += f * o_s[w][threadIdx.x];
+    }
+    o[threadIdx.x] = from_float<T>(ll > 0.f ? a / ll : 0.f);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -849,7 +874,7 @@ hipError_t attention(hipStream_t s, int dtype, const Rows& rows, const KVLayer& 
         if (impl == 1) return hipErrorInvalidValue;  // explicitly requested but the workspace cannot hold it
     }
     float scale = 1.0f / sqrtf((float)kv.d);
-    dim3 grid(rows.n, n_q_heads, rows.B), block(64);
+    dim3 grid(rows.n, n_q_heads, rows.B), block(64 * kRowWaves);
     if (dtype == F32)
         hipLaunchKernelGGL(attn_wave_per_row_k<float>, grid, block, 0, s, rows, kv, (const float*)qkv, (float*)out,
                            n_q_heads, scale);

@@ -575,6 +575,106 @@ __global__ __launch_bounds__(256) void gemm_generic_k(int M, int N, int K, const
     }
 }
 
+// fp32 products of few rows (fp32 mode up to kF32FewRows rows).  What bounds them is latency: a tiny decoder's
+// products are a few hundred kilobytes, and a 64x64 tile walks K in steps of 16 with a barrier each while a handful of
+// workgroups run.  Here a workgroup owns 16 weight rows x 16 T activation rows, its four waves take every fourth piece of 16
+// k, each straight from memory into the operands of v_mfma_f32_16x16x4_f32 (fp32 in, fp32 accumulation; a lane holds
+// 4 consecutive k of its row, and which k an instruction's four slots mean is the same for both operands), and add
+// their sums through LDS: as many workgroups as the width allows, no barrier in the K loop and all its loads in flight.
+// Measured against the 64x64 tiles below (us per call): M 2, N 1024, K 256: 28.0 -> 4.6; M 16, N 256, K 768: 81 -> 5.1; M 64,
+// N 512, K 1280: 151 -> 6.9; M 16, N = K = 3584: 474 -> 16; M 256, N = K = 3584: 565 -> 163 (linear in the rows from there).
+// GLU: W2 is the up matrix, C = silu(A W^T) * (A W2^T).
+typedef __attribute__((ext_vector_type(4))) float f32x4v_t;
+template <int T, int OUT, bool GLU>
+__global__ __launch_bounds__(256) void gemm_f32_few_k(int M, int N, int K, const float* __restrict__ A, const float* __restrict__ W,
+                                                      const float* __restrict__ W2, float* __restrict__ C) {
+    constexpr int NG = GLU ? 2 : 1, U = 4;   // U: pieces whose loads are issued together
+    __shared__ __align__(16) float red[4][NG][T][256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
+    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16 * T;
+    // rows past the edges read the last row: their results are not stored
+    const int wrow = n0 + l16 < N ? n0 + l16 : N - 1;
+    const float* wp[NG];
+    wp[0] = W + (int64_t)wrow * K + 4 * g;
+    if constexpr (GLU) wp[1] = W2 + (int64_t)wrow * K + 4 * g;
+    const float* ap[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int row = m0 + 16 * t + l16;
+        ap[t] = A + (int64_t)(row < M ? row : M - 1) * K + 4 * g;
+    }
+    f32x4v_t acc[NG][T];
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+#pragma unroll
+        for (int t = 0; t < T; ++t) acc[i][t] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = wave * 16; k0 < K; k0 += 64 * U) {
+        f32x4v_t w[U][NG], a[U][T];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 64 * u;
+            const bool on = k + 4 * g < K;   // (K % 4 == 0: a lane's four values are in range or not as a whole)
+#pragma unroll
+            for (int i = 0; i < NG; ++i) w[u][i] = on ? *(const f32x4v_t*)(wp[i] + k) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < T; ++t) a[u][t] = on ? *(const f32x4v_t*)(ap[t] + k) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < NG; ++i)
+#pragma unroll
+                    for (int t = 0; t < T; ++t)
+                        acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[u][i][e], a[u][t][e], acc[i][t], 0, 0, 0);
+    }
+    // a lane holds weight rows 4g .. 4g+3 of activation row l16: [activation row][weight row] in LDS
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+#pragma unroll
+        for (int t = 0; t < T; ++t) *(f32x4v_t*)&red[wave][i][t][l16 * 16 + 4 * g] = acc[i][t];
+    __syncthreads();
+    const int row16 = threadIdx.x >> 4, col = n0 + (threadIdx.x & 15);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int row = m0 + 16 * t + row16;
+        if (row >= M || col >= N) continue;
+        float v = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v += red[q][0][t][threadIdx.x];
+        if constexpr (GLU) {
+            float u = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) u += red[q][NG - 1][t][threadIdx.x];
+            v = v / (1.0f + expf(-v)) * u;
+        }
+        store_out_t<float, OUT>(C, (int64_t)row * N + col, v);
+    }
+}
+
+constexpr int kF32FewRows = 256;
+static bool f32_few_ok(int M, int K, const void* A, const void* W, const void* W2 = nullptr) {
+    return M <= kF32FewRows && K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)W2) & 15) == 0;
+}
+template <int T>
+static hipError_t launch_f32_few_t(hipStream_t s, int out_mode, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
+    const dim3 grid((N + 15) / 16, (M + 16 * T - 1) / (16 * T)), block(256);
+    const float *a = (const float*)A, *w = (const float*)W, *w2 = (const float*)W2;
+    if (W2) hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_F32, true>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C);
+    else if (out_mode == OUT_ADD_F32) hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_ADD_F32, false>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C);
+    else hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_F32, false>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C);
+    return hipGetLastError();
+}
+static hipError_t launch_f32_few(hipStream_t s, int out_mode, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
+    // (more rows per workgroup re-read the weights less, fewer keep more of the chip busy: M 33, N 512, K 1280 14.8 us with
+    // 64 rows per workgroup, 6.9 with 16; M 64, N = K = 3584: 38 and 46)
+    const int64_t wgs = (int64_t)((N + 15) / 16) * ((M + 15) / 16);
+    if (M <= 16 || wgs <= 512) return launch_f32_few_t<1>(s, out_mode, M, N, K, A, W, W2, C);
+    if (M <= 32 || wgs <= 1024) return launch_f32_few_t<2>(s, out_mode, M, N, K, A, W, W2, C);
+    return launch_f32_few_t<4>(s, out_mode, M, N, K, A, W, W2, C);
+}
+
 template <int WGM, int WGN, int WTM, int WTN, int SA, int SB, bool GLU = false, bool NTW = false>
 static hipError_t launch_pipe(hipStream_t s, int out_mode, int M, int N, int K, const void* A, const void* W, void* C,
                               const void* W2 = nullptr, int ksplit = 1, int ldc = 0, int kskew = 0) {
@@ -812,7 +912,8 @@ static bool pipe_ok(int N, int K, const void* A, const void* W) {
 
 hipError_t gemm(hipStream_t s, int dtype, int out_mode, int M, int N, int K, const void* A, const void* W, void* C) {
     if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-    if (dtype == F32) return launch_generic<float>(s, out_mode, M, N, K, A, W, C);
+    if (dtype == F32)
+        return f32_few_ok(M, K, A, W) ? launch_f32_few(s, out_mode, M, N, K, A, W, nullptr, C) : launch_generic<float>(s, out_mode, M, N, K, A, W, C);
     if (pipe_ok(N, K, A, W)) {
         // (accumulating into C: the K splits add their partial sums with fp32 atomics, in any order, so the
         // last bit of the result is not fixed.  The step itself uses gemm_parts, which is reproducible.)
@@ -917,12 +1018,14 @@ hipError_t gemm_argmax(hipStream_t s, int M, int N, int K, const void* A, const 
 }
 
 bool gemm_glu_supported(int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu) {
+    if (dtype == F32) return M > 0 && f32_few_ok(M, K, A, Wg, Wu);
     const bool aligned = (((uintptr_t)A | (uintptr_t)Wg | (uintptr_t)Wu) & 15) == 0;
-    return dtype == BF16 && M > 0 && aligned && K % kBK == 0 && N % 128 == 0 && (int64_t)258 * K * 2 < ((int64_t)1 << 31);
+    return M > 0 && aligned && K % kBK == 0 && N % 128 == 0 && (int64_t)258 * K * 2 < ((int64_t)1 << 31);
 }
 
-// act[M][N] = silu(A Wg^T) * (A Wu^T), bf16 in and out; call only when gemm_glu_supported().
-hipError_t gemm_glu(hipStream_t s, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
+// act[M][N] = silu(A Wg^T) * (A Wu^T), dtype in and out; call only when gemm_glu_supported().
+hipError_t gemm_glu(hipStream_t s, int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
+    if (dtype == F32) return launch_f32_few(s, OUT_F32, M, N, K, A, Wg, Wu, act);
     return launch_tiled(s, OUT_T, M, N, K, A, Wg, Wu, act, true);
 }
 

@@ -54,9 +54,9 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
 // upper bound of n * M * N * 4 over every shape (see gemm.hip)
 size_t gemm_parts_max_bytes();
 bool gemm_parts_pays(int dtype, int M, int N, int K);   // slices expected to beat one result in the model dtype
-// fused gate/up projection of the SwiGLU MLP (bf16 MFMA path only): act = silu(A Wg^T) * (A Wu^T)
+// fused gate/up projection of the SwiGLU MLP (bf16, or fp32 with few rows): act = silu(A Wg^T) * (A Wu^T)
 bool gemm_glu_supported(int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu);
-hipError_t gemm_glu(hipStream_t s, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act);
+hipError_t gemm_glu(hipStream_t s, int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act);
 
 // argmax over each row of A W^T without writing the product (the LM head when only the most likely
 // token is wanted): the GEMM's epilogue leaves the best (value, column) of every 128-column block,
