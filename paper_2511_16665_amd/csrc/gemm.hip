@@ -675,6 +675,202 @@ static hipError_t launch_f32_few(hipStream_t s, int out_mode, int M, int N, int 
     return launch_f32_few_t<4>(s, out_mode, M, N, K, A, W, W2, C);
 }
 
+// Few activation rows (M <= 32 * WTM, one row of tiles): the weights stream through once and nothing else counts.  A
+// workgroup of four waves owns 32 * WTN weight rows (GLU: half of them gate rows, half the matching up rows), WTN being free so
+// that the tiles come out at just under one per CU.  The K steps of 64 go through a ring of S slots (activation rows and
+// weight rows, both by global->LDS loads, S - 1 steps in flight); of a step's four 16-wide slices each wave multiplies one,
+// over the whole tile, so that a fragment is read from the LDS once, and the four waves' sums meet in LDS at the end.
+// A step's loads are whole 128-byte lines; fetched straight into MFMA operands (64 bytes per row and instruction)
+// the vector-memory front end is the limit instead: 68 us at M = 16 on the gate/up shape below.
+template <int WGM, int WTM, int WTN, int S, int OUT, bool GLU>
+__global__ __launch_bounds__(256 * WGM) void gemm_bf16_few_k(int M, int N, int K, const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
+                                                       const uint16_t* __restrict__ W2, void* __restrict__ C, int nbn, int ksplit) {
+    constexpr int NW = 4 * WGM, BM = 32 * WTM * WGM, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
+    constexpr int SLOT = (BM + BN) * 64;           // elements per slot: activation rows, then weight rows
+    constexpr int LB = (BN / 8 + NW - 1) / NW;     // 1 KB loads per wave and step: weights (a wave's last one may be idle)
+    constexpr int L = WTM + LB;                    // ... and activations
+    constexpr bool kIdle = (BN / 8) % NW != 0;
+    static_assert(S >= 3 && (S - 2) * L < 64, "the wait below counts the loads of S - 2 steps");
+    static_assert(S * SLOT * 2 >= 4 * 32 * BN * 4, "the ring also holds the four slices' sums of 32 rows");
+    extern __shared__ __align__(16) uint16_t lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5, slice = wave & 3, wm = wave >> 2;
+    const int tile = blockIdx.x % nbn, cut = blockIdx.x / nbn, n0 = tile * BNO;
+    const int nk = K / 64, kt0 = (int)((int64_t)nk * cut / ksplit), nt = (int)((int64_t)nk * (cut + 1) / ksplit) - kt0;
+    auto desc = [&](const uint16_t* base, uint32_t bytes) {   // raw buffer descriptor; rows past its size fetch nothing
+        const uint64_t p = (uint64_t)(uintptr_t)base;
+        u32x4_t d;
+        d[0] = __builtin_amdgcn_readfirstlane((uint32_t)p);
+        d[1] = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32) & 0xffffu);
+        d[2] = __builtin_amdgcn_readfirstlane(bytes);
+        d[3] = 0x00020000u;
+        return d;
+    };
+    const int cols = N - n0 < BNO ? N - n0 : BNO;
+    const u32x4_t rs_a = desc(A, (uint32_t)M * (uint32_t)K * 2u);
+    // load i of a wave covers 8 consecutive tile rows (BNO is a multiple of 8: they are gate rows or up rows as a whole)
+    const int r = lane >> 3, c = lane & 7;
+    u32x4_t rs_b[LB];
+    uint32_t off_a[WTM], off_b[LB], dst_b[LB];
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)lds;
+    const uint32_t lds_a = lds_base + (uint32_t)(wave * WTM) * 1024u;
+#pragma unroll
+    for (int i = 0; i < WTM; ++i) {
+        const int row = (wave * WTM + i) * 8 + r;
+        off_a[i] = ((uint32_t)row * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        // (an idle load has an empty descriptor, fetches nothing and aims at a kilobyte behind the ring)
+        const int row0 = (i * NW + wave) * 8, row = row0 + r;
+        const bool on = !kIdle || row0 < BN, up = GLU && row0 >= BNO;
+        rs_b[i] = desc((up ? W2 : W) + (int64_t)n0 * K, on ? (uint32_t)cols * (uint32_t)K * 2u : 0u);
+        off_b[i] = ((uint32_t)(up ? row - BNO : row) * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
+        dst_b[i] = lds_base + (on ? (uint32_t)(BM * 128 + row0 * 128) : (uint32_t)(S * SLOT * 2));
+    }
+    auto fetch = [&](int t, int slot) {   // step t (past the end: the last one again, so that the wait counts hold)
+        const uint32_t k2 = (uint32_t)(kt0 + (t < nt ? t : nt - 1)) * 128u, so = (uint32_t)slot * (SLOT * 2);
+#pragma unroll
+        for (int i = 0; i < LB; ++i)
+            dma_buf_16_nt(rs_b[i], off_b[i], k2, kIdle && i == LB - 1 && wave + i * NW >= BN / 8 ? dst_b[i] : dst_b[i] + so);
+#pragma unroll
+        for (int i = 0; i < WTM; ++i) dma_buf_16(rs_a, off_a[i], k2, lds_a + so + i * 1024u);
+    };
+    f32x16_t acc[WTM][WTN];
+#pragma unroll
+    for (int i = 0; i < WTM; ++i)
+#pragma unroll
+        for (int j = 0; j < WTN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+#pragma unroll
+    for (int t = 0; t < S - 1; ++t) fetch(t, t);
+    const int frag = l32 * 64 + ((2 * slice + lhi) ^ ((l32 >> 1) & 7)) * 8;   // row l32 of a block, this wave's slice
+    int slot = 0;
+    for (int t = 0; t < nt; ++t) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the last step's fragments have left their slot
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * L));           // step t has landed
+        __builtin_amdgcn_s_barrier();                                 // ... for every wave
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(t + S - 1, slot == 0 ? S - 1 : slot - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        const uint16_t* p = lds + slot * SLOT + frag;
+        bf16x8_t fa[WTM], fb[WTN];
+#pragma unroll
+        for (int i = 0; i < WTM; ++i) fa[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + (wm * WTM + i) * 32 * 64));
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) fb[j] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + (BM + j * 32) * 64));
+#pragma unroll
+        for (int i = 0; i < WTM; ++i)
+#pragma unroll
+            for (int j = 0; j < WTN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        slot = slot + 1 == S ? 0 : slot + 1;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the repeated fetches at the end as well: the ring is reused below
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    // the four slices' sums of 32 rows at a time: [slice][32][BN], then four columns per thread
+    float* red = (float*)lds;
+#pragma unroll
+    for (int blk = 0; blk < WGM * WTM; ++blk) {
+        const int rows = M - 32 * blk;             // (may be past 32)
+        if (rows <= 0) break;
+        if (blk > 0) __syncthreads();
+        if (wm == blk / WTM) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = 8 * (v >> 2) + 4 * lhi + (v & 3);
+                if (row < rows) {
+#pragma unroll
+                    for (int j = 0; j < WTN; ++j) red[(slice * 32 + row) * BN + j * 32 + l32] = acc[blk % WTM][j][v];
+                }
+            }
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < (rows < 32 ? rows : 32) * (BNO / 4); e += 64 * NW) {
+            const int row = e / (BNO / 4), col = (e - row * (BNO / 4)) * 4;
+            if (col >= cols) continue;
+            auto sum4 = [&](int c0) {
+                const float* p = red + row * BN + c0;
+                float4 s = *(const float4*)p;
+#pragma unroll
+                for (int q = 1; q < 4; ++q) {
+                    const float4 o = *(const float4*)(p + q * 32 * BN);
+                    s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
+                }
+                return s;
+            };
+            const float4 g = sum4(col);
+            const int64_t at = (int64_t)(32 * blk + row) * N + n0 + col;
+            if constexpr (GLU) {
+                const float4 u = sum4(BNO + col);
+                auto act = [](float x, float y) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)) * y; };
+                *(uint2*)((bf16*)C + at) = make_uint2(pack_bf16x2(act(g.x, u.x), act(g.y, u.y)), pack_bf16x2(act(g.z, u.z), act(g.w, u.w)));
+            } else {
+                *(float4*)((float*)C + (int64_t)cut * M * N + at) = g;
+            }
+        }
+    }
+}
+
+template <int WGM, int WTM, int WTN, bool GLU>
+static hipError_t launch_few(hipStream_t s, int M, int N, int K, const void* A, const void* W, const void* W2, void* C, int ksplit = 1) {
+    constexpr int BM = 32 * WTM * WGM, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
+    constexpr int kFit = 159 * 1024 / ((BM + BN) * 128), S = kFit < 8 ? kFit : 8;
+    constexpr size_t lds = (size_t)S * (BM + BN) * 128 + 1024;
+    auto kern = gemm_bf16_few_k<WGM, WTM, WTN, S, GLU ? OUT_T : OUT_SPLIT_F32, GLU>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const int nbn = (N + BNO - 1) / BNO;
+    hipLaunchKernelGGL(kern, dim3(nbn * ksplit), dim3(256 * WGM), lds, s, M, N, K, (const uint16_t*)A, (const uint16_t*)W, (const uint16_t*)W2, C, nbn,
+                       ksplit);
+    return hipGetLastError();
+}
+
+// Gate/up at up to 128 rows: the tile's weight rows in blocks of 32, the fewest that leave at most one workgroup per CU (in
+// two rounds the second one's CUs are idle half of the time).  0: the tiled launches below take the product.
+// Against those (us, best of three alternating runs on cold weights): N 18944, K 3584 (237 tiles of 80 columns): M = 1 59.0 ->
+// 42.9 (6.3 TB/s), M = 64 64.0 -> 47.7, M = 128 63.0 -> 56.9; N 27648, K 5120 (247 of 112): M = 1 90.7 -> 84.0, M = 64 101.8 ->
+// 90.7; N 11008, K 4096: M = 1 40.0 -> 35.0; N 4864, K 896: M = 1 10.6 -> 7.3, M = 64 11.3 -> 9.6.
+// Up to 64 rows, four blocks are the width of the 128x128 tiles, which then run one per CU with three slots and are the better
+// ones (N 14336, K 4096: 45.5 against 46.5); eight leave too few slots (N 32768, K 8192: 169 against 197).  Above 64
+// rows, the narrow widths lose to 128x128 tiles (N 8960, K 1536, M = 100: 19.3 against 21.5), and more than
+// six do not fit the registers.
+static int few_glu_width(int M, int N) {
+    int wtn = 2;
+    while ((N + 16 * wtn - 1) / (16 * wtn) > 256) ++wtn;
+    if (M <= 64) return wtn == 4 || wtn > 7 ? 0 : wtn;
+    return M > 128 || wtn < 4 || wtn > 6 ? 0 : wtn;
+}
+static hipError_t launch_few_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
+#define TLT_FEW(g, m, n) if (M <= 32 * g * m && wtn == n) return launch_few<g, m, n, true>(s, M, N, K, A, W, W2, C);
+    TLT_FEW(1, 1, 2) TLT_FEW(1, 1, 3) TLT_FEW(1, 1, 5) TLT_FEW(1, 1, 6) TLT_FEW(1, 1, 7)
+    TLT_FEW(1, 2, 2) TLT_FEW(1, 2, 3) TLT_FEW(1, 2, 5) TLT_FEW(1, 2, 6) TLT_FEW(1, 2, 7)
+    TLT_FEW(2, 2, 4) TLT_FEW(2, 2, 5) TLT_FEW(2, 2, 6)
+#undef TLT_FEW
+    return hipErrorInvalidValue;
+}
+
+// Products kept as partial sums at up to 32 rows: tiles of 64 columns, cut along K so that the workgroups come out at
+// just under one per CU; wider tiles where their cuts fill more of the chip.  Returns the tile width in blocks of 32 columns.
+static int few_split_plan(int N, int K, int max_cuts, int* cuts) {
+    int best = 0, best_wgs = 0;
+    for (int wtn = 2; wtn <= 4; ++wtn) {
+        const int nbn = (N + 32 * wtn - 1) / (32 * wtn);
+        int ks = 256 / nbn;
+        if (ks > K / 64 / 6) ks = K / 64 / 6;
+        if (ks > max_cuts) ks = max_cuts;
+        if (ks < 1 || nbn > 256) continue;
+        if (best == 0 || (best_wgs < 200 && nbn * ks > best_wgs)) best = wtn, best_wgs = nbn * ks, *cuts = ks;
+    }
+    return best;
+}
+
 template <int WGM, int WGN, int WTM, int WTN, int SA, int SB, bool GLU = false, bool NTW = false>
 static hipError_t launch_pipe(hipStream_t s, int out_mode, int M, int N, int K, const void* A, const void* W, void* C,
                               const void* W2 = nullptr, int ksplit = 1, int ldc = 0, int kskew = 0) {
@@ -946,6 +1142,14 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
     if ((size_t)M * N * 4 > parts_bytes) return hipErrorInvalidValue;
     if (dtype == BF16 && pipe_ok(N, K, A, W)) {
         const size_t room = parts_bytes / ((size_t)M * N * 4);
+        if (M <= 32) {
+            int cuts = 1;
+            const int wtn = few_split_plan(N, K, room > 12 ? 12 : (int)room, &cuts);
+            *n_parts = cuts;
+            if (wtn == 2) return launch_few<1, 1, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+            if (wtn == 3) return launch_few<1, 1, 3, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+            if (wtn == 4) return launch_few<1, 1, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        }
         const SplitPlan sp = plan_split(M, N, K, room > 12 ? 12 : (int)room);
         if (sp.kind != 0 && (size_t)sp.ks * M * N * 4 <= parts_bytes) {
             *n_parts = sp.ks;
@@ -1026,6 +1230,7 @@ bool gemm_glu_supported(int dtype, int M, int N, int K, const void* A, const voi
 // act[M][N] = silu(A Wg^T) * (A Wu^T), dtype in and out; call only when gemm_glu_supported().
 hipError_t gemm_glu(hipStream_t s, int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
     if (dtype == F32) return launch_f32_few(s, OUT_F32, M, N, K, A, Wg, Wu, act);
+    if (const int wtn = few_glu_width(M, N)) return launch_few_glu(s, wtn, M, N, K, A, Wg, Wu, act);
     return launch_tiled(s, OUT_T, M, N, K, A, Wg, Wu, act, true);
 }
 

@@ -1,5 +1,6 @@
 """The few-row kernels at the edges of their tiles: fp32 products (16 weight rows x 16, 32 or 64 activation rows per
-workgroup, K in pieces of 16 dealt over four waves) and the paths of the decoder block that use them."""
+workgroup, K in pieces of 16 dealt over four waves), bf16 gate/up products (tiles of 32 to 112 columns, K steps through a
+ring of slots), bf16 products kept as partial sums, and the paths of the decoder block that use them."""
 import dataclasses
 
 import numpy as np
@@ -7,7 +8,7 @@ import pytest
 import torch
 
 from paper_2511_16665_amd import binding as tlt
-from synth import TINY
+from synth import MID, TINY
 
 from test_gpu_verify import test_verify_forward_matches_oracle as _verify_matches_oracle
 
@@ -42,3 +43,41 @@ def test_fp32_product(M, N, K, out_mode):
 def test_fp32_forward(n, ctxs, mlp):
     cfg = dataclasses.replace(TINY, name=f"tiny-mlp{mlp}", mlp=mlp)
     _verify_matches_oracle(cfg, "fp32", 1e-4, n, ctxs, 0.05, -1)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 640, 256), (32, 8192, 64),              # 32 columns per workgroup; one K step, fewer than the ring has slots
+    (17, 8320, 192), (33, 12288, 576),          # 48 columns, partial last tile; K steps past one turn of the ring
+    (32, 16512, 64), (64, 20480, 448),          # 80 columns
+    (5, 20608, 128), (40, 24576, 64),           # 96 columns
+    (31, 24704, 128), (64, 28672, 192),         # 112 columns
+    (65, 12416, 384), (128, 16384, 64),         # above 64 rows: two groups of waves, 64 columns
+    (97, 16512, 320), (128, 20608, 128),        # 80 and 96 columns, partial last tiles
+    (64, 14336, 128), (66, 640, 128), (100, 24704, 64), (129, 16512, 64),   # beside the ranges: the tiled kernel
+])
+def test_bf16_gate_up(M, N, K):
+    g = torch.Generator().manual_seed(M + N + K)
+    A = torch.randn((M, K), generator=g).bfloat16()
+    W, U = ((torch.randn((N, K), generator=g) / K ** 0.5).bfloat16() for _ in range(2))
+    act = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print(f"gate/up M={M} N={N} K={K}", flush=True)
+    tlt.gemm_glu(A.cuda(), W.cuda(), U.cuda(), act)
+    torch.cuda.synchronize()
+    Ad, Wd, Ud = A.cuda().double(), W.cuda().double(), U.cuda().double()
+    gate, up = Ad @ Wd.T, Ad @ Ud.T
+    want = torch.nn.functional.silu(gate) * up
+    # fp32 sums of K products each, |silu'| < 1.1; exponential and reciprocal to a few units of 2^-23; one rounding to bf16
+    sum_err = (K + 2) * 2.0 ** -24
+    bound = (1.1 * sum_err * (Ad.abs() @ Wd.abs().T) * up.abs() + torch.nn.functional.silu(gate).abs() * sum_err * (Ad.abs() @ Ud.abs().T)
+             + want.abs() * (2.0 ** -8 + (8 + gate.abs()) * 2.0 ** -22) + 1e-30)
+    assert bool(((act.double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("hidden,heads,n", [
+    (512, 4, 5),       # 64 columns per workgroup, one cut
+    (6144, 8, 32),     # output projection in two cuts, down in 96-column tiles
+    (8704, 68, 9),     # output projection in 128-column tiles
+])
+def test_bf16_forward_few_rows(hidden, heads, n):
+    cfg = dataclasses.replace(MID, name=f"mid-h{hidden}", hidden=hidden, n_q_heads=heads, n_kv_heads=4, mlp=3072, vocab=512, n_layers=1)
+    _verify_matches_oracle(cfg, "bf16", 2e-2, n, [70], 0.02, -1)
