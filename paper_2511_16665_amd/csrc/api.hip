@@ -25,7 +25,7 @@ struct ProfRec {
 };
 
 struct Plan {  // byte offsets into the workspace
-    size_t x, xn, qkv, parts, att, g, u, act, logits, argmax, feat, top_tok, top_logp, pool_token, pool_score, pool_parent,
+    size_t x, xn, qkv, rope_cs, rope_at, parts, att, g, u, act, logits, argmax, feat, top_tok, top_logp, pool_token, pool_score, pool_parent,
         pool_depth, pool_mask, fr_token, fr_src, fr_pool, fr_mask, row_map, attn_ws, accept_ws, topk_ws, status, total;
     size_t attn_ws_bytes, parts_bytes;
     int max_rows, pool_cap, feat_rows;
@@ -57,6 +57,8 @@ bool plan_workspace(const tlt_model_cfg& c, int B, int n, int D, int K, int max_
     p.xn = take(R * 2 * h * esz);
     p.qkv = take(R * qkv_dim * esz);
     // fp32 partial products of the projections whose sum joins the fp32 residual stream (or feeds the rotary kernel)
+    p.rope_cs = take(R * (size_t)c.head_dim * 4);
+    p.rope_at = take(R * 8);
     // (room for four slices of the widest product at the largest row count; a plan with more cuts than fit is not taken)
     p.parts_bytes = std::max(c.dtype == TLT_BF16 ? gemm_parts_max_bytes() : (size_t)0, (c.dtype == TLT_BF16 ? 4 : 1) * R * std::max(h, qkv_dim) * 4);
     p.parts = take(p.parts_bytes);
@@ -248,10 +250,10 @@ KVLayer kv_layer(const tlt_ctx* ctx, const tlt_kv* kv, int layer) {
 }
 
 // One decoder block over M = rows.B * rows.n rows whose residual stream sits in the workspace's x.
-// reuse_attn_plan: the attention work list in the workspace was built by an earlier layer of the same
-// forward (same rows, same sequence lengths) and is still valid.
+// later_layer: an earlier layer of the same forward (same rows, same sequence lengths) has left the attention work list
+// and the rotary table in the workspace.
 int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const Rows& rows, const KVLayer& kv,
-                  bool reuse_attn_plan = false) {
+                  bool later_layer = false) {
     const tlt_model_cfg& c = ctx->cfg;
     const Plan& p = ctx->plan;
     char* ws = ctx->ws;
@@ -262,6 +264,8 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     int rc;
     float* parts = (float*)(ws + p.parts);
     int n_parts = 1;
+    RopeTable tab;   // (the drafter is one layer: nothing to keep)
+    if (!ctx->in_draft) tab.cs = (float*)(ws + p.rope_cs), tab.at = (int64_t*)(ws + p.rope_at);
     if ((rc = norm_x(ctx, s, M, w.attn_norm, ws + p.xn))) return rc;
     if (dt == TLT_BF16 && qkv_dim % 128 == 0 && (size_t)M * qkv_dim * 4 * 2 <= p.parts_bytes &&
         (M <= 256 || gemm_parts_pays(dt, M, qkv_dim, h))) {
@@ -270,11 +274,11 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
         // above where the cost model of the cuts expects it to pay: a few hundred rows).
         if ((rc = run_gemm_parts(ctx, s, M, qkv_dim, h, ws + p.xn, w.wqkv, &n_parts))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * (4 * n_parts + e),
-                rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, parts, n_parts));
+                rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer, parts, n_parts));
     } else {
         if ((rc = run_gemm(ctx, s, OUT_T, M, qkv_dim, h, ws + p.xn, w.wqkv, ws + p.qkv))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * e * 2,
-                rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv));
+                rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer));
     }
     {
         // algorithmic traffic: one pass over the cached K and V of every sequence (bounded by the
@@ -284,7 +288,7 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
         const double flops = 4.0 * c.head_dim * c.n_q_heads * (double)rows.n * keys;
         TLT_RUN(ctx, s, ctx->in_draft ? CLS_ATTN_DRAFT : CLS_ATTN, flops, bytes,
                 attention(s, dt, rows, kv, ws + p.qkv, ws + p.att, c.n_q_heads, ws + p.attn_ws, p.attn_ws_bytes, ctx->attn_impl,
-                          reuse_attn_plan, ctx->status_ready ? status_word(ctx) : nullptr));
+                          later_layer, ctx->status_ready ? status_word(ctx) : nullptr));
     }
     // the output projection's product (fp32, possibly several partial products of a K split) joins the
     // residual stream inside the norm kernel that follows: plain stores in the GEMM's epilogue instead of

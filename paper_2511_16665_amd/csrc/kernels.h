@@ -86,8 +86,14 @@ hipError_t add_parts(hipStream_t s, int64_t count, float* x, const float* parts,
 // (bias: optional [(Hq+2Hkv)*d] in dtype, added to q, k and v before the rotation; src32: optional
 // fp32 copy of the projection to read instead of qkv, which then only receives the rotated q)
 // (src32 may hold n_src partial products [n_src][M][qkv_dim], which are summed in order)
+// tab: what every layer of a forward needs of its rows, left by a call with from_table false (cs null: not wanted) and read by those
+// with from_table true, for the same rows, lengths and block table.
+struct RopeTable {
+    float* cs = nullptr;     // [M][d]: cosines, then sines, of the d / 2 pairs
+    int64_t* at = nullptr;   // [M]: element offset of the row's cache slot (kv head 0), -1: none, -2: row not active
+};
 hipError_t rope_kv_write(hipStream_t s, int dtype, const Rows& rows, const KVLayer& kv, void* qkv, int n_q_heads,
-                         float theta, const void* bias, const float* src32 = nullptr, int n_src = 1);
+                         float theta, const void* bias, const RopeTable& tab, bool from_table, const float* src32 = nullptr, int n_src = 1);
 hipError_t swiglu(hipStream_t s, int dtype, int64_t count, const void* g, const void* u, void* out);
 // Rows [B][n]: xin[r] = [embed[tok[r]] ; hidden[src row]] in dtype (2h wide).  The hidden row is
 // b*src_seq_stride + src[r] when src_seq_stride > 0, else src[r].  Rows with tok < 0, src < 0,
