@@ -731,10 +731,10 @@ __global__ __launch_bounds__(512) void attn_mfma_k(Rows rows, KVLayer kv, const 
 
 // One wave per (b, kv head, row), four rows per workgroup: merges the chunks' partial outputs
 // (running max in raw score units).
-// BATCH: the loads of four chunks are issued before any of them is used.  With few rows in all (plain decoding, small
-// batches) a wave's chunks, one load latency each, are the whole kernel (12 -> 5 us at batch 1, 16 chunks); with the
-// chip full of waves the plain loop is the faster one (14 against 16 us at the benchmark shape).  The sums run in
-// chunk order either way.
+// BATCH: the lanes read a chunk's maximum and sum each, and the outputs of 16 chunks are requested together.  With few rows in
+// all (plain decoding, small batches) a wave's chunks, one load latency each, are the whole kernel (batch 1, 17 chunks:
+// 12 us one after the other, 6.3 four at a time, 4.8 this way; 3 sequences x 23 nodes 7.2 -> 6.0); with the chip full of waves the plain loop is the faster one (14 against 16 us at the
+// benchmark shape).  The sums run in chunk order either way.
 template <bool BATCH>
 __global__ __launch_bounds__(256) void attn_combine_k(Rows rows, KVLayer kv, const float* __restrict__ part_o,
                                                      const float* __restrict__ part_ml, uint16_t* __restrict__ out,
@@ -760,29 +760,32 @@ __global__ __launch_bounds__(256) void attn_combine_k(Rows rows, KVLayer kv, con
     float M = kNegBig;
     float a0 = 0.f, a1 = 0.f, L = 0.f;
     if constexpr (BATCH) {
-        for (int c0 = 0; c0 < used; c0 += 4) {
-            float m4[4];
+        constexpr int U = 16;
+        float2 ml = make_float2(kNegBig, 0.f), v[U];   // lane c: chunk c's (maximum, sum)
+        auto fetch = [&](int c0) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) m4[u] = c0 + u < used ? part_ml[(pbase + (c0 + u) * pstride) * 2] : kNegBig;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) M = fmaxf(M, m4[u]);
-        }
-        for (int c0 = 0; c0 < used; c0 += 4) {
-            float2 ml4[4], v4[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t pr = pbase + (c0 + u) * pstride;
-                const bool on = c0 + u < used;
-                ml4[u] = on ? *(const float2*)(part_ml + pr * 2) : make_float2(kNegBig, 0.f);
-                v4[u] = on ? *(const float2*)(part_o + pr * kD + lane * 2) : make_float2(0.f, 0.f);
+            for (int u = 0; u < U; ++u)
+                v[u] = c0 + u < used ? *(const float2*)(part_o + (pbase + (c0 + u) * pstride) * kD + lane * 2) : make_float2(0.f, 0.f);
+        };
+        if (lane < used) ml = *(const float2*)(part_ml + (pbase + lane * pstride) * 2);
+        fetch(0);
+        M = ml.x;
+        for (int c = lane + 64; c < used; c += 64) M = fmaxf(M, part_ml[(pbase + c * pstride) * 2]);
+        M = wave_max(M);
+        float w_lane = exp2f((ml.x - M) * scale_log2);
+        for (int c0 = 0; c0 < used; c0 += U) {
+            if (c0 > 0) fetch(c0);
+            if (c0 > 0 && (c0 & 63) == 0) {
+                ml = c0 + lane < used ? *(const float2*)(part_ml + (pbase + (c0 + lane) * pstride) * 2) : make_float2(kNegBig, 0.f);
+                w_lane = exp2f((ml.x - M) * scale_log2);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < U; ++u) {
                 if (c0 + u < used) {   // wave-uniform
-                    const float w = exp2f((ml4[u].x - M) * scale_log2);
-                    L += ml4[u].y * w;
-                    a0 += v4[u].x * w;
-                    a1 += v4[u].y * w;
+                    const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_lane), (c0 + u) & 63));
+                    L += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ml.y), (c0 + u) & 63)) * w;
+                    a0 += v[u].x * w;
+                    a1 += v[u].y * w;
                 }
             }
         }
