@@ -66,6 +66,14 @@ __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__
     const int64_t src = row_map ? row_map[r] : r;
     T* o = out + (int64_t)r * h;
     float4 v[NK];
+    // (the gains are requested with the row, not after the reduction: one memory latency instead of two)
+    typedef __attribute__((ext_vector_type(sizeof(T)))) uint32_t gain_t;   // four T
+    gain_t gv[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const int c = threadIdx.x + k * NTHR;
+        gv[k] = c < h4 ? ((const gain_t*)gamma)[c] : gain_t{};
+    }
     float ss = 0.f;
     if (src >= 0) {
         float4* xr = (float4*)(x + src * h);
@@ -111,9 +119,15 @@ __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__
     for (int k = 0; k < NK; ++k) {
         const int c = threadIdx.x + k * NTHR;
         if (c >= h4) continue;
-        const T* g = gamma + 4 * c;
-        float y[4] = {v[k].x * inv * to_float(g[0]), v[k].y * inv * to_float(g[1]), v[k].z * inv * to_float(g[2]),
-                      v[k].w * inv * to_float(g[3])};
+        float g[4];
+        if constexpr (sizeof(T) == 2) {
+            g[0] = __uint_as_float(gv[k][0] << 16), g[1] = __uint_as_float(gv[k][0] & 0xffff0000u);
+            g[2] = __uint_as_float(gv[k][1] << 16), g[3] = __uint_as_float(gv[k][1] & 0xffff0000u);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) g[q] = __uint_as_float(gv[k][q]);
+        }
+        float y[4] = {v[k].x * inv * g[0], v[k].y * inv * g[1], v[k].z * inv * g[2], v[k].w * inv * g[3]};
         if (src < 0) y[0] = y[1] = y[2] = y[3] = 0.f;
         if constexpr (sizeof(T) == 2) {
             *(uint2*)(o + 4 * c) = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
@@ -414,9 +428,10 @@ template <typename T, typename TA>
 static void rmsnorm_launch_t(hipStream_t s, int M, int h, float* x, const void* gamma, float eps, void* out,
                              const int32_t* row_map, const void* add, float* zero, int zero_n, int n_add, bool assign) {
     const int64_t add_stride = (int64_t)M * h;
-    const bool vec_ok = h % 4 == 0 && (((uintptr_t)x | (uintptr_t)add | (uintptr_t)zero) & 15) == 0 && zero_n % 4 == 0;
-    if (vec_ok && h <= 4096 && add && n_add > 4 && sizeof(TA) == 4)
-        // many slices (few rows, so few workgroups): one 16-byte position per thread and all its slices' loads in
+    const bool vec_ok = h % 4 == 0 && (((uintptr_t)x | (uintptr_t)add | (uintptr_t)zero) & 15) == 0 && zero_n % 4 == 0 &&
+                        ((uintptr_t)gamma & (4 * sizeof(T) - 1)) == 0;
+    if (vec_ok && h <= 4096 && add && (n_add > 4 || M <= 64) && sizeof(TA) == 4)
+        // many slices or few rows (so few workgroups): one 16-byte position per thread and all its slices' loads in
         // flight at once
         hipLaunchKernelGGL((rmsnorm_vec_k<T, 1, TA, 12, 1024>), dim3(M), dim3(1024), 0, s, h, x, (const T*)gamma, eps, (T*)out,
                            row_map, (const TA*)add, zero, zero_n, n_add, add_stride, (int)assign);
