@@ -166,11 +166,12 @@ constexpr int kMaxChunk = 4096;  // keys per chunk: bounds the page-id table kep
 // Work decomposition.  A work item is (sequence, key range); each item is run by n_kv * row_groups
 // workgroups.  The key ranges are cut ON THE DEVICE from the actual sequence lengths (the host only
 // knows an upper bound): a one-workgroup planning kernel picks the item length so that the chip
-// gets about two items per CU (8 .. 64 tiles of 64 keys), gives every sequence equally long chunks,
+// gets whole rounds of items (kMinTiles .. 64 tiles of 64 keys), gives every sequence equally long chunks,
 // and lists the items longest first.  Workgroups are dispatched in list order, so the long items
 // start first and the short ones fill the tail (longest-processing-time-first list scheduling).
 struct AttnItem {
     int b, k_begin, k_end, slot;   // slot: index of this item's partial result (slots of a sequence are contiguous)
+    int page[kAhead * kKT / 16];   // pages of the first kAhead tiles (-1: none): their fetches need not wait for the block table
 };
 struct AttnWork {        // lives in the workspace, written by attn_plan_k
     int n_items;
@@ -208,92 +209,127 @@ static size_t attn_work_bytes(int B, int max_items) {
     return (sizeof(AttnWork) + (size_t)2 * B * sizeof(int) + (size_t)max_items * sizeof(AttnItem) + 255) / 256 * 256;
 }
 
+// Shortest chunk: with one or a few sequences, shorter chunks put more of the CUs to work, but every one adds a partial
+// result to the merge (one sequence of 8192, main + merging kernel: 8 tiles 11.1 + 4.8 us, 4 tiles 8.5 + 6.0, 3 and 2 tiles 8.4
+// + 6.5; three of 5000, 161 query rows: 22.1 + 5.9, 4 tiles 19.9 + 7.4).
+constexpr int kMinTiles = 4;
+constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the planning kernel keeps in LDS
+
+// One workgroup, so a chain of latencies: lengths are read once, and the counting, the search for the chunk size, the running
+// sums and the sort are spread over its threads (1 sequence 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.4, 64 sequences 20.9 -> 9.7
+// against one thread walking the sequences; once per forward and drafter level).
 __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ seq_len, int B, int n_region, int heads,
                                                    int max_items, AttnWork* __restrict__ work, int len_bound,
-                                                   unsigned int* __restrict__ status) {
-    __shared__ int s_T, s_total, s_hist[66], s_pos[66];
+                                                   unsigned int* __restrict__ status, const int32_t* __restrict__ block_table,
+                                                   int max_pages, int64_t n_pages) {
+    extern __shared__ int s_len[];   // [min(B, kPlanCached)] lengths, then as many first slots
+    __shared__ int s_total, s_items, s_hist[66], s_pos[66], s_count[65];
     int* slot0 = (int*)(work + 1);
     int* nch = slot0 + B;
     AttnItem* items = (AttnItem*)(nch + B);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int* s_slot = s_len + min(B, kPlanCached);
+    auto total_of = [&](int b) { return max(b < kPlanCached ? s_len[b] : seq_len[b], 0) + n_region; };
+    auto tiles_of = [&](int b) { return (total_of(b) + kKT - 1) / kKT; };
+    auto slot_of = [&](int b) { return b < kPlanCached ? s_slot[b] : slot0[b]; };
     if (tid < 66) s_hist[tid] = 0;
-    // the grid and the item list were sized from the caller's length bound: a longer sequence would lose
-    // part of its context, which only the device can see
-    if (status)
-        for (int b = tid; b < B; b += 256)
-            if (seq_len[b] > len_bound) atomicOr(status, 1u);
+    if (tid < 65) s_count[tid] = 0;
+    if (tid == 0) s_total = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int b = tid; b < B; b += 256) {
+        const int len = seq_len[b];
+        if (b < kPlanCached) s_len[b] = len;
+        mine += (max(len, 0) + n_region + kKT - 1) / kKT;
+        // the grid and the item list were sized from the caller's length bound: a longer sequence would lose
+        // part of its context, which only the device can see
+        if (status && len > len_bound) atomicOr(status, 1u);
+    }
+    if (mine) atomicAdd(&s_total, mine);
+    __syncthreads();
     // A workgroup takes a whole CU (248 VGPRs per wave, 128 KB of LDS), so the work items run in rounds of
     // 256.  Measured at the 7B benchmark shape (attention ms per step): one round of 256 items 4.02, two
     // rounds 4.33, four 4.20, and 4.6-4.8 when the count falls between whole rounds (384, 768 items): the
-    // fewest whole rounds that the 64-tile cap on a chunk allows are the target.
-    __shared__ int s_count[65];   // items for every chunk size T = 8 .. 64 (one candidate per thread)
-    if (tid >= 8 && tid <= 64) {
-        int64_t items = 0;
-        for (int b = 0; b < B; ++b) items += ((max(seq_len[b], 0) + n_region + kKT - 1) / kKT + tid - 1) / tid;
-        s_count[tid] = (int)(items < 0x7fffffff / 64 ? items : 0x7fffffff / 64);
+    // fewest whole rounds that the 64-tile cap on a chunk allows are the target, and of the chunk sizes that
+    // fit them the smallest (items closest to filling the rounds).  Thread (t, part) counts the items of chunk size t.
+    {
+        const int t = (tid & 63) + 1;
+        int64_t items_t = 0;
+        if (t >= kMinTiles)
+            for (int b = wave; b < B; b += 4) items_t += (tiles_of(b) + t - 1) / t;
+        atomicAdd(&s_count[t], (int)(items_t < 0x7fffffff / 256 ? items_t : 0x7fffffff / 256));
     }
     __syncthreads();
-    if (tid == 0) {
-        // fewest rounds first; within a round count the smallest chunk size that fits (items closest to
-        // filling the rounds).  Ends at the latest when T = 64 fits, which some round count always allows.
-        int64_t total = 0;
-        for (int b = 0; b < B; ++b) total += (max(seq_len[b], 0) + n_region + kKT - 1) / kKT;
-        int64_t r = (total * heads + 256 * 64 - 1) / (256 * 64);
-        int T = 64;
-        for (r = r < 1 ? 1 : r;; ++r) {
-            bool found = false;
-            for (int t = 8; t <= 64 && !found; ++t)
-                if ((int64_t)s_count[t] * heads <= 256 * r) {
-                    T = t;
-                    found = true;
-                }
-            if (found) break;
-        }
-        s_T = T;
+    int T;
+    {
+        const int t = lane + 1;
+        const int rounds0 = (int)max(((int64_t)s_total * heads + 256 * 64 - 1) / (256 * 64), (int64_t)1);
+        const int rounds_t = t >= kMinTiles ? (int)(((int64_t)s_count[t] * heads + 255) / 256) : 0x7fffffff;
+        int r = max(rounds_t, 1);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) r = min(r, __shfl_xor(r, o, 64));
+        r = max(r, rounds0);
+        T = __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(rounds_t <= r));   // lane t - 1 stands for t
     }
-    __syncthreads();
-    if (tid == 0) {
+    // chunks of every sequence and the slots they take: running sums, 64 sequences at a time
+    if (wave == 0) {
         int acc = 0;
-        for (int b = 0; b < B; ++b) {
-            const int tiles = (max(seq_len[b], 0) + n_region + kKT - 1) / kKT;
-            const int k = (tiles + s_T - 1) / s_T;
-            slot0[b] = acc;
-            nch[b] = k;
-            acc += k;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+            const int b = b0 + lane, k = b < B ? (tiles_of(b) + T - 1) / T : 0;
+            int sum = k;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int up = __shfl_up(sum, o, 64);
+                if (lane >= o) sum += up;
+            }
+            if (b < B) {
+                slot0[b] = acc + sum - k, nch[b] = k;
+                if (b < kPlanCached) s_slot[b] = acc + sum - k;
+            }
+            acc += __shfl(sum, 63, 64);
         }
-        s_total = acc < max_items ? acc : max_items;   // cannot exceed the bound when seq_len respects the host's
-        work->n_items = s_total;
+        acc = acc < max_items ? acc : max_items;
+        if (lane == 0) work->n_items = s_items = acc;   // cannot exceed the bound when seq_len respects the host's
     }
     __syncthreads();
-    // counting sort by tile count, longest first
-    for (int b = tid; b < B; b += 256) {
-        const int total_b = max(seq_len[b], 0) + n_region;
-        const int tiles = (total_b + kKT - 1) / kKT, k = nch[b];
-        const int per = k > 0 ? (tiles + k - 1) / k : 0;
-        for (int j = 0; j < k; ++j) {
-            const int kb = j * per * kKT, ke = min(total_b, kb + per * kKT);
-            if (slot0[b] + j < max_items) atomicAdd(&s_hist[ke > kb ? (ke - kb + kKT - 1) / kKT : 0], 1);
+    // counting sort by tile count, longest first, a thread per item: the sequence is the last one whose slots start at or
+    // before it (one without chunks starts where the next one does)
+    struct Chunk { int b, kb, tiles; };
+    auto chunk_of = [&](int i) {
+        int lo = 0, hi = B;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (slot_of(mid) <= i) lo = mid; else hi = mid;
         }
+        const int tiles = tiles_of(lo), k = (tiles + T - 1) / T, per = (tiles + k - 1) / k, first = (i - slot_of(lo)) * per;
+        return Chunk{lo, first * kKT, max(min(per, tiles - first), 0)};
+    };
+    const int n_items = s_items;
+    for (int i = tid; i < n_items; i += 256) atomicAdd(&s_hist[chunk_of(i).tiles], 1);
+    __syncthreads();
+    if (wave == 0) {   // s_pos[t] = items longer than t
+        const int h = s_hist[64 - lane];
+        int sum = h;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(sum, o, 64);
+            if (lane >= o) sum += up;
+        }
+        s_pos[64 - lane] = sum - h;
+        if (lane == 63) s_pos[0] = sum;
     }
     __syncthreads();
-    if (tid == 0) {
-        int acc = 0;
-        for (int t = 65; t >= 0; --t) {
-            s_pos[t] = acc;
-            acc += s_hist[t];
+    for (int i = tid; i < n_items; i += 256) {
+        const Chunk c = chunk_of(i);
+        AttnItem it;
+        it.b = c.b, it.k_begin = c.kb, it.k_end = min(total_of(c.b), c.kb + c.tiles * kKT), it.slot = i;
+#pragma unroll
+        for (int q = 0; q < kAhead * kKT / 16; ++q) {
+            const int lp = c.kb / 16 + q;
+            const int pg = lp < max_pages && lp * 16 < it.k_end ? block_table[(int64_t)c.b * max_pages + lp] : -1;
+            it.page[q] = pg >= 0 && pg < n_pages ? pg : -1;
         }
-    }
-    __syncthreads();
-    for (int b = tid; b < B; b += 256) {
-        const int total_b = max(seq_len[b], 0) + n_region;
-        const int tiles = (total_b + kKT - 1) / kKT, k = nch[b];
-        const int per = k > 0 ? (tiles + k - 1) / k : 0;
-        for (int j = 0; j < k; ++j) {
-            const int kb = j * per * kKT, ke = min(total_b, kb + per * kKT);
-            if (slot0[b] + j >= max_items) continue;
-            const int pos = atomicAdd(&s_pos[ke > kb ? (ke - kb + kKT - 1) / kKT : 0], 1);
-            items[pos] = AttnItem{b, kb, ke, slot0[b] + j};
-        }
+        items[atomicAdd(&s_pos[c.tiles], 1)] = it;
     }
 }
 
@@ -328,13 +364,16 @@ template <int NT>
 __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, const uint16_t* __restrict__ qkv,
                                           float* __restrict__ part_o, float* __restrict__ part_ml,
                                           const AttnWork* __restrict__ work, int heads, int n_q_heads, int row_tiles,
-                                          int tiles_per_group, int r_pad, float scale_log2, float lazy_raw) {
+                                          int tiles_per_group, int r_pad, float scale_log2, float lazy_raw, int max_items) {
     constexpr int TPW = NT > 0 ? NT : 1;   // array extents (nothing is computed in them when NT = 0)
     extern __shared__ __align__(16) uint16_t lds[];
     int rank, kh, rg;
     attn_decode(blockIdx.x, heads, kv.n_kv, rank, kh, rg);
-    if (rank >= work->n_items) return;  // uniform
-    const AttnItem item = ((const AttnItem*)((const int*)(work + 1) + 2 * rows.B))[rank];
+    // (the item is requested together with the count, not after it: where the grid reaches past the list, entry 0 stands in)
+    const int n_items = work->n_items;
+    const AttnItem* item_p = (const AttnItem*)((const int*)(work + 1) + 2 * rows.B) + (rank < max_items ? rank : 0);
+    const AttnItem item = *item_p;
+    if (rank >= n_items) return;  // uniform
     const int b = item.b;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, g4 = lane >> 4;
@@ -388,41 +427,6 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
     const uint16_t* vpool = (const uint16_t*)kv.v;
     int32_t* page_ids = (int32_t*)(lds + kStages * kStageElems);
     uint64_t* mask_lds = (uint64_t*)(page_ids + kMaxChunk / 16 + 2);  // [n][2] visibility bits of this sequence's rows
-    {
-        for (int i = tid; i < n; i += 512) {
-            uint64_t m0 = 0, m1 = 0;
-            if (i < nv) {
-                if (rows.mask) {
-                    const uint64_t* mp = rows.mask + (int64_t)(b * n + i) * rows.mask_words;
-                    m0 = mp[0];
-                    m1 = rows.mask_words > 1 ? mp[1] : 0ull;
-                } else {  // causal within the new rows
-                    m0 = i >= 63 ? ~0ull : ((2ull << i) - 1ull);
-                    m1 = i < 64 ? 0ull : (i >= 127 ? ~0ull : ((2ull << (i - 64)) - 1ull));
-                }
-            }
-            mask_lds[2 * i] = m0;
-            mask_lds[2 * i + 1] = m1;
-        }
-        // page ids of this chunk, range-checked once (-1 = not backed by the block table)
-        const int first_page = k_begin / kv.page_size;
-        const int n_pg = (k_end - 1) / kv.page_size - first_page + 1;
-        int unbacked = 0;
-        for (int pi = tid; pi < n_pg; pi += 512) {
-            const int lp = first_page + pi;
-            int pg = lp < kv.max_pages ? kv.block_table[(int64_t)b * kv.max_pages + lp] : -1;
-            pg = (pg >= 0 && pg < kv.n_pages) ? pg : -1;
-            page_ids[pi] = pg;
-            unbacked |= pg < 0;
-        }
-        // slots whose DMA is skipped (unbacked pages: a caller error) must still hold finite values:
-        // only then is the ring zeroed first
-        if (__syncthreads_or(unbacked)) {
-            u32x4_t z = {0u, 0u, 0u, 0u};
-            for (int e = tid; e < kStages * kStageElems / 8; e += 512) *(u32x4_t*)(lds + e * 8) = z;
-        }
-    }
-    __syncthreads();
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const int n_tiles = (k_end - k_begin + kKT - 1) / kKT;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)lds;
@@ -451,7 +455,8 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
         d[3] = 0x00020000u;
         return d;
     };
-    auto issue_dma = [&](int tile, int stage) {
+    // page_of: page of the 16 keys that start at index 16 * i of the chunk
+    auto issue_dma = [&](int tile, int stage, auto page_of) {
         const int t0 = k_begin + tile * kKT;
         const int last = k_end - 1;
         int kb[2], pgv[2];
@@ -460,7 +465,7 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
             int k0 = t0 + (wave_u + 8 * e) * 4;             // first key of the 4-key block
             k0 = k0 <= last ? k0 : (last & ~3);             // blocks past the end re-read the last key's block
             kb[e] = k0;
-            pgv[e] = page_ids[(k0 - k_begin) >> 4];         // page_size is 16 for this kernel
+            pgv[e] = page_of((k0 - k_begin) >> 4);          // page_size is 16 for this kernel
         }
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
@@ -475,8 +480,52 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
             dma_buf_16(desc(vpool + off, size), row | cv[e], 0u, dst + kKT * kD * 2u);
         }
     };
+    // the first tiles' pages come with the work item: the fetches start before the masks and the block table are read (with
+    // the item asked for together with the count: 8.5 -> 8.1 us at one sequence of 8192, 53.7 -> 53.0 at 16, 16 nodes each)
+    auto first_tiles = [&]() {
 #pragma unroll
-    for (int st = 0; st < kAhead; ++st) issue_dma(st < n_tiles ? st : n_tiles - 1, st);
+        for (int st = 0; st < kAhead; ++st)
+            issue_dma(st < n_tiles ? st : n_tiles - 1, st, [&](int i) { return item_p->page[__builtin_amdgcn_readfirstlane(i)]; });
+    };
+    first_tiles();
+    {
+        for (int i = tid; i < n; i += 512) {
+            uint64_t m0 = 0, m1 = 0;
+            if (i < nv) {
+                if (rows.mask) {
+                    const uint64_t* mp = rows.mask + (int64_t)(b * n + i) * rows.mask_words;
+                    m0 = mp[0];
+                    m1 = rows.mask_words > 1 ? mp[1] : 0ull;
+                } else {  // causal within the new rows
+                    m0 = i >= 63 ? ~0ull : ((2ull << i) - 1ull);
+                    m1 = i < 64 ? 0ull : (i >= 127 ? ~0ull : ((2ull << (i - 64)) - 1ull));
+                }
+            }
+            mask_lds[2 * i] = m0;
+            mask_lds[2 * i + 1] = m1;
+        }
+        // page ids of this chunk, range-checked once (-1 = not backed by the block table)
+        const int first_page = k_begin / kv.page_size;
+        const int n_pg = (k_end - 1) / kv.page_size - first_page + 1;
+        int unbacked = 0;
+        for (int pi = tid; pi < n_pg; pi += 512) {
+            const int lp = first_page + pi;
+            int pg = lp < kv.max_pages ? kv.block_table[(int64_t)b * kv.max_pages + lp] : -1;
+            pg = (pg >= 0 && pg < kv.n_pages) ? pg : -1;
+            page_ids[pi] = pg;
+            unbacked |= pg < 0;
+        }
+        // slots whose DMA is skipped (unbacked pages: a caller error) must still hold finite values:
+        // only then is the ring zeroed, and the first tiles are fetched again
+        if (__syncthreads_or(unbacked)) {
+            __builtin_amdgcn_s_waitcnt(0x0F70u);
+            __syncthreads();
+            u32x4_t z = {0u, 0u, 0u, 0u};
+            for (int e = tid; e < kStages * kStageElems / 8; e += 512) *(u32x4_t*)(lds + e * 8) = z;
+            __syncthreads();
+            first_tiles();
+        }
+    }
 
     // Drain every load issued so far (Q fragments, table reads, the first DMAs) once, here, so that the
     // compiler's own wait bookkeeping enters the loop clean and adds no vmcnt(0) of its own inside it,
@@ -567,7 +616,7 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
     };
     auto tile_fetch = [&](int it) {
         const int nxt = it + kAhead;
-        issue_dma(nxt < n_tiles ? nxt : n_tiles - 1, nxt % kStages);
+        issue_dma(nxt < n_tiles ? nxt : n_tiles - 1, nxt % kStages, [&](int i) { return page_ids[i]; });
     };
     if (late) tile_wait(0);
     for (int it = 0; it < n_tiles; ++it) {
@@ -712,7 +761,7 @@ __global__ __launch_bounds__(512) void attn_mfma_k(Rows rows, KVLayer kv, const 
                                                    float* __restrict__ part_o, float* __restrict__ part_ml,
                                                    const AttnWork* __restrict__ work, int heads, int n_q_heads,
                                                    int row_tiles, int tiles_per_group, int r_pad, float scale_log2,
-                                                   float lazy_raw) {
+                                                   float lazy_raw, int max_items) {
     // row tiles of this wave that exist (tile indices rise with t, so they are the first n_on)
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int rank_, kh_, rg;
@@ -721,7 +770,7 @@ __global__ __launch_bounds__(512) void attn_mfma_k(Rows rows, KVLayer kv, const 
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
         n_on += ((wave + 8 * t) < tiles_per_group && rg * tiles_per_group + wave + 8 * t < row_tiles) ? 1 : 0;
-#define TLT_BODY(N) attn_body<N>(rows, kv, qkv, part_o, part_ml, work, heads, n_q_heads, row_tiles, tiles_per_group, r_pad, scale_log2, lazy_raw)
+#define TLT_BODY(N) attn_body<N>(rows, kv, qkv, part_o, part_ml, work, heads, n_q_heads, row_tiles, tiles_per_group, r_pad, scale_log2, lazy_raw, max_items)
     if (n_on >= TPW) TLT_BODY(TPW);
     else if (TPW >= 2 && n_on == TPW - 1) TLT_BODY((TPW >= 2 ? TPW - 1 : 0));
     else if (TPW >= 3 && n_on == TPW - 2) TLT_BODY((TPW >= 3 ? TPW - 2 : 0));
@@ -837,13 +886,14 @@ static hipError_t launch_attn_mfma(hipStream_t s, const Rows& rows, const KVLaye
     const int tiles_per_group = (p.row_tiles + p.row_groups - 1) / p.row_groups;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)kD);
     if (!reuse_plan)
-        hipLaunchKernelGGL(attn_plan_k, dim3(1), dim3(256), 0, s, kv.seq_len, rows.B, rows.n_region, p.heads, p.max_items, work,
-                           kv.seq_len_bound, status);
+        hipLaunchKernelGGL(attn_plan_k, dim3(1), dim3(256), 2 * sizeof(int) * (rows.B < kPlanCached ? rows.B : kPlanCached), s, kv.seq_len,
+                           rows.B, rows.n_region, p.heads, p.max_items, work, kv.seq_len_bound, status, kv.block_table, kv.max_pages,
+                           kv.n_pages);
     // (ids come in groups of 8 (item, kv head) pairs x row groups: see attn_decode)
     const int id_groups = (p.max_items * kv.n_kv + 7) / 8;
     hipLaunchKernelGGL(kern, dim3(id_groups * 8 * p.row_groups), dim3(512), lds, s, rows, kv, (const uint16_t*)qkv, part_o,
                        part_ml, work, p.heads, n_q_heads, p.row_tiles, tiles_per_group, p.r_pad, scale_log2,
-                       8.0f / scale_log2);
+                       8.0f / scale_log2, p.max_items);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int R = rows.n * (n_q_heads / kv.n_kv);

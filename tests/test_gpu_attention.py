@@ -22,6 +22,8 @@ pytestmark = pytest.mark.gpu
     (28, 4, 64, [2100, 5], 1),              # 448 rows: two row groups
     (4, 4, 1, [1, 16, 1000], 1),            # one row, one query head per kv head
     (14, 2, 8, [9000], 1),                  # one long sequence cut into many chunks
+    (28, 4, 1, [8191], 1),                  # one row: chunks of the shortest length, more than 16 of them
+    (4, 1, 2, [17 * (i % 9) for i in range(70)], 1),   # more sequences than a wave has lanes, many of one tile
 ])
 def test_attention_matches_oracle(Hq, Hkv, n, ctxs, impl):
     d, page = 128, 16
@@ -60,3 +62,27 @@ def test_attention_matches_oracle(Hq, Hkv, n, ctxs, impl):
                 visible[i, c + j] = bool((int(mask[b, i]) >> j) & 1)
         want = dec.attention(q[b], K, V, visible)
         assert rel_err(got[b], want) <= 2e-2, (b, rel_err(got[b], want))
+
+
+def test_attention_with_a_page_missing_from_the_table():
+    """A page the block table does not back (a caller's mistake), in a chunk's first tiles and in a later one: nothing is read
+    for it, that sequence's rows stay finite, and the other sequence is not touched."""
+    Hq, Hkv, n, d, page = 8, 2, 5, 128, 16
+    ctxs = np.array([900, 700], dtype=np.int32)
+    table, n_pages = random_block_table(ctxs + n + 8, page, seed=3, extra_pages=3)
+    broken = table.copy()
+    broken[0, 1], broken[0, 40] = -1, n_pages
+    k, v = fill_kv_pool(1, n_pages, Hkv, page, d, seed=9, dtype=torch.bfloat16)
+    qkv = torch.randn((2, n, (Hq + 2 * Hkv) * d), generator=torch.Generator().manual_seed(1)).bfloat16().cuda()
+    mask = torch.tensor([[(2 << i) - 1 for i in range(n)]] * 2, dtype=torch.int64).cuda()
+    outs = []
+    for t in (table, broken):
+        kv = tlt.KV(k[0].cuda(), v[0].cuda(), torch.from_numpy(t.astype(np.int32)).cuda(), torch.from_numpy(ctxs).cuda(), int(ctxs.max()))
+        out = torch.full((2, n, Hq * d), 7.0, dtype=torch.bfloat16, device="cuda")
+        ws = tlt.attention_workspace(2, n, Hq, Hkv, d, int(ctxs.max()) + n + 8)
+        print("attention, pages missing:", int((t < 0).sum() + (t >= n_pages).sum()), flush=True)
+        assert tlt.attention(tlt.TLT_BF16, Hq, page, qkv, mask, kv, out, ws, 1) == 0
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert torch.equal(outs[0][1], outs[1][1])
+    assert bool(torch.isfinite(outs[1][0]).all())
