@@ -114,7 +114,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
     constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;  // 1 KB DMA instructions per wave per tile: A part, W part
     constexpr int NR = WTM + WTN;                     // fragment reads per slice
     static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile rows must split evenly over the waves");
-    static_assert(LA % 2 == 0 && LB % 2 == 0 && WTM >= 2, "schedule: each operand's loads are split over two slices");
+    static_assert(LA % 2 == 0 && WTM >= 2, "schedule: each operand's loads are split over two slices");
     static_assert(SA >= 2 && SB >= 2, "at least double buffering");
     constexpr int RQ = (NR + WTM / 2 - 1) / (WTM / 2);   // fragment reads issued by each of the first WTM/2 MFMA rows
     // loads that may still be in flight when tile t+1 must be complete (issue order per step: W, then A)
@@ -123,7 +123,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
     constexpr int BNO = GLU ? BN / 2 : BN;            // output columns per workgroup
     // widths that do not divide the 128 columns every launch is a multiple of: the last column tile may be partial
     constexpr bool kPartialN = BNO % 64 != 0;
-    static_assert(!GLU || (NW % 2 == 0 && WTN % 2 == 0), "gate and up halves split over waves and over a wave's column tiles");
+    static_assert(!GLU || NW % 2 == 0, "gate and up halves split over waves");
+    // GLU with an odd number of column tiles: each is 16 gate rows and the 16 up rows that belong to them (else a wave's
+    // first column tiles are gate rows, as many up rows follow)
+    constexpr bool kMixed = GLU && WTN % 2 != 0;
+    static_assert(!kMixed || (WGN == 1 && BNO % 16 == 0), "one wave across the columns, swizzle of the up half as the gate half's");
     extern __shared__ __align__(16) uint16_t lds[];   // SA A slots, then SB W slots
 
     // Persistent workgroups: XCD x (ids are dealt round-robin over the XCDs) owns the logical tiles
@@ -307,10 +311,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
     const int fragA = (wm * (WTM * 32) + l32) * BKS;
     // tile row of column tile j of this wave (GLU: j < WTN/2 are gate rows, the rest the matching up rows)
     auto colrow = [&](int j) {
-        return GLU ? (j / (WTN / 2)) * (BN / 2) + (j % (WTN / 2)) * 32 : j * 32;
+        return kMixed ? j * 16 : GLU ? (j / (WTN / 2)) * (BN / 2) + (j % (WTN / 2)) * 32 : j * 32;
     };
-    const int fragB = ((GLU ? wn * (WTN / 2 * 32) : wn * (WTN * 32)) + l32) * BKS;
-    const int sw = (l32 >> 1) & 7;
+    const int fragB = (kMixed ? (l32 & 15) + (l32 >> 4) * (BN / 2) : (GLU ? wn * (WTN / 2 * 32) : wn * (WTN * 32)) + l32) * BKS;
+    const int sw = (l32 >> 1) & 7;   // (rows 16 apart, and the two halves, share their swizzle)
 
     bf16x8_t fa[2][WTM], fb[2][WTN];
     // read q of a slice's NR fragment reads: the W fragments first (every MFMA row needs them all)
@@ -356,7 +360,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
             // the first slice's fragments were requested a whole slice ago; waiting here, before the next
             // reads are issued, keeps the compiler from waiting for those as well
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            TLT_SLICE(0, pa, pb, 1, 1, pb_, LB / 2, LB / 2)           // W cursor, second half
+            TLT_SLICE(0, pa, pb, 1, 1, pb_, LB / 2, LB - LB / 2)      // W cursor, second half
             advance_b();
             TLT_SLICE(1, pa, pb, 2, 0, pa_, 0, LA / 2)                // A cursor, first half
             TLT_SLICE(0, pa, pb, 3, 0, pa_, LA / 2, LA / 2)           //           second half
@@ -424,6 +428,35 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
                     C2[o] = bi[e];
                 }
             }
+        } else if constexpr (kMixed && OUT == OUT_T) {
+            // Lanes l and l + 16 of a half-wave hold gate and up of one column.  Swapping the odd 16-lane rows of one
+            // accumulator with the even ones of the next gives both to one lane: the lower lane row v, the upper one
+            // row v + 1.  Neighbouring lanes then trade a value, so that each stores two adjacent columns.
+            const int odd16 = (l32 >> 4) & 1, odd = lane & 1;
+#pragma unroll
+            for (int i = 0; i < WTM; ++i)
+#pragma unroll
+                for (int jj = 0; jj < WTN; ++jj)
+#pragma unroll
+                    for (int vq = 0; vq < 4; ++vq) {
+                        float r[2];
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            float x0, x1;   // (see below: out of their registers here, not all at once)
+                            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x0) : "a"(acc[i][jj][4 * vq + 2 * e]));
+                            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x1) : "a"(acc[i][jj][4 * vq + 2 * e + 1]));
+                            const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+                            const float g = __uint_as_float(p[0]), u = __uint_as_float(p[1]);
+                            r[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+                        }
+                        // r[0]: row 4 vq + odd16, r[1]: two rows on; even lanes keep the first, odd ones the second
+                        const float other = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(odd ? r[0] : r[1]), 0xB1, 0xF, 0xF, false));
+                        const uint32_t out = odd ? pack_bf16x2(other, r[1]) : pack_bf16x2(r[0], other);
+                        const int row = ti.m0 + wm * (WTM * 32) + i * 32 + 8 * vq + 4 * lhi + 2 * odd + odd16;
+                        const int col0 = ti.n0 + jj * 16;   // (ncols is a multiple of 16: a block is valid or not as a whole)
+                        if (row < M && (!kPartialN || col0 < ncols)) *(uint32_t*)((bf16*)C + (int64_t)row * N + col0 + (l32 & 14)) = out;
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
         } else if constexpr (GLU && OUT == OUT_T) {
             // A lane holds one column of four consecutive rows (v = 4 vq .. 4 vq + 3) of each 32x32 block: stored
             // as they lie, that is 2 bytes per lane and store instruction, and the tile's 512 of those cost
@@ -993,14 +1026,15 @@ static hipError_t launch_tiled(hipStream_t s, int out_mode, int M, int N, int K,
             void* c = (char*)C + (size_t)main_tiles * 256 * c_elt;
             return launch_pipe<2, 2, 4, 2, 3, 4, false, true>(s, out_mode, M, N - main_tiles * 256, K, A, w, c, nullptr, 1, N);
         }
-        // gate/up with well under a round of big tiles: 256 rows x 96 output columns per workgroup (four waves of
-        // 64 rows x 3 + 3 column blocks, the last tile partial) puts the weights on 4/3 as many CUs.  A CU pulls cold
-        // weights at ~35 GB/s at most, however many loads it keeps in flight, and the activation rows that every
-        // workgroup re-reads from L2 go through the same path, so the gain is less than the 4/3: best of four
-        // interleaved runs on cold weights, M = 144 .. 256: 7B shape (148 -> 198 tiles) 84-86 -> 80-82 us, N = 13824,
-        // K = 5120 (108 -> 144) 111 -> 102-104; with 192 -> 256 tiles (N = 24576) 102-105 -> 102-110, so not there
-        if (glu && tiles256 <= 160 && (N + 95) / 96 <= 256)
-            return launch_pipe<4, 1, 2, 6, 3, 2, true, true>(s, OUT_T, M, N, K, A, W, C, W2, 1, N);
+        // gate/up with well under a round of big tiles: 256 rows x 80 output columns per workgroup (four waves of
+        // 64 rows x 5 column blocks of 16 gate and 16 up rows, the last tile partial) puts the weights on nearly all CUs, and the
+        // narrower tile leaves room for a third weight slot.  A CU pulls cold weights at ~35 GB/s at most, however many loads
+        // it keeps in flight, and the activation rows that every workgroup re-reads from L2 go through the same path.
+        // Against 96 columns with two slots (three alternating runs on cold weights, M = 129 .. 256): 7B shape (198 -> 237
+        // tiles) 77-79 -> 64-69 us, N 13824, K 5120 97-99 -> 80-85, N 20480, K 4096 88-93 -> 75-82.  Past 160 big tiles 80
+        // columns would make more than a round (and 96 there gain nothing over the big tiles: N = 24576 102-105 -> 102-110).
+        if (glu && tiles256 <= 160)
+            return launch_pipe<4, 1, 2, 5, 3, 3, true, true>(s, OUT_T, M, N, K, A, W, C, W2, 1, N);
         return big(N);
     }
     // up to 128 rows: half of a 256-row tile would be padding, and the LDS it frees holds a third weight slot

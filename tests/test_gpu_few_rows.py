@@ -53,7 +53,9 @@ def test_fp32_forward(n, ctxs, mlp):
     (31, 24704, 128), (64, 28672, 192),         # 112 columns
     (65, 12416, 384), (128, 16384, 64),         # above 64 rows: two groups of waves, 64 columns
     (97, 16512, 320), (128, 20608, 128),        # 80 and 96 columns, partial last tiles
-    (64, 14336, 128), (66, 640, 128), (100, 24704, 64), (129, 16512, 64),   # beside the ranges: the tiled kernel
+    (64, 14336, 128), (66, 640, 128), (100, 24704, 64),       # beside the ranges: the tiled kernel
+    (129, 16512, 64), (200, 12800, 448), (256, 20480, 192),   # 256 rows x 80 columns, gate and up rows in turns of 16
+    (250, 20608, 192),                                        # one more column tile: 256x256 tiles
 ])
 def test_bf16_gate_up(M, N, K):
     g = torch.Generator().manual_seed(M + N + K)
