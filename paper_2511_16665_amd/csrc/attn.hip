@@ -5,16 +5,18 @@
 // tree node; a causal prefix for chains).
 //
 // impl 0 ("wave-per-row"): one workgroup of four wavefronts per (row, query head), each wave taking every fourth tile
-//   of 64 keys; lanes own keys for the score pass and head dimensions for the value pass; online softmax across a wave's
+//   of 64 keys; lanes own keys for the score pass and pieces of value rows for the value pass; online softmax across a wave's
 //   tiles, the waves merged at the end.  Any dtype, any head_dim that is a multiple of 64 up to 256.  Used for fp32
-//   mode and as a cross-check.  Bound by load latency: keys are read in 16-byte pieces, the values of 16 keys at a time
-//   (4 heads of 64, 130 keys: 40 us with one wave and 4-byte loads, one after the other -> 14).
+//   mode and as a cross-check.  Bound by load latency: a key's elements are requested 64 together, values by rows spread
+//   over the lanes, 16 rows of every lane group together (4 heads of 64, 130 keys: 40 us with one wave and 4-byte loads, one
+//   after the other; 13.7 with four waves, 16-byte key loads and 16 keys' values at a time; 7.6 this way).
 // impl 1 ("MFMA split-KV"): the bf16 / head_dim 128 production kernel, described further down.
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace tlt {
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;   // 16-byte register vector
 constexpr int kRowWaves = 4;   // waves of impl 0's workgroup (64 * kRowWaves covers the largest head_dim)
 
 __device__ __forceinline__ bool region_visible(const Rows& rows, int r, int i, int j) {
@@ -24,12 +26,21 @@ __device__ __forceinline__ bool region_visible(const Rows& rows, int r, int i, i
     return (w >> (j & 63)) & 1ull;
 }
 
+// element e of a 16-byte piece
+template <typename T>
+__device__ __forceinline__ float element(u32x4_t v, int e) {
+    if constexpr (sizeof(T) == 4) return __uint_as_float(v[e]);
+    else return __uint_as_float((e & 1) ? v[e >> 1] & 0xffff0000u : v[e >> 1] << 16);
+}
+
 template <typename T>
 __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows, KVLayer kv, const T* __restrict__ qkv,
                                                                       T* __restrict__ out, int n_q_heads, float scale) {
-    constexpr int VEC = 16 / sizeof(T), kU = 16;
-    __shared__ __align__(16) float q_s[256];
-    __shared__ float o_s[kRowWaves][256], m_s[kRowWaves], l_s[kRowWaves];
+    typedef u32x4_t __attribute__((aligned(2))) piece_t;   // (a caller's pool may start at any element: one load all the same)
+    constexpr int VEC = 16 / sizeof(T), kU = 16, kGroups = 64 * VEC / 64;   // (groups: at head_dim 64, the smallest)
+    __shared__ __align__(16) float q_s[256], o_s[kRowWaves][kGroups][256];
+    __shared__ float m_s[kRowWaves], l_s[kRowWaves], p_s[kRowWaves][64];
+    __shared__ int64_t base_s[kRowWaves][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
     const int r = b * rows.n + i;
@@ -47,8 +58,12 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows,
     __syncthreads();
     const T* kc = (const T*)kv.k;
     const T* vc = (const T*)kv.v;
+    // values: d / VEC lanes read a key's row in 16-byte pieces, so the wave's lanes hold `groups` keys at a time
+    const int lpk = d / VEC, groups = 64 / lpk, grp = lane / lpk, piece = (lane - grp * lpk) * VEC;
     float m = -INFINITY, l = 0.f;
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    float acc[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
     for (int t0 = 64 * wave; t0 < total; t0 += 64 * kRowWaves) {
         const int key = t0 + lane;
         bool vis = key < total && (key < ctx || region_visible(rows, r, i, key - ctx));
@@ -60,12 +75,14 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows,
         if (!vis) base = 0;   // (row 0 of the pool: its weight below is zero)
         float s = 0.f;
         const T* kp = kc + base;
-#pragma unroll 8
-        for (int c = 0; c < d; c += VEC) {
-            T kk[VEC];
-            *(uint4*)kk = *(const uint4*)(kp + c);
+        for (int c0 = 0; c0 < d; c0 += 64) {   // (a key's 64 elements requested together)
+            u32x4_t kk[64 / VEC];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) s = fmaf(q_s[c + e], to_float(kk[e]), s);
+            for (int c = 0; c < 64 / VEC; ++c) kk[c] = *(const piece_t*)(kp + c0 + c * VEC);
+#pragma unroll
+            for (int c = 0; c < 64 / VEC; ++c)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) s = fmaf(q_s[c0 + c * VEC + e], element<T>(kk[c], e), s);
         }
         if (!vis) s = -INFINITY;
         const float m_new = fmaxf(m, wave_max(s));
@@ -75,28 +92,33 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows,
         l = l * corr + wave_sum(p);
         m = m_new;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] *= corr;
+        for (int e = 0; e < VEC; ++e) acc[e] *= corr;
+        p_s[wave][lane] = p;       // (read back by the same wave only)
+        base_s[wave][lane] = base;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         const int nk = min(64, total - t0);
-        for (int k0 = 0; k0 < nk; k0 += kU) {   // (kU keys' loads in flight; keys past nk have weight zero and read row 0)
-            float pk[kU], vv[kU][4];
+        for (int k0 = 0; k0 < nk; k0 += kU * groups) {   // (kU rows per lane in flight; keys past nk have weight zero and read row 0)
+            u32x4_t vv[kU];
+            float pk[kU];
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                pk[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), k0 + u));
-                const int64_t bk = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, k0 + u) |
-                                   (int64_t)__builtin_amdgcn_readlane((int)(base >> 32), k0 + u) << 32;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) vv[u][t] = lane + 64 * t < d ? to_float(vc[bk + lane + 64 * t]) : 0.f;
+                const int k = k0 + u * groups + grp;
+                const bool on = k < 64 && grp < groups;
+                pk[u] = on ? p_s[wave][k] : 0.f;
+                vv[u] = *(const piece_t*)(vc + (on ? base_s[wave][k] : 0) + (on ? piece : 0));
             }
 #pragma unroll
             for (int u = 0; u < kU; ++u)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) acc[t] = pk[u] != 0.f ? fmaf(pk[u], vv[u][t], acc[t]) : acc[t];
+                for (int e = 0; e < VEC; ++e) acc[e] = pk[u] != 0.f ? fmaf(pk[u], element<T>(vv[u], e), acc[e]) : acc[e];
         }
+        __builtin_amdgcn_wave_barrier();
     }
-    // the waves' partial results, merged in wave order
+    // the partial results, merged in wave and group order
+    if (grp < groups)
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-        if (lane + 64 * t < d) o_s[wave][lane + 64 * t] = acc[t];
+        for (int e = 0; e < VEC; ++e) o_s[wave][grp][piece + e] = acc[e];
     if (lane == 0) {
         m_s[wave] = m;
         l_s[wave] = l;
@@ -111,7 +133,9 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows,
     for (int w = 0; w < kRowWaves; ++w) {
         const float f = m_s[w] == -INFINITY ? 0.f : expf(m_s[w] - mm);
         ll += f * l_s[w];
-        a += f * o_s[w][threadIdx.x];
+        float o_w = 0.f;
+        for (int g = 0; g < groups; ++g) o_w += o_s[w][g][threadIdx.x];
+        a += f * o_w;
     }
     o[threadIdx.x] = from_float<T>(ll > 0.f ? a / ll : 0.f);
 }
@@ -140,7 +164,6 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows,
 // second kernel merges the chunks.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;
 
 // max over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48) without going through the LDS
 // crossbar: v_permlane32_swap / v_permlane16_swap exchange half-waves / odd and even 16-lane rows of

@@ -83,3 +83,10 @@ def test_bf16_gate_up(M, N, K):
 def test_bf16_forward_few_rows(hidden, heads, n):
     cfg = dataclasses.replace(MID, name=f"mid-h{hidden}", hidden=hidden, n_q_heads=heads, n_kv_heads=4, mlp=3072, vocab=512, n_layers=1)
     _verify_matches_oracle(cfg, "bf16", 2e-2, n, [70], 0.02, -1)
+
+
+@pytest.mark.parametrize("dtype,d", [("fp32", 64), ("fp32", 192), ("fp32", 256), ("bf16", 64), ("bf16", 192)])
+def test_row_attention_head_dims(dtype, d):
+    """Value rows spread over the lanes: 4, 1 (with idle lanes), 1, 8 and 2 rows (with idle lanes) at a time."""
+    cfg = dataclasses.replace(TINY, name=f"tiny-d{d}", head_dim=d, hidden=512, mlp=768)
+    _verify_matches_oracle(cfg, dtype, 1e-4 if dtype == "fp32" else 2e-2, 7, [0, 61, 65, 330], 0.05, 0)

@@ -173,7 +173,7 @@ def test_fused_row_argmax_refuses_shapes_it_does_not_cover():
 def test_fused_gate_up_projection_matches_float64(M, N, K):
     """tlt_gemm_glu: silu(A Wg^T) * (A Wu^T) in one kernel (256-row weight tiles for the whole rounds of
     the chip, 128-row tiles for the rest, ragged M tail; one row of 128x256 or 256x256 tiles when M is small, or
-    of tiles 96 output columns wide, the last of them partial: 18944 = 197 x 96 + 32, 12928 = 134 x 96 + 64),
+    of tiles 80 output columns wide, the last of them partial: 18944 = 236 x 80 + 64, 12928 = 161 x 80 + 48),
     against float64 on sampled rows."""
     g = torch.Generator().manual_seed(M + K)
     A = torch.randn((M, K), generator=g).bfloat16()
