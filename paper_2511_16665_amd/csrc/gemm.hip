@@ -690,6 +690,15 @@ constexpr int kF32FewRows = 256;
 static bool f32_few_ok(int M, int K, const void* A, const void* W, const void* W2 = nullptr) {
     return M <= kF32FewRows && K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W | (uintptr_t)W2) & 15) == 0;
 }
+// Where the 64x64 tiles are many, no workgroup waits for the others any more and they share their rows through LDS: from
+// 1500 of them above 96 rows, and from 512 above 32 rows where K is one step of a wave (us, few-row and tiled kernel on the same
+// buffers: M 256, N 152064, K 896: 1875 and 1506; M 256, N 32000, K 2048: 803 and 724; M 160, N 152064, K 64: 159 and 92; on the
+// other side M 256, N 16000, K 896: 184 and 203; M 65, N 64000, K 256: 79 and 95).  The fused gate/up
+// product saves an activation kernel besides and stays (M 256, N 32768, K 896: 582 against two products of 341).
+static bool f32_tiles_pay(int M, int N, int K) {
+    const int64_t tiles = (int64_t)((N + 63) / 64) * ((M + 63) / 64);
+    return M > 32 && (K <= 64 ? tiles >= 512 : M > 96 && tiles >= 1500);
+}
 template <int T>
 static hipError_t launch_f32_few_t(hipStream_t s, int out_mode, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
     const dim3 grid((N + 15) / 16, (M + 16 * T - 1) / (16 * T)), block(256);
@@ -1143,7 +1152,8 @@ static bool pipe_ok(int N, int K, const void* A, const void* W) {
 hipError_t gemm(hipStream_t s, int dtype, int out_mode, int M, int N, int K, const void* A, const void* W, void* C) {
     if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
     if (dtype == F32)
-        return f32_few_ok(M, K, A, W) ? launch_f32_few(s, out_mode, M, N, K, A, W, nullptr, C) : launch_generic<float>(s, out_mode, M, N, K, A, W, C);
+        return f32_few_ok(M, K, A, W) && !f32_tiles_pay(M, N, K) ? launch_f32_few(s, out_mode, M, N, K, A, W, nullptr, C)
+                                                                 : launch_generic<float>(s, out_mode, M, N, K, A, W, C);
     if (pipe_ok(N, K, A, W)) {
         // (accumulating into C: the K splits add their partial sums with fp32 atomics, in any order, so the
         // last bit of the result is not fixed.  The step itself uses gemm_parts, which is reproducible.)

@@ -35,6 +35,25 @@ def test_fp32_product(M, N, K, out_mode):
     assert bool(((out.cpu().double() - want).abs() <= bound).all())
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (97, 48000, 256), (193, 24000, 132),    # 1500 tiles of 64x64, the fewest that go there
+    (33, 32768, 64), (160, 10881, 64),      # K of 64: 512 and 513 of them
+])
+def test_fp32_wide_product_takes_the_tiled_kernel(M, N, K):
+    """Where the 64x64 tiles are the faster ones: the same bits as from operands that are not 16-byte aligned, which the few-row
+    kernel never takes (it adds up K in another order)."""
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    A, W = (torch.randn(s, generator=g, device="cuda") for s in ((M, K), (N, K)))
+    shifted = torch.empty(M * K + 1, device="cuda")[1:].view(M, K)
+    shifted.copy_(A)
+    out, want = (torch.empty((M, N), device="cuda") for _ in range(2))
+    print(f"wide fp32 product M={M} N={N} K={K}", flush=True)
+    tlt.gemm(tlt.TLT_F32, 1, A, W, out)
+    tlt.gemm(tlt.TLT_F32, 1, shifted, W, want)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+
+
 @pytest.mark.parametrize("n,ctxs,mlp", [
     (1, [0, 600], 84),          # one row; key tiles of a wave before and after the first round; a ragged MLP width
     (16, [63, 64, 257], 20),    # 48 rows
