@@ -883,11 +883,16 @@ static hipError_t launch_few(hipStream_t s, int M, int N, int K, const void* A, 
 // ones (N 14336, K 4096: 45.5 against 46.5); eight leave too few slots (N 32768, K 8192: 169 against 197).  Above 64
 // rows, the narrow widths lose to 128x128 tiles (N 8960, K 1536, M = 100: 19.3 against 21.5), and more than
 // six do not fit the registers.
-static int few_glu_width(int M, int N) {
+// The four slices' sums meet in LDS, 32 rows at a time, which few K steps do not pay for: the more rows and the wider the tile, the
+// longer K has to be (us, this kernel and the tiled one on the same buffers: M 128, N 18944: K 512 17.8 and 14.5, K 2048 40.9
+// and 40.0, K 3584 56.3 and 63.2; M 64, N 11008: K 512 9.8 and 9.3, K 1024 even, K 2048 23.8 and 24.0; M 64, N 28672: K 2048 56.2 and
+// 52.4, K 3584 67.5 and 71.7; two blocks, or up to 32 rows and six, gain from K = 256 on).
+static int few_glu_width(int M, int N, int K) {
     int wtn = 2;
     while ((N + 16 * wtn - 1) / (16 * wtn) > 256) ++wtn;
-    if (M <= 64) return wtn == 4 || wtn > 7 ? 0 : wtn;
-    return M > 128 || wtn < 4 || wtn > 6 ? 0 : wtn;
+    if (M > 128 || wtn > 7 || (M <= 64 ? wtn == 4 : wtn < 4 || wtn > 6)) return 0;
+    const int k_min = M <= 32 ? (wtn < 7 ? 0 : 512) : M <= 64 ? (wtn == 2 ? 0 : wtn < 7 ? 1024 : 2560) : (wtn == 4 ? 512 : 2560);
+    return K < k_min ? 0 : wtn;
 }
 static hipError_t launch_few_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
 #define TLT_FEW(g, m, n) if (M <= 32 * g * m && wtn == n) return launch_few<g, m, n, true>(s, M, N, K, A, W, W2, C);
@@ -1274,7 +1279,7 @@ bool gemm_glu_supported(int dtype, int M, int N, int K, const void* A, const voi
 // act[M][N] = silu(A Wg^T) * (A Wu^T), dtype in and out; call only when gemm_glu_supported().
 hipError_t gemm_glu(hipStream_t s, int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
     if (dtype == F32) return launch_f32_few(s, OUT_F32, M, N, K, A, Wg, Wu, act);
-    if (const int wtn = few_glu_width(M, N)) return launch_few_glu(s, wtn, M, N, K, A, Wg, Wu, act);
+    if (const int wtn = few_glu_width(M, N, K)) return launch_few_glu(s, wtn, M, N, K, A, Wg, Wu, act);
     return launch_tiled(s, OUT_T, M, N, K, A, Wg, Wu, act, true);
 }
 

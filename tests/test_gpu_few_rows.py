@@ -66,12 +66,14 @@ def test_fp32_forward(n, ctxs, mlp):
 
 @pytest.mark.parametrize("M,N,K", [
     (1, 640, 256), (32, 8192, 64),              # 32 columns per workgroup; one K step, fewer than the ring has slots
-    (17, 8320, 192), (33, 12288, 576),          # 48 columns, partial last tile; K steps past one turn of the ring
-    (32, 16512, 64), (64, 20480, 448),          # 80 columns
-    (5, 20608, 128), (40, 24576, 64),           # 96 columns
-    (31, 24704, 128), (64, 28672, 192),         # 112 columns
-    (65, 12416, 384), (128, 16384, 64),         # above 64 rows: two groups of waves, 64 columns
-    (97, 16512, 320), (128, 20608, 128),        # 80 and 96 columns, partial last tiles
+    (17, 8320, 192), (33, 12288, 1088),         # 48 columns, partial last tile; K steps past one turn of the ring
+    (32, 16512, 64), (64, 20480, 1024),         # 80 columns
+    (5, 20608, 128), (40, 24576, 1024),         # 96 columns
+    (31, 24704, 512), (64, 28672, 2560),        # 112 columns
+    (65, 12416, 512), (128, 16384, 576),        # above 64 rows: two groups of waves, 64 columns
+    (97, 16512, 2560), (128, 20608, 2624),      # 80 and 96 columns, partial last tiles
+    (33, 12288, 576), (64, 20480, 448), (40, 24576, 64), (31, 24704, 128), (64, 28672, 192),   # K too short for it: the tiled kernel
+    (65, 12416, 384), (128, 16384, 64), (97, 16512, 320), (128, 20608, 128),
     (64, 14336, 128), (66, 640, 128), (100, 24704, 64),       # beside the ranges: the tiled kernel
     (129, 16512, 64), (200, 12800, 448), (256, 20480, 192),   # 256 rows x 80 columns, gate and up rows in turns of 16
     (250, 20608, 192),                                        # one more column tile: 256x256 tiles
@@ -92,6 +94,21 @@ def test_bf16_gate_up(M, N, K):
     bound = (1.1 * sum_err * (Ad.abs() @ Wd.abs().T) * up.abs() + torch.nn.functional.silu(gate).abs() * sum_err * (Ad.abs() @ Ud.abs().T)
              + want.abs() * (2.0 ** -8 + (8 + gate.abs()) * 2.0 ** -22) + 1e-30)
     assert bool(((act.double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 8320, 960), (64, 24576, 960), (32, 28672, 448), (64, 28672, 2496), (65, 13824, 448), (128, 18944, 2496)])
+def test_bf16_gate_up_with_short_k_takes_the_tiled_kernel(M, N, K):
+    """One K step less than the few-row kernel asks for: the same bits as the first rows of a product of 300 rows (the tiled kernels
+    all add up K in one order, the few-row kernel in four)."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((300, K), generator=g, device="cuda").bfloat16()
+    W, U = ((torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16() for _ in range(2))
+    act, want = (torch.empty((m, N), dtype=torch.bfloat16, device="cuda") for m in (M, 300))
+    print(f"gate/up M={M} N={N} K={K} and 300 rows", flush=True)
+    assert tlt.gemm_glu(A[:M].contiguous(), W, U, act) == 0
+    assert tlt.gemm_glu(A, W, U, want) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(act, want[:M])
 
 
 @pytest.mark.parametrize("hidden,heads,n", [
