@@ -286,6 +286,11 @@ int tlt_gemm(void *stream, int dtype, int out_mode, int M, int N, int K, const v
  * covered (N % 128, K % 64, operands not 16-byte aligned, act not 8-byte aligned). */
 int tlt_gemm_glu(void *stream, int M, int N, int K, const void *A, const void *Wg, const void *Wu, void *act);
 
+/* A W^T of bf16 DEVICE operands as the decoder block keeps it for its next kernel: parts[0 .. *n_parts - 1][M][N], fp32 partial
+ * products over consecutive ranges of K, whose sum in that order is the product.  *n_parts (HOST) follows from the shape and the
+ * room.  parts: DEVICE, 16-byte aligned, room for at least one slice (TLT_ESHAPE) and used as far as parts_bytes allows. */
+int tlt_gemm_parts(void *stream, int M, int N, int K, const void *A, const void *W, float *parts, size_t parts_bytes, int *n_parts);
+
 /* Measurement aid (no step of the decoding path): the rate the matrix pipes sustain with nothing else running.
  * 256 workgroups of four waves; every wave repeats, `iters` times, the 64 matrix instructions (32x32x16, bf16 in,
  * fp32 accumulation) that a 128x128 wave tile of the GEMM kernels issues per 64-wide K tile, in those kernels'

@@ -26,7 +26,7 @@ EXPORTS = [
     "tlt_tree_finalize", "tlt_verify_forward", "tlt_accept", "tlt_kv_commit", "tlt_gemm", "tlt_set_attention_impl",
     "tlt_profile_begin", "tlt_profile_read", "tlt_mab_create", "tlt_mab_destroy", "tlt_mab_select", "tlt_mab_record",
     "tlt_mab_median_reward", "tlt_ngram_create", "tlt_ngram_destroy", "tlt_ngram_insert", "tlt_ngram_propose",
-    "tlt_template_build", "tlt_draft_sample", "tlt_gemm_argmax", "tlt_gemm_glu", "tlt_draft_pool", "tlt_set_oproj_rounding", "tlt_device_status", "tlt_accept_sample_static", "tlt_attention", "tlt_attention_workspace_bytes",
+    "tlt_template_build", "tlt_draft_sample", "tlt_gemm_argmax", "tlt_gemm_glu", "tlt_gemm_parts", "tlt_draft_pool", "tlt_set_oproj_rounding", "tlt_device_status", "tlt_accept_sample_static", "tlt_attention", "tlt_attention_workspace_bytes",
     "tlt_graph_pool_create", "tlt_graph_pool_destroy", "tlt_graph_pool_step", "tlt_graph_pool_count", "tlt_mfma_stream",
 ]
 
@@ -110,6 +110,7 @@ def load() -> C.CDLL:
     lib.tlt_kv_commit.argtypes = [C.c_void_p, C.c_void_p, C.c_int, C.POINTER(KVC), C.c_void_p, C.c_void_p, C.c_int]
     lib.tlt_gemm.argtypes = [C.c_void_p] + [C.c_int] * 5 + [C.c_void_p] * 3
     lib.tlt_gemm_glu.argtypes = [C.c_void_p] + [C.c_int] * 3 + [C.c_void_p] * 4
+    lib.tlt_gemm_parts.argtypes = [C.c_void_p] + [C.c_int] * 3 + [C.c_void_p] * 3 + [C.c_size_t, C.POINTER(C.c_int)]
     lib.tlt_gemm_argmax.argtypes = [C.c_void_p] + [C.c_int] * 3 + [C.c_void_p] * 3 + [C.c_size_t, C.c_void_p]
     lib.tlt_mfma_stream.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int]
     lib.tlt_set_attention_impl.argtypes = [C.c_void_p, C.c_int]
@@ -474,6 +475,17 @@ def gemm_glu(A, Wg, Wu, act):
     """act = silu(A Wg^T) * (A Wu^T) for bf16 device tensors A [M, K], Wg/Wu [N, K], act [M, N]; returns the code."""
     M, K = A.shape
     return load().tlt_gemm_glu(_stream(), M, Wg.shape[0], K, _ptr(A), _ptr(Wg), _ptr(Wu), _ptr(act))
+
+
+def gemm_parts(A, W, parts):
+    """tlt_gemm_parts: A [M, K], W [N, K] bf16, parts a flat fp32 device tensor; returns the slices [n_parts, M, N] written to it."""
+    M, K = A.shape
+    N = W.shape[0]
+    n = C.c_int()
+    rc = load().tlt_gemm_parts(_stream(), M, N, K, _ptr(A), _ptr(W), _ptr(parts), parts.numel() * 4, C.byref(n))
+    if rc:
+        raise TltError(rc, "tlt_gemm_parts")
+    return parts[:n.value * M * N].view(n.value, M, N)
 
 
 def mfma_stream(frags, out, iters):

@@ -920,6 +920,12 @@ int tlt_gemm_glu(void* stream, int M, int N, int K, const void* A, const void* W
     return gemm_glu((hipStream_t)stream, TLT_BF16, M, N, K, A, Wg, Wu, act) == hipSuccess ? TLT_OK : TLT_EHIP;
 }
 
+int tlt_gemm_parts(void* stream, int M, int N, int K, const void* A, const void* W, float* parts, size_t parts_bytes, int* n_parts) {
+    if (M < 1 || N < 1 || K < 1 || !A || !W || !parts || !n_parts || ((uintptr_t)parts & 15) != 0) return TLT_EINVAL;
+    if (parts_bytes < (size_t)M * N * 4) return TLT_ESHAPE;
+    return gemm_parts((hipStream_t)stream, TLT_BF16, M, N, K, A, W, parts, parts_bytes, n_parts) == hipSuccess ? TLT_OK : TLT_EHIP;
+}
+
 int tlt_gemm_argmax(void* stream, int M, int N, int K, const void* A, const void* W, void* ws, size_t ws_bytes,
                     int32_t* out) {
     if (M < 1 || N < 1 || K < 1 || !A || !W || !ws || !out) return TLT_EINVAL;

@@ -904,8 +904,16 @@ static hipError_t launch_few_glu(hipStream_t s, int wtn, int M, int N, int K, co
 }
 
 // Products kept as partial sums at up to 32 rows: tiles of 64 columns, cut along K so that the workgroups come out at
-// just under one per CU; wider tiles where their cuts fill more of the chip.  Returns the tile width in blocks of 32 columns.
-static int few_split_plan(int N, int K, int max_cuts, int* cuts) {
+// just under one per CU; wider tiles where their cuts fill more of the chip.  Returns the tile width in blocks of 32 columns, 0
+// where the general plan of the cuts is the better one:
+// - the cuts' first columns an odd multiple of 2048 apart (wider tiles: any multiple), in more than 2048 rows.  Whatever it is that
+//   these streams collide in, they do so at every row count, and the general plan's more and shorter cuts do not (us, this kernel
+//   and the general plan, slices read back at 4 TB/s included, same buffers, M = 16): N 8192: K 4096 17.1 and 14.9, K 12288 41.3 and
+//   35.8, K 28672 up to 92 and 78; N 10240, K 8192 34.1 and 31.3; N 4096, K 8192 18.1 and 15.7; N 14336, K 6144 37.4 and 33.1.  At other K
+//   this kernel wins by 2 to 30 % (N 8192: K 5120 by 7, K 8192 by 6; N 4096, K 4096 by 12; N 14336, K 12288 by 16).
+// - the general plan has more than four times the cuts: a wave here adds up a quarter of its cut, and the sums would run longer
+//   than before (N 18432, K 16384: 7 cuts against 1, error to float64 2.9e-7 and 3.9e-7).
+static int few_split_plan(int N, int K, int general_cuts, int max_cuts, int* cuts) {
     int best = 0, best_wgs = 0;
     for (int wtn = 2; wtn <= 4; ++wtn) {
         const int nbn = (N + 32 * wtn - 1) / (32 * wtn);
@@ -915,6 +923,9 @@ static int few_split_plan(int N, int K, int max_cuts, int* cuts) {
         if (ks < 1 || nbn > 256) continue;
         if (best == 0 || (best_wgs < 200 && nbn * ks > best_wgs)) best = wtn, best_wgs = nbn * ks, *cuts = ks;
     }
+    if (best == 0 || general_cuts > 4 * *cuts) return 0;
+    const int apart = *cuts * 2048;
+    if (N > 2048 && K % apart == 0 && (best > 2 || (K / apart) % 2 != 0)) return 0;
     return best;
 }
 
@@ -1191,15 +1202,15 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
     if ((size_t)M * N * 4 > parts_bytes) return hipErrorInvalidValue;
     if (dtype == BF16 && pipe_ok(N, K, A, W)) {
         const size_t room = parts_bytes / ((size_t)M * N * 4);
+        const SplitPlan sp = plan_split(M, N, K, room > 12 ? 12 : (int)room);
         if (M <= 32) {
             int cuts = 1;
-            const int wtn = few_split_plan(N, K, room > 12 ? 12 : (int)room, &cuts);
-            *n_parts = cuts;
+            const int wtn = few_split_plan(N, K, sp.ks, room > 12 ? 12 : (int)room, &cuts);
+            if (wtn != 0) *n_parts = cuts;
             if (wtn == 2) return launch_few<1, 1, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
             if (wtn == 3) return launch_few<1, 1, 3, false>(s, M, N, K, A, W, nullptr, parts, cuts);
             if (wtn == 4) return launch_few<1, 1, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
         }
-        const SplitPlan sp = plan_split(M, N, K, room > 12 ? 12 : (int)room);
         if (sp.kind != 0 && (size_t)sp.ks * M * N * 4 <= parts_bytes) {
             *n_parts = sp.ks;
             if (sp.kind == 1) return launch_pipe<2, 2, 4, 2, 3, 4>(s, OUT_SPLIT_F32, M, N, K, A, W, parts, nullptr, sp.ks, 0, sp.skew);

@@ -111,6 +111,32 @@ def test_bf16_gate_up_with_short_k_takes_the_tiled_kernel(M, N, K):
     assert torch.equal(act, want[:M])
 
 
+@pytest.mark.parametrize("M,N,K,room,slices", [
+    (1, 640, 1280, 12, 3), (17, 640, 1280, 2, 2),     # 64-column tiles, 20 K steps in three cuts; room for two slices only
+    (32, 512, 8256, 12, 12),                          # the most cuts, 129 K steps
+    (17, 14336, 1088, 12, 1),                         # no cut
+    (31, 10240, 2624, 12, 2),                         # 96-column tiles, the last one partial, 41 K steps
+    (32, 9216, 2624, 12, 3),                          # 128-column tiles
+    (5, 512, 256, 12, 1),                             # K too short to cut: the general plan
+    (16, 4096, 8192, 12, 8), (32, 10240, 8192, 12, 3), (1, 8192, 4096, 12, 4),   # cuts an odd multiple of 2048 apart: the general plan
+    (1, 18432, 5184, 12, 7),                          # the general plan has more than four times the cuts
+])
+def test_bf16_partial_products(M, N, K, room, slices):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    W = (torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16()
+    buf = torch.full((room * M * N,), float("nan"), device="cuda")
+    print(f"partial products M={M} N={N} K={K}", flush=True)
+    parts = tlt.gemm_parts(A, W, buf)
+    torch.cuda.synchronize()
+    assert parts.shape[0] == slices
+    assert bool(torch.isnan(buf[parts.numel():]).all())   # nothing behind the last slice
+    Ad, Wd = A.double(), W.double()
+    # K products of bf16 values, exact in fp32, and their sums in fp32, in any order (the slices are added up in float64 here)
+    bound = K * 2.0 ** -24 * (Ad.abs() @ Wd.abs().T)
+    assert bool(((parts.double().sum(0) - Ad @ Wd.T).abs() <= bound).all())
+
+
 @pytest.mark.parametrize("hidden,heads,n", [
     (512, 4, 5),       # 64 columns per workgroup, one cut
     (6144, 8, 32),     # output projection in two cuts, down in 96-column tiles
