@@ -56,9 +56,10 @@ bool plan_workspace(const tlt_model_cfg& c, int B, int n, int D, int K, int max_
     p.x = take(R * h * 4);
     p.xn = take(R * 2 * h * esz);
     p.qkv = take(R * qkv_dim * esz);
-    // fp32 partial products of the projections whose sum joins the fp32 residual stream (or feeds the rotary kernel)
+    // cosines, sines and cache slots of a forward's rows: written by its first layer, read by the others
     p.rope_cs = take(R * (size_t)c.head_dim * 4);
     p.rope_at = take(R * 8);
+    // fp32 partial products of the projections whose sum joins the fp32 residual stream (or feeds the rotary kernel)
     // (room for four slices of the widest product at the largest row count; a plan with more cuts than fit is not taken)
     p.parts_bytes = std::max(c.dtype == TLT_BF16 ? gemm_parts_max_bytes() : (size_t)0, (c.dtype == TLT_BF16 ? 4 : 1) * R * std::max(h, qkv_dim) * 4);
     p.parts = take(p.parts_bytes);

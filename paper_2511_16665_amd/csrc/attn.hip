@@ -239,8 +239,9 @@ constexpr int kMinTiles = 4;
 constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the planning kernel keeps in LDS
 
 // One workgroup, so a chain of latencies: lengths are read once, and the counting, the search for the chunk size, the running
-// sums and the sort are spread over its threads (1 sequence 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.4, 64 sequences 20.9 -> 9.7
-// against one thread walking the sequences; once per forward and drafter level).
+// sums and the sort are spread over its threads (once per forward and drafter level; against one thread walking the sequences, in
+// a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.4, 64 sequences 20.9 -> 9.7, 1 sequence of 200 the same 4.7; called by
+// itself again and again, everything warm, 1 to 4 sequences of 64 to 100 take 1 us more, 3.1-3.8 -> 4.2-4.7).
 __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ seq_len, int B, int n_region, int heads,
                                                    int max_items, AttnWork* __restrict__ work, int len_bound,
                                                    unsigned int* __restrict__ status, const int32_t* __restrict__ block_table,
@@ -804,8 +805,9 @@ __global__ __launch_bounds__(512) void attn_mfma_k(Rows rows, KVLayer kv, const 
 // One wave per (b, kv head, row), four rows per workgroup: merges the chunks' partial outputs
 // (running max in raw score units).
 // BATCH: the lanes read a chunk's maximum and sum each, and the outputs of 16 chunks are requested together.  With few rows in
-// all (plain decoding, small batches) a wave's chunks, one load latency each, are the whole kernel (batch 1, 17 chunks:
-// 12 us one after the other, 6.3 four at a time, 4.8 this way; 3 sequences x 23 nodes 7.2 -> 6.0); with the chip full of waves the plain loop is the faster one (14 against 16 us at the
+// all (plain decoding, small batches) a wave's chunks, one load latency each, are the whole kernel (on the 17 chunks that one
+// sequence of 8192 had at 8 tiles each: 12 us one after the other, 6.3 four at a time, 4.8 this way; on its 33 at 4 tiles 6.1; 3
+// sequences x 23 nodes 7.3); with the chip full of waves the plain loop is the faster one (14 against 16 us at the
 // benchmark shape).  The sums run in chunk order either way.
 template <bool BATCH>
 __global__ __launch_bounds__(256) void attn_combine_k(Rows rows, KVLayer kv, const float* __restrict__ part_o,

@@ -432,7 +432,8 @@ static void rmsnorm_launch_t(hipStream_t s, int M, int h, float* x, const void* 
                         ((uintptr_t)gamma & (4 * sizeof(T) - 1)) == 0;
     if (vec_ok && h <= 4096 && add && (n_add > 4 || M <= 64) && sizeof(TA) == 4)
         // many slices or few rows (so few workgroups): one 16-byte position per thread and all its slices' loads in
-        // flight at once
+        // flight at once.  (Few rows and up to four slices, against 256 threads, us per norm inside a forward of 1-32 rows: widths
+        // 3584 and 4096 1.4 less, 1536 0.4 less, 256 to 1024 and 2048 the same within 0.3, though most waves are idle at 256.)
         hipLaunchKernelGGL((rmsnorm_vec_k<T, 1, TA, 12, 1024>), dim3(M), dim3(1024), 0, s, h, x, (const T*)gamma, eps, (T*)out,
                            row_map, (const TA*)add, zero, zero_n, n_add, add_stride, (int)assign);
     else if (vec_ok && h <= 4096)

@@ -717,11 +717,12 @@ static hipError_t launch_f32_few(hipStream_t s, int out_mode, int M, int N, int 
     return launch_f32_few_t<4>(s, out_mode, M, N, K, A, W, W2, C);
 }
 
-// Few activation rows (M <= 32 * WTM, one row of tiles): the weights stream through once and nothing else counts.  A
-// workgroup of four waves owns 32 * WTN weight rows (GLU: half of them gate rows, half the matching up rows), WTN being free so
-// that the tiles come out at just under one per CU.  The K steps of 64 go through a ring of S slots (activation rows and
-// weight rows, both by global->LDS loads, S - 1 steps in flight); of a step's four 16-wide slices each wave multiplies one,
-// over the whole tile, so that a fragment is read from the LDS once, and the four waves' sums meet in LDS at the end.
+// Few activation rows (M <= 32 * WTM * WGM, one row of tiles): the weights stream through once and nothing else counts.  A
+// workgroup owns 32 * WTN weight rows (GLU: half of them gate rows, half the matching up rows), WTN being free so
+// that the tiles come out at just under one per CU, and has WGM groups of four waves (two above 64 rows), a group 32 * WTM of
+// the activation rows.  The K steps of 64 go through a ring of S slots (activation rows and
+// weight rows, both by global->LDS loads, S - 1 steps in flight); of a step's four 16-wide slices each wave of a group multiplies
+// one, over the group's rows, so that the group reads a fragment from the LDS once, and its four waves' sums meet in LDS at the end.
 // A step's loads are whole 128-byte lines; fetched straight into MFMA operands (64 bytes per row and instruction)
 // the vector-memory front end is the limit instead: 68 us at M = 16 on the gate/up shape below.
 template <int WGM, int WTM, int WTN, int S, int OUT, bool GLU>
@@ -1053,8 +1054,9 @@ static hipError_t launch_tiled(hipStream_t s, int out_mode, int M, int N, int K,
         }
         // gate/up with well under a round of big tiles: 256 rows x 80 output columns per workgroup (four waves of
         // 64 rows x 5 column blocks of 16 gate and 16 up rows, the last tile partial) puts the weights on nearly all CUs, and the
-        // narrower tile leaves room for a third weight slot.  A CU pulls cold weights at ~35 GB/s at most, however many loads
-        // it keeps in flight, and the activation rows that every workgroup re-reads from L2 go through the same path.
+        // narrower tile leaves room for a third weight slot.  What bounds it is a CU's load path, which the activation rows that
+        // every workgroup re-reads from L2 share with the cold weights: 3.0 MB per workgroup in 64-69 us here (43-47 GB/s), 3.2 MB
+        // in 77-79 us (41-42) with 96 columns and two slots.
         // Against 96 columns with two slots (three alternating runs on cold weights, M = 129 .. 256): 7B shape (198 -> 237
         // tiles) 77-79 -> 64-69 us, N 13824, K 5120 97-99 -> 80-85, N 20480, K 4096 88-93 -> 75-82.  Past 160 big tiles 80
         // columns would make more than a round (and 96 there gain nothing over the big tiles: N = 24576 102-105 -> 102-110).
