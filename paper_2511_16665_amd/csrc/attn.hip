@@ -240,8 +240,9 @@ constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the pla
 
 // One workgroup, so a chain of latencies: lengths are read once, and the counting, the search for the chunk size, the running
 // sums and the sort are spread over its threads (once per forward and drafter level; against one thread walking the sequences, in
-// a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.4, 64 sequences 20.9 -> 9.7, 1 sequence of 200 the same 4.7; called by
-// itself again and again, everything warm, 1 to 4 sequences of 64 to 100 take 1 us more, 3.1-3.8 -> 4.2-4.7).
+// a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.0, 64 sequences 20.9 -> 9.4; called by itself again and again,
+// everything warm, 1 to 6 sequences of 30 to 250 the same within 0.3 us).  A step of a scan is a trip through the LDS crossbar:
+// no scan has more of them than its length needs (0.5 us).
 __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ seq_len, int B, int n_region, int heads,
                                                    int max_items, AttnWork* __restrict__ work, int len_bound,
                                                    unsigned int* __restrict__ status, const int32_t* __restrict__ block_table,
@@ -289,10 +290,8 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         const int t = lane + 1;
         const int rounds0 = (int)max(((int64_t)s_total * heads + 256 * 64 - 1) / (256 * 64), (int64_t)1);
         const int rounds_t = t >= kMinTiles ? (int)(((int64_t)s_count[t] * heads + 255) / 256) : 0x7fffffff;
-        int r = max(rounds_t, 1);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) r = min(r, __shfl_xor(r, o, 64));
-        r = max(r, rounds0);
+        // (longer chunks never make more items: the fewest rounds are those of the longest)
+        const int r = max(__builtin_amdgcn_readlane(rounds_t, 63), rounds0);
         T = __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(rounds_t <= r));   // lane t - 1 stands for t
     }
     // chunks of every sequence and the slots they take: running sums, 64 sequences at a time
@@ -301,8 +300,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         for (int b0 = 0; b0 < B; b0 += 64) {
             const int b = b0 + lane, k = b < B ? (tiles_of(b) + T - 1) / T : 0;
             int sum = k;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
+            for (int o = 1; o < min(B - b0, 64); o <<= 1) {
                 const int up = __shfl_up(sum, o, 64);
                 if (lane >= o) sum += up;
             }
@@ -310,7 +308,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
                 slot0[b] = acc + sum - k, nch[b] = k;
                 if (b < kPlanCached) s_slot[b] = acc + sum - k;
             }
-            acc += __shfl(sum, 63, 64);
+            acc += __builtin_amdgcn_readlane(sum, min(B - b0, 64) - 1);
         }
         acc = acc < max_items ? acc : max_items;
         if (lane == 0) work->n_items = s_items = acc;   // cannot exceed the bound when seq_len respects the host's
@@ -334,8 +332,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     if (wave == 0) {   // s_pos[t] = items longer than t
         const int h = s_hist[64 - lane];
         int sum = h;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
+        for (int o = 1; o < T; o <<= 1) {   // (no chunk is longer than T: the lanes before T's hold zeros)
             const int up = __shfl_up(sum, o, 64);
             if (lane >= o) sum += up;
         }
