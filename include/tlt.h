@@ -137,6 +137,16 @@ int tlt_draft_expand(tlt_ctx *ctx, void *stream, int B, int depth, int topk, int
                      const float *hidden, int hidden_n, const int32_t *root_tokens, tlt_kv *draft_kv,
                      tlt_tree *out_tree);
 
+/* Prompt ingestion: tokens[b][0 .. n_tokens-1] (DEVICE, rows token_stride > n_tokens apart) go into both caches behind what they
+ * hold, tokens[b][1 .. n_tokens] being the tokens that follow them (the drafter's entries pair a token with the hidden state
+ * before it); both caches' seq_len advance by n_tokens, and the drafter is left as an extend over these positions
+ * leaves it.  The same as chain trees of at most `chunk` (<= max_n) tokens through tlt_verify_forward, tlt_kv_commit and the
+ * extend of tlt_draft_expand one after the other, but with several chunks of a sequence in one pass over the weights: within a block
+ * the keys and values of all of them are written before any of them attends.  TLT_ENOTIMPL (nothing enqueued): the workspace does not
+ * hold two chunks of every sequence, or there is one chunk only; go chunk by chunk then. */
+int tlt_prefill(tlt_ctx *ctx, void *stream, int B, int n_tokens, int chunk, const int32_t *tokens, int token_stride,
+                tlt_kv *kv, tlt_kv *draft_kv);
+
 /* Read-out of the candidate pool the last tlt_draft_expand(B, depth, topk, ...) of this context left
  * in the workspace (Section 5.1: every level's topk * topk candidates stay candidates for the final
  * selection): DEVICE arrays [B][topk + (depth-1)*topk^2] in creation order (level, then the parent's

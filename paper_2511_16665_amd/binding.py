@@ -27,7 +27,7 @@ EXPORTS = [
     "tlt_profile_begin", "tlt_profile_read", "tlt_mab_create", "tlt_mab_destroy", "tlt_mab_select", "tlt_mab_record",
     "tlt_mab_median_reward", "tlt_ngram_create", "tlt_ngram_destroy", "tlt_ngram_insert", "tlt_ngram_propose",
     "tlt_template_build", "tlt_draft_sample", "tlt_gemm_argmax", "tlt_gemm_glu", "tlt_gemm_parts", "tlt_draft_pool", "tlt_set_oproj_rounding", "tlt_device_status", "tlt_accept_sample_static", "tlt_attention", "tlt_attention_workspace_bytes",
-    "tlt_graph_pool_create", "tlt_graph_pool_destroy", "tlt_graph_pool_step", "tlt_graph_pool_count", "tlt_mfma_stream",
+    "tlt_graph_pool_create", "tlt_graph_pool_destroy", "tlt_graph_pool_step", "tlt_graph_pool_count", "tlt_mfma_stream", "tlt_prefill",
 ]
 
 
@@ -93,6 +93,7 @@ def load() -> C.CDLL:
     lib.tlt_draft_expand.argtypes = [C.c_void_p, C.c_void_p] + [C.c_int] * 5 + [C.c_void_p] * 3 + [C.c_int, C.c_void_p, C.c_int,
                                                                                          C.c_void_p, C.POINTER(KVC),
                                                                                          C.POINTER(TreeC)]
+    lib.tlt_prefill.argtypes = [C.c_void_p, C.c_void_p] + [C.c_int] * 3 + [C.c_void_p, C.c_int, C.POINTER(KVC), C.POINTER(KVC)]
     lib.tlt_draft_pool.argtypes = [C.c_void_p, C.c_void_p] + [C.c_int] * 3 + [C.c_void_p] * 3
     lib.tlt_template_build.argtypes = [C.c_int] * 3 + [C.POINTER(C.c_int32)] * 4
     lib.tlt_draft_sample.argtypes = [C.c_void_p, C.c_void_p] + [C.c_int] * 4 + [C.c_float] + [C.c_void_p] * 3 + \
@@ -264,6 +265,16 @@ class Context:
         self._check(self.lib.tlt_draft_expand(self.handle, _stream(), B, depth, topk, n_verify, mode, _ptr(new_tokens),
                                               _ptr(new_src), _ptr(n_new), new_stride, _ptr(hidden), hidden_n,
                                               _ptr(root_tokens), C.byref(kvc), tree_ref), "tlt_draft_expand")
+
+    def prefill(self, B, n_tokens, chunk, tokens, kv: KV, draft_kv: KV) -> bool:
+        """tokens [B, > n_tokens] int32 (device).  False: this context takes such prompts chunk by chunk only (nothing was done)."""
+        kvc, dkvc = kv.c(), draft_kv.c()
+        rc = self.lib.tlt_prefill(self.handle, _stream(), B, n_tokens, chunk, _ptr(tokens), tokens.shape[1], C.byref(kvc),
+                                  C.byref(dkvc))
+        if rc == -5:   # TLT_ENOTIMPL
+            return False
+        self._check(rc, "tlt_prefill")
+        return True
 
     def draft_pool(self, B, depth, topk):
         """(token, parent, score) device tensors [B, topk + (depth-1)*topk^2] of the last expansion's pool."""

@@ -535,6 +535,160 @@ static int draft_extend_rows(tlt_ctx* ctx, hipStream_t s, int B, const int32_t* 
     return TLT_OK;
 }
 
+// Workspace of a prefill pass of B * C virtual sequences of m rows, carved from what lies in front of the feature rows of the
+// ordinary plan: a pass wants no logits, whose room is most of the workspace.
+struct PrefillPlan {
+    Plan plan;
+    size_t tok, nxt, src, n_valid, len_t, len_d, vtab_t, vtab_d;
+};
+static bool plan_prefill(const tlt_ctx* ctx, int BC, int m, const tlt_kv* kv, const tlt_kv* dkv, int bound, PrefillPlan& q) {
+    const tlt_model_cfg& c = ctx->cfg;
+    const size_t esz = esz_of(ctx), R = (size_t)BC * m, h = c.hidden, F = c.mlp;
+    const size_t q_dim = (size_t)c.n_q_heads * c.head_dim, qkv_dim = q_dim + 2 * (size_t)c.n_kv_heads * c.head_dim;
+    Plan& p = q.plan;
+    p = ctx->plan;   // (feature rows and status word stay where they are)
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = align_up(o + bytes);
+        return at;
+    };
+    p.max_rows = (int)R;
+    p.x = take(R * h * 4);
+    p.xn = take(R * 2 * h * esz);
+    p.qkv = take(R * qkv_dim * esz);
+    p.rope_cs = take(R * (size_t)c.head_dim * 4);
+    p.rope_at = take(R * 8);
+    p.att = take(R * q_dim * esz);
+    p.act = take(R * F * esz);
+    bool fused = true;   // (else gate and up need buffers of their own)
+    auto takes = [&](const tlt_layer_weights& w) { return gemm_glu_supported(c.dtype, (int)R, c.mlp, c.hidden, ctx->ws, w.wg, w.wu); };
+    for (int l = 0; l < c.n_layers; ++l) fused = fused && takes(ctx->target.layers[l]);
+    fused = fused && takes(ctx->draft.layers[0]);
+    p.g = take(fused ? 0 : R * F * esz);
+    p.u = take(fused ? 0 : R * F * esz);
+    q.tok = take(R * 4);
+    q.nxt = take(R * 4);
+    q.src = take(R * 4);
+    q.n_valid = take((size_t)BC * 4);
+    q.len_t = take((size_t)BC * 4);
+    q.len_d = take((size_t)BC * 4);
+    q.vtab_t = take((size_t)BC * kv->max_pages * 4);
+    q.vtab_d = take((size_t)BC * dkv->max_pages * 4);
+    p.attn_ws_bytes = attention_workspace_bytes(BC, m, c.n_q_heads, c.n_kv_heads, c.head_dim, bound);
+    p.attn_ws = take(p.attn_ws_bytes);
+    // partial products: what is left, up to what any plan of cuts asks for; three slices of the widest at the least
+    const size_t slice = R * std::max(h, qkv_dim) * 4, want = (c.dtype == TLT_BF16 ? 3 : 1) * slice;
+    p.parts = o;
+    if (o + want > ctx->plan.feat) return false;
+    p.parts_bytes = std::min(ctx->plan.feat - o, std::max(want, 12 * slice));
+    return true;
+}
+
+// Rows of a pass: what a product of this model's widths needs to run at the rate of large ones (7B shape, 4 prompts of 301 tokens:
+// five passes of 256 rows 27.5 ms, one of 1200 16.1).
+constexpr int kPrefillRows = 2048;
+
+int tlt_prefill(tlt_ctx* ctx, void* stream, int B, int n_tokens, int chunk, const int32_t* tokens, int token_stride, tlt_kv* kv,
+                tlt_kv* draft_kv) {
+    if (!ctx || !ctx->have_draft || B < 1 || n_tokens < 1 || chunk < 1 || !tokens || token_stride <= n_tokens) return TLT_EINVAL;
+    if (B > ctx->max_batch || chunk > ctx->max_n) return TLT_ESHAPE;
+    int rc;
+    if ((rc = check_kv(ctx, kv, n_tokens)) || (rc = check_kv(ctx, draft_kv, n_tokens))) return rc;
+    // chunks of equal length, and as many of each sequence in a pass as the workspace holds
+    int nc = (n_tokens + chunk - 1) / chunk;
+    const int m = (n_tokens + nc - 1) / nc;
+    nc = (n_tokens + m - 1) / m;
+    const int bound = std::max(kv->seq_len_bound, draft_kv->seq_len_bound) + n_tokens;
+    PrefillPlan q;
+    int C = std::min(nc, std::max(1, kPrefillRows / (B * m)));
+    while (C > 1 && !plan_prefill(ctx, B * C, m, kv, draft_kv, bound, q)) --C;
+    if (C < 2) return TLT_ENOTIMPL;
+    C = (nc + (nc + C - 1) / C - 1) / ((nc + C - 1) / C);   // (as many passes, evenly filled)
+    if (!plan_prefill(ctx, B * C, m, kv, draft_kv, bound, q)) return TLT_ENOTIMPL;
+
+    hipStream_t s = (hipStream_t)stream;
+    if ((rc = ensure_status(ctx, s))) return rc;
+    struct PlanSwap {   // the block's kernels find the pass's buffers where they find a step's
+        tlt_ctx* c;
+        Plan saved;
+        PlanSwap(tlt_ctx* x, const Plan& p) : c(x), saved(x->plan) { c->plan = p; }
+        ~PlanSwap() {
+            c->plan = saved;
+            c->in_draft = false;
+        }
+    } swap(ctx, q.plan);
+    const tlt_model_cfg& c = ctx->cfg;
+    const Plan& p = ctx->plan;
+    char* ws = ctx->ws;
+    const int h = c.hidden, V = c.vocab;
+    const double e = (double)esz_of(ctx);
+    float* x = (float*)(ws + p.x);
+    PrefillPass pass;
+    pass.tokens = tokens;
+    pass.token_stride = token_stride;
+    pass.n_tokens = n_tokens;
+    pass.m = m;
+    pass.seq_len_t = kv->seq_len;
+    pass.seq_len_d = draft_kv->seq_len;
+    pass.table_t = kv->block_table;
+    pass.table_d = draft_kv->block_table;
+    pass.pages_t = kv->max_pages;
+    pass.pages_d = draft_kv->max_pages;
+    pass.tok = (int32_t*)(ws + q.tok);
+    pass.nxt = (int32_t*)(ws + q.nxt);
+    pass.src = (int32_t*)(ws + q.src);
+    pass.n_valid = (int32_t*)(ws + q.n_valid);
+    pass.len_t = (int32_t*)(ws + q.len_t);
+    pass.len_d = (int32_t*)(ws + q.len_d);
+    pass.vtab_t = (int32_t*)(ws + q.vtab_t);
+    pass.vtab_d = (int32_t*)(ws + q.vtab_d);
+    auto virtual_kv = [&](const tlt_kv* of, int32_t* lens, int32_t* table) {
+        tlt_kv v = *of;
+        v.seq_len = lens;
+        v.block_table = table;
+        v.seq_len_bound = of->seq_len_bound + n_tokens - 1;
+        return v;
+    };
+    const tlt_kv vt = virtual_kv(kv, pass.len_t, pass.vtab_t), vd = virtual_kv(draft_kv, pass.len_d, pass.vtab_d);
+    for (int done = 0; done < n_tokens;) {
+        const int left = (n_tokens - done + m - 1) / m, Cp = std::min(C, left), BC = B * Cp, M = BC * m;
+        const int taken = std::min(Cp * m, n_tokens - done);
+        pass.done = done;
+        pass.C = Cp;
+        ctx->pending_parts = 0;
+        TLT_RUN(ctx, s, CLS_OTHER, 0, 0, prefill_rows(s, B, pass));
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * (e + 4), embed_rows(s, c.dtype, M, h, V, pass.tok, ctx->target.embed, x));
+        Rows rows;   // causal within a chunk
+        rows.B = BC;
+        rows.n = m;
+        rows.n_valid = pass.n_valid;
+        rows.pos_stride = 1;
+        rows.n_region = m;
+        for (int l = 0; l < c.n_layers; ++l)
+            if ((rc = layer_forward(ctx, s, ctx->target.layers[l], rows, kv_layer(ctx, &vt, l), l > 0))) return rc;
+        if ((rc = fold_pending(ctx, s, M))) return rc;
+        // the drafter's entries of the same positions, from the hidden states in x
+        ctx->in_draft = true;
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * (4 + 3 * e),
+                draft_input(s, c.dtype, BC, m, h, V, pass.nxt, pass.src, pass.n_valid, m, (int64_t)M, x, ctx->target.embed, ws + p.xn));
+        if ((rc = draft_fc(ctx, s, M, ws + p.xn))) return rc;
+        if ((rc = layer_forward(ctx, s, ctx->draft.layers[0], rows, kv_layer(ctx, &vd, 0)))) return rc;
+        ctx->in_draft = false;
+        done += taken;
+        if (done == n_tokens) {   // (only the last position's output is wanted, as feature row 0; rows past it in its chunk: pad)
+            if ((rc = fold_pending(ctx, s, M))) return rc;
+            const int pad = Cp * m - taken;
+            TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * 8,
+                    gather_last_rows(s, B, Cp * m, h, nullptr, x - (int64_t)pad * h, (float*)(ws + p.feat), p.feat_rows));
+        }
+        ctx->pending_parts = 0;
+        TLT_RUN(ctx, s, CLS_OTHER, 0, 0, add_i32(s, B, kv->seq_len, nullptr, taken));
+        TLT_RUN(ctx, s, CLS_OTHER, 0, 0, add_i32(s, B, draft_kv->seq_len, nullptr, taken));
+    }
+    return TLT_OK;
+}
+
 int tlt_draft_expand(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int n_verify, int mode,
                      const int32_t* new_tokens, const int32_t* new_src, const int32_t* n_new, int new_stride,
                      const float* hidden, int hidden_n, const int32_t* root_tokens, tlt_kv* draft_kv, tlt_tree* out_tree) {

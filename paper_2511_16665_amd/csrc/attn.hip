@@ -246,15 +246,17 @@ constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the pla
 __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ seq_len, int B, int n_region, int heads,
                                                    int max_items, AttnWork* __restrict__ work, int len_bound,
                                                    unsigned int* __restrict__ status, const int32_t* __restrict__ block_table,
-                                                   int max_pages, int64_t n_pages) {
-    extern __shared__ int s_len[];   // [min(B, kPlanCached)] lengths, then as many first slots
+                                                   int max_pages, int64_t n_pages, const int32_t* __restrict__ n_valid) {
+    extern __shared__ int s_len[];   // [min(B, kPlanCached)] keys of a sequence, then as many first slots
     __shared__ int s_total, s_items, s_hist[66], s_pos[66], s_count[65];
     int* slot0 = (int*)(work + 1);
     int* nch = slot0 + B;
     AttnItem* items = (AttnItem*)(nch + B);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int* s_slot = s_len + min(B, kPlanCached);
-    auto total_of = [&](int b) { return max(b < kPlanCached ? s_len[b] : seq_len[b], 0) + n_region; };
+    // n_valid (causal rows only): the slots of a sequence's inactive rows are not written and no row sees them
+    auto keys_of = [&](int b, int len) { return max(len, 0) + (n_valid ? min(max(n_valid[b], 0), n_region) : n_region); };
+    auto total_of = [&](int b) { return b < kPlanCached ? s_len[b] : keys_of(b, seq_len[b]); };
     auto tiles_of = [&](int b) { return (total_of(b) + kKT - 1) / kKT; };
     auto slot_of = [&](int b) { return b < kPlanCached ? s_slot[b] : slot0[b]; };
     if (tid < 66) s_hist[tid] = 0;
@@ -263,9 +265,9 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     __syncthreads();
     int mine = 0;
     for (int b = tid; b < B; b += 256) {
-        const int len = seq_len[b];
-        if (b < kPlanCached) s_len[b] = len;
-        mine += (max(len, 0) + n_region + kKT - 1) / kKT;
+        const int len = seq_len[b], keys = keys_of(b, len);
+        if (b < kPlanCached) s_len[b] = keys;
+        mine += (keys + kKT - 1) / kKT;
         // the grid and the item list were sized from the caller's length bound: a longer sequence would lose
         // part of its context, which only the device can see
         if (status && len > len_bound) atomicOr(status, 1u);
@@ -910,7 +912,7 @@ static hipError_t launch_attn_mfma(hipStream_t s, const Rows& rows, const KVLaye
     if (!reuse_plan)
         hipLaunchKernelGGL(attn_plan_k, dim3(1), dim3(256), 2 * sizeof(int) * (rows.B < kPlanCached ? rows.B : kPlanCached), s, kv.seq_len,
                            rows.B, rows.n_region, p.heads, p.max_items, work, kv.seq_len_bound, status, kv.block_table, kv.max_pages,
-                           kv.n_pages);
+                           kv.n_pages, rows.mask ? nullptr : rows.n_valid);
     // (ids come in groups of 8 (item, kv head) pairs x row groups: see attn_decode)
     const int id_groups = (p.max_items * kv.n_kv + 7) / 8;
     hipLaunchKernelGGL(kern, dim3(id_groups * 8 * p.row_groups), dim3(512), lds, s, rows, kv, (const uint16_t*)qkv, part_o,

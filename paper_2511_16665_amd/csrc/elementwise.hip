@@ -409,6 +409,30 @@ __global__ void iota_scaled_k(int n, int32_t* out, int scale) {
     if (i < n) out[i] = i * scale;
 }
 
+// One workgroup per virtual sequence b * C + j = chunk j of sequence b in this pass (see PrefillPass).
+__global__ void prefill_rows_k(PrefillPass p) {
+    const int v = blockIdx.x, b = v / p.C, j = v - b * p.C;
+    const int start = p.done + j * p.m, cnt = min(p.m, p.n_tokens - start);
+    if (threadIdx.x == 0) {
+        p.n_valid[v] = cnt;
+        p.len_t[v] = p.seq_len_t[b] + j * p.m;
+        p.len_d[v] = p.seq_len_d[b] + j * p.m;
+    }
+    const int32_t* t = p.tokens + (int64_t)b * p.token_stride + start;
+    for (int i = threadIdx.x; i < p.m; i += blockDim.x) {
+        p.tok[(int64_t)v * p.m + i] = i < cnt ? t[i] : -1;
+        p.nxt[(int64_t)v * p.m + i] = i < cnt ? t[i + 1] : -1;
+        p.src[(int64_t)v * p.m + i] = i;
+    }
+    for (int i = threadIdx.x; i < p.pages_t; i += blockDim.x) p.vtab_t[(int64_t)v * p.pages_t + i] = p.table_t[(int64_t)b * p.pages_t + i];
+    for (int i = threadIdx.x; i < p.pages_d; i += blockDim.x) p.vtab_d[(int64_t)v * p.pages_d + i] = p.table_d[(int64_t)b * p.pages_d + i];
+}
+
+hipError_t prefill_rows(hipStream_t s, int B, const PrefillPass& p) {
+    hipLaunchKernelGGL(prefill_rows_k, dim3(B * p.C), dim3(256), 0, s, p);
+    return hipGetLastError();
+}
+
 #define DISPATCH_T(dtype, ...)              \
     if ((dtype) == F32) {                   \
         using T = float;                    \

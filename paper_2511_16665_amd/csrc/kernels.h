@@ -109,6 +109,19 @@ hipError_t gather_last_rows(hipStream_t s, int B, int n, int h, const int32_t* n
                             int dst_seq_stride);
 hipError_t iota_scaled(hipStream_t s, int n, int32_t* out, int scale);
 
+// A pass over C consecutive chunks of m prompt tokens of each of B sequences: every chunk is a (virtual) sequence of its own, whose
+// block table is its sequence's and whose length ends where the chunk begins.
+struct PrefillPass {
+    const int32_t* tokens = nullptr;   // [B][token_stride]
+    int token_stride = 0, n_tokens = 0, done = 0, C = 0, m = 0;   // done: tokens of each sequence that earlier passes took
+    const int32_t *seq_len_t = nullptr, *seq_len_d = nullptr, *table_t = nullptr, *table_d = nullptr;   // [B], [B][pages]
+    int pages_t = 0, pages_d = 0;
+    // out: [B * C][m] tokens, tokens after them, 0 .. m-1; [B * C] valid rows and lengths; [B * C][pages]
+    int32_t *tok = nullptr, *nxt = nullptr, *src = nullptr, *n_valid = nullptr, *len_t = nullptr, *len_d = nullptr;
+    int32_t *vtab_t = nullptr, *vtab_d = nullptr;
+};
+hipError_t prefill_rows(hipStream_t s, int B, const PrefillPass& p);
+
 // ---- attn.hip
 size_t attention_workspace_bytes(int B, int n, int n_q_heads, int n_kv_heads, int d, int max_ctx);
 // status (optional): device word whose bit 0 is raised when some seq_len[b] exceeds kv.seq_len_bound (the MFMA

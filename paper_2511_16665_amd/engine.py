@@ -57,6 +57,15 @@ class Engine:
         B, P = prompts.shape
         chunk = chunk or self.max_n
         body = P - 1
+        if body > chunk and B <= self.B and self.dkv is not None:
+            # several chunks of every prompt per pass, where the workspace holds them
+            tokens = torch.from_numpy(np.ascontiguousarray(prompts, dtype=np.int32)).cuda()
+            if self.ctx.prefill(B, body, chunk, tokens, self.kv, self.dkv):
+                self.kv.seq_len_bound += body
+                self.dkv.seq_len_bound += body
+                self.root.copy_(tokens[:, -1])
+                self.have_pending = False
+                return
         for o in range(0, body, chunk):
             m = min(chunk, body - o)
             t = self.tree(m)
