@@ -228,9 +228,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
     // (descriptor, absolute K tile index, end of the tile's K range).  When a cursor reaches the end of
     // its tile it jumps to the `next` triple, which the compute loop points at its following tile, or,
     // after the last one, back at the last K tile (harmless re-fetches keep the schedule uniform).  All
-    // of it is scalar selects: the K loop stays one basic block.  A cursor runs at most SA-1 K tiles
-    // ahead, so with at least SA K tiles per tile (the launcher's condition for giving a workgroup more
-    // than one) it never needs more than the one following tile.
+    // of it is scalar selects: the K loop stays one basic block.  A cursor runs at most SA-1 (SB-1) K
+    // tiles ahead, so with at least max(SA, SB) K tiles per tile (the launcher's condition for giving a workgroup
+    // more than one) it never needs more than the one following tile.
     const TileInfo ti0 = tile_info(0);
     u32x4_t rsA = desc_a(ti0), rsB = desc_b(ti0), rsA_nx = rsA, rsB_nx = rsB;
     int a_kt = ti0.kt0, a_end = ti0.kt0 + ti0.nt, b_kt = a_kt, b_end = a_end;
@@ -381,6 +381,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
             // still carries, so it costs 2*NV exchanges instead of 5*NV; a lane ends with rows
             // k = lane32*NV/32 .. of the wave's NV = WTM*16 (row index k = i*16 + v within its half).
             constexpr int NV = WTM * 16;
+            const int col0 = (int)split_stride + ti.n0;   // (this launch's first column in the whole product, no cuts here)
             float bv[NV];
             int bi[NV];
 #pragma unroll
@@ -388,12 +389,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     float m = acc[i][0][v];
-                    int mi = ti.n0 + wn * (WTN * 32) + l32;
+                    int mi = col0 + wn * (WTN * 32) + l32;
 #pragma unroll
                     for (int jj = 1; jj < WTN; ++jj)
                         if (acc[i][jj][v] > m) {   // strictly greater: the lower column wins a tie
                             m = acc[i][jj][v];
-                            mi = ti.n0 + wn * (WTN * 32) + jj * 32 + l32;
+                            mi = col0 + wn * (WTN * 32) + jj * 32 + l32;
                         }
                     bv[i * 16 + v] = m;
                     bi[i * 16 + v] = mi;
@@ -945,8 +946,8 @@ static hipError_t launch_pipe(hipStream_t s, int out_mode, int M, int N, int K, 
     const size_t lds = ((size_t)SA * BM + (size_t)SB * BN) * 64 * sizeof(uint16_t);
     // persistent workgroups: as many as the chip holds at once (32 CUs per XCD, LDS-limited occupancy)
     const int occupancy = lds <= 80 * 1024 ? 2 : 1;
-    // (a workgroup that walks several tiles needs at least SA K tiles in each)
-    const bool persistent = (K / 64) / ksplit >= SA;
+    // (a workgroup that walks several tiles needs as many K tiles in each as either cursor may run ahead)
+    const bool persistent = (K / 64) / ksplit >= (SA > SB ? SA : SB);
     const int wg_per_xcd = (!persistent || per_xcd < 32 * occupancy) ? per_xcd : 32 * occupancy;
     dim3 grid(wg_per_xcd * 8), block(64 * WGM * WGN);
 #define LAUNCH(OUT)                                                                                                   \
@@ -1007,6 +1008,15 @@ static hipError_t launch_tiled(hipStream_t s, int out_mode, int M, int N, int K,
             if (tiles > 256) return launch_pipe<2, 2, 2, 2, 3, 2, true>(s, OUT_T, M, n_cols, K, A, w, c, w2, 1, N);
             return launch_pipe<2, 2, 2, 2, 3, 3, true>(s, OUT_T, M, n_cols, K, A, w, c, w2, 1, N);
         }
+        // up to 64 rows: tiles of 64 rows (half of a 128-row tile would be padding), four waves side by side; the LDS that is freed holds a
+        // third weight slot with two workgroups per CU, or eight with one.  What bounds it is how much of the weight stream a CU
+        // has in flight.  Against 128x128 tiles, whose two workgroups per CU had two slots (us, same buffers, cold weights): N 152064,
+        // K 3584: 1 row 183 -> 162 (6.7 TB/s), 16 rows 189 -> 173, 32 rows 202 -> 188; N 128256, K 8192: 358 -> 339, 352 -> 336, 365 -> 350;
+        // N 32000, K 4096: 56 -> 55; one tile per CU: N 16384, K 4096 40 -> 34 at 1 row, 39.3 -> 38.1 at 64; N 8192, K 8192 61 -> 49, 64 -> 58.
+        if (M <= 64) {
+            if (tiles > 256) return launch_pipe<1, 4, 2, 1, 3, 3, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);
+            return launch_pipe<1, 4, 2, 1, 4, 8, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);
+        }
         if (nbm128 == 1) {
             if (tiles > 256) return launch_pipe<2, 2, 2, 2, 3, 2, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);
             return launch_pipe<2, 2, 2, 2, 3, 3, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);
@@ -1066,7 +1076,10 @@ static hipError_t launch_tiled(hipStream_t s, int out_mode, int M, int N, int K,
     }
     // up to 128 rows: half of a 256-row tile would be padding, and the LDS it frees holds a third weight slot
     // (gate/up at M = 128: 85 -> 70 us, LM head: 261 -> 251; at the 32B shape 406 -> 343)
-    if (M > 64 && M <= 128 && tiles256 >= 100 && N % bno256 == 0) {
+    // (from 33 rows on where whole rounds of them leave less than half a round: the wider tile re-reads the activation rows half as often.
+    // N 152064, K 3584: 48 rows 201 us in 64-row tiles, 192 this way, 64 rows 210 and 198; K 5120: 300 and 277; at K 896 58.8 and 62.9)
+    const bool wide64 = !glu && M > 32 && M <= 64 && K >= 2048 && tiles256 > 256 && tiles256 % 256 <= 128;
+    if (((M > 64 && M <= 128) || wide64) && tiles256 >= 100 && N % bno256 == 0) {
         if (glu) return launch_pipe<2, 2, 2, 4, 3, 3, true, true>(s, OUT_T, M, N, K, A, W, C, W2, 1, N);
         // (more than a round: whole rounds, the rest in 128x128 tiles: LM head 227-250 -> 219-241 us, 32B shape 313-343 -> 297-325)
         const int main_tiles = tiles256 / 256 * 256;
@@ -1216,6 +1229,10 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
         if (sp.kind != 0 && (size_t)sp.ks * M * N * 4 <= parts_bytes) {
             *n_parts = sp.ks;
             if (sp.kind == 1) return launch_pipe<2, 2, 4, 2, 3, 4>(s, OUT_SPLIT_F32, M, N, K, A, W, parts, nullptr, sp.ks, 0, sp.skew);
+            // (tiles of 64 rows, see launch_tiled: N = K = 3584 9.9 -> 9.3 us at 64 rows, N 4608 10.6 -> 10.0, N 3584, K 18944 26.8 -> 24.8 at
+            // 40 rows and 26.5 -> 26.2 at 64; the sums are the same bit for bit)
+            if (sp.kind == 3 && M <= 64)
+                return launch_pipe<1, 4, 2, 1, 3, 3, false, true>(s, OUT_SPLIT_F32, M, N, K, A, W, parts, nullptr, sp.ks, 0, sp.skew);
             if (sp.kind == 3 && M <= 128)
                 return launch_pipe<2, 2, 2, 2, 3, 3, false, true>(s, OUT_SPLIT_F32, M, N, K, A, W, parts, nullptr, sp.ks, 0, sp.skew);
             if (sp.kind == 3) return launch_pipe<2, 2, 2, 2, 3, 3>(s, OUT_SPLIT_F32, M, N, K, A, W, parts, nullptr, sp.ks, 0, sp.skew);
@@ -1226,30 +1243,35 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
 }
 
 // ---- fused row argmax (big tiles only: every 256-row weight tile yields two 128-column blocks)
-__global__ __launch_bounds__(256) void argmax_blocks_k(int M, int P, const float* __restrict__ pv,
-                                                       const int32_t* __restrict__ pi, int32_t* __restrict__ out) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= M) return;
+// (a workgroup per row: its blocks, five per thread at 152064 columns, are all requested at once; a wave per row took 11.4 us
+// at 84 rows, this 4.9)
+__global__ __launch_bounds__(256) void argmax_blocks_k(int P, const float* __restrict__ pv, const int32_t* __restrict__ pi, int32_t* __restrict__ out) {
+    __shared__ float sv[4];
+    __shared__ int si[4];
+    const int64_t row = (int64_t)blockIdx.x * P;
     float v = -INFINITY;
     int i = 0x7fffffff;
-    for (int p = lane; p < P; p += 64) {
-        const float ov = pv[(int64_t)row * P + p];
-        const int oi = pi[(int64_t)row * P + p];
-        if (ov > v || (ov == v && oi < i)) {
-            v = ov;
-            i = oi;
-        }
-    }
+    for (int p0 = threadIdx.x; p0 < P; p0 += 256 * 8) {
+        float ov[8];
+        int oi[8];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(v, o, 64);
-        const int oi = __shfl_xor(i, o, 64);
-        if (ov > v || (ov == v && oi < i)) {
-            v = ov;
-            i = oi;
+        for (int u = 0; u < 8; ++u) {
+            const bool on = p0 + 256 * u < P;
+            ov[u] = on ? pv[row + p0 + 256 * u] : -INFINITY;
+            oi[u] = on ? pi[row + p0 + 256 * u] : 0x7fffffff;
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (better(ov[u], oi[u], v, i)) v = ov[u], i = oi[u];
     }
-    if (lane == 0) out[row] = i;
+    wave_best(v, i);
+    if ((threadIdx.x & 63) == 0) sv[threadIdx.x >> 6] = v, si[threadIdx.x >> 6] = i;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int w = 1; w < 4; ++w)
+        if (better(sv[w], si[w], v, i)) v = sv[w], i = si[w];
+    out[blockIdx.x] = i;
 }
 
 bool gemm_argmax_supported(int dtype, int M, int N, int K, const void* A, const void* W) {
@@ -1260,26 +1282,49 @@ bool gemm_argmax_supported(int dtype, int M, int N, int K, const void* A, const 
 
 size_t gemm_argmax_workspace_bytes(int M, int N) { return (size_t)M * (N / 128) * 8; }
 
-hipError_t gemm_argmax(hipStream_t s, int M, int N, int K, const void* A, const void* W, void* ws, int32_t* out) {
-    constexpr int SA = 3, SB = 2;
-    const int P = N / 128;
-    float* pv = (float*)ws;
-    int32_t* pi = (int32_t*)(pv + (size_t)M * P);
-    const int nbm = (M + 255) / 256, nbn = N / 256, total = nbm * nbn, per_xcd = (total + 7) / 8;
-    const size_t lds = ((size_t)SA * 256 + (size_t)SB * 256) * 64 * sizeof(uint16_t);
-    const int wg_per_xcd = per_xcd < 32 ? per_xcd : 32;
-    auto kern = gemm_bf16_pipe_k<2, 2, 4, 4, SA, SB, OUT_ROWMAX, false>;
+// One launch of the row-maximum kernel over the columns col0 .. col0 + n_cols - 1, a multiple of its tile's width.
+template <int WGM, int WGN, int WTM, int SA, int SB, bool NTW>
+static hipError_t launch_rowmax(hipStream_t s, int M, int N, int K, const void* A, const void* W, float* pv, int32_t* pi, int col0, int n_cols) {
+    constexpr int BM = 32 * WTM * WGM, BN = 128 * WGN;   // (four column tiles per wave: blocks of 128 columns)
+    const int P = N / 128, nbm = (M + BM - 1) / BM, total = nbm * (n_cols / BN), per_xcd = (total + 7) / 8;
+    const size_t lds = ((size_t)SA * BM + (size_t)SB * BN) * 64 * sizeof(uint16_t);
+    const bool persistent = K / 64 >= (SA > SB ? SA : SB);   // (see launch_pipe)
+    const int wg_per_xcd = !persistent || per_xcd < 32 ? per_xcd : 32;
+    auto kern = gemm_bf16_pipe_k<WGM, WGN, WTM, 4, SA, SB, OUT_ROWMAX, false, NTW>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3(wg_per_xcd * 8), dim3(256), lds, s, M, P, K, (const uint16_t*)A, (const uint16_t*)W,
-                       (const uint16_t*)nullptr, (void*)pv, nbm, total, per_xcd, 1, wg_per_xcd, pi, 0, (int64_t)0, nbn * 256);
-    hipError_t e = hipGetLastError();
+    hipLaunchKernelGGL(kern, dim3(wg_per_xcd * 8), dim3(64 * WGM * WGN), lds, s, M, P, K, (const uint16_t*)A, (const uint16_t*)W + (int64_t)col0 * K,
+                       (const uint16_t*)nullptr, (void*)(pv + col0 / 128), nbm, total, per_xcd, 1, wg_per_xcd, pi + col0 / 128, 0, (int64_t)col0,
+                       n_cols);
+    return hipGetLastError();
+}
+
+hipError_t gemm_argmax(hipStream_t s, int M, int N, int K, const void* A, const void* W, void* ws, int32_t* out) {
+    const int P = N / 128;
+    float* pv = (float*)ws;
+    int32_t* pi = (int32_t*)(pv + (size_t)M * P);
+    hipError_t e;
+    if (M <= 256) {
+        // one row of tiles: whole rounds of the chip in 256-column tiles, what is left in 128-column ones (as launch_tiled cuts the stored
+        // product), weights with the non-temporal hint; up to 128 rows in tiles of 128 rows.  N 152064, K 3584, us against 256x256 tiles in
+        // one launch: 65 rows 280 -> 232, 128 rows 277 -> 233, 129 rows 281 -> 251, 256 rows 301 -> 283.
+        const int tiles = N / 256, main_cols = (tiles > 256 ? tiles / 256 * 256 : tiles) * 256;
+        if (M <= 128) e = launch_rowmax<2, 2, 2, 3, 3, true>(s, M, N, K, A, W, pv, pi, 0, main_cols);
+        else e = launch_rowmax<2, 2, 4, 3, 2, true>(s, M, N, K, A, W, pv, pi, 0, main_cols);
+        if (e != hipSuccess) return e;
+        if (main_cols < N) {
+            if (M <= 128) e = launch_rowmax<2, 1, 2, 3, 4, true>(s, M, N, K, A, W, pv, pi, main_cols, N - main_cols);
+            else e = launch_rowmax<4, 1, 2, 3, 4, true>(s, M, N, K, A, W, pv, pi, main_cols, N - main_cols);
+        }
+    } else {
+        e = launch_rowmax<2, 2, 4, 3, 2, false>(s, M, N, K, A, W, pv, pi, 0, N);
+    }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(argmax_blocks_k, dim3((M + 3) / 4), dim3(256), 0, s, M, P, pv, pi, out);
+    hipLaunchKernelGGL(argmax_blocks_k, dim3(M), dim3(256), 0, s, P, pv, pi, out);
     return hipGetLastError();
 }
 
