@@ -25,8 +25,8 @@ struct ProfRec {
 };
 
 struct Plan {  // byte offsets into the workspace
-    size_t x, xn, qkv, rope_cs, rope_at, parts, att, g, u, act, logits, argmax, feat, top_tok, top_logp, pool_token, pool_score, pool_parent,
-        pool_depth, pool_mask, fr_token, fr_src, fr_pool, fr_mask, row_map, attn_ws, accept_ws, topk_ws, status, total;
+    size_t x, xn, qkv, rope_cs, rope_at, parts, att, g, u, act, logits, argmax, feat, pool_token, pool_score, pool_parent,
+        pool_depth, pool_mask, fr_token, fr_src, fr_pool, fr_mask, attn_ws, accept_ws, topk_ws, status, total;
     size_t attn_ws_bytes, parts_bytes;
     int max_rows, pool_cap, feat_rows;
 };
@@ -70,8 +70,6 @@ bool plan_workspace(const tlt_model_cfg& c, int B, int n, int D, int K, int max_
     p.logits = take(R * V * 4);
     p.argmax = take(R * 4);
     p.feat = take((size_t)B * p.feat_rows * h * 4);
-    p.top_tok = take((size_t)B * K * K * 4);
-    p.top_logp = take((size_t)B * K * K * 4);
     p.pool_token = take((size_t)B * p.pool_cap * 4);
     p.pool_score = take((size_t)B * p.pool_cap * 4);
     p.pool_parent = take((size_t)B * p.pool_cap * 4);
@@ -82,7 +80,6 @@ bool plan_workspace(const tlt_model_cfg& c, int B, int n, int D, int K, int max_
     p.fr_src = take(FRN * 4);
     p.fr_pool = take(FRN * 4);
     p.fr_mask = take(FRN * 16);
-    p.row_map = take((size_t)B * 4);
     p.attn_ws_bytes = attention_workspace_bytes(B, std::max(n, K), c.n_q_heads, c.n_kv_heads, c.head_dim, max_ctx);
     p.attn_ws = take(p.attn_ws_bytes);
     p.accept_ws = take(accept_sample_workspace_bytes(B, c.vocab));
@@ -215,21 +212,19 @@ int fold_pending(tlt_ctx* ctx, hipStream_t s, int M) {
     return TLT_OK;
 }
 
-// out = rmsnorm(x) * gamma over the M rows of the residual stream, x first absorbing what is pending.
-int norm_x(tlt_ctx* ctx, hipStream_t s, int M, const void* gamma, void* out) {
+// out = rmsnorm(x) * gamma over M rows of the residual stream, x first absorbing what is pending for its x_rows rows (0: M; with
+// another io, for the rows that the norm reads: the others are dropped).
+int norm_x(tlt_ctx* ctx, hipStream_t s, int M, const void* gamma, void* out, const NormIO& io = NormIO(), int x_rows = 0) {
     const tlt_model_cfg& c = ctx->cfg;
     float* x = (float*)(ctx->ws + ctx->plan.x);
     const double e = (double)esz_of(ctx);
-    if (ctx->pending_parts > 0) {
-        const int n = ctx->pending_parts;
-        const bool assign = ctx->pending_assign;
-        ctx->pending_parts = 0;
-        ctx->pending_assign = false;
-        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * c.hidden * (8 + 4 * n + e),
-                rmsnorm_add(s, c.dtype, M, c.hidden, x, ctx->ws + ctx->plan.parts, true, gamma, c.rms_eps, out, n, assign));
-    } else {
-        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * c.hidden * (4 + e), rmsnorm(s, c.dtype, M, c.hidden, x, gamma, c.rms_eps, out, nullptr));
-    }
+    const int n = ctx->pending_parts;
+    const bool assign = ctx->pending_assign;
+    ctx->pending_parts = 0;
+    ctx->pending_assign = false;
+    TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * c.hidden * ((n > 0 ? 8 : 4) + 4 * n + e),
+            rmsnorm(s, c.dtype, M, c.hidden, x, gamma, c.rms_eps, out, io, n > 0 ? ctx->ws + ctx->plan.parts : nullptr, true, n,
+                    x_rows > 0 ? x_rows : M, assign));
     return TLT_OK;
 }
 
@@ -297,7 +292,7 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     if (dt == TLT_BF16 && !ctx->oproj_f32 && M > 256) {   // (measurement switch: the product rounded to the model dtype)
         if ((rc = run_gemm(ctx, s, OUT_T, M, h, q_dim, ws + p.att, w.wo, parts))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * (8 + 2 * e),
-                rmsnorm_add(s, dt, M, h, x, parts, false, w.mlp_norm, c.rms_eps, ws + p.xn));
+                rmsnorm(s, dt, M, h, x, w.mlp_norm, c.rms_eps, ws + p.xn, NormIO(), parts, false, 1, M));
     } else {
         if ((rc = run_gemm_parts(ctx, s, M, h, q_dim, ws + p.att, w.wo, &n_parts))) return rc;
         ctx->pending_parts = n_parts;
@@ -471,8 +466,9 @@ int tlt_verify_forward(tlt_ctx* ctx, void* stream, int B, const tlt_tree* tree, 
     // are wanted, a plain add)
     if (out_logits || out_argmax || out_lse) {
         float* logits = out_logits ? out_logits : (float*)(ws + p.logits);
-        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn))) return rc;
-        if (out_hidden) TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * 8, copy_f32(s, (int64_t)M * h, x, out_hidden));
+        NormIO io;
+        io.copy = out_hidden;   // (the stream ends here: its rows leave x for the caller's buffer on the way, where that is wanted)
+        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn, io))) return rc;
         if (!out_logits && !out_lse && gemm_argmax_supported(c.dtype, M, V, h, ws + p.xn, ctx->target.lm_head)) {
             // only the most likely tokens are wanted: the logits never leave the LM head's registers
             // (block partials go where the logits would have gone: M * V/128 * 8 bytes of M * V * 4)
@@ -503,7 +499,7 @@ static int draft_fc(tlt_ctx* ctx, hipStream_t s, int M, const void* xin) {
 }
 
 // Drafter catch-up shared by both expansion modes: entries for the newly committed positions, the
-// last one's output as feature row 0, committed length advanced.
+// last one's output as feature row 0 and, normalised, in the workspace's xn, committed length advanced.
 static int draft_extend_rows(tlt_ctx* ctx, hipStream_t s, int B, const int32_t* new_tokens, const int32_t* new_src,
                              const int32_t* n_new, int new_stride, const float* hidden, int hidden_n, tlt_kv* draft_kv,
                              KVLayer& kvl) {
@@ -512,7 +508,6 @@ static int draft_extend_rows(tlt_ctx* ctx, hipStream_t s, int B, const int32_t* 
     char* ws = ctx->ws;
     const int h = c.hidden, V = c.vocab, dt = c.dtype;
     const double e = (double)esz_of(ctx);
-    float* x = (float*)(ws + p.x);
     float* feat = (float*)(ws + p.feat);
     const int FR = p.feat_rows;
     int rc;
@@ -528,9 +523,13 @@ static int draft_extend_rows(tlt_ctx* ctx, hipStream_t s, int B, const int32_t* 
     rows.pos_stride = 1;
     rows.n_region = new_stride;
     if ((rc = layer_forward(ctx, s, ctx->draft.layers[0], rows, kvl))) return rc;
-    if ((rc = fold_pending(ctx, s, M))) return rc;
-    TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * 8, gather_last_rows(s, B, new_stride, h, n_new, x, feat, FR));
-    TLT_RUN(ctx, s, CLS_OTHER, 0, 0, add_i32(s, B, draft_kv->seq_len, n_new, 0));
+    NormIO io;
+    io.n_valid = n_new;
+    io.n = new_stride;
+    io.copy = feat;
+    io.copy_stride = FR;
+    io.len = draft_kv->seq_len;
+    if ((rc = norm_x(ctx, s, B, ctx->target.final_norm, ws + p.xn, io, M))) return rc;
     kvl.seq_len_bound += new_stride;
     return TLT_OK;
 }
@@ -680,7 +679,7 @@ int tlt_prefill(tlt_ctx* ctx, void* stream, int B, int n_tokens, int chunk, cons
             if ((rc = fold_pending(ctx, s, M))) return rc;
             const int pad = Cp * m - taken;
             TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * 8,
-                    gather_last_rows(s, B, Cp * m, h, nullptr, x - (int64_t)pad * h, (float*)(ws + p.feat), p.feat_rows));
+                    gather_last_rows(s, B, Cp * m, h, x - (int64_t)pad * h, (float*)(ws + p.feat), p.feat_rows));
         }
         ctx->pending_parts = 0;
         TLT_RUN(ctx, s, CLS_OTHER, 0, 0, add_i32(s, B, kv->seq_len, nullptr, taken));
@@ -722,12 +721,8 @@ int tlt_draft_expand(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
     char* ws = ctx->ws;
     const int h = c.hidden, V = c.vocab, dt = c.dtype;
     const double e = (double)esz_of(ctx);
-    float* x = (float*)(ws + p.x);
     float* feat = (float*)(ws + p.feat);
     float* logits = (float*)(ws + p.logits);
-    int32_t* top_tok = (int32_t*)(ws + p.top_tok);
-    float* top_logp = (float*)(ws + p.top_logp);
-    int32_t* row_map = (int32_t*)(ws + p.row_map);
     const int FR = p.feat_rows;
     const tlt_layer_weights& lw = ctx->draft.layers[0];
     KVLayer kvl = kv_layer(ctx, draft_kv, 0);
@@ -749,12 +744,13 @@ int tlt_draft_expand(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
     st.fr_mask = (uint64_t*)(ws + p.fr_mask);
 
     // root distribution: feature row 0 of every sequence -> final norm -> LM head -> top-k
-    TLT_RUN(ctx, s, CLS_OTHER, 0, 0, iota_scaled(s, B, row_map, FR));
-    TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * (4 + e),
-            rmsnorm(s, dt, B, h, feat, ctx->target.final_norm, c.rms_eps, ws + p.xn, row_map));
+    if (!do_extend) {   // (an extend has left it in xn)
+        NormIO io;
+        io.src_stride = FR;
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * (4 + e), rmsnorm(s, dt, B, h, feat, ctx->target.final_norm, c.rms_eps, ws + p.xn, io));
+    }
     if ((rc = run_gemm(ctx, s, OUT_F32, B, V, h, ws + p.xn, ctx->target.lm_head, logits))) return rc;
-    TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * V * 4, row_topk_logp(s, B, V, topk, logits, top_tok, top_logp, ws + p.topk_ws));
-    TLT_RUN(ctx, s, CLS_OTHER, 0, 0, draft_level0(s, B, topk, top_tok, top_logp, st, FR));
+    TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * V * 4, draft_level(s, B, topk, 0, V, logits, ws + p.topk_ws, st));
 
     for (int level = 1; level < depth; ++level) {
         const int M = B * topk;
@@ -772,11 +768,14 @@ int tlt_draft_expand(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
         rows.mask_words = 2;
         rows.n_region = level * topk;
         if ((rc = layer_forward(ctx, s, lw, rows, kvl))) return rc;
-        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn))) return rc;   // (absorbs the pending down projection into x)
-        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * 8, scatter_rows(s, M, topk, h, x, feat, FR, 1 + (level - 1) * topk));
+        NormIO io;   // the block's output (x and the pending down projection) goes to the level's feature rows
+        io.copy = feat;
+        io.copy_n = topk;
+        io.copy_stride = FR;
+        io.copy_base = 1 + (level - 1) * topk;
+        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn, io))) return rc;
         if ((rc = run_gemm(ctx, s, OUT_F32, M, V, h, ws + p.xn, ctx->target.lm_head, logits))) return rc;
-        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * V * 4, row_topk_logp(s, M, V, topk, logits, top_tok, top_logp, ws + p.topk_ws));
-        TLT_RUN(ctx, s, CLS_OTHER, 0, 0, draft_level_select(s, B, topk, level, top_tok, top_logp, st, FR));
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * V * 4, draft_level(s, B, topk, level, V, logits, ws + p.topk_ws, st));
     }
     TLT_RUN(ctx, s, CLS_OTHER, 0, 0,
             draft_prune(s, B, pool_n, out_tree->n, root_tokens, new_tokens, n_new, new_stride, st, out_tree->token, out_tree->parent, out_tree->depth,
@@ -841,10 +840,8 @@ int tlt_draft_sample(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
     char* ws = ctx->ws;
     const int h = c.hidden, V = c.vocab, dt = c.dtype;
     const double e = (double)esz_of(ctx);
-    float* x = (float*)(ws + p.x);
     float* feat = (float*)(ws + p.feat);
     float* logits = (float*)(ws + p.logits);
-    int32_t* row_map = (int32_t*)(ws + p.row_map);
     int32_t* fr_token = (int32_t*)(ws + p.fr_token);
     int32_t* fr_src = (int32_t*)(ws + p.fr_src);
     uint64_t* fr_mask = (uint64_t*)(ws + p.fr_mask);
@@ -869,9 +866,11 @@ int tlt_draft_sample(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
     lv.node[0] = 0;
     lv.first_child[0] = (uint8_t)first_child[0];
     lv.n_child[0] = (uint8_t)n_child[0];
-    TLT_RUN(ctx, s, CLS_OTHER, 0, 0, iota_scaled(s, B, row_map, FR));
-    TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * (4 + e),
-            rmsnorm(s, dt, B, h, feat, ctx->target.final_norm, c.rms_eps, ws + p.xn, row_map));
+    if (!do_extend) {   // (an extend has left it in xn)
+        NormIO io;
+        io.src_stride = FR;
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * (4 + e), rmsnorm(s, dt, B, h, feat, ctx->target.final_norm, c.rms_eps, ws + p.xn, io));
+    }
     if ((rc = run_gemm(ctx, s, OUT_F32, B, V, h, ws + p.xn, ctx->target.lm_head, logits))) return rc;
     TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * V * 12,
             softmax_draw(s, B, n, V, temperature, lv, logits, u_draw, out_tree->token, out_draft_q,
@@ -912,8 +911,12 @@ int tlt_draft_sample(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
         rows.mask_words = 1;
         rows.n_region = slot_base + lv.R;
         if ((rc = layer_forward(ctx, s, lw, rows, kvl))) return rc;
-        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn))) return rc;   // (absorbs the pending down projection into x)
-        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * 8, scatter_rows(s, M, lv.R, h, x, feat, FR, 1 + slot_base));
+        NormIO io;
+        io.copy = feat;
+        io.copy_n = lv.R;
+        io.copy_stride = FR;
+        io.copy_base = 1 + slot_base;
+        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn, io))) return rc;
         if ((rc = run_gemm(ctx, s, OUT_F32, M, V, h, ws + p.xn, ctx->target.lm_head, logits))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * V * 12,
                 softmax_draw(s, B, n, V, temperature, lv, logits, u_draw, out_tree->token, out_draft_q,

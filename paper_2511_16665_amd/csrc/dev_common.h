@@ -37,16 +37,24 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+// The value combined over all lanes, in every lane, pairing lanes 32, 16, 8, 4, 2 and 1 apart in that order: the half-waves and the odd and
+// even 16-lane rows through v_permlane32_swap / v_permlane16_swap (swapping a register with a copy of itself leaves the own and the
+// partner's value side by side), the lanes of a row through DPP rotations by 8 and 4 and the two quad permutations.  (A shuffle goes
+// through the LDS crossbar: six dependent trips of ~100 clocks.  The sums are the same bit for bit.)
+template <typename F>
+__device__ __forceinline__ float wave_all(float v, F f) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    v = f(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, false)));   // row_ror:8
+    v = f(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xF, 0xF, false)));   // row_ror:4
+    v = f(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false)));    // quad_perm:[2,3,0,1]
+    v = f(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false)));    // quad_perm:[1,0,3,2]
     return v;
 }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
+__device__ __forceinline__ float wave_max(float v) { return wave_all(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float wave_sum(float v) { return wave_all(v, [](float a, float b) { return a + b; }); }
 
 // 16 bytes per lane from global memory straight into LDS at lds_byte_offset + lane * 16 (the offset
 // must be wave-uniform).  Issued through inline assembly on purpose: the compiler then does not

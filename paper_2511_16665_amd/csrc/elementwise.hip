@@ -6,41 +6,76 @@
 
 namespace tlt {
 
-template <typename T>
-__global__ void embed_rows_k(int M, int h, int V, const int32_t* __restrict__ tokens, const T* __restrict__ embed,
-                             float* __restrict__ x) {
-    int r = blockIdx.x;
-    int t = tokens[r];
-    bool ok = t >= 0 && t < V;
+// Four consecutive elements at a 4-element boundary (8 or 16 bytes) as floats, and back.
+__device__ __forceinline__ float4 load_four(const float* p) { return *(const float4*)p; }
+__device__ __forceinline__ float4 load_four(const bf16* p) {
+    const uint2 v = *(const uint2*)p;
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+}
+__device__ __forceinline__ void store_four(float* p, const float4& v) { *(float4*)p = v; }
+__device__ __forceinline__ void store_four(bf16* p, const float4& v) { *(uint2*)p = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)); }
+
+// VEC: h % 4 == 0 and every base on a boundary of four elements (the rows are then, too): a row's loads are a few per thread and all
+// in flight at once; element by element it was a chain of them (256 rows of 3584: 10.6 -> 5.3 us; the drafter's input below, 8 rows: 7.7 -> 5.2).
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void embed_rows_k(int M, int h, int V, const int32_t* __restrict__ tokens, const T* __restrict__ embed,
+                                                    float* __restrict__ x) {
+    const int r = blockIdx.x, t = tokens[r];
+    const bool ok = t >= 0 && t < V;
     const T* e = embed + (int64_t)(ok ? t : 0) * h;
-    for (int c = threadIdx.x; c < h; c += blockDim.x) x[(int64_t)r * h + c] = ok ? to_float(e[c]) : 0.f;
+    float* o = x + (int64_t)r * h;
+    if constexpr (VEC) {
+#pragma unroll 4
+        for (int c = 4 * threadIdx.x; c < h; c += 4 * 256) store_four(o + c, ok ? load_four(e + c) : make_float4(0.f, 0.f, 0.f, 0.f));
+    } else {
+        for (int c = threadIdx.x; c < h; c += 256) o[c] = ok ? to_float(e[c]) : 0.f;
+    }
 }
 
-// `add` (optional, [rows][h] in TA = T or float, no row_map then): the residual stream takes x[r] += add[r]
+// Row r of a norm launch: where it is read, and where it goes with its addends absorbed (see NormIO).
+struct NormRow {
+    const float* in;
+    float* keep;      // null: it stays where it is
+    int64_t src;      // row of x, and of the addends
+    bool absorb;
+};
+__device__ __forceinline__ NormRow norm_row(const NormIO& io, int h, float* x, bool add) {
+    const int r = blockIdx.x;
+    NormRow o;
+    o.src = (int64_t)r * io.src_stride;
+    float* copy = io.copy ? io.copy + ((int64_t)(r / io.copy_n) * io.copy_stride + io.copy_base + r % io.copy_n) * h : nullptr;
+    bool have = true;
+    if (io.n > 0) {
+        const int raw = io.n_valid[r], nv = raw < io.n ? raw : io.n;
+        have = nv > 0;
+        o.src = (int64_t)r * io.n + (have ? nv - 1 : 0);
+        if (io.len && threadIdx.x == 0) io.len[r] += raw;
+    }
+    o.in = have ? x + o.src * h : copy;   // (no new row: the one that was kept last time)
+    o.absorb = have && add;
+    o.keep = !have ? nullptr : (copy ? copy : (add ? x + o.src * h : nullptr));
+    return o;
+}
+
+// `add` (optional, [n_add][rows of x][h] in TA = T or float): the residual stream takes x[r] += add[r]
 // first -- the output projection leaves its product there instead of read-modify-writing x itself.
 template <typename T, typename TA>
 __global__ __launch_bounds__(256) void rmsnorm_k(int h, float* __restrict__ x, const T* __restrict__ gamma,
-                                                 float eps, T* __restrict__ out, const int32_t* __restrict__ row_map,
-                                                 const TA* __restrict__ add, float* __restrict__ zero, int zero_n, int n_add,
+                                                 float eps, T* __restrict__ out, NormIO io, const TA* __restrict__ add, int n_add,
                                                  int64_t add_stride, int assign) {
     __shared__ float red[4];
-    int r = blockIdx.x;
-    if (zero)
-        for (int c = threadIdx.x; c < zero_n; c += 256) zero[(int64_t)r * zero_n + c] = 0.f;
-    int64_t src = row_map ? row_map[r] : r;
-    T* o = out + (int64_t)r * h;
-    if (src < 0) {
-        for (int c = threadIdx.x; c < h; c += 256) o[c] = from_float<T>(0.f);
-        return;
-    }
-    float* xr = x + src * h;
+    const NormRow row = norm_row(io, h, x, add != nullptr);
+    T* o = out + (int64_t)blockIdx.x * h;
+    auto value = [&](int c) {
+        float v = (row.absorb && assign) ? 0.f : row.in[c];
+        if (row.absorb)
+            for (int k = 0; k < n_add; ++k) v += to_float(add[k * add_stride + row.src * h + c]);
+        return v;
+    };
     float ss = 0.f;
     for (int c = threadIdx.x; c < h; c += 256) {
-        float v = (add && assign) ? 0.f : xr[c];
-        if (add) {   // (each element is read, updated and later re-read by the same thread)
-            for (int k = 0; k < n_add; ++k) v += to_float(add[k * add_stride + src * h + c]);
-            xr[c] = v;
-        }
+        const float v = value(c);
+        if (row.keep) row.keep[c] = v;   // (each element is read, kept and read again by the same thread)
         ss += v * v;
     }
     ss = wave_sum(ss);
@@ -48,23 +83,20 @@ __global__ __launch_bounds__(256) void rmsnorm_k(int h, float* __restrict__ x, c
     __syncthreads();
     float tot = red[0] + red[1] + red[2] + red[3];
     float inv = 1.0f / sqrtf(tot / (float)h + eps);
-    for (int c = threadIdx.x; c < h; c += 256) o[c] = from_float<T>(xr[c] * inv * to_float(gamma[c]));
+    const float* again = row.keep ? row.keep : row.in;
+    for (int c = threadIdx.x; c < h; c += 256) o[c] = from_float<T>(again[c] * inv * to_float(gamma[c]));
 }
 
 // Same, for h % 4 == 0 and h <= 1024 * NK: the row is read once with 16-byte loads and stays in
 // registers (NK float4 per thread) between the reduction and the scaling.
 template <typename T, int NK, typename TA, int NB = 4, int NTHR = 256>   // NB: slices of `add` whose loads are issued together
 __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__ x, const T* __restrict__ gamma,
-                                                     float eps, T* __restrict__ out, const int32_t* __restrict__ row_map,
-                                                     const TA* __restrict__ add, float* __restrict__ zero, int zero_n, int n_add,
-                                                     int64_t add_stride, int assign) {
+                                                     float eps, T* __restrict__ out, NormIO io, const TA* __restrict__ add,
+                                                     int n_add, int64_t add_stride, int assign) {
     __shared__ float red[NTHR / 64];
-    const int r = blockIdx.x, h4 = h >> 2;
-    if (zero)   // row r of a second buffer cleared on the way (zero_n % 4 == 0, 16-byte aligned: the launcher checks)
-        for (int c = threadIdx.x; c < (zero_n >> 2); c += NTHR)
-            ((float4*)(zero + (int64_t)r * zero_n))[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int64_t src = row_map ? row_map[r] : r;
-    T* o = out + (int64_t)r * h;
+    const int h4 = h >> 2;
+    const NormRow row = norm_row(io, h, x, add != nullptr);
+    T* o = out + (int64_t)blockIdx.x * h;
     float4 v[NK];
     // (the gains are requested with the row, not after the reduction: one memory latency instead of two)
     typedef __attribute__((ext_vector_type(sizeof(T)))) uint32_t gain_t;   // four T
@@ -75,14 +107,13 @@ __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__
         gv[k] = c < h4 ? ((const gain_t*)gamma)[c] : gain_t{};
     }
     float ss = 0.f;
-    if (src >= 0) {
-        float4* xr = (float4*)(x + src * h);
+    {
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
             const int c = threadIdx.x + k * NTHR;
-            v[k] = (c < h4 && !(add && assign)) ? xr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (add && c < h4) {
-                const TA* a = add + src * h + 4 * c;
+            v[k] = (c < h4 && !(row.absorb && assign)) ? ((const float4*)row.in)[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+            if (row.absorb && c < h4) {
+                const TA* a = add + row.src * h + 4 * c;
                 if constexpr (sizeof(TA) == 2) {
                     const uint2 pk = *(const uint2*)a;
                     v[k].x += __uint_as_float(pk.x << 16);
@@ -103,8 +134,8 @@ __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__
                         }
                     }
                 }
-                xr[c] = v[k];
             }
+            if (row.keep && c < h4) ((float4*)row.keep)[c] = v[k];
             ss += v[k].x * v[k].x + v[k].y * v[k].y + v[k].z * v[k].z + v[k].w * v[k].w;
         }
     }
@@ -114,7 +145,7 @@ __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__
     float tot = 0.f;
 #pragma unroll
     for (int w = 0; w < NTHR / 64; ++w) tot += red[w];
-    const float inv = src >= 0 ? 1.0f / sqrtf(tot / (float)h + eps) : 0.f;
+    const float inv = 1.0f / sqrtf(tot / (float)h + eps);
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
         const int c = threadIdx.x + k * NTHR;
@@ -128,7 +159,6 @@ __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__
             for (int q = 0; q < 4; ++q) g[q] = __uint_as_float(gv[k][q]);
         }
         float y[4] = {v[k].x * inv * g[0], v[k].y * inv * g[1], v[k].z * inv * g[2], v[k].w * inv * g[3]};
-        if (src < 0) y[0] = y[1] = y[2] = y[3] = 0.f;
         if constexpr (sizeof(T) == 2) {
             *(uint2*)(o + 4 * c) = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
         } else {
@@ -347,8 +377,8 @@ __global__ void swiglu_k(int64_t count, const T* __restrict__ g, const T* __rest
     }
 }
 
-template <typename T>
-__global__ void draft_input_k(int n, int h, int V, const int32_t* __restrict__ tok, const int32_t* __restrict__ src,
+template <typename T, bool VEC>   // (VEC: as embed_rows_k)
+__global__ __launch_bounds__(256) void draft_input_k(int n, int h, int V, const int32_t* __restrict__ tok, const int32_t* __restrict__ src,
                               const int32_t* __restrict__ n_valid, int src_seq_stride, int64_t hidden_rows,
                               const float* __restrict__ hidden, const T* __restrict__ embed, T* __restrict__ xin) {
     int r = blockIdx.x;
@@ -362,7 +392,19 @@ __global__ void draft_input_k(int n, int h, int V, const int32_t* __restrict__ t
     }
     ok = ok && sr < hidden_rows;
     T* o = xin + (int64_t)r * 2 * h;
-    for (int c = threadIdx.x; c < h; c += blockDim.x) {
+    if constexpr (VEC) {
+        const T* e = embed + (int64_t)(ok ? t : 0) * h;
+        const float* hid = hidden + (ok ? sr : 0) * h;
+        const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+        for (int c = 4 * threadIdx.x; c < h; c += 4 * 256) {
+            const float4 a = ok ? load_four(e + c) : z, b4 = ok ? load_four(hid + c) : z;
+            store_four(o + c, a);
+            store_four(o + h + c, b4);
+        }
+        return;
+    }
+    for (int c = threadIdx.x; c < h; c += 256) {
         o[c] = ok ? embed[(int64_t)t * h + c] : from_float<T>(0.f);
         o[h + c] = ok ? from_float<T>(hidden[sr * h + c]) : from_float<T>(0.f);
     }
@@ -385,28 +427,11 @@ __global__ void copy_f32_k(int64_t count, const float4* __restrict__ src, float4
     for (; i < count; i += stride) dst[i] = src[i];
 }
 
-// dst row (r / n) * dst_seq_stride + dst_base + r % n  <-  src row r   (h floats, h % 4 == 0)
-__global__ void scatter_rows_k(int n, int h4, const float4* __restrict__ src, float4* __restrict__ dst, int dst_seq_stride,
-                               int dst_base) {
-    int r = blockIdx.x;
-    int64_t d = (int64_t)(r / n) * dst_seq_stride + dst_base + (r % n);
-    for (int c = threadIdx.x; c < h4; c += blockDim.x) dst[d * h4 + c] = src[(int64_t)r * h4 + c];
-}
-
-// Per sequence: last active row of x [B][n][h] -> dst row b * dst_seq_stride; nothing when n_valid[b] <= 0.
-__global__ void gather_last_rows_k(int n, int h4, const int32_t* __restrict__ n_valid, const float4* __restrict__ src,
-                                   float4* __restrict__ dst, int dst_seq_stride) {
-    int b = blockIdx.x;
-    int nv = n_valid ? n_valid[b] : n;
-    if (nv > n) nv = n;
-    if (nv <= 0) return;
-    int64_t sr = (int64_t)b * n + nv - 1, d = (int64_t)b * dst_seq_stride;
+// Last row of every n rows of x -> dst row b * dst_seq_stride.
+__global__ void gather_last_rows_k(int n, int h4, const float4* __restrict__ src, float4* __restrict__ dst, int dst_seq_stride) {
+    const int b = blockIdx.x;
+    const int64_t sr = (int64_t)b * n + n - 1, d = (int64_t)b * dst_seq_stride;
     for (int c = threadIdx.x; c < h4; c += blockDim.x) dst[d * h4 + c] = src[sr * h4 + c];
-}
-
-__global__ void iota_scaled_k(int n, int32_t* out, int scale) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = i * scale;
 }
 
 // One workgroup per virtual sequence b * C + j = chunk j of sequence b in this pass (see PrefillPass).
@@ -444,52 +469,46 @@ hipError_t prefill_rows(hipStream_t s, int B, const PrefillPass& p) {
 
 hipError_t embed_rows(hipStream_t s, int dtype, int M, int h, int V, const int32_t* tokens, const void* embed, float* x) {
     if (M <= 0) return hipSuccess;
-    DISPATCH_T(dtype, hipLaunchKernelGGL(embed_rows_k<T>, dim3(M), dim3(256), 0, s, M, h, V, tokens, (const T*)embed, x));
+    const uintptr_t four = dtype == F32 ? 15 : 7;
+    if (h % 4 == 0 && ((uintptr_t)embed & four) == 0 && ((uintptr_t)x & 15) == 0) {
+        DISPATCH_T(dtype, hipLaunchKernelGGL((embed_rows_k<T, true>), dim3(M), dim3(256), 0, s, M, h, V, tokens, (const T*)embed, x));
+    } else {
+        DISPATCH_T(dtype, hipLaunchKernelGGL((embed_rows_k<T, false>), dim3(M), dim3(256), 0, s, M, h, V, tokens, (const T*)embed, x));
+    }
     return hipGetLastError();
 }
 
 template <typename T, typename TA>
-static void rmsnorm_launch_t(hipStream_t s, int M, int h, float* x, const void* gamma, float eps, void* out,
-                             const int32_t* row_map, const void* add, float* zero, int zero_n, int n_add, bool assign) {
-    const int64_t add_stride = (int64_t)M * h;
-    const bool vec_ok = h % 4 == 0 && (((uintptr_t)x | (uintptr_t)add | (uintptr_t)zero) & 15) == 0 && zero_n % 4 == 0 &&
+static void rmsnorm_launch_t(hipStream_t s, int M, int h, float* x, const void* gamma, float eps, void* out, const NormIO& io,
+                             const void* add, int n_add, int64_t add_rows, bool assign) {
+    const int64_t add_stride = add_rows * h;
+    const bool vec_ok = h % 4 == 0 && (((uintptr_t)x | (uintptr_t)add | (uintptr_t)io.copy) & 15) == 0 &&
                         ((uintptr_t)gamma & (4 * sizeof(T) - 1)) == 0;
     if (vec_ok && h <= 4096 && add && (n_add > 4 || M <= 64) && sizeof(TA) == 4)
         // many slices or few rows (so few workgroups): one 16-byte position per thread and all its slices' loads in
         // flight at once.  (Few rows and up to four slices, against 256 threads, us per norm inside a forward of 1-32 rows: widths
         // 3584 and 4096 1.4 less, 1536 0.4 less, 256 to 1024 and 2048 the same within 0.3, though most waves are idle at 256.)
         hipLaunchKernelGGL((rmsnorm_vec_k<T, 1, TA, 12, 1024>), dim3(M), dim3(1024), 0, s, h, x, (const T*)gamma, eps, (T*)out,
-                           row_map, (const TA*)add, zero, zero_n, n_add, add_stride, (int)assign);
+                           io, (const TA*)add, n_add, add_stride, (int)assign);
     else if (vec_ok && h <= 4096)
-        hipLaunchKernelGGL((rmsnorm_vec_k<T, 4, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, row_map,
-                           (const TA*)add, zero, zero_n, n_add, add_stride, (int)assign);
+        hipLaunchKernelGGL((rmsnorm_vec_k<T, 4, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, io,
+                           (const TA*)add, n_add, add_stride, (int)assign);
     else if (vec_ok && h <= 8192)   // (the 32B and 70B widths)
-        hipLaunchKernelGGL((rmsnorm_vec_k<T, 8, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, row_map,
-                           (const TA*)add, zero, zero_n, n_add, add_stride, (int)assign);
+        hipLaunchKernelGGL((rmsnorm_vec_k<T, 8, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, io,
+                           (const TA*)add, n_add, add_stride, (int)assign);
     else
-        hipLaunchKernelGGL((rmsnorm_k<T, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, row_map,
-                           (const TA*)add, zero, zero_n, n_add, add_stride, (int)assign);
+        hipLaunchKernelGGL((rmsnorm_k<T, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, io,
+                           (const TA*)add, n_add, add_stride, (int)assign);
 }
 
-static hipError_t rmsnorm_launch(hipStream_t s, int dtype, int M, int h, float* x, const void* gamma, float eps, void* out,
-                                 const int32_t* row_map, const void* add, bool add_f32 = false, float* zero = nullptr,
-                                 int zero_n = 0, int n_add = 1, bool assign = false) {
+hipError_t rmsnorm(hipStream_t s, int dtype, int M, int h, float* x, const void* gamma, float eps, void* out, const NormIO& io,
+                   const void* add, bool add_f32, int n_add, int64_t add_rows, bool assign) {
     if (M <= 0) return hipSuccess;
     if (add && !add_f32 && dtype != F32 && n_add != 1) return hipErrorInvalidValue;   // several addends: fp32 partial products only
-    if (dtype == F32) rmsnorm_launch_t<float, float>(s, M, h, x, gamma, eps, out, row_map, add, zero, zero_n, n_add, assign);
-    else if (add_f32) rmsnorm_launch_t<bf16, float>(s, M, h, x, gamma, eps, out, row_map, add, zero, zero_n, n_add, assign);
-    else rmsnorm_launch_t<bf16, bf16>(s, M, h, x, gamma, eps, out, row_map, add, zero, zero_n, n_add, assign);
+    if (dtype == F32) rmsnorm_launch_t<float, float>(s, M, h, x, gamma, eps, out, io, add, n_add, add_rows, assign);
+    else if (!add || add_f32) rmsnorm_launch_t<bf16, float>(s, M, h, x, gamma, eps, out, io, add, n_add, add_rows, assign);
+    else rmsnorm_launch_t<bf16, bf16>(s, M, h, x, gamma, eps, out, io, add, n_add, add_rows, assign);
     return hipGetLastError();
-}
-
-hipError_t rmsnorm(hipStream_t s, int dtype, int M, int h, const float* x, const void* gamma, float eps, void* out,
-                   const int32_t* row_map, float* zero, int zero_n) {
-    return rmsnorm_launch(s, dtype, M, h, const_cast<float*>(x), gamma, eps, out, row_map, nullptr, false, zero, zero_n);   // x is only read
-}
-
-hipError_t rmsnorm_add(hipStream_t s, int dtype, int M, int h, float* x, const void* add, bool add_f32, const void* gamma,
-                       float eps, void* out, int n_add, bool assign) {
-    return rmsnorm_launch(s, dtype, M, h, x, gamma, eps, out, nullptr, add, add_f32, nullptr, 0, n_add, assign);
 }
 
 __global__ void add_parts_k(int64_t count4, float4* __restrict__ x, const float4* __restrict__ parts, int n_parts, int assign) {
@@ -555,8 +574,14 @@ hipError_t draft_input(hipStream_t s, int dtype, int B, int n, int h, int V, con
                        const int32_t* n_valid, int src_seq_stride, int64_t hidden_rows, const float* hidden,
                        const void* embed, void* xin) {
     if (B * n <= 0) return hipSuccess;
-    DISPATCH_T(dtype, hipLaunchKernelGGL(draft_input_k<T>, dim3(B * n), dim3(256), 0, s, n, h, V, tok, src, n_valid,
-                                         src_seq_stride, hidden_rows, hidden, (const T*)embed, (T*)xin));
+    const uintptr_t four = dtype == F32 ? 15 : 7;
+    const bool vec = h % 4 == 0 && (((uintptr_t)embed | (uintptr_t)xin) & four) == 0 && ((uintptr_t)hidden & 15) == 0;
+#define TLT_DRAFT_INPUT(VEC)                                                                                                     \
+    DISPATCH_T(dtype, hipLaunchKernelGGL((draft_input_k<T, VEC>), dim3(B * n), dim3(256), 0, s, n, h, V, tok, src, n_valid,      \
+                                         src_seq_stride, hidden_rows, hidden, (const T*)embed, (T*)xin))
+    if (vec) { TLT_DRAFT_INPUT(true); }
+    else { TLT_DRAFT_INPUT(false); }
+#undef TLT_DRAFT_INPUT
     return hipGetLastError();
 }
 
@@ -584,24 +609,9 @@ hipError_t zero_f32(hipStream_t s, int64_t count, float* dst) {
     return hipGetLastError();
 }
 
-hipError_t scatter_rows(hipStream_t s, int R, int n, int h, const float* src, float* dst, int dst_seq_stride, int dst_base) {
-    if (R <= 0) return hipSuccess;
-    hipLaunchKernelGGL(scatter_rows_k, dim3(R), dim3(256), 0, s, n, h / 4, (const float4*)src, (float4*)dst, dst_seq_stride,
-                       dst_base);
-    return hipGetLastError();
-}
-
-hipError_t gather_last_rows(hipStream_t s, int B, int n, int h, const int32_t* n_valid, const float* src, float* dst,
-                            int dst_seq_stride) {
+hipError_t gather_last_rows(hipStream_t s, int B, int n, int h, const float* src, float* dst, int dst_seq_stride) {
     if (B <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gather_last_rows_k, dim3(B), dim3(256), 0, s, n, h / 4, n_valid, (const float4*)src, (float4*)dst,
-                       dst_seq_stride);
-    return hipGetLastError();
-}
-
-hipError_t iota_scaled(hipStream_t s, int n, int32_t* out, int scale) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(iota_scaled_k, dim3((n + 255) / 256), dim3(256), 0, s, n, out, scale);
+    hipLaunchKernelGGL(gather_last_rows_k, dim3(B), dim3(256), 0, s, n, h / 4, (const float4*)src, (float4*)dst, dst_seq_stride);
     return hipGetLastError();
 }
 

@@ -73,14 +73,21 @@ hipError_t mfma_stream(hipStream_t s, const void* frags, float* out, int iters);
 
 // ---- elementwise.hip
 hipError_t embed_rows(hipStream_t s, int dtype, int M, int h, int V, const int32_t* tokens, const void* embed, float* x);
-// out[r] = rmsnorm(x[row_map ? row_map[r] : r]) * gamma, stored in dtype.  Rows with row_map < 0 give zeros.
-// zero (optional): a second fp32 buffer [M][zero_n] cleared row by row in the same launch.
-hipError_t rmsnorm(hipStream_t s, int dtype, int M, int h, const float* x, const void* gamma, float eps, void* out,
-                   const int32_t* row_map, float* zero = nullptr, int zero_n = 0);
-// x[r] += sum_k add[k][r] (add [n_add][M][h] in fp32 when add_f32, else one [M][h] in dtype; assign: x[r] = that sum
-// instead), then out[r] = rmsnorm(x[r]) * gamma.  The sum runs in the order k = 0, 1, ...: reproducible.
-hipError_t rmsnorm_add(hipStream_t s, int dtype, int M, int h, float* x, const void* add, bool add_f32, const void* gamma,
-                       float eps, void* out, int n_add = 1, bool assign = false);
+// Which row of x row r of a norm launch is, and where it is kept once the addends are absorbed.
+struct NormIO {
+    int src_stride = 1;                // row r * src_stride ...
+    const int32_t* n_valid = nullptr;  // ... or, with n > 0, the last active of sequence r's n rows (its n_valid[r]-th)
+    int n = 0;
+    // kept in copy row (r / copy_n) * copy_stride + copy_base + r % copy_n; null: back in x, if there are addends.  A sequence
+    // without active rows keeps its copy row, which is then the row to normalise.
+    float* copy = nullptr;
+    int copy_n = 1, copy_stride = 1, copy_base = 0;
+    int32_t* len = nullptr;            // with n > 0 (optional): len[r] += n_valid[r]
+};
+// x[row] += sum_k add[k][row] (add [n_add][add_rows][h], optional, in fp32 when add_f32, else n_add = 1 in dtype; assign: x[row] = that
+// sum instead), then out[r] = rmsnorm(x[row]) * gamma in dtype.  The sum runs in the order k = 0, 1, ...: reproducible.
+hipError_t rmsnorm(hipStream_t s, int dtype, int M, int h, float* x, const void* gamma, float eps, void* out, const NormIO& io = NormIO(),
+                   const void* add = nullptr, bool add_f32 = true, int n_add = 0, int64_t add_rows = 0, bool assign = false);
 // x += sum_k parts[k] (or x = with assign), count floats each (a multiple of 4)
 hipError_t add_parts(hipStream_t s, int64_t count, float* x, const float* parts, int n_parts, bool assign);
 // (bias: optional [(Hq+2Hkv)*d] in dtype, added to q, k and v before the rotation; src32: optional
@@ -104,10 +111,8 @@ hipError_t draft_input(hipStream_t s, int dtype, int B, int n, int h, int V, con
 hipError_t add_i32(hipStream_t s, int n, int32_t* dst, const int32_t* a, int add_const);
 hipError_t copy_f32(hipStream_t s, int64_t count, const float* src, float* dst);
 hipError_t zero_f32(hipStream_t s, int64_t count, float* dst);   // a kernel, not a memset: safe to capture in a graph
-hipError_t scatter_rows(hipStream_t s, int R, int n, int h, const float* src, float* dst, int dst_seq_stride, int dst_base);
-hipError_t gather_last_rows(hipStream_t s, int B, int n, int h, const int32_t* n_valid, const float* src, float* dst,
-                            int dst_seq_stride);
-hipError_t iota_scaled(hipStream_t s, int n, int32_t* out, int scale);
+// the last of every n rows of src -> row b * dst_seq_stride of dst
+hipError_t gather_last_rows(hipStream_t s, int B, int n, int h, const float* src, float* dst, int dst_seq_stride);
 
 // A pass over C consecutive chunks of m prompt tokens of each of B sequences: every chunk is a (virtual) sequence of its own, whose
 // block table is its sequence's and whose length ends where the chunk begins.
@@ -136,9 +141,7 @@ hipError_t row_argmax(hipStream_t s, int M, int V, const float* logits, int32_t*
                       size_t scratch_bytes = 0);
 // out [M][2]: (max, log-sum-exp) of every row
 hipError_t row_lse(hipStream_t s, int M, int V, const float* logits, float* out);
-// per row: log-softmax statistics and the K best (token, log-prob) pairs, best first.
 size_t row_topk_workspace_bytes(int M, int V, int K);
-hipError_t row_topk_logp(hipStream_t s, int M, int V, int K, const float* logits, int32_t* tok, float* logp, void* ws);
 
 struct DraftState {  // device arrays owned by the workspace; P = pool capacity per sequence
     int P = 0;
@@ -152,12 +155,10 @@ struct DraftState {  // device arrays owned by the workspace; P = pool capacity 
     uint64_t* fr_mask = nullptr;     // [B][K][2] visibility over provisional drafter rows
     uint64_t* pool_mask = nullptr;   // [B][P][2] mask of expanded candidates (valid for frontier members)
 };
-// level 0: root candidates -> pool[0..K) and first frontier (all of them, in rank order).
-hipError_t draft_level0(hipStream_t s, int B, int K, const int32_t* top_tok, const float* top_logp, DraftState st,
-                        int feat_rows_per_seq);
-// level >= 1: K*K children of the frontier -> pool, next frontier = K best by path score.
-hipError_t draft_level_select(hipStream_t s, int B, int K, int level, const int32_t* top_tok, const float* top_logp,
-                              DraftState st, int feat_rows_per_seq);
+// One drafter level's logits [B (level 0) or B * K][V] -> its candidates in the pool (per row the K best (token, log-probability)
+// pairs, best first) and the next frontier: level 0 all K root candidates in rank order, then the K best by path score of the frontier's
+// K*K children.  ws: row_topk_workspace_bytes(B * K, V, K) bytes.  K <= 16.
+hipError_t draft_level(hipStream_t s, int B, int K, int level, int V, const float* logits, void* ws, DraftState st);
 hipError_t draft_prune(hipStream_t s, int B, int pool_n, int n_tree, const int32_t* root_tokens,
                        const int32_t* new_tokens, const int32_t* n_new, int new_stride, DraftState st, int32_t* token, int32_t* parent, int32_t* depth, uint64_t* anc_mask, float* score);
 hipError_t tree_finalize(hipStream_t s, int B, int n, const int32_t* parent, int32_t* depth, uint64_t* anc_mask);

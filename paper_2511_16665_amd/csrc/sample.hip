@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void row_lse_k(int V, const float* __restrict_
 // (1) One wave per (row, segment of kTopkSeg logits): the segment is read once into registers, then
 //     its max, its sum of exponentials and its K best entries in the (value desc, index asc) order
 //     are written out.
-// (2) One wave per row merges the segments: the K best of the union of the per-segment lists are
+// (2) One wave per row merges the segments (draft_level_k): the K best of the union of the per-segment lists are
 //     the K best of the row because the order is total.
 constexpr int kTopkSeg = 2048;     // logits per wave: 32 per lane, held in registers
 constexpr int kTopkPerLane = kTopkSeg / 64;
@@ -287,135 +287,134 @@ __global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, c
     }
 }
 
-__global__ __launch_bounds__(64) void row_topk_merge_k(int K, int n_seg, const float* __restrict__ seg_stat,
-                                                       const float* __restrict__ seg_val,
-                                                       const int32_t* __restrict__ seg_idx, int32_t* __restrict__ tok,
-                                                       float* __restrict__ logp) {
-    const int row = blockIdx.x, lane = threadIdx.x;
-    const int64_t o = (int64_t)row * n_seg;
-    float mx = -INFINITY;
-    for (int sgm = lane; sgm < n_seg; sgm += 64) mx = fmaxf(mx, seg_stat[2 * (o + sgm)]);
-    mx = wave_max(mx);
-    float se = 0.f;
-    for (int sgm = lane; sgm < n_seg; sgm += 64) se += seg_stat[2 * (o + sgm) + 1] * expf(seg_stat[2 * (o + sgm)] - mx);
-    se = wave_sum(se);
-    const float lse = mx + logf(se);
-    const int n_cand = n_seg * K;
-    // the candidates are read once: a lane keeps up to kMergeRegs of them in registers (75 segments x 8 at the
-    // 152064-token vocabulary: 10 per lane); longer lists are scanned from memory in every round
-    constexpr int kMergeRegs = 20;
-    const bool in_regs = n_cand <= 64 * kMergeRegs;
-    float rv[kMergeRegs];
-    int rj[kMergeRegs];
+// Drafter tree bookkeeping.  Feature-buffer rows per sequence: 0 = output of the entry holding the
+// root token; 1 + (level-1)*K + r = output of frontier node r of `level`.  Provisional drafter
+// cache row of that node = (level-1)*K + r past the committed length; masks are over those rows.
+//
+// One workgroup per sequence, one wave per row of the level (one at level 0, else the K frontier nodes): each merges its row's segments
+// into the row's K best (token, log-probability) pairs, then the workgroup turns the level's children into pool entries and
+// picks the next frontier: at level 0 all K of them in rank order, later the K best of the K*K by path score.
+// What bounds it is a chain of latencies: all of a row's candidates and statistics are requested together, candidates and pool entries meet
+// in LDS.  In two kernels, a merge with its loads one after the other and the selection, a level took 14.3 + 4.9 us at 8 rows, this
+// 11.7 (K = 8, 152064 tokens).
+// MR: candidates per lane held in registers (75 segments x 8 at 152064 tokens: 10); 0: scanned from memory in every round.
+template <int MR>
+__global__ __launch_bounds__(1024) void draft_level_k(int K, int level, int n_seg, const float* __restrict__ seg_stat,
+                                                      const float* __restrict__ seg_val, const int32_t* __restrict__ seg_idx,
+                                                      DraftState st) {
+    __shared__ float s_logp[16][16], sc[256], par_score[16];
+    __shared__ int s_tok[16][16], par_pool[16];
+    __shared__ uint64_t par_mask[16][2];
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = threadIdx.x, KK = K * K;
+    {
+        const int64_t o = ((int64_t)b * (level == 0 ? 1 : K) + wave) * n_seg;
+        const int n_cand = n_seg * K;
+        float rv[MR > 0 ? MR : 1];
+        int rj[MR > 0 ? MR : 1];
 #pragma unroll
-    for (int r = 0; r < kMergeRegs; ++r) {
-        const int c = lane + 64 * r;
-        const bool on = in_regs && c < n_cand;
-        rv[r] = on ? seg_val[o * K + c] : -INFINITY;
-        rj[r] = on ? seg_idx[o * K + c] : 0x7fffffff;
-    }
-    float pv = INFINITY;
-    int pi = -1;
-    for (int k = 0; k < K; ++k) {
-        float cv = -INFINITY;
-        int ci = 0x7fffffff;
-        if (in_regs) {
+        for (int r = 0; r < MR; ++r) {
+            const int i = lane + 64 * r;
+            const bool on = i < n_cand;
+            rv[r] = on ? seg_val[o * K + i] : -INFINITY;
+            rj[r] = on ? seg_idx[o * K + i] : 0x7fffffff;
+        }
+        // (two statistics per lane cover 128 segments, 262144 tokens; longer rows loop)
+        float2 stat[2];
 #pragma unroll
-            for (int r = 0; r < kMergeRegs; ++r) {
-                const float v = rv[r];
-                const int j = rj[r];
+        for (int u = 0; u < 2; ++u)
+            stat[u] = lane + 64 * u < n_seg ? *(const float2*)(seg_stat + 2 * (o + lane + 64 * u)) : make_float2(-INFINITY, 0.f);
+        int pp = 0;
+        if (level > 0 && c < K) {
+            pp = st.fr_pool[b * K + c];
+            par_pool[c] = pp;
+            par_score[c] = st.pool_score[(int64_t)b * st.P + pp];
+            par_mask[c][0] = st.pool_mask[2 * ((int64_t)b * st.P + pp)];
+            par_mask[c][1] = st.pool_mask[2 * ((int64_t)b * st.P + pp) + 1];
+        }
+        float mx = fmaxf(stat[0].x, stat[1].x);
+        for (int sgm = lane + 128; sgm < n_seg; sgm += 64) mx = fmaxf(mx, seg_stat[2 * (o + sgm)]);
+        mx = wave_max(mx);
+        float se = 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (lane + 64 * u < n_seg) se += stat[u].y * expf(stat[u].x - mx);
+        for (int sgm = lane + 128; sgm < n_seg; sgm += 64) se += seg_stat[2 * (o + sgm) + 1] * expf(seg_stat[2 * (o + sgm)] - mx);
+        se = wave_sum(se);
+        const float lse = mx + logf(se);
+        float pv = INFINITY;
+        int pi = -1;
+        for (int k = 0; k < K; ++k) {
+            float cv = -INFINITY;
+            int ci = 0x7fffffff;
+            auto consider = [&](float v, int j) {
                 const bool after = v < pv || (v == pv && j > pi);
                 if (j != 0x7fffffff && after && better(v, j, cv, ci)) {
                     cv = v;
                     ci = j;
                 }
+            };
+            if constexpr (MR > 0) {
+#pragma unroll
+                for (int r = 0; r < MR; ++r) consider(rv[r], rj[r]);
+            } else {
+                for (int i = lane; i < n_cand; i += 64) consider(seg_val[o * K + i], seg_idx[o * K + i]);
             }
-        } else {
-            for (int c = lane; c < n_cand; c += 64) {
-                float v = seg_val[o * K + c];
-                int j = seg_idx[o * K + c];
-                bool after = v < pv || (v == pv && j > pi);
-                if (j != 0x7fffffff && after && better(v, j, cv, ci)) {
-                    cv = v;
-                    ci = j;
-                }
+            wave_best(cv, ci);
+            pv = cv;
+            pi = ci;
+            if (lane == 0) {
+                const bool have = ci != 0x7fffffff;
+                s_tok[wave][k] = have ? ci : -1;
+                s_logp[wave][k] = have ? cv - lse : -INFINITY;
             }
         }
-        wave_best(cv, ci);
-        pv = cv;
-        pi = ci;
-        if (lane == 0) {
-            bool have = ci != 0x7fffffff;
-            tok[(int64_t)row * K + k] = have ? ci : -1;
-            logp[(int64_t)row * K + k] = have ? cv - lse : -INFINITY;
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// Drafter tree bookkeeping.  Feature-buffer rows per sequence: 0 = output of the entry holding the
-// root token; 1 + (level-1)*K + r = output of frontier node r of `level`.  Provisional drafter
-// cache row of that node = (level-1)*K + r past the committed length; masks are over those rows.
-__global__ void draft_level0_k(int B, int K, const int32_t* __restrict__ top_tok, const float* __restrict__ top_logp,
-                               DraftState st) {
-    int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= B * K) return;
-    int b = idx / K, r = idx - b * K;
-    int64_t p = (int64_t)b * st.P + r;
-    st.pool_token[p] = top_tok[idx];
-    st.pool_score[p] = top_logp[idx];
-    st.pool_parent[p] = -1;
-    st.pool_depth[p] = 1;
-    uint64_t m0 = r < 64 ? (1ull << r) : 0ull, m1 = r >= 64 ? (1ull << (r - 64)) : 0ull;
-    st.pool_mask[2 * p] = m0;
-    st.pool_mask[2 * p + 1] = m1;
-    st.fr_token[idx] = top_tok[idx];
-    st.fr_src[idx] = 0;
-    st.fr_pool[idx] = r;
-    st.fr_mask[2 * idx] = m0;
-    st.fr_mask[2 * idx + 1] = m1;
-}
-
-__global__ __launch_bounds__(256) void draft_level_select_k(int K, int level, const int32_t* __restrict__ top_tok,
-                                                            const float* __restrict__ top_logp, DraftState st) {
-    __shared__ float sc[256];
-    __shared__ int par_pool[16];
-    __shared__ uint64_t par_mask[16][2];
-    const int b = blockIdx.x, c = threadIdx.x, KK = K * K;
-    if (c < K) {
-        int pp = st.fr_pool[b * K + c];
-        par_pool[c] = pp;
-        par_mask[c][0] = st.pool_mask[2 * ((int64_t)b * st.P + pp)];
-        par_mask[c][1] = st.pool_mask[2 * ((int64_t)b * st.P + pp) + 1];
     }
     __syncthreads();
+    if (level == 0) {
+        if (c >= K) return;
+        const int64_t p = (int64_t)b * st.P + c;
+        const int token = s_tok[0][c], o = b * K + c;
+        const uint64_t m0 = 1ull << c;   // (K <= 16)
+        st.pool_token[p] = token;
+        st.pool_score[p] = s_logp[0][c];
+        st.pool_parent[p] = -1;
+        st.pool_depth[p] = 1;
+        st.pool_mask[2 * p] = m0;
+        st.pool_mask[2 * p + 1] = 0;
+        st.fr_token[o] = token;
+        st.fr_src[o] = 0;
+        st.fr_pool[o] = c;
+        st.fr_mask[2 * o] = m0;
+        st.fr_mask[2 * o + 1] = 0;
+        return;
+    }
+    // (K waves of 64 threads: at least K * K of them)
     float score = -INFINITY;
     int token = -1, fr = 0;
     if (c < KK) {
         fr = c / K;
-        int64_t src = ((int64_t)b * K + fr) * K + (c - fr * K);
-        token = top_tok[src];
-        score = st.pool_score[(int64_t)b * st.P + par_pool[fr]] + top_logp[src];
-        int64_t p = (int64_t)b * st.P + K + (int64_t)(level - 1) * KK + c;
+        token = s_tok[fr][c - fr * K];
+        score = par_score[fr] + s_logp[fr][c - fr * K];
+        sc[c] = score;
+        const int64_t p = (int64_t)b * st.P + K + (int64_t)(level - 1) * KK + c;
         st.pool_token[p] = token;
         st.pool_score[p] = score;
         st.pool_parent[p] = par_pool[fr];
         st.pool_depth[p] = level + 1;
     }
-    sc[c] = score;
     __syncthreads();
     if (c < KK) {
         int rank = 0;
         for (int j = 0; j < KK; ++j) rank += better(sc[j], j, score, c) ? 1 : 0;
         if (rank < K) {
-            int slot = level * K + rank;  // provisional row of this node when it runs at level+1
-            uint64_t m0 = par_mask[fr][0] | (slot < 64 ? (1ull << slot) : 0ull);
-            uint64_t m1 = par_mask[fr][1] | (slot >= 64 ? (1ull << (slot - 64)) : 0ull);
-            int pool_idx = K + (level - 1) * KK + c;
-            int64_t p = (int64_t)b * st.P + pool_idx;
+            const int slot = level * K + rank;  // provisional row of this node when it runs at level+1
+            const uint64_t m0 = par_mask[fr][0] | (slot < 64 ? (1ull << slot) : 0ull);
+            const uint64_t m1 = par_mask[fr][1] | (slot >= 64 ? (1ull << (slot - 64)) : 0ull);
+            const int pool_idx = K + (level - 1) * KK + c;
+            const int64_t p = (int64_t)b * st.P + pool_idx;
             st.pool_mask[2 * p] = m0;
             st.pool_mask[2 * p + 1] = m1;
-            int o = b * K + rank;
+            const int o = b * K + rank;
             st.fr_token[o] = token;
             st.fr_src[o] = 1 + (level - 1) * K + fr;
             st.fr_pool[o] = pool_idx;
@@ -425,38 +424,54 @@ __global__ __launch_bounds__(256) void draft_level_select_k(int K, int level, co
     }
 }
 
-// One workgroup per sequence.  LDS: score[P], node_of[P] (node index or -1).
-__global__ __launch_bounds__(256) void draft_prune_k(int pool_n, int n_tree, const int32_t* __restrict__ root_tokens,
+// One workgroup per sequence.  LDS: score[P], node_of[P] (node index or -1), tpar[n_tree].
+// A candidate's rank is the number of better ones: several threads count a part of the pool each where the pool is smaller than the
+// workgroup, and the kept ones are numbered by ballots (one sequence, a pool of 392: 30.4 -> 14.8 us; with 256 threads, each walking
+// the pool twice per candidate, it was the longest of the drafter's small kernels).
+constexpr int kPruneThreads = 1024;
+__global__ __launch_bounds__(kPruneThreads) void draft_prune_k(int pool_n, int n_tree, const int32_t* __restrict__ root_tokens,
                                                      const int32_t* __restrict__ new_tokens,
                                                      const int32_t* __restrict__ n_new, int new_stride, DraftState st, int32_t* __restrict__ token,
                                                      int32_t* __restrict__ parent, int32_t* __restrict__ depth,
                                                      uint64_t* __restrict__ anc_mask, float* __restrict__ score) {
     extern __shared__ float lds_f[];
+    __shared__ int s_count[kPruneThreads / 64];
     float* sc = lds_f;
-    int* node_of = (int*)(lds_f + pool_n);
+    int* node_of = (int*)(lds_f + pool_n);   // first the rank
     int* tpar = node_of + pool_n;  // [n_tree] parent node of each tree node
-    const int b = blockIdx.x;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t pb = (int64_t)b * st.P;
-    for (int i = threadIdx.x; i < pool_n; i += 256) sc[i] = st.pool_score[pb + i];
+    for (int i = tid; i < pool_n; i += kPruneThreads) sc[i] = st.pool_score[pb + i], node_of[i] = 0;
     __syncthreads();
     const int keep = n_tree - 1;
-    for (int i = threadIdx.x; i < pool_n; i += 256) {
-        float s = sc[i];
+    const int parts = pool_n < kPruneThreads ? kPruneThreads / pool_n : 1;
+    for (int w = tid; w < pool_n * parts; w += kPruneThreads) {
+        const int part = w / pool_n, i = w - part * pool_n, j1 = pool_n * (part + 1) / parts;
+        const float s = sc[i];
         int rank = 0;
-        for (int j = 0; j < pool_n; ++j) rank += better(sc[j], j, s, i) ? 1 : 0;
-        node_of[i] = rank < keep ? 0 : -1;
+#pragma unroll 8
+        for (int j = pool_n * part / parts; j < j1; ++j) rank += better(sc[j], j, s, i) ? 1 : 0;
+        if (rank) atomicAdd(&node_of[i], rank);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < pool_n; i += 256) {
-        if (node_of[i] < 0) continue;
-        int before = 0;
-        for (int j = 0; j < i; ++j) before += node_of[j] >= 0 ? 1 : 0;  // flags are still 0 / -1 here
-        sc[i] = __int_as_float(before + 1);                             // stash; scores are re-read from global
+    // kept candidates become nodes 1, 2, ... in creation order
+    int before = 1;
+    for (int i0 = 0; i0 < pool_n; i0 += kPruneThreads) {
+        const int i = i0 + tid;
+        const bool on = i < pool_n && node_of[i] < keep;
+        const uint64_t m = __ballot(on);
+        if (lane == 0) s_count[wave] = __popcll(m);
+        __syncthreads();
+        int mine = before, all = 0;
+#pragma unroll
+        for (int w = 0; w < kPruneThreads / 64; ++w) {
+            mine += w < wave ? s_count[w] : 0;
+            all += s_count[w];
+        }
+        if (i < pool_n) node_of[i] = on ? mine + __popcll(m & ((1ull << lane) - 1)) : -1;
+        before += all;
+        __syncthreads();
     }
-    __syncthreads();
-    for (int i = threadIdx.x; i < pool_n; i += 256)
-        if (node_of[i] >= 0) node_of[i] = __float_as_int(sc[i]);
-    __syncthreads();
     const int64_t tb = (int64_t)b * n_tree;
     if (threadIdx.x == 0) {
         int root = -1;  // explicit root, else the last token handed to the drafter's catch-up
@@ -472,7 +487,7 @@ __global__ __launch_bounds__(256) void draft_prune_k(int pool_n, int n_tree, con
         score[tb] = 0.f;
         tpar[0] = -1;
     }
-    for (int i = threadIdx.x; i < pool_n; i += 256) {
+    for (int i = threadIdx.x; i < pool_n; i += kPruneThreads) {
         int nd = node_of[i];
         if (nd < 0) continue;
         int pp = st.pool_parent[pb + i];
@@ -484,7 +499,7 @@ __global__ __launch_bounds__(256) void draft_prune_k(int pool_n, int n_tree, con
         tpar[nd] = pn;
     }
     __syncthreads();
-    for (int nd = threadIdx.x; nd < n_tree; nd += 256) {
+    for (int nd = threadIdx.x; nd < n_tree; nd += kPruneThreads) {
         uint64_t m = 0;
         int a = nd, guard = 0;
         while (a >= 0 && guard++ < 64) {
@@ -1333,8 +1348,10 @@ size_t row_topk_workspace_bytes(int M, int V, int K) {
     return (size_t)M * n_seg * (2 + 2 * (size_t)K) * 4 + 256;
 }
 
-hipError_t row_topk_logp(hipStream_t s, int M, int V, int K, const float* logits, int32_t* tok, float* logp, void* ws) {
+hipError_t draft_level(hipStream_t s, int B, int K, int level, int V, const float* logits, void* ws, DraftState st) {
+    const int M = level == 0 ? B : B * K;
     if (M <= 0) return hipSuccess;
+    if (K > 16) return hipErrorInvalidValue;
     const int n_seg = (V + kTopkSeg - 1) / kTopkSeg;
     float* seg_stat = (float*)ws;
     float* seg_val = seg_stat + (size_t)M * n_seg * 2;
@@ -1346,28 +1363,17 @@ hipError_t row_topk_logp(hipStream_t s, int M, int V, int K, const float* logits
         hipLaunchKernelGGL(row_topk_seg_k<false>, grid, dim3(256), 0, s, V, K, n_seg, logits, seg_stat, seg_val, seg_idx);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(row_topk_merge_k, dim3(M), dim3(64), 0, s, K, n_seg, seg_stat, seg_val, seg_idx, tok, logp);
-    return hipGetLastError();
-}
-
-hipError_t draft_level0(hipStream_t s, int B, int K, const int32_t* top_tok, const float* top_logp, DraftState st,
-                        int feat_rows_per_seq) {
-    (void)feat_rows_per_seq;
-    hipLaunchKernelGGL(draft_level0_k, dim3((B * K + 255) / 256), dim3(256), 0, s, B, K, top_tok, top_logp, st);
-    return hipGetLastError();
-}
-
-hipError_t draft_level_select(hipStream_t s, int B, int K, int level, const int32_t* top_tok, const float* top_logp,
-                              DraftState st, int feat_rows_per_seq) {
-    (void)feat_rows_per_seq;
-    hipLaunchKernelGGL(draft_level_select_k, dim3(B), dim3(256), 0, s, K, level, top_tok, top_logp, st);
+    const dim3 block(64 * (level == 0 ? 1 : K));
+    if (n_seg * K <= 640) hipLaunchKernelGGL(draft_level_k<10>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
+    else if (n_seg * K <= 1280) hipLaunchKernelGGL(draft_level_k<20>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
+    else hipLaunchKernelGGL(draft_level_k<0>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
     return hipGetLastError();
 }
 
 hipError_t draft_prune(hipStream_t s, int B, int pool_n, int n_tree, const int32_t* root_tokens,
                        const int32_t* new_tokens, const int32_t* n_new, int new_stride, DraftState st, int32_t* token, int32_t* parent, int32_t* depth, uint64_t* anc_mask, float* score) {
     size_t lds = sizeof(float) * (size_t)pool_n * 2 + sizeof(int) * (size_t)n_tree;
-    hipLaunchKernelGGL(draft_prune_k, dim3(B), dim3(256), lds, s, pool_n, n_tree, root_tokens, new_tokens, n_new,
+    hipLaunchKernelGGL(draft_prune_k, dim3(B), dim3(kPruneThreads), lds, s, pool_n, n_tree, root_tokens, new_tokens, n_new,
                        new_stride, st, token, parent, depth, anc_mask, score);
     return hipGetLastError();
 }
