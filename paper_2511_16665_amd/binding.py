@@ -27,7 +27,7 @@ EXPORTS = [
     "tlt_profile_begin", "tlt_profile_read", "tlt_mab_create", "tlt_mab_destroy", "tlt_mab_select", "tlt_mab_record",
     "tlt_mab_median_reward", "tlt_ngram_create", "tlt_ngram_destroy", "tlt_ngram_insert", "tlt_ngram_propose",
     "tlt_template_build", "tlt_draft_sample", "tlt_gemm_argmax", "tlt_gemm_glu", "tlt_gemm_parts", "tlt_draft_pool", "tlt_set_oproj_rounding", "tlt_device_status", "tlt_accept_sample_static", "tlt_attention", "tlt_attention_workspace_bytes",
-    "tlt_graph_pool_create", "tlt_graph_pool_destroy", "tlt_graph_pool_step", "tlt_graph_pool_count", "tlt_mfma_stream", "tlt_prefill",
+    "tlt_graph_pool_create", "tlt_graph_pool_destroy", "tlt_graph_pool_step", "tlt_graph_pool_count", "tlt_mfma_stream", "tlt_prefill", "tlt_step_report",
 ]
 
 
@@ -121,6 +121,7 @@ def load() -> C.CDLL:
                                                                C.c_size_t, C.c_int]
     lib.tlt_set_oproj_rounding.argtypes = [C.c_void_p, C.c_int]
     lib.tlt_device_status.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_uint32)]
+    lib.tlt_step_report.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.POINTER(C.c_uint32)]
     lib.tlt_profile_begin.argtypes = [C.c_void_p, C.c_int]
     lib.tlt_profile_read.argtypes = [C.c_void_p, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_double),
                                      C.POINTER(C.c_double)]
@@ -327,6 +328,15 @@ class Context:
         if check:
             self._check(rc, "tlt_device_status")
         return flags.value
+
+    def step_report(self, words: torch.Tensor, pinned: torch.Tensor) -> np.ndarray:
+        """Synchronises the current stream and returns a copy of the int32 device tensor `words` (1-D), by way of `pinned` (pinned host
+        int32, one element more); raises like device_status."""
+        assert words.dtype == pinned.dtype == torch.int32 and pinned.is_pinned() and pinned.numel() > words.numel()
+        flags = C.c_uint32()
+        self._check(self.lib.tlt_step_report(self.handle, _stream(), _ptr(words), words.numel(), C.c_void_p(pinned.data_ptr()),
+                                             C.byref(flags)), "tlt_step_report")
+        return pinned.numpy()[: words.numel()].copy()
 
     def set_oproj_rounding(self, round_to_model_dtype: bool):
         self._check(self.lib.tlt_set_oproj_rounding(self.handle, int(round_to_model_dtype)), "tlt_set_oproj_rounding")

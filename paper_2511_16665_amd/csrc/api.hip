@@ -228,6 +228,26 @@ int norm_x(tlt_ctx* ctx, hipStream_t s, int M, const void* gamma, void* out, con
     return TLT_OK;
 }
 
+// The norm of the M rows of the stream for a product that normalises its own rows (gemm_f32_norm_supported): what is pending is absorbed on
+// the way, and the rows go to x_out.  Nothing is pending afterwards.
+NormIn norm_in(tlt_ctx* ctx, const float* x, const void* gamma, float* x_out) {
+    NormIn n;
+    n.x = x;
+    n.add = ctx->pending_parts > 0 ? (const float*)(ctx->ws + ctx->plan.parts) : nullptr;   // (fp32 mode: one product)
+    n.gamma = (const float*)gamma;
+    n.eps = ctx->cfg.rms_eps;
+    n.assign = ctx->pending_assign;
+    n.x_out = x_out;
+    return n;
+}
+void absorbed(tlt_ctx* ctx) {
+    ctx->pending_parts = 0;
+    ctx->pending_assign = false;
+}
+
+// The final norm and the LM head, the stream's rows kept in io's copy rows (or not at all).
+int norm_lm_head(tlt_ctx* ctx, hipStream_t s, int M, const NormIO& io, float* logits);
+
 KVLayer kv_layer(const tlt_ctx* ctx, const tlt_kv* kv, int layer) {
     const tlt_model_cfg& c = ctx->cfg;
     KVLayer k;
@@ -262,8 +282,22 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     int n_parts = 1;
     RopeTable tab;   // (the drafter is one layer: nothing to keep)
     if (!ctx->in_draft) tab.cs = (float*)(ws + p.rope_cs), tab.at = (int64_t*)(ws + p.rope_at);
-    if ((rc = norm_x(ctx, s, M, w.attn_norm, ws + p.xn))) return rc;
-    if (dt == TLT_BF16 && qkv_dim % 128 == 0 && (size_t)M * qkv_dim * 4 * 2 <= p.parts_bytes &&
+    // fp32 mode with few rows: both norms belong to the products behind them.  The stream's rows then go to xn and, at the second norm, back.
+    float* x1 = (float*)(ws + p.xn);
+    const NormIn n1 = norm_in(ctx, x, w.attn_norm, x1);
+    const bool own_norm = ctx->pending_parts <= 1 && gemm_f32_norm_supported(dt, M, qkv_dim, h, n1, w.wqkv, nullptr) &&
+                          gemm_f32_norm_supported(dt, M, F, h, n1, w.wg, w.wu) && ((uintptr_t)w.mlp_norm & 15) == 0;
+    if (own_norm) {
+        TLT_RUN(ctx, s, ctx->in_draft ? CLS_GEMM_DRAFT : CLS_GEMM, 2.0 * M * qkv_dim * h, ((double)M * h * 3 + (double)qkv_dim * (h + M)) * e,
+                gemm_f32_norm(s, M, qkv_dim, h, n1, w.wqkv, ws + p.qkv));
+        absorbed(ctx);
+    } else if ((rc = norm_x(ctx, s, M, w.attn_norm, ws + p.xn))) {
+        return rc;
+    }
+    if (own_norm) {
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * e * 2,
+                rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer));
+    } else if (dt == TLT_BF16 && qkv_dim % 128 == 0 && (size_t)M * qkv_dim * 4 * 2 <= p.parts_bytes &&
         (M <= 256 || gemm_parts_pays(dt, M, qkv_dim, h))) {
         // too few tiles for the chip unless the projection is cut along K, which leaves fp32 partial products;
         // the rotary kernel sums them and leaves q in the model dtype (always up to 256 rows, one row of tiles;
@@ -297,9 +331,13 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
         if ((rc = run_gemm_parts(ctx, s, M, h, q_dim, ws + p.att, w.wo, &n_parts))) return rc;
         ctx->pending_parts = n_parts;
         ctx->pending_assign = false;
-        if ((rc = norm_x(ctx, s, M, w.mlp_norm, ws + p.xn))) return rc;
+        if (!own_norm && (rc = norm_x(ctx, s, M, w.mlp_norm, ws + p.xn))) return rc;
     }
-    if (gemm_glu_supported(dt, M, F, h, ws + p.xn, w.wg, w.wu)) {
+    if (own_norm) {
+        TLT_RUN(ctx, s, ctx->in_draft ? CLS_GEMM_DRAFT : CLS_GEMM, 4.0 * M * F * h, ((double)M * h * 3 + 2.0 * F * h + (double)M * F) * e,
+                gemm_f32_norm_glu(s, M, F, h, norm_in(ctx, x1, w.mlp_norm, x), w.wg, w.wu, ws + p.act));
+        absorbed(ctx);
+    } else if (gemm_glu_supported(dt, M, F, h, ws + p.xn, w.wg, w.wu)) {
         TLT_RUN(ctx, s, ctx->in_draft ? CLS_GEMM_DRAFT : CLS_GEMM, 4.0 * M * F * h,
                 ((double)M * h + 2.0 * F * h + (double)M * F) * e, gemm_glu(s, dt, M, F, h, ws + p.xn, w.wg, w.wu, ws + p.act));
     } else {
@@ -312,6 +350,22 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     ctx->pending_parts = n_parts;
     ctx->pending_assign = false;
     return TLT_OK;
+}
+
+int norm_lm_head(tlt_ctx* ctx, hipStream_t s, int M, const NormIO& io, float* logits) {
+    const tlt_model_cfg& c = ctx->cfg;
+    NormIn n = norm_in(ctx, (const float*)(ctx->ws + ctx->plan.x), ctx->target.final_norm, io.copy);
+    n.out_n = io.copy_n;
+    n.out_stride = io.copy_stride;
+    n.out_base = io.copy_base;
+    if (ctx->pending_parts <= 1 && gemm_f32_norm_supported(c.dtype, M, c.vocab, c.hidden, n, ctx->target.lm_head, nullptr)) {
+        TLT_RUN(ctx, s, ctx->in_draft ? CLS_GEMM_DRAFT : CLS_GEMM, 2.0 * M * c.vocab * c.hidden,
+                ((double)M * c.hidden * 3 + (double)c.vocab * (c.hidden + M)) * 4, gemm_f32_norm(s, M, c.vocab, c.hidden, n, ctx->target.lm_head, logits));
+        absorbed(ctx);
+        return TLT_OK;
+    }
+    int rc = norm_x(ctx, s, M, ctx->target.final_norm, ctx->ws + ctx->plan.xn, io);
+    return rc ? rc : run_gemm(ctx, s, OUT_F32, M, c.vocab, c.hidden, ctx->ws + ctx->plan.xn, ctx->target.lm_head, logits);
 }
 
 int check_kv(const tlt_ctx* ctx, const tlt_kv* kv, int new_rows) {
@@ -421,6 +475,19 @@ int tlt_device_status(tlt_ctx* ctx, void* stream, uint32_t* flags) {
     return (host & TLT_STATUS_CONTEXT_TRUNCATED) ? TLT_ESHAPE : ((host & TLT_STATUS_NO_RENDEZVOUS) ? TLT_ESYNC : TLT_OK);
 }
 
+int tlt_step_report(tlt_ctx* ctx, void* stream, const int32_t* words, int n, int32_t* out, uint32_t* flags) {
+    if (!ctx || !words || n < 1 || n > (1 << 24) || !out) return TLT_EINVAL;
+    if (flags) *flags = 0;
+    hipStream_t s = (hipStream_t)stream;
+    hipError_t e = report_words(s, n, words, ctx->status_ready ? status_word(ctx) : nullptr, out);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(ctx, e);
+    const uint32_t raised = (uint32_t)out[n];
+    if (flags) *flags = raised;
+    if (raised != 0 && (e = zero_f32(s, 64, (float*)status_word(ctx))) != hipSuccess) return fail(ctx, e);
+    return (raised & TLT_STATUS_CONTEXT_TRUNCATED) ? TLT_ESHAPE : ((raised & TLT_STATUS_NO_RENDEZVOUS) ? TLT_ESYNC : TLT_OK);
+}
+
 int tlt_set_oproj_rounding(tlt_ctx* ctx, int round_to_model_dtype) {
     if (!ctx) return TLT_EINVAL;
     ctx->oproj_f32 = round_to_model_dtype == 0;
@@ -468,14 +535,14 @@ int tlt_verify_forward(tlt_ctx* ctx, void* stream, int B, const tlt_tree* tree, 
         float* logits = out_logits ? out_logits : (float*)(ws + p.logits);
         NormIO io;
         io.copy = out_hidden;   // (the stream ends here: its rows leave x for the caller's buffer on the way, where that is wanted)
-        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn, io))) return rc;
         if (!out_logits && !out_lse && gemm_argmax_supported(c.dtype, M, V, h, ws + p.xn, ctx->target.lm_head)) {
+            if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn, io))) return rc;
             // only the most likely tokens are wanted: the logits never leave the LM head's registers
             // (block partials go where the logits would have gone: M * V/128 * 8 bytes of M * V * 4)
             TLT_RUN(ctx, s, CLS_GEMM, 2.0 * M * V * h, ((double)M * h + (double)V * h) * e,
                     gemm_argmax(s, M, V, h, ws + p.xn, ctx->target.lm_head, logits, out_argmax));
         } else {
-            if ((rc = run_gemm(ctx, s, OUT_F32, M, V, h, ws + p.xn, ctx->target.lm_head, logits))) return rc;
+            if ((rc = norm_lm_head(ctx, s, M, io, logits))) return rc;
             if (out_argmax) TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * V * 4, row_argmax(s, M, V, logits, out_argmax, ws + p.parts, p.parts_bytes));   // (nothing is pending: the slices' buffer is idle)
             if (out_lse) TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * V * 8, row_lse(s, M, V, logits, out_lse));
         }
@@ -773,8 +840,7 @@ int tlt_draft_expand(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
         io.copy_n = topk;
         io.copy_stride = FR;
         io.copy_base = 1 + (level - 1) * topk;
-        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn, io))) return rc;
-        if ((rc = run_gemm(ctx, s, OUT_F32, M, V, h, ws + p.xn, ctx->target.lm_head, logits))) return rc;
+        if ((rc = norm_lm_head(ctx, s, M, io, logits))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * V * 4, draft_level(s, B, topk, level, V, logits, ws + p.topk_ws, st));
     }
     TLT_RUN(ctx, s, CLS_OTHER, 0, 0,
@@ -916,8 +982,7 @@ int tlt_draft_sample(tlt_ctx* ctx, void* stream, int B, int depth, int topk, int
         io.copy_n = lv.R;
         io.copy_stride = FR;
         io.copy_base = 1 + slot_base;
-        if ((rc = norm_x(ctx, s, M, ctx->target.final_norm, ws + p.xn, io))) return rc;
-        if ((rc = run_gemm(ctx, s, OUT_F32, M, V, h, ws + p.xn, ctx->target.lm_head, logits))) return rc;
+        if ((rc = norm_lm_head(ctx, s, M, io, logits))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * V * 12,
                 softmax_draw(s, B, n, V, temperature, lv, logits, u_draw, out_tree->token, out_draft_q,
                          ctx->pending_parts == 0 ? ws + p.parts : nullptr, p.parts_bytes));   // (the slices' buffer is idle here)

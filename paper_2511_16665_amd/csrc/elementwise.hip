@@ -415,6 +415,12 @@ __global__ void add_i32_k(int n, int32_t* dst, const int32_t* a, int add_const) 
     if (i < n) dst[i] += (a ? a[i] : 0) + add_const;
 }
 
+__global__ void report_words_k(int n, const int32_t* __restrict__ src, const unsigned int* __restrict__ status, int32_t* __restrict__ dst) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = src[i];
+    else if (i == n) dst[n] = status ? (int32_t)*status : 0;
+}
+
 __global__ void zero_f32_k(int64_t count, float4* __restrict__ dst) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -588,6 +594,11 @@ hipError_t draft_input(hipStream_t s, int dtype, int B, int n, int h, int V, con
 hipError_t add_i32(hipStream_t s, int n, int32_t* dst, const int32_t* a, int add_const) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(add_i32_k, dim3((n + 255) / 256), dim3(256), 0, s, n, dst, a, add_const);
+    return hipGetLastError();
+}
+
+hipError_t report_words(hipStream_t s, int n, const int32_t* src, const unsigned int* status, int32_t* dst) {
+    hipLaunchKernelGGL(report_words_k, dim3(n / 256 + 1), dim3(256), 0, s, n, src, status, dst);
     return hipGetLastError();
 }
 

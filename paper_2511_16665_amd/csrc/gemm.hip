@@ -618,12 +618,17 @@ __global__ __launch_bounds__(256) void gemm_generic_k(int M, int N, int K, const
 // Measured against the 64x64 tiles below (us per call): M 2, N 1024, K 256: 28.0 -> 4.6; M 16, N 256, K 768: 81 -> 5.1; M 64,
 // N 512, K 1280: 151 -> 6.9; M 16, N = K = 3584: 474 -> 16; M 256, N = K = 3584: 565 -> 163 (linear in the rows from there).
 // GLU: W2 is the up matrix, C = silu(A W^T) * (A W2^T).
+// NORM: the rows of A are made here: every workgroup normalises its (at most 16) rows into LDS, and the first one of a row block leaves the
+// rows it read, the addend absorbed, for the next reader of the stream.  A tiny decoder's step is as long as its launches are many: a norm of
+// its own costs a launch of 2.9 us on the host and 2.5-3 us of the chip, here it is 8 KB per workgroup from the caches.
 typedef __attribute__((ext_vector_type(4))) float f32x4v_t;
-template <int T, int OUT, bool GLU>
+template <int T, int OUT, bool GLU, bool NORM = false>
 __global__ __launch_bounds__(256) void gemm_f32_few_k(int M, int N, int K, const float* __restrict__ A, const float* __restrict__ W,
-                                                      const float* __restrict__ W2, float* __restrict__ C) {
+                                                      const float* __restrict__ W2, float* __restrict__ C, NormIn ni) {
     constexpr int NG = GLU ? 2 : 1, U = 4;   // U: pieces whose loads are issued together
+    static_assert(!NORM || T == 1, "the normalised rows of one 16-row block fit the LDS");
     __shared__ __align__(16) float red[4][NG][T][256];
+    extern __shared__ __align__(16) float xn_s[];   // NORM: [16][K + 4]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
     const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16 * T;
     // rows past the edges read the last row: their results are not stored
@@ -631,11 +636,41 @@ __global__ __launch_bounds__(256) void gemm_f32_few_k(int M, int N, int K, const
     const float* wp[NG];
     wp[0] = W + (int64_t)wrow * K + 4 * g;
     if constexpr (GLU) wp[1] = W2 + (int64_t)wrow * K + 4 * g;
-    const float* ap[T];
+    const float* ap[T];   // (NORM: A is null and nothing is read through it)
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int row = m0 + 16 * t + l16;
         ap[t] = A + (int64_t)(row < M ? row : M - 1) * K + 4 * g;
+    }
+    if constexpr (NORM) {
+        // a wave per row, four rows each; K <= 1024: at most four 16-byte pieces per lane (the launcher checks)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = m0 + wave + 4 * q;
+            if (r >= M) break;   // (wave-uniform; rows past the end are never stored, what their LDS holds does not matter)
+            f32x4v_t v[4], gam[4];
+            float ss = 0.f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = 4 * lane + 256 * u;
+                const bool on = c < K;
+                v[u] = on && !(ni.add && ni.assign) ? *(const f32x4v_t*)(ni.x + (int64_t)r * K + c) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
+                gam[u] = on ? *(const f32x4v_t*)(ni.gamma + c) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
+                if (ni.add && on) v[u] += *(const f32x4v_t*)(ni.add + (int64_t)r * K + c);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) ss += v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2] + v[u][3] * v[u][3];
+            const float inv = 1.0f / sqrtf(wave_sum(ss) / (float)K + ni.eps);
+            float* keep = blockIdx.x == 0 && ni.x_out ? ni.x_out + ((int64_t)(r / ni.out_n) * ni.out_stride + ni.out_base + r % ni.out_n) * K : nullptr;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = 4 * lane + 256 * u;
+                if (c >= K) continue;
+                *(f32x4v_t*)(xn_s + (wave + 4 * q) * (K + 4) + c) = v[u] * inv * gam[u];
+                if (keep) *(f32x4v_t*)(keep + c) = v[u];
+            }
+        }
+        __syncthreads();
     }
     f32x4v_t acc[NG][T];
 #pragma unroll
@@ -651,7 +686,10 @@ __global__ __launch_bounds__(256) void gemm_f32_few_k(int M, int N, int K, const
 #pragma unroll
             for (int i = 0; i < NG; ++i) w[u][i] = on ? *(const f32x4v_t*)(wp[i] + k) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int t = 0; t < T; ++t) a[u][t] = on ? *(const f32x4v_t*)(ap[t] + k) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < T; ++t) {
+                if constexpr (NORM) a[u][t] = on ? *(const f32x4v_t*)(xn_s + l16 * (K + 4) + 4 * g + k) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
+                else a[u][t] = on ? *(const f32x4v_t*)(ap[t] + k) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -704,9 +742,9 @@ template <int T>
 static hipError_t launch_f32_few_t(hipStream_t s, int out_mode, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
     const dim3 grid((N + 15) / 16, (M + 16 * T - 1) / (16 * T)), block(256);
     const float *a = (const float*)A, *w = (const float*)W, *w2 = (const float*)W2;
-    if (W2) hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_F32, true>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C);
-    else if (out_mode == OUT_ADD_F32) hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_ADD_F32, false>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C);
-    else hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_F32, false>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C);
+    if (W2) hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_F32, true>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C, NormIn());
+    else if (out_mode == OUT_ADD_F32) hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_ADD_F32, false>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C, NormIn());
+    else hipLaunchKernelGGL((gemm_f32_few_k<T, OUT_F32, false>), grid, block, 0, s, M, N, K, a, w, w2, (float*)C, NormIn());
     return hipGetLastError();
 }
 static hipError_t launch_f32_few(hipStream_t s, int out_mode, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
@@ -716,6 +754,33 @@ static hipError_t launch_f32_few(hipStream_t s, int out_mode, int M, int N, int 
     if (M <= 16 || wgs <= 512) return launch_f32_few_t<1>(s, out_mode, M, N, K, A, W, W2, C);
     if (M <= 32 || wgs <= 1024) return launch_f32_few_t<2>(s, out_mode, M, N, K, A, W, W2, C);
     return launch_f32_few_t<4>(s, out_mode, M, N, K, A, W, W2, C);
+}
+
+// Up to 16 rows (one row block) of at most 1024 elements: every workgroup then reads all rows, at most 64 KB and the addend's as many, which the
+// saved launch pays for while the workgroups are few enough to run at once.
+bool gemm_f32_norm_supported(int dtype, int M, int N, int K, const NormIn& n, const void* W, const void* W2) {
+    return dtype == F32 && M <= 16 && K <= 1024 && N <= 16 * 512 && f32_few_ok(M, K, n.x, W, W2) &&
+           (((uintptr_t)n.add | (uintptr_t)n.gamma | (uintptr_t)n.x_out) & 15) == 0;
+}
+template <bool GLU>
+static hipError_t launch_f32_norm(hipStream_t s, int M, int N, int K, const NormIn& n, const void* W, const void* W2, void* C) {
+    if (M <= 0 || N <= 0) return hipSuccess;
+    const size_t lds = (size_t)16 * (K + 4) * sizeof(float);
+    auto kern = gemm_f32_few_k<1, OUT_F32, GLU, true>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 16 * (1024 + 4) * (int)sizeof(float));
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((N + 15) / 16), dim3(256), lds, s, M, N, K, (const float*)nullptr, (const float*)W, (const float*)W2, (float*)C, n);
+    return hipGetLastError();
+}
+hipError_t gemm_f32_norm(hipStream_t s, int M, int N, int K, const NormIn& n, const void* W, void* C) {
+    return launch_f32_norm<false>(s, M, N, K, n, W, nullptr, C);
+}
+hipError_t gemm_f32_norm_glu(hipStream_t s, int M, int N, int K, const NormIn& n, const void* Wg, const void* Wu, void* act) {
+    return launch_f32_norm<true>(s, M, N, K, n, Wg, Wu, act);
 }
 
 // Few activation rows (M <= 32 * WTM * WGM, one row of tiles): the weights stream through once and nothing else counts.  A

@@ -54,6 +54,19 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
 // upper bound of n * M * N * 4 over every shape (see gemm.hip)
 size_t gemm_parts_max_bytes();
 bool gemm_parts_pays(int dtype, int M, int N, int K);   // slices expected to beat one result in the model dtype
+// The rmsnorm in front of a product, done by the product's own workgroups: its rows are those of x (plus the addend, or the addend alone
+// with assign), normalised; the rows themselves, the addend absorbed, are left in x_out, which must be another buffer than x (or null).
+struct NormIn {
+    const float *x = nullptr, *add = nullptr, *gamma = nullptr;   // x null: no norm
+    float eps = 0.f;
+    bool assign = false;
+    float* x_out = nullptr;   // row r: (r / out_n) * out_stride + out_base + r % out_n
+    int out_n = 1, out_stride = 1, out_base = 0;
+};
+// fp32 only: whether gemm_f32_norm / the fused gate/up product take the norm of so many rows of so wide a stream
+bool gemm_f32_norm_supported(int dtype, int M, int N, int K, const NormIn& n, const void* W, const void* W2);
+hipError_t gemm_f32_norm(hipStream_t s, int M, int N, int K, const NormIn& n, const void* W, void* C);                       // C = norm(x) W^T
+hipError_t gemm_f32_norm_glu(hipStream_t s, int M, int N, int K, const NormIn& n, const void* Wg, const void* Wu, void* act);
 // fused gate/up projection of the SwiGLU MLP (bf16, or fp32 with few rows): act = silu(A Wg^T) * (A Wu^T)
 bool gemm_glu_supported(int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu);
 hipError_t gemm_glu(hipStream_t s, int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act);
@@ -109,6 +122,8 @@ hipError_t draft_input(hipStream_t s, int dtype, int B, int n, int h, int V, con
                        const int32_t* n_valid, int src_seq_stride, int64_t hidden_rows, const float* hidden,
                        const void* embed, void* xin);
 hipError_t add_i32(hipStream_t s, int n, int32_t* dst, const int32_t* a, int add_const);
+// dst (mapped host memory) = the n words at src, then the word at status (0 where that is null)
+hipError_t report_words(hipStream_t s, int n, const int32_t* src, const unsigned int* status, int32_t* dst);
 hipError_t copy_f32(hipStream_t s, int64_t count, const float* src, float* dst);
 hipError_t zero_f32(hipStream_t s, int64_t count, float* dst);   // a kernel, not a memset: safe to capture in a graph
 // the last of every n rows of src -> row b * dst_seq_stride of dst

@@ -38,8 +38,10 @@ class Engine:
         B = batch
         self.stride = min(max_depth, max_n - 1) + 1      # longest accepted path + bonus token
         i32 = lambda *s: torch.full(s, -1, dtype=torch.int32, device=dev)
-        self.accept_len, self.n_out = i32(B), i32(B)
-        self.path_idx, self.out_tokens = i32(B, self.stride), i32(B, self.stride)
+        self._result = i32(B * (1 + self.stride))        # what a step returns, read back together
+        self.accept_len, self.out_tokens = self._result[:B], self._result[B:].view(B, self.stride)
+        self._pinned = None
+        self.n_out, self.path_idx = i32(B), i32(B, self.stride)
         self.pending_hidden, self.pending_max_new = None, 0
         self.root = i32(B)
         self._trees = {}
@@ -131,9 +133,7 @@ class Engine:
         self.pending_hidden = hid
         self.have_pending = True
         if sync:
-            al = self.accept_len.cpu().numpy()
-            out = self.out_tokens.cpu().numpy()
-            self.ctx.device_status()          # raises when a kernel saw a length beyond its bound or could not rendezvous
+            al, out = self._read_result()
             inc = int(al.max()) + 1
         else:
             al = out = None
@@ -165,13 +165,19 @@ class Engine:
         self.ctx.kv_commit(B, self.kv, self.accept_len, self.path_idx, self.stride)
         self.pending_hidden = hid
         self.have_pending = True
-        al = self.accept_len.cpu().numpy()
-        out = self.out_tokens.cpu().numpy()
-        self.ctx.device_status()
+        al, out = self._read_result()
         inc = int(al.max()) + 1
         self.kv.seq_len_bound += inc
         self.pending_max_new = inc
         return al, out
+
+    def _read_result(self):
+        """(accept_len [B], out_tokens [B, stride]) as numpy arrays, in the step's one synchronisation; raises when a kernel saw
+        a length beyond its bound or could not rendezvous."""
+        if self._pinned is None:
+            self._pinned = torch.empty(self._result.numel() + 1, dtype=torch.int32, pin_memory=True)
+        res = self.ctx.step_report(self._result, self._pinned)
+        return res[: self.B], res[self.B:].reshape(self.B, self.stride)
 
     def draft_q(self, n):
         return self._big("q", n)
@@ -214,8 +220,8 @@ class Engine:
         self.ctx.accept(B, 0, 1.0, t, None, am, None, None, None, self.stride, self.accept_len, self.path_idx,
                         self.out_tokens, self.n_out)
         self.ctx.kv_commit(B, self.kv, self.accept_len, self.path_idx, self.stride)
-        al = self.accept_len.cpu().numpy()
-        out = self.out_tokens.cpu().numpy()
+        res = self._result.cpu().numpy()
+        al, out = res[:B], res[B:].reshape(B, self.stride)
         inc = int(al.max()) + 1
         self.kv.seq_len_bound += inc
         if keep_drafter:
