@@ -386,15 +386,15 @@ __device__ __forceinline__ void attn_decode(int id, int heads, int n_kv, int& ra
 template <int NT>
 __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, const uint16_t* __restrict__ qkv,
                                           float* __restrict__ part_o, float* __restrict__ part_ml,
-                                          const AttnWork* __restrict__ work, int heads, int n_q_heads, int row_tiles,
+                                          const AttnWork* __restrict__ work, int n_seq, int heads, int n_kv, int n_q_heads, int row_tiles,
                                           int tiles_per_group, int r_pad, float scale_log2, float lazy_raw, int max_items) {
     constexpr int TPW = NT > 0 ? NT : 1;   // array extents (nothing is computed in them when NT = 0)
     extern __shared__ __align__(16) uint16_t lds[];
     int rank, kh, rg;
-    attn_decode(blockIdx.x, heads, kv.n_kv, rank, kh, rg);
+    attn_decode(blockIdx.x, heads, n_kv, rank, kh, rg);   // (n_kv = kv.n_kv, n_seq = rows.B: in registers from the start)
     // (the item is requested together with the count, not after it: where the grid reaches past the list, entry 0 stands in)
     const int n_items = work->n_items;
-    const AttnItem* item_p = (const AttnItem*)((const int*)(work + 1) + 2 * rows.B) + (rank < max_items ? rank : 0);
+    const AttnItem* item_p = (const AttnItem*)((const int*)(work + 1) + 2 * n_seq) + (rank < max_items ? rank : 0);
     const AttnItem item = *item_p;
     if (rank >= n_items) return;  // uniform
     const int b = item.b;
@@ -780,20 +780,19 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
 }
 
 template <int TPW>
-__global__ __launch_bounds__(512) void attn_mfma_k(Rows rows, KVLayer kv, const uint16_t* __restrict__ qkv,
-                                                   float* __restrict__ part_o, float* __restrict__ part_ml,
-                                                   const AttnWork* __restrict__ work, int heads, int n_q_heads,
-                                                   int row_tiles, int tiles_per_group, int r_pad, float scale_log2,
-                                                   float lazy_raw, int max_items) {
+__global__ __launch_bounds__(512) void attn_mfma_k(const AttnWork* __restrict__ work, int n_seq, int heads, int n_kv, int max_items,
+                                                   int row_tiles, int tiles_per_group, const uint16_t* __restrict__ qkv,
+                                                   float* __restrict__ part_o, float* __restrict__ part_ml, int n_q_heads, int r_pad,
+                                                   float scale_log2, float lazy_raw, Rows rows, KVLayer kv) {
     // row tiles of this wave that exist (tile indices rise with t, so they are the first n_on)
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int rank_, kh_, rg;
-    attn_decode(blockIdx.x, heads, kv.n_kv, rank_, kh_, rg);
+    attn_decode(blockIdx.x, heads, n_kv, rank_, kh_, rg);
     int n_on = 0;
 #pragma unroll
     for (int t = 0; t < TPW; ++t)
         n_on += ((wave + 8 * t) < tiles_per_group && rg * tiles_per_group + wave + 8 * t < row_tiles) ? 1 : 0;
-#define TLT_BODY(N) attn_body<N>(rows, kv, qkv, part_o, part_ml, work, heads, n_q_heads, row_tiles, tiles_per_group, r_pad, scale_log2, lazy_raw, max_items)
+#define TLT_BODY(N) attn_body<N>(rows, kv, qkv, part_o, part_ml, work, n_seq, heads, n_kv, n_q_heads, row_tiles, tiles_per_group, r_pad, scale_log2, lazy_raw, max_items)
     if (n_on >= TPW) TLT_BODY(TPW);
     else if (TPW >= 2 && n_on == TPW - 1) TLT_BODY((TPW >= 2 ? TPW - 1 : 0));
     else if (TPW >= 3 && n_on == TPW - 2) TLT_BODY((TPW >= 3 ? TPW - 2 : 0));
@@ -809,27 +808,26 @@ __global__ __launch_bounds__(512) void attn_mfma_k(Rows rows, KVLayer kv, const 
 // sequences x 23 nodes 7.3); with the chip full of waves the plain loop is the faster one (14 against 16 us at the
 // benchmark shape).  The sums run in chunk order either way.
 template <bool BATCH>
-__global__ __launch_bounds__(256) void attn_combine_k(Rows rows, KVLayer kv, const float* __restrict__ part_o,
-                                                     const float* __restrict__ part_ml, uint16_t* __restrict__ out,
-                                                     const AttnWork* __restrict__ work, int n_q_heads, int max_items,
-                                                     int r_pad, float scale_log2) {
+__global__ __launch_bounds__(256) void attn_combine_k(const AttnWork* __restrict__ work, const float* __restrict__ part_o,
+                                                     const float* __restrict__ part_ml, uint16_t* __restrict__ out, int n_seq, int n,
+                                                     int n_q_heads, int n_kv, int max_items, int r_pad, float scale_log2,
+                                                     const int32_t* __restrict__ n_valid) {
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6), kh = blockIdx.y, b = blockIdx.z, lane = threadIdx.x & 63;
-    const int G = n_q_heads / kv.n_kv;
-    const int n = rows.n;
+    const int G = n_q_heads / n_kv;
     if (r >= n * G) return;  // wave-uniform
     const int i = r / G, gq = r - i * G;
-    const int nv = rows.n_valid ? min(rows.n_valid[b], n) : n;
+    const int nv = n_valid ? min(n_valid[b], n) : n;
     uint32_t* o = (uint32_t*)(out + ((int64_t)(b * n + i) * n_q_heads + kh * G + gq) * kD);
     const int* slot0 = (const int*)(work + 1);
     const int first = slot0[b];
-    int used = slot0[rows.B + b];
+    int used = slot0[n_seq + b];
     if (first + used > max_items) used = max(max_items - first, 0);
     if (i >= nv || used <= 0) {
         o[lane] = 0u;
         return;
     }
-    const int64_t pbase = ((int64_t)first * kv.n_kv + kh) * r_pad + r;
-    const int64_t pstride = (int64_t)kv.n_kv * r_pad;
+    const int64_t pbase = ((int64_t)first * n_kv + kh) * r_pad + r;
+    const int64_t pstride = (int64_t)n_kv * r_pad;
     float M = kNegBig;
     float a0 = 0.f, a1 = 0.f, L = 0.f;
     if constexpr (BATCH) {
@@ -915,18 +913,20 @@ static hipError_t launch_attn_mfma(hipStream_t s, const Rows& rows, const KVLaye
                            kv.n_pages, rows.mask ? nullptr : rows.n_valid);
     // (ids come in groups of 8 (item, kv head) pairs x row groups: see attn_decode)
     const int id_groups = (p.max_items * kv.n_kv + 7) / 8;
-    hipLaunchKernelGGL(kern, dim3(id_groups * 8 * p.row_groups), dim3(512), lds, s, rows, kv, (const uint16_t*)qkv, part_o,
-                       part_ml, work, p.heads, n_q_heads, p.row_tiles, tiles_per_group, p.r_pad, scale_log2,
-                       8.0f / scale_log2, p.max_items);
+    hipLaunchKernelGGL(kern, dim3(id_groups * 8 * p.row_groups), dim3(512), lds, s, (const AttnWork*)work, rows.B, p.heads, kv.n_kv,
+                       p.max_items, p.row_tiles, tiles_per_group, (const uint16_t*)qkv, part_o, part_ml, n_q_heads, p.r_pad, scale_log2,
+                       8.0f / scale_log2, rows, kv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int R = rows.n * (n_q_heads / kv.n_kv);
     if ((int64_t)R * kv.n_kv * rows.B <= 4096)   // (waves: half of what the chip holds at once)
-        hipLaunchKernelGGL(attn_combine_k<true>, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, rows, kv, part_o, part_ml,
-                           (uint16_t*)out, work, n_q_heads, p.max_items, p.r_pad, scale_log2);
+        hipLaunchKernelGGL(attn_combine_k<true>, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
+                           (const float*)part_o, (const float*)part_ml, (uint16_t*)out, rows.B, rows.n, n_q_heads, kv.n_kv, p.max_items, p.r_pad,
+                           scale_log2, rows.n_valid);
     else
-        hipLaunchKernelGGL(attn_combine_k<false>, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, rows, kv, part_o, part_ml,
-                           (uint16_t*)out, work, n_q_heads, p.max_items, p.r_pad, scale_log2);
+        hipLaunchKernelGGL(attn_combine_k<false>, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
+                           (const float*)part_o, (const float*)part_ml, (uint16_t*)out, rows.B, rows.n, n_q_heads, kv.n_kv, p.max_items, p.r_pad,
+                           scale_log2, rows.n_valid);
     return hipGetLastError();
 }
 

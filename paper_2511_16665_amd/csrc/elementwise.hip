@@ -39,9 +39,17 @@ struct NormRow {
     int64_t src;      // row of x, and of the addends
     bool absorb;
 };
+template <bool PLAIN>   // row r of x, kept there (io is the default one, and its words need not be waited for)
 __device__ __forceinline__ NormRow norm_row(const NormIO& io, int h, float* x, bool add) {
     const int r = blockIdx.x;
     NormRow o;
+    if constexpr (PLAIN) {
+        o.src = r;
+        o.in = x + (int64_t)r * h;
+        o.absorb = add;
+        o.keep = add ? x + (int64_t)r * h : nullptr;
+        return o;
+    }
     o.src = (int64_t)r * io.src_stride;
     float* copy = io.copy ? io.copy + ((int64_t)(r / io.copy_n) * io.copy_stride + io.copy_base + r % io.copy_n) * h : nullptr;
     bool have = true;
@@ -61,10 +69,10 @@ __device__ __forceinline__ NormRow norm_row(const NormIO& io, int h, float* x, b
 // first -- the output projection leaves its product there instead of read-modify-writing x itself.
 template <typename T, typename TA>
 __global__ __launch_bounds__(256) void rmsnorm_k(int h, float* __restrict__ x, const T* __restrict__ gamma,
-                                                 float eps, T* __restrict__ out, NormIO io, const TA* __restrict__ add, int n_add,
-                                                 int64_t add_stride, int assign) {
+                                                 float eps, T* __restrict__ out, const TA* __restrict__ add, int n_add,
+                                                 int64_t add_stride, int assign, NormIO io) {
     __shared__ float red[4];
-    const NormRow row = norm_row(io, h, x, add != nullptr);
+    const NormRow row = norm_row<false>(io, h, x, add != nullptr);
     T* o = out + (int64_t)blockIdx.x * h;
     auto value = [&](int c) {
         float v = (row.absorb && assign) ? 0.f : row.in[c];
@@ -89,13 +97,13 @@ __global__ __launch_bounds__(256) void rmsnorm_k(int h, float* __restrict__ x, c
 
 // Same, for h % 4 == 0 and h <= 1024 * NK: the row is read once with 16-byte loads and stays in
 // registers (NK float4 per thread) between the reduction and the scaling.
-template <typename T, int NK, typename TA, int NB = 4, int NTHR = 256>   // NB: slices of `add` whose loads are issued together
+template <typename T, int NK, typename TA, bool PLAIN, int NB = 4, int NTHR = 256>   // NB: slices of `add` whose loads are issued together
 __global__ __launch_bounds__(NTHR) void rmsnorm_vec_k(int h, float* __restrict__ x, const T* __restrict__ gamma,
-                                                     float eps, T* __restrict__ out, NormIO io, const TA* __restrict__ add,
-                                                     int n_add, int64_t add_stride, int assign) {
+                                                     float eps, T* __restrict__ out, const TA* __restrict__ add,
+                                                     int n_add, int64_t add_stride, int assign, NormIO io) {
     __shared__ float red[NTHR / 64];
     const int h4 = h >> 2;
-    const NormRow row = norm_row(io, h, x, add != nullptr);
+    const NormRow row = norm_row<PLAIN>(io, h, x, add != nullptr);
     T* o = out + (int64_t)blockIdx.x * h;
     float4 v[NK];
     // (the gains are requested with the row, not after the reduction: one memory latency instead of two)
@@ -187,13 +195,13 @@ union Piece {   // 16 bytes of T
 // one load to wait for.  7B shape, us per layer before and after: 1 row 8.3 -> 4.7, 64 rows 9.3 -> 6.3, 256 rows 9.9 ->
 // 7.2, 1536 rows 13.0 -> 9.8 (kernel traces).
 template <typename T, bool SRC32, bool TBL>   // SRC32: the projection arrives as fp32 partial products (its own instance: it needs many more registers)
-__global__ __launch_bounds__(kRopeThreads) void rope_kv_write_k(Rows rows, KVLayer kv, T* __restrict__ qkv, int n_q_heads,
-                                                       float theta, const T* __restrict__ bias,
-                                                       const float* __restrict__ src32, int n_src, int64_t src_stride, RopeTable tab) {
+__global__ __launch_bounds__(kRopeThreads) void rope_kv_write_k(const float* __restrict__ src32, T* __restrict__ qkv, const int64_t* __restrict__ tab_at,
+                                                       const float* __restrict__ tab_cs, int64_t src_stride, int n_src, int n_q_heads, int n_kv,
+                                                       int d, const T* __restrict__ bias, float theta, Rows rows, KVLayer kv, RopeTable tab) {
     extern __shared__ __align__(16) float cs[];  // [d/2] cos, [d/2] sin
-    const int d = kv.d, half = d >> 1;
+    const int half = d >> 1;   // (the first words, which a wave has from the start, are all that its loads need: n_kv = kv.n_kv, d = kv.d)
     const int r = blockIdx.x;
-    const int qkv_dim = (n_q_heads + 2 * kv.n_kv) * d;
+    const int qkv_dim = (n_q_heads + 2 * n_kv) * d;
     T* row = qkv + (int64_t)r * qkv_dim;
     // src32 (optional): the projection's product still in fp32 (a split-K GEMM accumulated it there);
     // q then goes to `qkv` in T for the attention kernel, exactly as when it is rotated in place
@@ -268,8 +276,8 @@ __global__ __launch_bounds__(kRopeThreads) void rope_kv_write_k(Rows rows, KVLay
     // head, both halves of each pair, or VEC consecutive elements of v
     constexpr int VEC = 16 / sizeof(T);
     const int cph = half / VEC;   // pieces per half head
-    const int n_piece = (n_q_heads + kv.n_kv) * cph, n_all = n_piece + kv.n_kv * d / VEC;
-    const int v0 = (n_q_heads + kv.n_kv) * d;
+    const int n_piece = (n_q_heads + n_kv) * cph, n_all = n_piece + n_kv * d / VEC;
+    const int v0 = (n_q_heads + n_kv) * d;
     auto load = [&](int e, u32x4_t& lo, u32x4_t& hi) {   // (plain vectors: unions merged over the two branches end in scratch)
         if (e < n_piece) {
             const int hd = e / cph, j0 = (e - hd * cph) * VEC;
@@ -289,8 +297,8 @@ __global__ __launch_bounds__(kRopeThreads) void rope_kv_write_k(Rows rows, KVLay
     int64_t at;   // element offset of the row's slot in the cache (head 0); -1: no page, -2: the row is not active
     const float* c_row = cs;
     if constexpr (TBL) {
-        at = tab.at[r];
-        c_row = tab.cs + (int64_t)r * d;
+        at = tab_at[r];
+        c_row = tab_cs + (int64_t)r * d;
     } else {
         const int b = r / rows.n, i = r - b * rows.n;
         at = -2;
@@ -490,21 +498,22 @@ static void rmsnorm_launch_t(hipStream_t s, int M, int h, float* x, const void* 
     const int64_t add_stride = add_rows * h;
     const bool vec_ok = h % 4 == 0 && (((uintptr_t)x | (uintptr_t)add | (uintptr_t)io.copy) & 15) == 0 &&
                         ((uintptr_t)gamma & (4 * sizeof(T) - 1)) == 0;
+    const bool plain = io.src_stride == 1 && io.n == 0 && !io.copy;
+    auto launch = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(M), dim3(threads), 0, s, h, x, (const T*)gamma, eps, (T*)out, (const TA*)add, n_add, add_stride,
+                           (int)assign, io);
+    };
     if (vec_ok && h <= 4096 && add && (n_add > 4 || M <= 64) && sizeof(TA) == 4)
         // many slices or few rows (so few workgroups): one 16-byte position per thread and all its slices' loads in
         // flight at once.  (Few rows and up to four slices, against 256 threads, us per norm inside a forward of 1-32 rows: widths
         // 3584 and 4096 1.4 less, 1536 0.4 less, 256 to 1024 and 2048 the same within 0.3, though most waves are idle at 256.)
-        hipLaunchKernelGGL((rmsnorm_vec_k<T, 1, TA, 12, 1024>), dim3(M), dim3(1024), 0, s, h, x, (const T*)gamma, eps, (T*)out,
-                           io, (const TA*)add, n_add, add_stride, (int)assign);
+        plain ? launch(rmsnorm_vec_k<T, 1, TA, true, 12, 1024>, 1024) : launch(rmsnorm_vec_k<T, 1, TA, false, 12, 1024>, 1024);
     else if (vec_ok && h <= 4096)
-        hipLaunchKernelGGL((rmsnorm_vec_k<T, 4, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, io,
-                           (const TA*)add, n_add, add_stride, (int)assign);
+        plain ? launch(rmsnorm_vec_k<T, 4, TA, true>, 256) : launch(rmsnorm_vec_k<T, 4, TA, false>, 256);
     else if (vec_ok && h <= 8192)   // (the 32B and 70B widths)
-        hipLaunchKernelGGL((rmsnorm_vec_k<T, 8, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, io,
-                           (const TA*)add, n_add, add_stride, (int)assign);
+        plain ? launch(rmsnorm_vec_k<T, 8, TA, true>, 256) : launch(rmsnorm_vec_k<T, 8, TA, false>, 256);
     else
-        hipLaunchKernelGGL((rmsnorm_k<T, TA>), dim3(M), dim3(256), 0, s, h, x, (const T*)gamma, eps, (T*)out, io,
-                           (const TA*)add, n_add, add_stride, (int)assign);
+        launch(rmsnorm_k<T, TA>, 256);
 }
 
 hipError_t rmsnorm(hipStream_t s, int dtype, int M, int h, float* x, const void* gamma, float eps, void* out, const NormIO& io,
@@ -558,8 +567,9 @@ hipError_t rope_kv_write(hipStream_t s, int dtype, const Rows& rows, const KVLay
     const size_t lds = from_table ? 0 : sizeof(float) * kv.d;
     const int64_t src_stride = (int64_t)M * qkv_dim;
 #define TLT_ROPE(SRC, TBL)                                                                                                  \
-    DISPATCH_T(dtype, hipLaunchKernelGGL((rope_kv_write_k<T, SRC, TBL>), dim3(M), dim3(threads), lds, s, rows, kv, (T*)qkv, \
-                                         n_q_heads, theta, (const T*)bias, src32, n_src, src_stride, tab))
+    DISPATCH_T(dtype, hipLaunchKernelGGL((rope_kv_write_k<T, SRC, TBL>), dim3(M), dim3(threads), lds, s, src32, (T*)qkv, \
+                                         (const int64_t*)tab.at, (const float*)tab.cs, src_stride, n_src, n_q_heads, kv.n_kv, kv.d,    \
+                                         (const T*)bias, theta, rows, kv, tab))
     if (src32 && from_table) { TLT_ROPE(true, true); }
     else if (src32) { TLT_ROPE(true, false); }
     else if (from_table) { TLT_ROPE(false, true); }
