@@ -183,31 +183,39 @@ __global__ __launch_bounds__(256) void row_lse_k(int V, const float* __restrict_
 // (2) One wave per row merges the segments (draft_level_k): the K best of the union of the per-segment lists are
 //     the K best of the row because the order is total.
 constexpr int kTopkSeg = 2048;     // logits per wave: 32 per lane, held in registers
-constexpr int kTopkPerLane = kTopkSeg / 64;
+
+// exp(d) for d <= 0: the product with log2(e) in two words around the hardware's exp2, whose error of one unit the result keeps (a product in
+// one word loses |d| units).  A third of the library function's instructions, which also cover overflow and denormal results: below -200 it is 0.
+__device__ __forceinline__ float exp_nonpositive(float d) {
+    d = d < -200.f ? -200.f : d;   // (a NaN stays one)
+    const float t = d * 1.44269502f;
+    const float lo = fmaf(d, 1.92596299e-8f, fmaf(d, 1.44269502f, -t));
+    const float r = __builtin_amdgcn_exp2f(t);
+    return fmaf(r, lo * 0.693147181f, r);
+}
 
 // One WAVE per segment, no LDS and no barriers.  A lane owns 32 logits (eight 16-byte pieces, so
 // the wave's loads are fully coalesced) and keeps its two best in the (value desc, index asc) order.
-// Each of the K rounds takes the best lane candidate of the wave (xor-shuffle reduction) and the
+// Each of the K rounds takes the best lane candidate of the wave and the
 // winning lane moves on to its second candidate; only a lane that wins a third time has to rescan
 // its registers, which on real logits almost never happens, and the wave skips that code unless
 // some lane needs it.
-template <bool VEC4>
-__global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, const float* __restrict__ logits,
-                                                      float* __restrict__ seg_stat, float* __restrict__ seg_val,
-                                                      int32_t* __restrict__ seg_idx) {
+// What bounds it is the vector ALU: the scan for the best two, the exponentials, K rounds.  All segments but a row's last lie inside it and
+// test no index (152064 logits, K = 8, us: 8 rows 11.3 -> 9.3, 128 rows 35 -> 26, 256 rows 60 -> 44; segments of 4096 logits, which
+// halve the rounds, take 17, 31 and 49).
+template <bool VEC4, bool FULL>   // FULL: the segment lies inside the row
+__device__ __forceinline__ void topk_segment(const float* __restrict__ src, int V, int K, int j0, float* __restrict__ stat, float* __restrict__ val,
+                                             int32_t* __restrict__ idx) {
+    constexpr int E = kTopkSeg / 64;
     const int lane = threadIdx.x & 63;
-    const int seg = blockIdx.x * 4 + (threadIdx.x >> 6), row = blockIdx.y;
-    if (seg >= n_seg) return;  // wave-uniform
-    const int j0 = seg * kTopkSeg;
-    const float* src = logits + (int64_t)row * V;
-    float v[kTopkPerLane];
+    float v[E];
     // element e of this lane has index j0 + (e / 4) * 256 + lane * 4 + (e % 4): increasing in e
 #pragma unroll
-    for (int c = 0; c < kTopkPerLane / 4; ++c) {
+    for (int c = 0; c < E / 4; ++c) {
         const int j = j0 + c * 256 + lane * 4;
         if (VEC4) {
-            float4 x = j + 3 < V ? *(const float4*)(src + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            if (j + 3 >= V && j < V) {   // ragged end of the row
+            float4 x = FULL || j + 3 < V ? *(const float4*)(src + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+            if (!FULL && j + 3 >= V && j < V) {   // ragged end of the row
                 x.x = src[j];
                 x.y = j + 1 < V ? src[j + 1] : -INFINITY;
                 x.z = j + 2 < V ? src[j + 2] : -INFINITY;
@@ -215,21 +223,21 @@ __global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, c
             v[4 * c] = x.x, v[4 * c + 1] = x.y, v[4 * c + 2] = x.z, v[4 * c + 3] = x.w;
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * c + e] = j + e < V ? src[j + e] : -INFINITY;
+            for (int e = 0; e < 4; ++e) v[4 * c + e] = FULL || j + e < V ? src[j + e] : -INFINITY;
         }
     }
     auto index_of = [&](int e) { return j0 + (e >> 2) * 256 + lane * 4 + (e & 3); };
+    auto valid = [&](int e) { return FULL || index_of(e) < V; };
     // local best two; indices of a lane increase with e, so strict '>' keeps the lower index on ties
     float b1 = -INFINITY, b2 = -INFINITY;
     int e1 = -1, e2 = -1;
 #pragma unroll
-    for (int e = 0; e < kTopkPerLane; ++e) {
-        const float x = index_of(e) < V ? v[e] : -INFINITY;
-        const bool valid = index_of(e) < V;
-        if (valid && (e1 < 0 || x > b1)) {
+    for (int e = 0; e < E; ++e) {
+        const float x = v[e];
+        if (valid(e) && (e1 < 0 || x > b1)) {
             b2 = b1, e2 = e1;
             b1 = x, e1 = e;
-        } else if (valid && (e2 < 0 || x > b2)) {
+        } else if (valid(e) && (e2 < 0 || x > b2)) {
             b2 = x, e2 = e;
         }
     }
@@ -237,12 +245,11 @@ __global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, c
     const float mx = wave_max(b1);
     float se = 0.f;
 #pragma unroll
-    for (int e = 0; e < kTopkPerLane; ++e) se += index_of(e) < V ? expf(v[e] - mx) : 0.f;
+    for (int e = 0; e < E; ++e) se += valid(e) ? exp_nonpositive(v[e] - mx) : 0.f;
     se = wave_sum(se);
-    const int64_t o = (int64_t)row * n_seg + seg;
     if (lane == 0) {
-        seg_stat[2 * o] = mx;
-        seg_stat[2 * o + 1] = se;
+        stat[0] = mx;
+        stat[1] = se;
     }
     // K rounds
     float cv = b1;                                  // this lane's current candidate
@@ -255,8 +262,8 @@ __global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, c
         wave_best(wv, wi);
         if (lane == 0) {
             const bool have = wi != 0x7fffffff;
-            seg_val[o * K + k] = have ? wv : -INFINITY;
-            seg_idx[o * K + k] = have ? wi : 0x7fffffff;
+            val[k] = have ? wv : -INFINITY;
+            idx[k] = have ? wi : 0x7fffffff;
         }
         const bool won = wi != 0x7fffffff && wi == ci;
         if (won) {
@@ -273,8 +280,8 @@ __global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, c
                 float nv = -INFINITY;
                 int ne = -1;
 #pragma unroll
-                for (int e = 0; e < kTopkPerLane; ++e) {
-                    const bool ok = index_of(e) < V && !((taken >> e) & 1u);
+                for (int e = 0; e < E; ++e) {
+                    const bool ok = valid(e) && !((taken >> e) & 1u);
                     if (ok && (ne < 0 || v[e] > nv)) {
                         nv = v[e];
                         ne = e;
@@ -285,6 +292,19 @@ __global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, c
             }
         }
     }
+}
+
+template <bool VEC4>
+__global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, const float* __restrict__ logits,
+                                                      float* __restrict__ seg_stat, float* __restrict__ seg_val,
+                                                      int32_t* __restrict__ seg_idx) {
+    const int seg = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), row = blockIdx.y;
+    if (seg >= n_seg) return;
+    const int j0 = seg * kTopkSeg;
+    const float* src = logits + (int64_t)row * V;
+    const int64_t o = (int64_t)row * n_seg + seg;
+    if (j0 + kTopkSeg <= V) topk_segment<VEC4, true>(src, V, K, j0, seg_stat + 2 * o, seg_val + o * K, seg_idx + o * K);
+    else topk_segment<VEC4, false>(src, V, K, j0, seg_stat + 2 * o, seg_val + o * K, seg_idx + o * K);
 }
 
 // Drafter tree bookkeeping.  Feature-buffer rows per sequence: 0 = output of the entry holding the
@@ -1364,7 +1384,8 @@ hipError_t draft_level(hipStream_t s, int B, int K, int level, int V, const floa
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 block(64 * (level == 0 ? 1 : K));
-    if (n_seg * K <= 640) hipLaunchKernelGGL(draft_level_k<10>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
+    if (n_seg * K <= 320) hipLaunchKernelGGL(draft_level_k<5>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
+    else if (n_seg * K <= 640) hipLaunchKernelGGL(draft_level_k<10>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
     else if (n_seg * K <= 1280) hipLaunchKernelGGL(draft_level_k<20>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
     else hipLaunchKernelGGL(draft_level_k<0>, dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st);
     return hipGetLastError();
