@@ -800,15 +800,12 @@ __global__ __launch_bounds__(512) void attn_mfma_k(const AttnWork* __restrict__ 
 #undef TLT_BODY
 }
 
-// One wave per (b, kv head, row), four rows per workgroup: merges the chunks' partial outputs
-// (running max in raw score units).
-// BATCH: the lanes read a chunk's maximum and sum each, and the outputs of 16 chunks are requested together.  With few rows in
-// all (plain decoding, small batches) a wave's chunks, one load latency each, are the whole kernel (on the 17 chunks that one
-// sequence of 8192 had at 8 tiles each: 12 us one after the other, 6.3 four at a time, 4.8 this way; on its 33 at 4 tiles 6.1; 3
-// sequences x 23 nodes 7.3); with the chip full of waves the plain loop is the faster one (14 against 16 us at the
-// benchmark shape).  The sums run in chunk order either way.
-template <bool BATCH>
-__global__ __launch_bounds__(256) void attn_combine_k(const AttnWork* __restrict__ work, const float* __restrict__ part_o,
+// The chunks' partial outputs merged (running max in raw score units), in chunk order, by one of two kernels.
+// With few rows in all (plain decoding, small batches) a wave's chunks, one load latency each, are the whole kernel: one wave per (b, kv head,
+// row), four rows per workgroup; the lanes read a chunk's maximum and sum each, and the outputs of 16 chunks are requested together (on the 17
+// chunks that one sequence of 8192 had at 8 tiles each: 12 us one after the other, 6.3 four at a time, 4.8 this way; on its 33 at 4 tiles
+// 6.1; 3 sequences x 23 nodes 7.3).
+__global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __restrict__ work, const float* __restrict__ part_o,
                                                      const float* __restrict__ part_ml, uint16_t* __restrict__ out, int n_seq, int n,
                                                      int n_q_heads, int n_kv, int max_items, int r_pad, float scale_log2,
                                                      const int32_t* __restrict__ n_valid) {
@@ -830,7 +827,7 @@ __global__ __launch_bounds__(256) void attn_combine_k(const AttnWork* __restrict
     const int64_t pstride = (int64_t)n_kv * r_pad;
     float M = kNegBig;
     float a0 = 0.f, a1 = 0.f, L = 0.f;
-    if constexpr (BATCH) {
+    {
         constexpr int U = 16;
         float2 ml = make_float2(kNegBig, 0.f), v[U];   // lane c: chunk c's (maximum, sum)
         auto fetch = [&](int c0) {
@@ -860,19 +857,66 @@ __global__ __launch_bounds__(256) void attn_combine_k(const AttnWork* __restrict
                 }
             }
         }
-    } else {
-    for (int c = 0; c < used; ++c) M = fmaxf(M, part_ml[(pbase + c * pstride) * 2]);
-    for (int c = 0; c < used; ++c) {
-        const int64_t pr = pbase + c * pstride;
-        const float w = exp2f((part_ml[pr * 2] - M) * scale_log2);
-        L += part_ml[pr * 2 + 1] * w;
-        const float2 v = *(const float2*)(part_o + pr * kD + lane * 2);
-        a0 += v.x * w;
-        a1 += v.y * w;
-    }
     }
     const float inv = L > 0.f ? 1.0f / L : 0.f;
     o[lane] = pack_bf16x2(a0 * inv, a1 * inv);
+}
+
+// With the chip full of waves, several rounds of them, a wave's load latency counts once per round: half a wave per row, 16 bytes per lane and
+// four chunks' outputs requested together make the rounds half as many (us, against a wave per row with one chunk after the other: 32 sequences x
+// 48 nodes 17.2 -> 11.5, the 32B shape's 16 x 32 16.1 -> 11.0, 4 x 64 9.4 -> 7.7, 1200 prompt rows 12.2 -> 7.0; a wave per row with four
+// chunks requested together 17.2).
+__global__ __launch_bounds__(256) void attn_combine_k(const AttnWork* __restrict__ work, const float* __restrict__ part_o,
+                                                     const float* __restrict__ part_ml, uint16_t* __restrict__ out, int n_seq, int n,
+                                                     int n_q_heads, int n_kv, int max_items, int r_pad, float scale_log2,
+                                                     const int32_t* __restrict__ n_valid) {
+    constexpr int U = 4;
+    const int r = blockIdx.x * 8 + (threadIdx.x >> 5), kh = blockIdx.y, b = blockIdx.z, l32 = threadIdx.x & 31;
+    const int G = n_q_heads / n_kv;
+    if (r >= n * G) return;
+    const int* slot0 = (const int*)(work + 1);
+    const int first = slot0[b];
+    int used = slot0[n_seq + b];
+    if (first + used > max_items) used = max(max_items - first, 0);
+    const int i = r / G, gq = r - i * G;
+    const int nv = n_valid ? min(n_valid[b], n) : n;
+    uint2* o = (uint2*)(out + ((int64_t)(b * n + i) * n_q_heads + kh * G + gq) * kD) + l32;
+    if (i >= nv || used <= 0) {
+        *o = make_uint2(0u, 0u);
+        return;
+    }
+    const int64_t pbase = ((int64_t)first * n_kv + kh) * r_pad + r;
+    const int64_t pstride = (int64_t)n_kv * r_pad;
+    f32x4_t v[U];
+    float2 ml[U];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c0 + u < used) {   // (uniform)
+                ml[u] = *(const float2*)(part_ml + (pbase + (c0 + u) * pstride) * 2);
+                v[u] = *(const f32x4_t*)(part_o + (pbase + (c0 + u) * pstride) * kD + l32 * 4);
+            }
+    };
+    fetch(0);
+    float M = kNegBig, L = 0.f;
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < used) M = fmaxf(M, ml[u].x);
+    for (int c = U; c < used; ++c) M = fmaxf(M, part_ml[(pbase + c * pstride) * 2]);
+    for (int c0 = 0; c0 < used; c0 += U) {
+        if (c0 > 0) fetch(c0);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (c0 + u < used) {
+                const float w = exp2f((ml[u].x - M) * scale_log2);
+                L += ml[u].y * w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += v[u][e] * w;
+            }
+    }
+    const float inv = L > 0.f ? 1.0f / L : 0.f;
+    *o = make_uint2(pack_bf16x2(acc[0] * inv, acc[1] * inv), pack_bf16x2(acc[2] * inv, acc[3] * inv));
 }
 
 static size_t attn_need_bytes(int B, const AttnPlan& p, int n_kv) {
@@ -920,11 +964,11 @@ static hipError_t launch_attn_mfma(hipStream_t s, const Rows& rows, const KVLaye
     if (e != hipSuccess) return e;
     const int R = rows.n * (n_q_heads / kv.n_kv);
     if ((int64_t)R * kv.n_kv * rows.B <= 4096)   // (waves: half of what the chip holds at once)
-        hipLaunchKernelGGL(attn_combine_k<true>, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
+        hipLaunchKernelGGL(attn_combine_few_k, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
                            (const float*)part_o, (const float*)part_ml, (uint16_t*)out, rows.B, rows.n, n_q_heads, kv.n_kv, p.max_items, p.r_pad,
                            scale_log2, rows.n_valid);
     else
-        hipLaunchKernelGGL(attn_combine_k<false>, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
+        hipLaunchKernelGGL(attn_combine_k, dim3((R + 7) / 8, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
                            (const float*)part_o, (const float*)part_ml, (uint16_t*)out, rows.B, rows.n, n_q_heads, kv.n_kv, p.max_items, p.r_pad,
                            scale_log2, rows.n_valid);
     return hipGetLastError();
