@@ -857,38 +857,34 @@ __global__ __launch_bounds__(kDrawThreads) void softmax_draw_k(int n, int V, flo
 
 // ------------------------------------------------------------------------------------------------
 // Acceptance.
-__global__ void accept_greedy_k(int B, int n, int stride, const int32_t* __restrict__ token,
+// A wave per sequence, a lane per node (n <= 64): a step of the walk is a comparison in every lane and a ballot.  (A thread per sequence walked
+// its nodes one load after the other: 16 trees of 16 nodes 14.9 us, 32 of 48 nodes 38; this 4.9.)
+__global__ __launch_bounds__(256) void accept_greedy_k(int B, int n, int stride, const int32_t* __restrict__ token,
                                 const int32_t* __restrict__ parent, const int32_t* __restrict__ argmax,
                                 int32_t* __restrict__ accept_len, int32_t* __restrict__ path_idx,
                                 int32_t* __restrict__ out_tokens, int32_t* __restrict__ n_out) {
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
+    const int b = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
     if (b >= B) return;
-    const int32_t* tok = token + (int64_t)b * n;
-    const int32_t* par = parent + (int64_t)b * n;
-    const int32_t* best = argmax + (int64_t)b * n;
-    int32_t* path = path_idx + (int64_t)b * stride;
-    int32_t* out = out_tokens + (int64_t)b * stride;
-    for (int j = 0; j < stride; ++j) {
-        path[j] = -1;
-        out[j] = -1;
-    }
-    int cur = 0, a = 0;
-    path[0] = 0;
+    const int64_t at = (int64_t)b * n + lane;
+    const bool on = lane < n;
+    const int tok = on ? token[at] : 0, par = on ? parent[at] : -2, best = on ? argmax[at] : 0;
+    int cur = 0, a = 0, my_path = -1, my_out = -1;   // lane j: the path's and the output's entry j
     for (;;) {
-        int t = best[cur];
-        out[a] = t;
-        int next = -1;
-        for (int c = cur + 1; c < n; ++c)
-            if (par[c] == cur && tok[c] == t) {
-                next = c;
-                break;
-            }
-        if (next < 0 || a + 1 >= stride) break;
-        cur = next;
-        path[++a] = cur;
+        const int t = __builtin_amdgcn_readlane(best, cur);
+        if (lane == a) my_path = cur, my_out = t;
+        const uint64_t next = __ballot(on && lane > cur && par == cur && tok == t);
+        if (next == 0 || a + 1 >= stride) break;
+        cur = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)next) - 1);   // (the first such child)
+        ++a;
     }
-    accept_len[b] = a;
-    n_out[b] = a + 1;
+    for (int j = lane; j < stride; j += 64) {
+        path_idx[(int64_t)b * stride + j] = j < 64 ? my_path : -1;
+        out_tokens[(int64_t)b * stride + j] = j < 64 ? my_out : -1;
+    }
+    if (lane == 0) {
+        accept_len[b] = a;
+        n_out[b] = a + 1;
+    }
 }
 
 // Recursive rejection sampling.  Integer weights W (target), Qw (draft) and the residual R live in
@@ -1463,7 +1459,7 @@ hipError_t accept_greedy(hipStream_t s, int B, int n, int V, int stride, const i
                          const float* logits, const int32_t* argmax, int32_t* accept_len, int32_t* path_idx,
                          int32_t* out_tokens, int32_t* n_out) {
     (void)V; (void)logits;
-    hipLaunchKernelGGL(accept_greedy_k, dim3((B + 63) / 64), dim3(64), 0, s, B, n, stride, token, parent, argmax,
+    hipLaunchKernelGGL(accept_greedy_k, dim3((B + 3) / 4), dim3(256), 0, s, B, n, stride, token, parent, argmax,
                        accept_len, path_idx, out_tokens, n_out);
     return hipGetLastError();
 }
