@@ -1110,8 +1110,6 @@ static hipError_t launch_tiled(hipStream_t s, int out_mode, int M, int N, int K,
         return launch_pipe<2, 2, 4, 4, 3, 2>(s, out_mode, M, n_cols, K, A, W, C, nullptr, 1, N);
     };
     const int tiles256 = nbm256 * nbn256;
-    // (with M <= 64 three quarters of a 256-row tile would be padding: the 128x128 tiles stream the
-    // weights faster)
     // one row of big tiles, a hundred or more of them, streams cold weights faster than twice as
     // many TA-bound small ones
     if (nbm256 == 1 && M > 128 && tiles256 >= 100 && N % bno256 == 0) {
