@@ -268,12 +268,19 @@ KVLayer kv_layer(const tlt_ctx* ctx, const tlt_kv* kv, int layer) {
 // One decoder block over M = rows.B * rows.n rows whose residual stream sits in the workspace's x.
 // later_layer: an earlier layer of the same forward (same rows, same sequence lengths) has left the attention work list
 // and the rotary table in the workspace.
+// Rows of a block whose output is wanted: row `row` of every `n` (B of them), or none (B = 0).  The block's keys and values are written for all rows.
+struct WantedRows {
+    int B, n, row;
+};
+
+// With `wanted` (the last block of a forward only) the stream holds the wanted rows alone, densely, afterwards.
 int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const Rows& rows, const KVLayer& kv,
-                  bool later_layer = false) {
+                  bool later_layer = false, const WantedRows* wanted = nullptr) {
     const tlt_model_cfg& c = ctx->cfg;
     const Plan& p = ctx->plan;
     char* ws = ctx->ws;
-    const int M = rows.B * rows.n, h = c.hidden, F = c.mlp, dt = c.dtype;
+    int M = rows.B * rows.n;
+    const int h = c.hidden, F = c.mlp, dt = c.dtype;
     const int q_dim = c.n_q_heads * c.head_dim, qkv_dim = q_dim + 2 * c.n_kv_heads * c.head_dim;
     const double e = (double)esz_of(ctx);
     float* x = (float*)(ws + p.x);
@@ -285,7 +292,7 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     // fp32 mode with few rows: both norms belong to the products behind them.  The stream's rows then go to xn and, at the second norm, back.
     float* x1 = (float*)(ws + p.xn);
     const NormIn n1 = norm_in(ctx, x, w.attn_norm, x1);
-    const bool own_norm = ctx->pending_parts <= 1 && gemm_f32_norm_supported(dt, M, qkv_dim, h, n1, w.wqkv, nullptr) &&
+    const bool own_norm = !wanted && ctx->pending_parts <= 1 && gemm_f32_norm_supported(dt, M, qkv_dim, h, n1, w.wqkv, nullptr) &&
                           gemm_f32_norm_supported(dt, M, F, h, n1, w.wg, w.wu) && ((uintptr_t)w.mlp_norm & 15) == 0;
     if (own_norm) {
         TLT_RUN(ctx, s, ctx->in_draft ? CLS_GEMM_DRAFT : CLS_GEMM, 2.0 * M * qkv_dim * h, ((double)M * h * 3 + (double)qkv_dim * (h + M)) * e,
@@ -310,6 +317,11 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * e * 2,
                 rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer));
     }
+    if (wanted && wanted->B == 0) {
+        ctx->pending_parts = 0;
+        return TLT_OK;
+    }
+    const char* att = ws + p.att;
     {
         // algorithmic traffic: one pass over the cached K and V of every sequence (bounded by the
         // host-known length) plus q in / out; flops: 4 * d per (query row, head, key)
@@ -320,15 +332,26 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
                 attention(s, dt, rows, kv, ws + p.qkv, ws + p.att, c.n_q_heads, ws + p.attn_ws, p.attn_ws_bytes, ctx->attn_impl,
                           later_layer, ctx->status_ready ? status_word(ctx) : nullptr));
     }
+    if (wanted) {
+        // the wanted rows of the stream to its front (by way of xn: source and destination rows may meet), those of the attention to where
+        // qkv was; both buffers are sized for all rows
+        M = wanted->B;
+        const int n = wanted->n, up = n - 1 - wanted->row, att_words = (int)(q_dim * esz_of(ctx) / 4);
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * 8, gather_last_rows(s, M, n, h, x - (int64_t)up * h, (float*)(ws + p.xn), 1));
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * 8, copy_f32(s, (int64_t)M * h, (const float*)(ws + p.xn), x));
+        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * q_dim * e * 2,
+                gather_last_rows(s, M, n, att_words, (const float*)att - (int64_t)up * att_words, (float*)(ws + p.qkv), 1));
+        att = ws + p.qkv;
+    }
     // the output projection's product (fp32, possibly several partial products of a K split) joins the
     // residual stream inside the norm kernel that follows: plain stores in the GEMM's epilogue instead of
     // a read-modify-write of the stream by every tile, and a sum formed in a fixed order
     if (dt == TLT_BF16 && !ctx->oproj_f32 && M > 256) {   // (measurement switch: the product rounded to the model dtype)
-        if ((rc = run_gemm(ctx, s, OUT_T, M, h, q_dim, ws + p.att, w.wo, parts))) return rc;
+        if ((rc = run_gemm(ctx, s, OUT_T, M, h, q_dim, att, w.wo, parts))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * (8 + 2 * e),
                 rmsnorm(s, dt, M, h, x, w.mlp_norm, c.rms_eps, ws + p.xn, NormIO(), parts, false, 1, M));
     } else {
-        if ((rc = run_gemm_parts(ctx, s, M, h, q_dim, ws + p.att, w.wo, &n_parts))) return rc;
+        if ((rc = run_gemm_parts(ctx, s, M, h, q_dim, att, w.wo, &n_parts))) return rc;
         ctx->pending_parts = n_parts;
         ctx->pending_assign = false;
         if (!own_norm && (rc = norm_x(ctx, s, M, w.mlp_norm, ws + p.xn))) return rc;
@@ -652,7 +675,7 @@ static bool plan_prefill(const tlt_ctx* ctx, int BC, int m, const tlt_kv* kv, co
 }
 
 // Rows of a pass: what a product of this model's widths needs to run at the rate of large ones (7B shape, 4 prompts of 301 tokens:
-// five passes of 256 rows 27.5 ms, one of 1200 16.1).
+// five passes of 256 rows 27.5 ms, one of 1200 15.9).
 constexpr int kPrefillRows = 2048;
 
 int tlt_prefill(tlt_ctx* ctx, void* stream, int B, int n_tokens, int chunk, const int32_t* tokens, int token_stride, tlt_kv* kv,
@@ -739,14 +762,16 @@ int tlt_prefill(tlt_ctx* ctx, void* stream, int B, int n_tokens, int chunk, cons
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * h * (4 + 3 * e),
                 draft_input(s, c.dtype, BC, m, h, V, pass.nxt, pass.src, pass.n_valid, m, (int64_t)M, x, ctx->target.embed, ws + p.xn));
         if ((rc = draft_fc(ctx, s, M, ws + p.xn))) return rc;
-        if ((rc = layer_forward(ctx, s, ctx->draft.layers[0], rows, kv_layer(ctx, &vd, 0)))) return rc;
+        // only the prompt's last position's output is wanted, as feature row 0 (4 prompts x 301 tokens: the block's other 1196 rows cost
+        // 0.4 ms of 16.2 behind its keys and values)
+        const bool last = done + taken == n_tokens;
+        const WantedRows wanted{last ? B : 0, Cp * m, taken - 1};
+        if ((rc = layer_forward(ctx, s, ctx->draft.layers[0], rows, kv_layer(ctx, &vd, 0), false, &wanted))) return rc;
         ctx->in_draft = false;
         done += taken;
-        if (done == n_tokens) {   // (only the last position's output is wanted, as feature row 0; rows past it in its chunk: pad)
-            if ((rc = fold_pending(ctx, s, M))) return rc;
-            const int pad = Cp * m - taken;
-            TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * 8,
-                    gather_last_rows(s, B, Cp * m, h, x - (int64_t)pad * h, (float*)(ws + p.feat), p.feat_rows));
+        if (last) {
+            if ((rc = fold_pending(ctx, s, B))) return rc;
+            TLT_RUN(ctx, s, CLS_OTHER, 0, (double)B * h * 8, gather_last_rows(s, B, 1, h, x, (float*)(ws + p.feat), p.feat_rows));
         }
         ctx->pending_parts = 0;
         TLT_RUN(ctx, s, CLS_OTHER, 0, 0, add_i32(s, B, kv->seq_len, nullptr, taken));

@@ -60,3 +60,5 @@ def test_prefill_equals_chunk_by_chunk(dtype, cfg, B, P, chunk, lens, monkeypatc
     al = [e.step(K, D, N) for e in engines]
     if dtype == "fp32":
         assert all(np.array_equal(x, y) for x, y in zip(*al))
+        ta, tb = (e.tree(N) for e in engines)   # grown from the drafter's output at the prompt's last position
+        assert torch.equal(ta.token, tb.token) and float((ta.score - tb.score).abs().max()) <= tol * max(1.0, float(ta.score.abs().max()))
