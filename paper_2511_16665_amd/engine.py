@@ -59,8 +59,9 @@ class Engine:
         B, P = prompts.shape
         chunk = chunk or self.max_n
         body = P - 1
-        if body > chunk and B <= self.B and self.dkv is not None:
-            # several chunks of every prompt per pass, where the workspace holds them
+        if body > chunk and B in (1, self.B) and self.dkv is not None:
+            # several chunks of every prompt per pass, where the workspace holds them (other counts do not fit the trees and roots
+            # of this engine: the copies below refuse them before anything is enqueued)
             tokens = torch.from_numpy(np.ascontiguousarray(prompts, dtype=np.int32)).cuda()
             if self.ctx.prefill(B, body, chunk, tokens, self.kv, self.dkv):
                 self.kv.seq_len_bound += body

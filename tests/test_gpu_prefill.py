@@ -62,3 +62,16 @@ def test_prefill_equals_chunk_by_chunk(dtype, cfg, B, P, chunk, lens, monkeypatc
         assert all(np.array_equal(x, y) for x, y in zip(*al))
         ta, tb = (e.tree(N) for e in engines)   # grown from the drafter's output at the prompt's last position
         assert torch.equal(ta.token, tb.token) and float((ta.score - tb.score).abs().max()) <= tol * max(1.0, float(ta.score.abs().max()))
+
+
+def test_prompts_of_another_count_than_the_engines_change_nothing():
+    e, _, _ = make_engine(WIDE, "bf16", *make_models(WIDE, 5, "bf16", std=0.05)[:2], 3, 64, 2, 2, 400, seed=4)
+    for B in (2, 4):
+        with pytest.raises(RuntimeError):
+            e.prefill(prompts(B, 200, WIDE.vocab, seed=3))
+        torch.cuda.synchronize()
+        for kv in (e.kv, e.dkv):
+            assert kv.seq_len_bound == 0 and not kv.seq_len.any() and not kv.k_pool.any()
+    e.prefill(prompts(1, 200, WIDE.vocab, seed=3))                     # (one prompt: the first sequence's)
+    assert e.kv.seq_len.tolist() == e.dkv.seq_len.tolist() == [199, 0, 0]
+    e.ctx.close()
