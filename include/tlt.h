@@ -346,8 +346,9 @@ enum { TLT_STATUS_CONTEXT_TRUNCATED = 1, TLT_STATUS_NO_RENDEZVOUS = 2 };
 int tlt_device_status(tlt_ctx *ctx, void *stream, uint32_t *flags);
 
 /* End of a step: the n words at `words` (DEVICE, e.g. accept_len and out_tokens side by side) go to out[0 .. n-1] and the status word to
- * out[n], in one synchronisation: a kernel writes them, so out is pinned HOST memory (hipHostMalloc), n + 1 words.  Synchronises
- * `stream`; *flags (HOST, may be NULL), clearing and return values as tlt_device_status.  out is written whatever the status. */
+ * out[n], in one synchronisation: a kernel writes them, so out is pinned HOST memory (hipHostMalloc), n + 1 words; TLT_EINVAL, with
+ * nothing enqueued, for memory that kernels cannot reach.  Synchronises `stream`; *flags (HOST, may be NULL), clearing and return values
+ * as tlt_device_status.  out is written whatever the status. */
 int tlt_step_report(tlt_ctx *ctx, void *stream, const int32_t *words, int n, int32_t *out, uint32_t *flags);
 
 /* Measurement switch: 1 = with more than 256 rows the attention output projection's product is rounded

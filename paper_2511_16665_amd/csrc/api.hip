@@ -498,11 +498,24 @@ int tlt_device_status(tlt_ctx* ctx, void* stream, uint32_t* flags) {
     return (host & TLT_STATUS_CONTEXT_TRUNCATED) ? TLT_ESHAPE : ((host & TLT_STATUS_NO_RENDEZVOUS) ? TLT_ESYNC : TLT_OK);
 }
 
+// The address at which kernels reach a word of the caller's pinned (or managed) host memory; null for any other memory (a kernel
+// that stored there would fault).  Asked of the runtime at every call: what an address belongs to may change between two.
+static int32_t* mapped_host_word(int32_t* p) {
+    hipPointerAttribute_t a = {};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();   // (memory that the runtime does not know: not an error of the next call)
+        return nullptr;
+    }
+    return a.type == hipMemoryTypeHost || a.type == hipMemoryTypeManaged ? (int32_t*)a.devicePointer : nullptr;
+}
+
 int tlt_step_report(tlt_ctx* ctx, void* stream, const int32_t* words, int n, int32_t* out, uint32_t* flags) {
     if (!ctx || !words || n < 1 || n > (1 << 24) || !out) return TLT_EINVAL;
+    int32_t* const dst = mapped_host_word(out);
+    if (!dst || mapped_host_word(out + n) != dst + n) return TLT_EINVAL;
     if (flags) *flags = 0;
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = report_words(s, n, words, ctx->status_ready ? status_word(ctx) : nullptr, out);
+    hipError_t e = report_words(s, n, words, ctx->status_ready ? status_word(ctx) : nullptr, dst);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail(ctx, e);
     const uint32_t raised = (uint32_t)out[n];

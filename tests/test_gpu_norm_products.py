@@ -1,5 +1,6 @@
 """fp32 mode with few rows, whose products normalise their own rows, against more rows of the same sequences (norms of their own); and the
 report that a step ends with."""
+import ctypes
 import dataclasses
 
 import numpy as np
@@ -65,3 +66,18 @@ def test_step_report_returns_the_words_and_raises_what_kernels_saw():
     e.ctx.verify_forward(2, t, e.kv, out_argmax=am)
     pinned = torch.empty(3, dtype=torch.int32, pin_memory=True)
     np.testing.assert_array_equal(e.ctx.step_report(am.view(-1), pinned), am.view(-1).cpu().numpy())
+
+
+def test_step_report_refuses_memory_that_kernels_cannot_reach():
+    tw, dw, _, _ = make_models(TINY, 7, "fp32", std=0.05)
+    e, _, _ = make_engine(TINY, "fp32", tw, dw, 3, 8, 2, 2, 200, seed=3)
+    words = torch.arange(64, dtype=torch.int32, device="cuda")
+    pageable, pinned = np.full(80, -9, np.int32), torch.full((80,), -9, dtype=torch.int32, pin_memory=True)
+    stream, flags = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream), ctypes.c_uint32(77)
+    report = lambda out, n: e.ctx.lib.tlt_step_report(e.ctx.handle, stream, words.data_ptr(), n, ctypes.c_void_p(out), ctypes.byref(flags))
+    for out in (pageable.ctypes.data, words.data_ptr()):            # ordinary host memory, device memory: refused on the host
+        assert report(out, 64) == -1 and flags.value == 77
+    torch.cuda.synchronize()                                         # (and no error is left behind)
+    assert (pageable == -9).all() and words.tolist() == list(range(64))
+    assert report(pinned.data_ptr() + 16, 64) == 0 and flags.value == 0   # from inside a pinned allocation
+    assert pinned[4:69].tolist() == list(range(64)) + [0] and pinned[:4].tolist() == [-9] * 4 and (pinned[69:] == -9).all()
