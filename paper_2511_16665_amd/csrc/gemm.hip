@@ -643,31 +643,41 @@ __global__ __launch_bounds__(256) void gemm_f32_few_k(int M, int N, int K, const
         ap[t] = A + (int64_t)(row < M ? row : M - 1) * K + 4 * g;
     }
     if constexpr (NORM) {
-        // a wave per row, four rows each; K <= 1024: at most four 16-byte pieces per lane (the launcher checks)
+        // a wave per row, four rows each; K <= 1024: at most four 16-byte pieces per lane (the launcher checks).  All rows are requested before the
+        // first is summed: one after the other, every four rows cost a trip to the caches per product (a forward of 8 blocks of 1024 elements,
+        // us: 8 rows 328 -> 296, 12 rows 365 -> 311, 16 rows 396 -> 326)
+        f32x4v_t v[4][4], add[4][4], gam[4];
+        const f32x4v_t zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int r = m0 + wave + 4 * q;
-            if (r >= M) break;   // (wave-uniform; rows past the end are never stored, what their LDS holds does not matter)
-            f32x4v_t v[4], gam[4];
-            float ss = 0.f;
+            const int r = m0 + wave + 4 * q;   // (wave-uniform; rows past the end are never stored, what their LDS holds does not matter)
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int c = 4 * lane + 256 * u;
-                const bool on = c < K;
-                v[u] = on && !(ni.add && ni.assign) ? *(const f32x4v_t*)(ni.x + (int64_t)r * K + c) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
-                gam[u] = on ? *(const f32x4v_t*)(ni.gamma + c) : f32x4v_t{0.f, 0.f, 0.f, 0.f};
-                if (ni.add && on) v[u] += *(const f32x4v_t*)(ni.add + (int64_t)r * K + c);
+                const bool on = r < M && c < K;
+                v[q][u] = on && !(ni.add && ni.assign) ? *(const f32x4v_t*)(ni.x + (int64_t)r * K + c) : zero;
+                add[q][u] = on && ni.add ? *(const f32x4v_t*)(ni.add + (int64_t)r * K + c) : zero;
+                if (q == 0) gam[u] = c < K ? *(const f32x4v_t*)(ni.gamma + c) : zero;
             }
+        }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) ss += v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2] + v[u][3] * v[u][3];
+        for (int q = 0; q < 4; ++q) {
+            const int r = m0 + wave + 4 * q;
+            if (r >= M) break;
+            float ss = 0.f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (ni.add) v[q][u] += add[q][u];
+                ss += v[q][u][0] * v[q][u][0] + v[q][u][1] * v[q][u][1] + v[q][u][2] * v[q][u][2] + v[q][u][3] * v[q][u][3];
+            }
             const float inv = 1.0f / sqrtf(wave_sum(ss) / (float)K + ni.eps);
             float* keep = blockIdx.x == 0 && ni.x_out ? ni.x_out + ((int64_t)(r / ni.out_n) * ni.out_stride + ni.out_base + r % ni.out_n) * K : nullptr;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int c = 4 * lane + 256 * u;
                 if (c >= K) continue;
-                *(f32x4v_t*)(xn_s + (wave + 4 * q) * (K + 4) + c) = v[u] * inv * gam[u];
-                if (keep) *(f32x4v_t*)(keep + c) = v[u];
+                *(f32x4v_t*)(xn_s + (wave + 4 * q) * (K + 4) + c) = v[q][u] * inv * gam[u];
+                if (keep) *(f32x4v_t*)(keep + c) = v[q][u];
             }
         }
         __syncthreads();
@@ -756,10 +766,14 @@ static hipError_t launch_f32_few(hipStream_t s, int out_mode, int M, int N, int 
     return launch_f32_few_t<4>(s, out_mode, M, N, K, A, W, W2, C);
 }
 
-// Up to 16 rows (one row block) of at most 1024 elements: every workgroup then reads all rows, at most 64 KB and the addend's as many, which the
-// saved launch pays for while the workgroups are few enough to run at once.
+// One row block of at most 1024 elements a row: every workgroup then reads all rows, at most 64 KB and the addend's as many, which the saved
+// launch pays for while the rows are few: up to 12, and up to 16 of at most 256 elements, where launches count most.  A forward of 8 blocks,
+// us, this way and with norms of their own (replayed from a graph; enqueued one by one where that differs by more than 2 %):
+//   width 64:   8 rows 186 / 194 (201 / 250)   12 rows 199 / 201 (207 / 257)   16 rows 209 / 202 (217 / 250)
+//   width 256:  8 rows 220 / 232 (226 / 261)   12 rows 232 / 239 (235 / 268)   16 rows 241 / 243 (244 / 274)
+//   width 1024: 8 rows 296 / 318               12 rows 311 / 325               16 rows 326 / 328, with 4096 to 8192 columns 483 / 477
 bool gemm_f32_norm_supported(int dtype, int M, int N, int K, const NormIn& n, const void* W, const void* W2) {
-    return dtype == F32 && M <= 16 && K <= 1024 && N <= 16 * 512 && f32_few_ok(M, K, n.x, W, W2) &&
+    return dtype == F32 && M <= (K <= 256 ? 16 : 12) && K <= 1024 && N <= 16 * 512 && f32_few_ok(M, K, n.x, W, W2) &&
            (((uintptr_t)n.add | (uintptr_t)n.gamma | (uintptr_t)n.x_out) & 15) == 0;
 }
 template <bool GLU>

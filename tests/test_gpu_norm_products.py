@@ -15,8 +15,10 @@ from gpu_util import make_engine, make_models
 pytestmark = pytest.mark.gpu
 
 
-# rows: 16 (the last count that is normalised in the products), 1, 5; widths at the limit, off the wave's 256 and 16, smaller than a wave's step
-@pytest.mark.parametrize("hidden,mlp,vocab,B,n", [(256, 768, 1024, 2, 8), (1024, 512, 8192, 1, 16), (1020, 200, 300, 1, 5), (64, 36, 64, 1, 1)])
+# rows: 16 and 12 (the last counts that are normalised in the products, up to 256 elements and above), 1, 5; widths at the limit, off the
+# wave's 256 and 16, smaller than a wave's step
+@pytest.mark.parametrize("hidden,mlp,vocab,B,n", [(256, 768, 1024, 2, 8), (1024, 512, 8192, 1, 16), (1020, 200, 300, 1, 5), (64, 36, 64, 1, 1),
+                                                  (1024, 512, 8192, 3, 4), (260, 100, 300, 2, 6), (252, 100, 300, 3, 5)])
 def test_products_that_normalise_their_rows(hidden, mlp, vocab, B, n):
     cfg = dataclasses.replace(TINY, hidden=hidden, mlp=mlp, vocab=vocab)
     tw, dw, _, _ = make_models(cfg, 7, "fp32", std=0.05)
