@@ -117,9 +117,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
     static_assert(LA % 2 == 0 && WTM >= 2, "schedule: each operand's loads are split over two slices");
     static_assert(SA >= 2 && SB >= 2, "at least double buffering");
     constexpr int RQ = (NR + WTM / 2 - 1) / (WTM / 2);   // fragment reads issued by each of the first WTM/2 MFMA rows
-    // loads that may still be in flight when tile t+1 must be complete (issue order per step: W, then A; loads retire in order, so slots
-    // of one operand beyond what the other's ring allows keep nothing more in flight)
-    constexpr int kInFlightA = (SA - 2) * (LA + LB), kInFlightB = (SB - 1) * LA + (SB - 2) * LB;
+    // loads that may still be in flight when tile t+1 must be complete: those issued after its A part (each step issues W, then A) and
+    // after its W part, fewest for W tile 1, which the prologue issues after the A tiles (later ones have (SB - 1) * LA + (SB - 2) * LB behind
+    // them).  Loads retire in order, so slots of one operand beyond what the other's ring allows keep nothing more in flight.
+    constexpr int kInFlightA = (SA - 2) * (LA + LB), kInFlightB = LA + (SB - 2) * LB;
     constexpr int kInFlight = kInFlightA < kInFlightB ? kInFlightA : kInFlightB;
     constexpr int BNO = GLU ? BN / 2 : BN;            // output columns per workgroup
     // widths that do not divide the 128 columns every launch is a multiple of: the last column tile may be partial
@@ -1089,16 +1090,16 @@ static hipError_t launch_tiled(hipStream_t s, int out_mode, int M, int N, int K,
             return launch_pipe<2, 2, 2, 2, 3, 3, true>(s, OUT_T, M, n_cols, K, A, w, c, w2, 1, N);
         }
         // up to 64 rows: tiles of 64 rows (half of a 128-row tile would be padding), four waves side by side; the LDS that is freed holds a
-        // third weight slot with two workgroups per CU, or four slots of each operand with one.  What bounds it is how much of the weight
+        // third weight slot with two workgroups per CU, or five (and four of activations) with one.  What bounds it is how much of the weight
         // stream a CU has in flight.  Against 128x128 tiles, whose two workgroups per CU had two slots (us, same buffers, cold weights): N
         // 152064, K 3584: 1 row 183 -> 162 (6.7 TB/s), 16 rows 189 -> 173, 32 rows 202 -> 188; N 128256, K 8192: 358 -> 339, 352 -> 336, 365 -> 350;
-        // N 32000, K 4096: 56 -> 55; one tile per CU: N 16384, K 4096 40 -> 33 at 1 row, 39.3 -> 36.9 at 64; N 8192, K 8192 61 -> 48, 64 -> 57.
-        // (With one tile per CU, four activation slots let two K steps' loads stay outstanding whatever the weight ring's length from four on:
-        // see kInFlight.  Eight weight slots only lengthened the first burst: N 16384, K 4096, 1 row 30.8 -> 29.8, 64 rows 37.8 -> 36.5; N 8192,
-        // K 8192 46.6 -> 45.7, 58.5 -> 57.7; N 32768, K 2048 31.0 -> 30.0, 33.8 -> 32.4.)
+        // N 32000, K 4096: 56 -> 55; one tile per CU: N 16384, K 4096 40 -> 33 at 1 row, 39.3 -> 37.3 at 64; N 8192, K 8192 61 -> 48, 64 -> 57.
+        // (With one tile per CU four activation slots leave two K steps' loads outstanding, see kInFlight, and five weight slots are what that
+        // takes; with eight the first burst was longer: N 16384, K 4096, 1 row 30.8 -> 30.1, 64 rows 37.8 -> 37.0; N 8192, K 8192 46.7 -> 45.9
+        // and 58.7 -> 58.1; N 32768, K 2048 31.1 -> 30.3, 33.8 -> 32.7.  With four, 10 loads instead of 12: 1 row 30.7, 48.7 and 30.3.)
         if (M <= 64) {
             if (tiles > 256) return launch_pipe<1, 4, 2, 1, 3, 3, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);
-            return launch_pipe<1, 4, 2, 1, 4, 4, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);
+            return launch_pipe<1, 4, 2, 1, 4, 5, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);
         }
         if (nbm128 == 1) {
             if (tiles > 256) return launch_pipe<2, 2, 2, 2, 3, 2, false, true>(s, out_mode, M, n_cols, K, A, w, c, nullptr, 1, N);

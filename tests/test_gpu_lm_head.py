@@ -22,7 +22,7 @@ def _operands(M, N, K, seed, small_ints=False):
 @pytest.mark.parametrize("M,N,K,mode", [
     (1, 38400, 192, 1),      # 300 tiles, two workgroups per CU, three K steps = the ring
     (33, 32896, 128, 0),     # 257 tiles, K shorter than the ring: no workgroup takes two
-    (64, 384, 64, 0),        # three tiles, one K step in a ring of four
+    (64, 384, 64, 0),        # three tiles, one K step in a ring of five
     (63, 32768, 576, 1),     # 256 tiles, one per CU, nine K steps
     (64, 70016, 1024, 1),    # several tiles per workgroup
     (48, 66304, 2048, 1),    # 128-row tiles: a whole round and a rest of three column tiles
