@@ -265,14 +265,14 @@ KVLayer kv_layer(const tlt_ctx* ctx, const tlt_kv* kv, int layer) {
     return k;
 }
 
-// One decoder block over M = rows.B * rows.n rows whose residual stream sits in the workspace's x.
-// later_layer: an earlier layer of the same forward (same rows, same sequence lengths) has left the attention work list
-// and the rotary table in the workspace.
 // Rows of a block whose output is wanted: row `row` of every `n` (B of them), or none (B = 0).  The block's keys and values are written for all rows.
 struct WantedRows {
     int B, n, row;
 };
 
+// One decoder block over M = rows.B * rows.n rows whose residual stream sits in the workspace's x.
+// later_layer: an earlier layer of the same forward (same rows, same sequence lengths) has left the attention work list
+// and the rotary table in the workspace.
 // With `wanted` (the last block of a forward only) the stream holds the wanted rows alone, densely, afterwards.
 int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const Rows& rows, const KVLayer& kv,
                   bool later_layer = false, const WantedRows* wanted = nullptr) {
@@ -307,8 +307,8 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     } else if (dt == TLT_BF16 && qkv_dim % 128 == 0 && (size_t)M * qkv_dim * 4 * 2 <= p.parts_bytes &&
         (M <= 256 || gemm_parts_pays(dt, M, qkv_dim, h))) {
         // too few tiles for the chip unless the projection is cut along K, which leaves fp32 partial products;
-        // the rotary kernel sums them and leaves q in the model dtype (always up to 256 rows, one row of tiles;
-        // above where the cost model of the cuts expects it to pay: a few hundred rows).
+        // the rotary kernel sums them, rounds the sums to the model dtype, as a product stored once is, and rotates (always up to
+        // 256 rows, one row of tiles; above where the cost model of the cuts expects it to pay: a few hundred rows).
         if ((rc = run_gemm_parts(ctx, s, M, qkv_dim, h, ws + p.xn, w.wqkv, &n_parts))) return rc;
         TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * (4 * n_parts + e),
                 rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer, parts, n_parts));
@@ -688,7 +688,9 @@ static bool plan_prefill(const tlt_ctx* ctx, int BC, int m, const tlt_kv* kv, co
 }
 
 // Rows of a pass: what a product of this model's widths needs to run at the rate of large ones (7B shape, 4 prompts of 301 tokens:
-// five passes of 256 rows 27.5 ms, one of 1200 15.9).
+// five passes of 256 rows 27.5 ms, one of 1200 15.9).  Four blocks of that shape, ms with at most 1024 / 2048 / 4096 rows: 4 x 301 3.17 /
+// 2.56 / 2.57, 8 x 250 4.31 / 3.94 / 3.94, 8 x 600 10.6 / 9.6 / 9.8, 16 x 257 10.4 (no two chunks fit) / 7.7 / 8.5; a single prompt of 2049 to
+// 4097 the same (its engine's workspace holds fewer rows).
 constexpr int kPrefillRows = 2048;
 
 int tlt_prefill(tlt_ctx* ctx, void* stream, int B, int n_tokens, int chunk, const int32_t* tokens, int token_stride, tlt_kv* kv,

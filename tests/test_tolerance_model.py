@@ -1,11 +1,12 @@
 """Where the bf16-mode tolerance comes from, rounding by rounding.
 
 A bf16 decoder hands bf16 activations from one contraction to the next; the float64 oracle keeps them
-exact.  The library rounds at exactly five points per block: the normalised rows entering the q/k/v
+exact.  The library rounds the operands of a block's five contractions: the normalised rows entering the q/k/v
 projection (xn), the rotated queries (q), the attention output entering the output projection (att),
 the normalised rows entering the MLP (xn2) and the gated product silu(gate)*up entering the down
-projection (act; gate and up themselves stay fp32 inside the fused kernel).  Keys and values are
-rounded too, but they are cache state and rounded on both sides.  The residual stream and the output
+projection (act; gate and up themselves stay fp32 inside the fused kernel); and the q/k/v product in front of
+the bias and the rotation (qkv), so queries, keys and (with a bias) values are rounded twice.  Keys and values
+as stored are cache state and rounded on both sides.  The residual stream and the output
 projection's product stay fp32.
 
 Rounding the ORACLE's own activations at those points, on the CPU, one point at a time and all
@@ -13,8 +14,8 @@ together, gives the per-rounding budget: each costs a relative rms error of a fe
 residual stream per block, they add in quadrature within a block, and the blocks' errors add in
 quadrature along the stack (about per_block * sqrt(L)).  The GPU parity tests hold stacks of up to
 four blocks to the flat 2e-2 and an L-block stack to max(2e-2, 1e-2 * sqrt(L)); this test keeps
-those figures honest, and shows what a sixth rounding (the output projection's product, which the
-library can be switched to round for measurements) would add.
+those figures honest, with and without the rounding in front of the rotation, and shows what one more (the output
+projection's product, which the library can be switched to round for measurements) would add.
 """
 import dataclasses
 
@@ -31,7 +32,7 @@ def _block(cfg, lw, x0, K, V, pos, slots, vis, rounded=()):
     r = lambda name, a: dec.round_to_bf16(a) if name in rounded else a
     n = x0.shape[0]
     xn = r("xn", dec.rmsnorm(x0, lw["attn_norm"], cfg.rms_eps))
-    qkv = xn @ lw["wqkv"].T
+    qkv = r("qkv", xn @ lw["wqkv"].T)
     q = qkv[:, : cfg.q_dim].reshape(n, cfg.n_q_heads, cfg.head_dim)
     k = qkv[:, cfg.q_dim: cfg.q_dim + cfg.kv_dim].reshape(n, cfg.n_kv_heads, cfg.head_dim)
     v = qkv[:, cfg.q_dim + cfg.kv_dim:].reshape(n, cfg.n_kv_heads, cfg.head_dim)
@@ -98,3 +99,14 @@ def test_per_rounding_budget_of_one_block():
     assert 0.7 * quad < together < 1.3 * quad
     # a sixth rounding is not free, and not dominant either
     assert together < with_oproj < 1.5 * together
+
+
+def test_rounding_in_front_of_the_rotation():
+    """The q/k/v product rounded as well: as large alone as the others, in quadrature with them, and four blocks still inside 2e-2."""
+    s = _setup(n_layers=4)
+    alone = _stack_errors(*s, rounded=("qkv",))[0]
+    five, six = (_stack_errors(*s, rounded=p)[0] for p in (POINTS, POINTS + ("qkv",)))
+    print("qkv alone, after 1..4 blocks:", alone, " five:", five, " with it:", six)
+    assert 2e-4 < alone[0] < 6e-3
+    quad = np.sqrt(alone[0] ** 2 + five[0] ** 2)
+    assert 0.7 * quad < six[0] < 1.3 * quad and six[0] < 1e-2 and six[-1] < 2e-2
