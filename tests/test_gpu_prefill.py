@@ -74,10 +74,11 @@ def test_step_after_prefill_starts_from_the_last_position(dtype, cfg, B, P, monk
     K, pools = 10, []
     for chunkwise in (True, False):
         e, _, _ = make_engine(cfg, dtype, tw, dw, B, 64, 2, K, P + 80, seed=4)
-        if chunkwise:
-            monkeypatch.setattr(e.ctx, "prefill", lambda *a: False)
+        used, real = [], e.ctx.prefill
+        monkeypatch.setattr(e.ctx, "prefill", lambda *a, no=chunkwise: False if no else used.append(real(*a)) or used[-1])
         print(f"step after prefill {dtype} B {B} P {P} chunkwise {chunkwise}", flush=True)
         e.prefill(pr)
+        assert chunkwise or used == [True]
         e.step(K, 1, 4)
         pools.append([x.cpu().numpy() for x in e.ctx.draft_pool(B, 1, K)])
         e.ctx.close()
