@@ -799,27 +799,26 @@ hipError_t gemm_f32_norm_glu(hipStream_t s, int M, int N, int K, const NormIn& n
     return launch_f32_norm<true>(s, M, N, K, n, Wg, Wu, act);
 }
 
-// Few activation rows (M <= 32 * WTM * WGM, one row of tiles): the weights stream through once and nothing else counts.  A
+// Few activation rows (M <= 32, one row of tiles): the weights stream through once and nothing else counts.  A
 // workgroup owns 32 * WTN weight rows (GLU: half of them gate rows, half the matching up rows), WTN being free so
-// that the tiles come out at just under one per CU, and has WGM groups of four waves (two above 64 rows), a group 32 * WTM of
-// the activation rows.  The K steps of 64 go through a ring of S slots (activation rows and
-// weight rows, both by global->LDS loads, S - 1 steps in flight); of a step's four 16-wide slices each wave of a group multiplies
-// one, over the group's rows, so that the group reads a fragment from the LDS once, and its four waves' sums meet in LDS at the end.
+// that the tiles come out at just under one per CU.  The K steps of 64 go through a ring of S slots (activation rows and
+// weight rows, both by global->LDS loads, S - 1 steps in flight); of a step's four 16-wide slices each of the four waves multiplies
+// one, so that a fragment is read from the LDS once, and the four waves' sums meet in LDS at the end.
 // A step's loads are whole 128-byte lines; fetched straight into MFMA operands (64 bytes per row and instruction)
 // the vector-memory front end is the limit instead: 68 us at M = 16 on the gate/up shape below.
-template <int WGM, int WTM, int WTN, int S, int OUT, bool GLU>
-__global__ __launch_bounds__(256 * WGM) void gemm_bf16_few_k(int M, int N, int K, const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
+template <int WTN, int S, int OUT, bool GLU>
+__global__ __launch_bounds__(256) void gemm_bf16_few_k(int M, int N, int K, const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                                                        const uint16_t* __restrict__ W2, void* __restrict__ C, int nbn, int ksplit) {
-    constexpr int NW = 4 * WGM, BM = 32 * WTM * WGM, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
+    constexpr int NW = 4, BM = 32, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
     constexpr int SLOT = (BM + BN) * 64;           // elements per slot: activation rows, then weight rows
     constexpr int LB = (BN / 8 + NW - 1) / NW;     // 1 KB loads per wave and step: weights (a wave's last one may be idle)
-    constexpr int L = WTM + LB;                    // ... and activations
+    constexpr int L = 1 + LB;                      // ... and activations
     constexpr bool kIdle = (BN / 8) % NW != 0;
     static_assert(S >= 3 && (S - 2) * L < 64, "the wait below counts the loads of S - 2 steps");
     static_assert(S * SLOT * 2 >= 4 * 32 * BN * 4, "the ring also holds the four slices' sums of 32 rows");
     extern __shared__ __align__(16) uint16_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l32 = lane & 31, lhi = lane >> 5, slice = wave & 3, wm = wave >> 2;
+    const int l32 = lane & 31, lhi = lane >> 5, slice = wave;
     const int tile = blockIdx.x % nbn, cut = blockIdx.x / nbn, n0 = tile * BNO;
     const int nk = K / 64, kt0 = (int)((int64_t)nk * cut / ksplit), nt = (int)((int64_t)nk * (cut + 1) / ksplit) - kt0;
     auto desc = [&](const uint16_t* base, uint32_t bytes) {   // raw buffer descriptor; rows past its size fetch nothing
@@ -836,14 +835,11 @@ __global__ __launch_bounds__(256 * WGM) void gemm_bf16_few_k(int M, int N, int K
     // load i of a wave covers 8 consecutive tile rows (BNO is a multiple of 8: they are gate rows or up rows as a whole)
     const int r = lane >> 3, c = lane & 7;
     u32x4_t rs_b[LB];
-    uint32_t off_a[WTM], off_b[LB], dst_b[LB];
+    uint32_t off_b[LB], dst_b[LB];
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)lds;
-    const uint32_t lds_a = lds_base + (uint32_t)(wave * WTM) * 1024u;
-#pragma unroll
-    for (int i = 0; i < WTM; ++i) {
-        const int row = (wave * WTM + i) * 8 + r;
-        off_a[i] = ((uint32_t)row * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
-    }
+    const uint32_t lds_a = lds_base + (uint32_t)wave * 1024u;
+    const int row_a = wave * 8 + r;
+    const uint32_t off_a = ((uint32_t)row_a * (uint32_t)K + (c ^ ((row_a >> 1) & 7)) * 8) * 2u;
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
         // (an idle load has an empty descriptor, fetches nothing and aims at a kilobyte behind the ring)
@@ -858,16 +854,13 @@ __global__ __launch_bounds__(256 * WGM) void gemm_bf16_few_k(int M, int N, int K
 #pragma unroll
         for (int i = 0; i < LB; ++i)
             dma_buf_16_nt(rs_b[i], off_b[i], k2, kIdle && i == LB - 1 && wave + i * NW >= BN / 8 ? dst_b[i] : dst_b[i] + so);
-#pragma unroll
-        for (int i = 0; i < WTM; ++i) dma_buf_16(rs_a, off_a[i], k2, lds_a + so + i * 1024u);
+        dma_buf_16(rs_a, off_a, k2, lds_a + so);
     };
-    f32x16_t acc[WTM][WTN];
+    f32x16_t acc[WTN];
 #pragma unroll
-    for (int i = 0; i < WTM; ++i)
+    for (int j = 0; j < WTN; ++j)
 #pragma unroll
-        for (int j = 0; j < WTN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 #pragma unroll
     for (int t = 0; t < S - 1; ++t) fetch(t, t);
     const int frag = l32 * 64 + ((2 * slice + lhi) ^ ((l32 >> 1) & 7)) * 8;   // row l32 of a block, this wave's slice
@@ -880,71 +873,60 @@ __global__ __launch_bounds__(256 * WGM) void gemm_bf16_few_k(int M, int N, int K
         fetch(t + S - 1, slot == 0 ? S - 1 : slot - 1);
         __builtin_amdgcn_sched_barrier(0);
         const uint16_t* p = lds + slot * SLOT + frag;
-        bf16x8_t fa[WTM], fb[WTN];
-#pragma unroll
-        for (int i = 0; i < WTM; ++i) fa[i] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + (wm * WTM + i) * 32 * 64));
+        bf16x8_t fb[WTN];
+        const bf16x8_t fa = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)p);
 #pragma unroll
         for (int j = 0; j < WTN; ++j) fb[j] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + (BM + j * 32) * 64));
 #pragma unroll
-        for (int i = 0; i < WTM; ++i)
-#pragma unroll
-            for (int j = 0; j < WTN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < WTN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa, fb[j], acc[j], 0, 0, 0);
         slot = slot + 1 == S ? 0 : slot + 1;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the repeated fetches at the end as well: the ring is reused below
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    // the four slices' sums of 32 rows at a time: [slice][32][BN], then four columns per thread
+    // the four slices' sums: [slice][32][BN], then four columns per thread
     float* red = (float*)lds;
 #pragma unroll
-    for (int blk = 0; blk < WGM * WTM; ++blk) {
-        const int rows = M - 32 * blk;             // (may be past 32)
-        if (rows <= 0) break;
-        if (blk > 0) __syncthreads();
-        if (wm == blk / WTM) {
+    for (int v = 0; v < 16; ++v) {
+        const int row = 8 * (v >> 2) + 4 * lhi + (v & 3);
+        if (row < M) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = 8 * (v >> 2) + 4 * lhi + (v & 3);
-                if (row < rows) {
-#pragma unroll
-                    for (int j = 0; j < WTN; ++j) red[(slice * 32 + row) * BN + j * 32 + l32] = acc[blk % WTM][j][v];
-                }
-            }
+            for (int j = 0; j < WTN; ++j) red[(slice * 32 + row) * BN + j * 32 + l32] = acc[j][v];
         }
-        __syncthreads();
-        for (int e = threadIdx.x; e < (rows < 32 ? rows : 32) * (BNO / 4); e += 64 * NW) {
-            const int row = e / (BNO / 4), col = (e - row * (BNO / 4)) * 4;
-            if (col >= cols) continue;
-            auto sum4 = [&](int c0) {
-                const float* p = red + row * BN + c0;
-                float4 s = *(const float4*)p;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < M * (BNO / 4); e += 64 * NW) {
+        const int row = e / (BNO / 4), col = (e - row * (BNO / 4)) * 4;
+        if (col >= cols) continue;
+        auto sum4 = [&](int c0) {
+            const float* p = red + row * BN + c0;
+            float4 s = *(const float4*)p;
 #pragma unroll
-                for (int q = 1; q < 4; ++q) {
-                    const float4 o = *(const float4*)(p + q * 32 * BN);
-                    s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
-                }
-                return s;
-            };
-            const float4 g = sum4(col);
-            const int64_t at = (int64_t)(32 * blk + row) * N + n0 + col;
-            if constexpr (GLU) {
-                const float4 u = sum4(BNO + col);
-                auto act = [](float x, float y) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)) * y; };
-                *(uint2*)((bf16*)C + at) = make_uint2(pack_bf16x2(act(g.x, u.x), act(g.y, u.y)), pack_bf16x2(act(g.z, u.z), act(g.w, u.w)));
-            } else {
-                *(float4*)((float*)C + (int64_t)cut * M * N + at) = g;
+            for (int q = 1; q < 4; ++q) {
+                const float4 o = *(const float4*)(p + q * 32 * BN);
+                s.x += o.x; s.y += o.y; s.z += o.z; s.w += o.w;
             }
+            return s;
+        };
+        const float4 g = sum4(col);
+        const int64_t at = (int64_t)row * N + n0 + col;
+        if constexpr (GLU) {
+            const float4 u = sum4(BNO + col);
+            auto act = [](float x, float y) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)) * y; };
+            *(uint2*)((bf16*)C + at) = make_uint2(pack_bf16x2(act(g.x, u.x), act(g.y, u.y)), pack_bf16x2(act(g.z, u.z), act(g.w, u.w)));
+        } else {
+            *(float4*)((float*)C + (int64_t)cut * M * N + at) = g;
         }
     }
 }
 
-template <int WGM, int WTM, int WTN, bool GLU>
+template <int WTN, bool GLU>
 static hipError_t launch_few(hipStream_t s, int M, int N, int K, const void* A, const void* W, const void* W2, void* C, int ksplit = 1) {
-    constexpr int BM = 32 * WTM * WGM, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
+    constexpr int BM = 32, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
     constexpr int kFit = 159 * 1024 / ((BM + BN) * 128), S = kFit < 8 ? kFit : 8;
     constexpr size_t lds = (size_t)S * (BM + BN) * 128 + 1024;
-    auto kern = gemm_bf16_few_k<WGM, WTM, WTN, S, GLU ? OUT_T : OUT_SPLIT_F32, GLU>;
+    auto kern = gemm_bf16_few_k<WTN, S, GLU ? OUT_T : OUT_SPLIT_F32, GLU>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -952,36 +934,25 @@ static hipError_t launch_few(hipStream_t s, int M, int N, int K, const void* A, 
         attr_set = true;
     }
     const int nbn = (N + BNO - 1) / BNO;
-    hipLaunchKernelGGL(kern, dim3(nbn * ksplit), dim3(256 * WGM), lds, s, M, N, K, (const uint16_t*)A, (const uint16_t*)W, (const uint16_t*)W2, C, nbn,
+    hipLaunchKernelGGL(kern, dim3(nbn * ksplit), dim3(256), lds, s, M, N, K, (const uint16_t*)A, (const uint16_t*)W, (const uint16_t*)W2, C, nbn,
                        ksplit);
     return hipGetLastError();
 }
 
-// Gate/up at up to 128 rows: the tile's weight rows in blocks of 32, the fewest that leave at most one workgroup per CU (in
+// Gate/up at up to 32 rows: the tile's weight rows in blocks of 32, the fewest that leave at most one workgroup per CU (in
 // two rounds the second one's CUs are idle half of the time).  0: the tiled launches below take the product.
 // Against those (us, best of three alternating runs on cold weights): N 18944, K 3584 (237 tiles of 80 columns): M = 1 59.0 ->
-// 42.9 (6.3 TB/s), M = 64 64.0 -> 47.7, M = 128 63.0 -> 56.9; N 27648, K 5120 (247 of 112): M = 1 90.7 -> 84.0, M = 64 101.8 ->
-// 90.7; N 11008, K 4096: M = 1 40.0 -> 35.0; N 4864, K 896: M = 1 10.6 -> 7.3, M = 64 11.3 -> 9.6.
-// Up to 64 rows, four blocks are the width of the 128x128 tiles, which then run one per CU with three slots and are the better
-// ones (N 14336, K 4096: 45.5 against 46.5); eight leave too few slots (N 32768, K 8192: 169 against 197).  Above 64
-// rows, the narrow widths lose to 128x128 tiles (N 8960, K 1536, M = 100: 19.3 against 21.5), and more than
-// six do not fit the registers.
-// The four slices' sums meet in LDS, 32 rows at a time, which few K steps do not pay for: the more rows and the wider the tile, the
-// longer K has to be (us, this kernel and the tiled one on the same buffers: M 128, N 18944: K 512 17.8 and 14.5, K 2048 40.9
-// and 40.0, K 3584 56.3 and 63.2; M 64, N 11008: K 512 9.8 and 9.3, K 1024 even, K 2048 23.8 and 24.0; M 64, N 28672: K 2048 56.2 and
-// 52.4, K 3584 67.5 and 71.7; two blocks, or up to 32 rows and six, gain from K = 256 on).
+// 42.9 (6.3 TB/s); N 27648, K 5120 (247 of 112): M = 1 90.7 -> 84.0; N 11008, K 4096: M = 1 40.0 -> 35.0; N 4864, K 896: M = 1 10.6 -> 7.3.
+// Four blocks are the width of the 64x128 tiles, which then run one per CU and are the better ones (N 14336, K 4096: 45.5 against 46.5); eight
+// leave too few slots (N 32768, K 8192: 169 against 197), and seven need a K that pays for the sums of the four slices.
 static int few_glu_width(int M, int N, int K) {
     int wtn = 2;
     while ((N + 16 * wtn - 1) / (16 * wtn) > 256) ++wtn;
-    if (M > 128 || wtn > 7 || (M <= 64 ? wtn == 4 : wtn < 4 || wtn > 6)) return 0;
-    const int k_min = M <= 32 ? (wtn < 7 ? 0 : 512) : M <= 64 ? (wtn == 2 ? 0 : wtn < 7 ? 1024 : 2560) : (wtn == 4 ? 512 : 2560);
-    return K < k_min ? 0 : wtn;
+    return M > 32 || wtn > 7 || wtn == 4 || (wtn == 7 && K < 512) ? 0 : wtn;
 }
 static hipError_t launch_few_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* W, const void* W2, void* C) {
-#define TLT_FEW(g, m, n) if (M <= 32 * g * m && wtn == n) return launch_few<g, m, n, true>(s, M, N, K, A, W, W2, C);
-    TLT_FEW(1, 1, 2) TLT_FEW(1, 1, 3) TLT_FEW(1, 1, 5) TLT_FEW(1, 1, 6) TLT_FEW(1, 1, 7)
-    TLT_FEW(1, 2, 2) TLT_FEW(1, 2, 3) TLT_FEW(1, 2, 5) TLT_FEW(1, 2, 6) TLT_FEW(1, 2, 7)
-    TLT_FEW(2, 2, 4) TLT_FEW(2, 2, 5) TLT_FEW(2, 2, 6)
+#define TLT_FEW(n) if (wtn == n) return launch_few<n, true>(s, M, N, K, A, W, W2, C);
+    TLT_FEW(2) TLT_FEW(3) TLT_FEW(5) TLT_FEW(6) TLT_FEW(7)
 #undef TLT_FEW
     return hipErrorInvalidValue;
 }
@@ -1010,6 +981,202 @@ static int few_split_plan(int N, int K, int general_cuts, int max_cuts, int* cut
     const int apart = *cuts * 2048;
     if (N > 2048 && K % apart == 0 && (best > 2 || (K / apart) % 2 != 0)) return 0;
     return best;
+}
+
+// Gate/up at 33 to 256 rows.  A wave owns 32 activation rows and the whole width of the tile, so a workgroup has as many waves (2 to 8) as the rows
+// fill and no matrix product is spent on padding beyond the last 32; the tile is as wide as leaves at most one workgroup per CU (32 * WTN
+// weight rows: 16 gate and the matching 16 up rows in turns, as the mixed tiles of gemm_bf16_pipe_k).  A K step's four 16-wide slices run as there:
+// the fragments of the next slice are read under a slice's products, the last slice's products run behind the barrier that publishes the next step,
+// and the step's loads (weights first) are dealt out behind the products, S - 1 steps ahead.
+// What bounds it: every byte, cold weights and the activation rows that each workgroup takes from L2 alike, comes through the CU's load path at
+// about 57 GB/s at 2.4 GHz (a load-only kernel with these loads: 40.7 us at 32 rows, 44.8 at 96, 49.6 at 192, 52.2 at 256 for N 18944, K 3584), and the
+// chip holds 1.6 to 2 GHz here under its power limit: what is saved is padding (128- and 256-row tiles) and the sums of four slices in
+// LDS (gemm_bf16_few_k).  Dispatch and measurements: mid_glu_width.
+template <int NW, int WTN, int S>
+__global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
+                                                           const uint16_t* __restrict__ W2, bf16* __restrict__ C, int per_xcd) {
+    constexpr int BM = 32 * NW, BN = 32 * WTN, BNO = BN / 2;
+    constexpr int SLOT = (BM + BN) * 64;           // elements per slot: activation rows, then weight rows
+    constexpr int LA = 4, LB = (BN / 8 + NW - 1) / NW, L = LA + LB;   // 1 KB loads per wave and step (a wave's last weight load may be idle)
+    constexpr bool kIdle = (BN / 8) % NW != 0;
+    extern __shared__ __align__(16) uint16_t lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, lhi = lane >> 5;
+    // (an XCD's workgroups own neighbouring columns: the lines that two tiles share are completed in its L2)
+    const int n0 = ((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3)) * BNO, nt = K / 64;
+    if (n0 >= N) return;
+    auto desc = [&](const uint16_t* base, uint32_t bytes) {   // raw buffer descriptor; rows past its size fetch nothing
+        const uint64_t p = (uint64_t)(uintptr_t)base;
+        u32x4_t d;
+        d[0] = __builtin_amdgcn_readfirstlane((uint32_t)p);
+        d[1] = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32) & 0xffffu);
+        d[2] = __builtin_amdgcn_readfirstlane(bytes);
+        d[3] = 0x00020000u;
+        return d;
+    };
+    const int cols = N - n0 < BNO ? N - n0 : BNO;
+    const u32x4_t rs_a = desc(A, (uint32_t)M * (uint32_t)K * 2u);
+    const int r = lane >> 3, c = lane & 7;
+    u32x4_t rs_b[LB];
+    uint32_t off_a[LA], off_b[LB], dst_b[LB];
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)lds;
+    const uint32_t lds_a = lds_base + (uint32_t)(wave * LA) * 1024u;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int row = (wave * LA + i) * 8 + r;
+        off_a[i] = ((uint32_t)row * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        // (an idle load has an empty descriptor, fetches nothing and aims at a kilobyte behind the ring)
+        const int row0 = (i * NW + wave) * 8, row = row0 + r;
+        const bool on = !kIdle || row0 < BN, up = row0 >= BNO;
+        rs_b[i] = desc((up ? W2 : W) + (int64_t)n0 * K, on ? (uint32_t)cols * (uint32_t)K * 2u : 0u);
+        off_b[i] = ((uint32_t)(up ? row - BNO : row) * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
+        dst_b[i] = lds_base + (on ? (uint32_t)(BM * 128 + row0 * 128) : (uint32_t)(S * SLOT * 2));
+    }
+    // load i of step t (past the end: the last step again, so that the wait counts hold), weights first
+    auto load = [&](int i, uint32_t k2, uint32_t so) {
+        if (i < LB) {
+            const uint32_t dst = kIdle && i == LB - 1 && wave + i * NW >= BN / 8 ? dst_b[i] : dst_b[i] + so;
+            dma_buf_16_nt(rs_b[i], off_b[i], k2, dst);
+        } else {
+            dma_buf_16(rs_a, off_a[i - LB], k2, lds_a + so + (i - LB) * 1024u);
+        }
+    };
+    auto koff = [&](int t) { return (uint32_t)(t < nt ? t : nt - 1) * 128u; };
+    f32x16_t acc[WTN];
+#pragma unroll
+    for (int j = 0; j < WTN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    constexpr int Q3 = (L + 3) / 4;                // loads issued under slice 3; the rest under slices 0 .. 2 of the next step
+    static_assert(S >= 3 && (S - 2) * L + Q3 < 64, "what the waits below count");
+#pragma unroll
+    for (int t = 0; t < S - 1; ++t)
+#pragma unroll
+        for (int i = 0; i < L; ++i) load(i, koff(t), (uint32_t)t * (SLOT * 2));
+#pragma unroll
+    for (int i = 0; i < Q3; ++i) load(i, koff(S - 1), (uint32_t)(S - 1) * (SLOT * 2));
+    const int sw = (l32 >> 1) & 7;
+    const int fragA = (wave * 32 + l32) * 64;
+    const int fragB = ((l32 & 15) + (l32 >> 4) * BNO) * 64;   // 16 gate rows and the 16 up rows that belong to them
+    bf16x8_t fa[2], fb[2][WTN];
+    auto read = [&](int buf, const uint16_t* p, int kk) {
+        const int ch = ((2 * kk + lhi) ^ sw) * 8;
+        fa[buf] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + fragA + ch));
+#pragma unroll
+        for (int j = 0; j < WTN; ++j)
+            fb[buf][j] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + BM * 64 + fragB + j * 16 * 64 + ch));
+    };
+    auto mul = [&](int buf) {
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf], fb[buf][j], acc[j], 0, 0, 0);
+    };
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * L + Q3));   // step 0 has landed
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    read(0, lds, 0);
+    int slot = 0, before = S - 1;                  // this step's slot; the one whose refill is under way
+    for (int t = 0; t < nt; ++t) {
+        const uint16_t* p = lds + slot * SLOT;
+        const int next = slot + 1 == S ? 0 : slot + 1;
+        const uint32_t k2 = koff(t + S - 1), so = (uint32_t)before * (SLOT * 2);
+#pragma unroll
+        for (int kk = 0; kk < 3; ++kk) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            read((kk + 1) & 1, p, kk + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(kk & 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = Q3 + kk * (L - Q3) / 3; i < Q3 + (kk + 1) * (L - Q3) / 3; ++i) load(i, k2, so);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * L));   // step t + 1 has landed
+        __builtin_amdgcn_s_barrier();                         // ... for every wave; this step's slot is free
+        __builtin_amdgcn_sched_barrier(0);
+        read(0, lds + next * SLOT, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        mul(1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < Q3; ++i) load(i, koff(t + S), (uint32_t)slot * (SLOT * 2));
+        __builtin_amdgcn_sched_barrier(0);
+        before = slot;
+        slot = next;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the repeated fetches at the end as well, before the LDS is released
+    // (as the mixed tiles of gemm_bf16_pipe_k: gate and up of a column lie in lanes l and l + 16 of a half-wave)
+    const int row0 = wave * 32 + 4 * lhi, odd16 = (l32 >> 4) & 1, odd = lane & 1;
+#pragma unroll
+    for (int j = 0; j < WTN; ++j)
+#pragma unroll
+        for (int vq = 0; vq < 4; ++vq) {
+            float x[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[j][4 * vq + 2 * e]), __float_as_uint(acc[j][4 * vq + 2 * e + 1]), false, false);
+                const float g = __uint_as_float(q[0]), u = __uint_as_float(q[1]);
+                x[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
+            }
+            const float other = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(odd ? x[0] : x[1]), 0xB1, 0xF, 0xF, false));
+            const uint32_t out = odd ? pack_bf16x2(other, x[1]) : pack_bf16x2(x[0], other);
+            const int row = row0 + 8 * vq + 2 * odd + odd16, col0 = j * 16;
+            if (row < M && col0 < cols) *(uint32_t*)(C + (int64_t)row * N + n0 + col0 + (l32 & 14)) = out;
+        }
+}
+
+template <int NW, int WTN>
+static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
+    constexpr int kSlot = (32 * NW + 32 * WTN) * 128, kFit = 159 * 1024 / kSlot, S = kFit < 6 ? kFit : 6;
+    constexpr size_t lds = (size_t)S * kSlot + 1024;
+    auto kern = gemm_bf16_mid_k<NW, WTN, S>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const int per_xcd = ((N + 16 * WTN - 1) / (16 * WTN) + 7) / 8;
+    hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(64 * NW), lds, s, M, N, K, (const uint16_t*)A, (const uint16_t*)Wg, (const uint16_t*)Wu, (bf16*)act, per_xcd);
+    return hipGetLastError();
+}
+
+// Width of gemm_bf16_mid_k's tiles in blocks of 16 gate and 16 up rows: the fewest that leave at most one workgroup per CU; 0: another kernel.
+// Limits measured against the kernels that ran before (us per call, p10 of 40 calls, cold weights, activations rewritten before every call,
+// about 4 us of event overhead in both figures):
+//   rows            40         64         72         128        160        192        224        256
+//   18944 x 3584    -          -          52.7/49.4  59.6/54.8  66.4/59.4  69.3/65.0  72.3/68.4  74.0/73.3   (5 blocks)
+//   27648 x 5120    -          -          96.0/91.7  104/101    127/110    128/124    133/154    138/157     (7)
+//   24576 x 6144    96.3/96.0  98.8/97.5  101/98     108/105    141/111    142/119    145/126    145/165     (6)
+//   13824 x 5120    -          -          61.8/58.2  72.2/66.4  84.0/74.2  84.2/74.5  86.7/79.5  87.4/81.6   (4)
+//   11008 x 4096    -          -          42.0/36.9  47.9/43.3  64.9/50.0  68.2/53.2  73.6/55.8  79.0/59.3   (3)
+//   8192 x 4096     29.0/26.0  30.3/28.7  41.6/29.1  45.8/35.4  41.3/40.7  42.6/45.3  44.1/48.0  46.5/49.0   (2)
+// Wide tiles with many rows have two slots only and lose; two blocks leave half of the chip idle.  At five blocks 256 rows are even alone and 2 %
+// slower in a step (eight waves draw more power than four of 64 rows).  With K below 1024 the wide ones still gain (18944 x 512, 128 rows: 16.8 ->
+// 15.3), the narrow ones above 128 rows (11008 x 512: 160 rows 16.0 -> 13.6) and up to 64 rows two blocks (4864 x 896: 15.9 -> 15.0).
+static int mid_glu_width(int M, int N, int K) {
+    int wtn = 2;
+    while ((N + 16 * wtn - 1) / (16 * wtn) > 256) ++wtn;
+    const int rows = wtn == 2 ? 128 : wtn <= 4 ? 256 : wtn <= 6 ? 224 : 192;
+    const int k_min = wtn >= 5 || (wtn == 2 && M <= 64) ? 64 : (wtn == 4 && M > 64) || M > 128 ? 512 : 1024;
+    return wtn <= 7 && M > 32 && M <= rows && K >= k_min ? wtn : 0;
+}
+static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
+#define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n>(s, M, N, K, A, Wg, Wu, act);
+    TLT_MID(2, 2) TLT_MID(2, 3) TLT_MID(2, 4) TLT_MID(2, 5) TLT_MID(2, 6) TLT_MID(2, 7)
+    TLT_MID(3, 2) TLT_MID(3, 3) TLT_MID(3, 4) TLT_MID(3, 5) TLT_MID(3, 6) TLT_MID(3, 7)
+    TLT_MID(4, 2) TLT_MID(4, 3) TLT_MID(4, 4) TLT_MID(4, 5) TLT_MID(4, 6) TLT_MID(4, 7)
+    TLT_MID(5, 3) TLT_MID(5, 4) TLT_MID(5, 5) TLT_MID(5, 6) TLT_MID(5, 7)
+    TLT_MID(6, 3) TLT_MID(6, 4) TLT_MID(6, 5) TLT_MID(6, 6) TLT_MID(6, 7)
+    TLT_MID(7, 3) TLT_MID(7, 4) TLT_MID(7, 5) TLT_MID(7, 6)
+    TLT_MID(8, 3) TLT_MID(8, 4)
+#undef TLT_MID
+    return hipErrorInvalidValue;
 }
 
 template <int WGM, int WGN, int WTM, int WTN, int SA, int SB, bool GLU = false, bool NTW = false>
@@ -1304,9 +1471,9 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
             int cuts = 1;
             const int wtn = few_split_plan(N, K, sp.ks, room > 12 ? 12 : (int)room, &cuts);
             if (wtn != 0) *n_parts = cuts;
-            if (wtn == 2) return launch_few<1, 1, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-            if (wtn == 3) return launch_few<1, 1, 3, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-            if (wtn == 4) return launch_few<1, 1, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+            if (wtn == 2) return launch_few<2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+            if (wtn == 3) return launch_few<3, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+            if (wtn == 4) return launch_few<4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
         }
         if (sp.kind != 0 && (size_t)sp.ks * M * N * 4 <= parts_bytes) {
             *n_parts = sp.ks;
@@ -1419,6 +1586,7 @@ bool gemm_glu_supported(int dtype, int M, int N, int K, const void* A, const voi
 // act[M][N] = silu(A Wg^T) * (A Wu^T), dtype in and out; call only when gemm_glu_supported().
 hipError_t gemm_glu(hipStream_t s, int dtype, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
     if (dtype == F32) return launch_f32_few(s, OUT_F32, M, N, K, A, Wg, Wu, act);
+    if (const int wtn = mid_glu_width(M, N, K)) return launch_mid_glu(s, wtn, M, N, K, A, Wg, Wu, act);
     if (const int wtn = few_glu_width(M, N, K)) return launch_few_glu(s, wtn, M, N, K, A, Wg, Wu, act);
     return launch_tiled(s, OUT_T, M, N, K, A, Wg, Wu, act, true);
 }

@@ -1,0 +1,36 @@
+"""Products of 33 to 256 activation rows at the edges of their tiles: 32 rows per wave, two to eight waves, tiles of every width."""
+import pytest
+import torch
+
+from paper_2511_16665_amd import binding as tlt
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (33, 8192, 64), (64, 640, 1024), (65, 8192, 1024), (128, 128, 1088),        # two blocks of 16 columns; one K step, fewer than the ring has slots
+    (63, 8320, 1024), (97, 12288, 1088), (129, 8320, 512), (256, 12288, 576),   # three: partial and whole last tiles
+    (40, 12416, 1024), (96, 16384, 512), (161, 16384, 640), (225, 12416, 512),  # four
+    (34, 20480, 64), (66, 16512, 128), (160, 16512, 64), (193, 18944, 320),     # five
+    (224, 20480, 192), (65, 20608, 64), (192, 24576, 128), (224, 20608, 448),   # five, six
+    (64, 24704, 64), (127, 28672, 192), (130, 24704, 128), (192, 28672, 64),    # seven
+    (257, 16512, 128), (225, 16512, 128), (193, 28672, 64), (32, 16512, 64),    # beside the ranges
+])
+def test_bf16_gate_up(M, N, K):
+    """The same bits as the first rows of a product of 300 rows (all tiles add up K in one order); 32 rows take four sums and round differently."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((300, K), generator=g, device="cuda").bfloat16()
+    W, U = ((torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16() for _ in range(2))
+    act = torch.full((M + 1, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    want = torch.empty((300, N), dtype=torch.bfloat16, device="cuda")
+    print(f"gate/up M={M} N={N} K={K} and 300 rows", flush=True)
+    assert tlt.gemm_glu(A[:M].contiguous(), W, U, act) == 0
+    assert tlt.gemm_glu(A, W, U, want) == 0
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(act[M]).all())   # nothing behind the last row
+    if M > 32:
+        assert torch.equal(act[:M], want[:M])
+    else:   # sums of K products in fp32 in another order (2^-24 each), one rounding to bf16 (2^-8) of either result
+        gate, up = (A[:M].double() @ x.double().T for x in (W, U))
+        err = (K + 2) * 2.0 ** -24 * (A[:M].double().abs() @ (W.double().abs() + U.double().abs()).T) * (1.1 * up.abs() + gate.abs() + 1)
+        assert bool(((act[:M].double() - want[:M].double()).abs() <= 2 * err + 2.0 ** -7 * want[:M].double().abs() + 1e-30).all())
