@@ -301,9 +301,12 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
     } else if ((rc = norm_x(ctx, s, M, w.attn_norm, ws + p.xn))) {
         return rc;
     }
+    // few rows per sequence in fp32 mode: the attention kernel rotates them and writes them to the cache
+    const bool own_rope = !wanted && attention_rope_supported(dt, rows, kv, ws + p.qkv, w.bqkv);
     if (own_norm) {
-        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * e * 2,
-                rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer));
+        if (!own_rope)
+            TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * e * 2,
+                    rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer));
     } else if (dt == TLT_BF16 && qkv_dim % 128 == 0 && (size_t)M * qkv_dim * 4 * 2 <= p.parts_bytes &&
         (M <= 256 || gemm_parts_pays(dt, M, qkv_dim, h))) {
         // too few tiles for the chip unless the projection is cut along K, which leaves fp32 partial products;
@@ -314,8 +317,9 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
                 rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer, parts, n_parts));
     } else {
         if ((rc = run_gemm(ctx, s, OUT_T, M, qkv_dim, h, ws + p.xn, w.wqkv, ws + p.qkv))) return rc;
-        TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * e * 2,
-                rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer));
+        if (!own_rope)
+            TLT_RUN(ctx, s, CLS_OTHER, 0, (double)M * qkv_dim * e * 2,
+                    rope_kv_write(s, dt, rows, kv, ws + p.qkv, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer));
     }
     if (wanted && wanted->B == 0) {
         ctx->pending_parts = 0;
@@ -329,8 +333,9 @@ int layer_forward(tlt_ctx* ctx, hipStream_t s, const tlt_layer_weights& w, const
         const double bytes = keys * 2.0 * c.n_kv_heads * c.head_dim * e + 2.0 * M * q_dim * e;
         const double flops = 4.0 * c.head_dim * c.n_q_heads * (double)rows.n * keys;
         TLT_RUN(ctx, s, ctx->in_draft ? CLS_ATTN_DRAFT : CLS_ATTN, flops, bytes,
-                attention(s, dt, rows, kv, ws + p.qkv, ws + p.att, c.n_q_heads, ws + p.attn_ws, p.attn_ws_bytes, ctx->attn_impl,
-                          later_layer, ctx->status_ready ? status_word(ctx) : nullptr));
+                own_rope ? attention_rope(s, rows, kv, ws + p.qkv, ws + p.att, c.n_q_heads, c.rope_theta, w.bqkv, tab, later_layer)
+                         : attention(s, dt, rows, kv, ws + p.qkv, ws + p.att, c.n_q_heads, ws + p.attn_ws, p.attn_ws_bytes, ctx->attn_impl,
+                                     later_layer, ctx->status_ready ? status_word(ctx) : nullptr));
     }
     if (wanted) {
         // the wanted rows of the stream to its front (by way of xn: source and destination rows may meet), those of the attention to where
@@ -769,6 +774,7 @@ int tlt_prefill(tlt_ctx* ctx, void* stream, int B, int n_tokens, int chunk, cons
         rows.n_valid = pass.n_valid;
         rows.pos_stride = 1;
         rows.n_region = m;
+        rows.shared_ctx = Cp > 1;
         for (int l = 0; l < c.n_layers; ++l)
             if ((rc = layer_forward(ctx, s, ctx->target.layers[l], rows, kv_layer(ctx, &vt, l), l > 0))) return rc;
         if ((rc = fold_pending(ctx, s, M))) return rc;

@@ -17,6 +17,7 @@
 namespace tlt {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;   // 16-byte register vector
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 constexpr int kRowWaves = 4;   // waves of impl 0's workgroup (64 * kRowWaves covers the largest head_dim)
 
 __device__ __forceinline__ bool region_visible(const Rows& rows, int r, int i, int j) {
@@ -140,6 +141,173 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows,
     o[threadIdx.x] = from_float<T>(ll > 0.f ? a / ll : 0.f);
 }
 
+// impl 0 on rows that the projection has just left (fp32, few rows per sequence): the rotation and the write of the new keys and values, a kernel of
+// their own otherwise, belong to this one.  Every workgroup rotates its query and its kv head's n new keys into LDS (n * d / 2 <= 256: an angle per
+// thread) and takes the new rows from there; the first query head of each kv head also leaves row i's key and value in the cache, which
+// nobody reads in this launch.  A tiny decoder's step is as long as its launches are many (2.4 us of the host each), and the chain of this one is two
+// loads long: lengths, block table and projection together, then keys and values together.  Sums and their order are those of the two kernels.
+__global__ __launch_bounds__(64 * kRowWaves) void attn_rope_rows_k(Rows rows, KVLayer kv, const float* __restrict__ qkv, float* __restrict__ out,
+                                                                   int n_q_heads, float scale, const float* __restrict__ bias, float theta, RopeTable tab,
+                                                                   bool from_table) {
+    constexpr int VEC = 4, kU = 16;
+    __shared__ __align__(16) float q_s[256], k_s[512 + 4 * 8], v_s[512], o_s[kRowWaves][4][256];
+    __shared__ float m_s[kRowWaves], l_s[kRowWaves], p_s[kRowWaves][64];
+    __shared__ const float* v_at[kRowWaves][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = blockIdx.x, hq = blockIdx.y, b = blockIdx.z, n = rows.n, r = b * n + i;
+    const int d = kv.d, half = d >> 1, n_kv = kv.n_kv, G = n_q_heads / n_kv, kh = hq / G;
+    const int qkv_dim = (n_q_heads + 2 * n_kv) * d;
+    float* o = out + ((int64_t)r * n_q_heads + hq) * d;
+    // everything that depends on no other load, requested together: the wave's first block-table entries among it
+    const int ctx = kv.seq_len[b];
+    const int nv = rows.n_valid ? rows.n_valid[b] : n;
+    auto page_of = [&](int slot) {   // -1: no page
+        const int lp = slot / kv.page_size;
+        const int pg = slot >= 0 && lp < kv.max_pages ? kv.block_table[(int64_t)b * kv.max_pages + lp] : -1;
+        return pg >= 0 && pg < kv.n_pages ? pg : -1;
+    };
+    const int pg_first = page_of(64 * wave + lane);
+    const int j = (int)threadIdx.x / half, p = (int)threadIdx.x - j * half;   // this thread's new row and pair
+    const bool on = j < n;
+    float k_lo = 0.f, k_hi = 0.f, v_lo = 0.f, v_hi = 0.f, q_lo = 0.f, q_hi = 0.f;
+    if (on) {
+        const float* row = qkv + (int64_t)(b * n + j) * qkv_dim;
+        const int ko = (n_q_heads + kh) * d + p, vo = (n_q_heads + n_kv + kh) * d + p, qo = hq * d + p;
+        k_lo = row[ko], k_hi = row[ko + half], v_lo = row[vo], v_hi = row[vo + half];
+        if (j == i) q_lo = row[qo], q_hi = row[qo + half];
+        if (bias) {
+            k_lo += bias[ko], k_hi += bias[ko + half], v_lo += bias[vo], v_hi += bias[vo + half];
+            if (j == i) q_lo += bias[qo], q_hi += bias[qo + half];
+        }
+    }
+    if (i >= nv) {   // (uniform: the row is not active)
+        if ((int)threadIdx.x < d) o[threadIdx.x] = 0.f;
+        return;
+    }
+    if (on) {
+        float c, sn;
+        const int64_t t = (int64_t)(b * n + j) * d + p;
+        if (from_table) {
+            c = tab.cs[t], sn = tab.cs[t + half];
+        } else {
+            const int pos = ctx + rows.pos_base + (rows.pos_off ? rows.pos_off[b * n + j] : rows.pos_stride * j);
+            double s64, c64;
+            sincos((double)pos * pow((double)theta, -2.0 * (double)p / (double)d), &s64, &c64);
+            c = (float)c64, sn = (float)s64;
+            if (tab.cs && hq == 0 && j == i) tab.cs[t] = c, tab.cs[t + half] = sn;
+        }
+        const float kl = k_lo * c - k_hi * sn, kr = k_hi * c + k_lo * sn;
+        k_s[j * (d + 4) + p] = kl, k_s[j * (d + 4) + half + p] = kr;
+        v_s[j * d + p] = v_lo, v_s[j * d + half + p] = v_hi;
+        if (j == i) {
+            q_s[p] = (q_lo * c - q_hi * sn) * scale, q_s[half + p] = (q_hi * c + q_lo * sn) * scale;
+            if (hq == kh * G) {
+                const int slot = ctx + rows.slot_base + i, pg = page_of(slot);
+                if (pg >= 0) {
+                    const int64_t at = (((int64_t)pg * n_kv + kh) * kv.page_size + slot % kv.page_size) * d + p;
+                    ((float*)kv.k)[at] = kl, ((float*)kv.k)[at + half] = kr;
+                    ((float*)kv.v)[at] = v_lo, ((float*)kv.v)[at + half] = v_hi;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int total = ctx + rows.n_region, first_new = ctx + rows.slot_base;
+    const int lpk = d / VEC, groups = 64 / lpk, grp = lane / lpk, piece = (lane - grp * lpk) * VEC;
+    float m = -INFINITY, l = 0.f;
+    float acc[VEC] = {0.f, 0.f, 0.f, 0.f};
+    for (int t0 = 64 * wave; t0 < total; t0 += 64 * kRowWaves) {
+        const int key = t0 + lane;
+        const int pg = t0 == 64 * wave ? pg_first : page_of(key);
+        const bool vis = key < total && pg >= 0 && (key < ctx || region_visible(rows, r, i, key - ctx));
+        const int64_t base = vis ? (((int64_t)pg * n_kv + kh) * kv.page_size + key % kv.page_size) * d : 0;   // (row 0 of the pool: its weight below is zero)
+        const bool fresh = vis && key >= first_new;
+        const float* kp = fresh ? k_s + (key - first_new) * (d + 4) : (const float*)kv.k + base;
+        v_at[wave][lane] = fresh ? v_s + (key - first_new) * d : (const float*)kv.v + base;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
+        __builtin_amdgcn_wave_barrier();
+        const int nk = min(64, total - t0);
+        f32x4_t vv[kU];
+        auto fetch_values = [&](int k0) {   // kU rows of every lane group
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int k = k0 + u * groups + grp;
+                vv[u] = *(const f32x4_t*)(v_at[wave][k < 64 && grp < groups ? k : 0] + (grp < groups ? piece : 0));
+            }
+        };
+        float s = 0.f;
+        for (int c0 = 0; c0 < d; c0 += 64) {   // (a key's 64 elements requested together, and the first values with the first of them)
+            f32x4_t kk[64 / VEC];
+#pragma unroll
+            for (int c = 0; c < 64 / VEC; ++c) kk[c] = *(const f32x4_t*)(kp + c0 + c * VEC);
+            if (c0 == 0) fetch_values(0);
+#pragma unroll
+            for (int c = 0; c < 64 / VEC; ++c)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) s = fmaf(q_s[c0 + c * VEC + e], kk[c][e], s);
+        }
+        if (!vis) s = -INFINITY;
+        const float m_new = fmaxf(m, wave_max(s));
+        if (m_new == -INFINITY) continue;  // nothing visible so far (uniform across the wave)
+        const float corr = expf(m - m_new);      // exp(-inf) = 0 on the first visible tile
+        const float w = vis ? expf(s - m_new) : 0.f;
+        l = l * corr + wave_sum(w);
+        m = m_new;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e] *= corr;
+        p_s[wave][lane] = w;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int k0 = 0; k0 < nk; k0 += kU * groups) {
+            if (k0 > 0) fetch_values(k0);
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const int k = k0 + u * groups + grp;
+                const float pk = k < 64 && grp < groups ? p_s[wave][k] : 0.f;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[e] = pk != 0.f ? fmaf(pk, vv[u][e], acc[e]) : acc[e];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    // the partial results, merged in wave and group order
+    if (grp < groups)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o_s[wave][grp][piece + e] = acc[e];
+    if (lane == 0) {
+        m_s[wave] = m;
+        l_s[wave] = l;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x >= d) return;
+    float mm = m_s[0];
+#pragma unroll
+    for (int w = 1; w < kRowWaves; ++w) mm = fmaxf(mm, m_s[w]);
+    float ll = 0.f, a = 0.f;
+#pragma unroll
+    for (int w = 0; w < kRowWaves; ++w) {
+        const float f = m_s[w] == -INFINITY ? 0.f : expf(m_s[w] - mm);
+        ll += f * l_s[w];
+        float o_w = 0.f;
+        for (int g = 0; g < groups; ++g) o_w += o_s[w][g][threadIdx.x];
+        a += f * o_w;
+    }
+    o[threadIdx.x] = ll > 0.f ? a / ll : 0.f;
+}
+
+bool attention_rope_supported(int dtype, const Rows& rows, const KVLayer& kv, const void* qkv, const void* bias) {
+    return dtype == F32 && !rows.shared_ctx && kv.d % 64 == 0 && kv.d <= 256 && rows.n * (kv.d / 2) <= 64 * kRowWaves &&
+           rows.n_region == rows.slot_base + rows.n && (((uintptr_t)qkv | (uintptr_t)kv.k | (uintptr_t)kv.v | (uintptr_t)bias) & 15) == 0;
+}
+
+hipError_t attention_rope(hipStream_t s, const Rows& rows, const KVLayer& kv, const void* qkv, void* out, int n_q_heads, float theta, const void* bias,
+                          const RopeTable& tab, bool from_table) {
+    if (rows.B * rows.n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(attn_rope_rows_k, dim3(rows.n, n_q_heads, rows.B), dim3(64 * kRowWaves), 0, s, rows, kv, (const float*)qkv, (float*)out, n_q_heads,
+                       1.0f / sqrtf((float)kv.d), (const float*)bias, theta, tab, from_table);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------------------------------------
 // impl 1 ("MFMA split-KV"), bf16, head_dim 128.
 //
@@ -163,7 +331,6 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_wave_per_row_k(Rows rows,
 // Each workgroup writes unnormalised partial outputs with their running max and sum (fp32); a
 // second kernel merges the chunks.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // max over the four 16-lane groups of a wave (lanes l, l^16, l^32, l^48) without going through the LDS
 // crossbar: v_permlane32_swap / v_permlane16_swap exchange half-waves / odd and even 16-lane rows of

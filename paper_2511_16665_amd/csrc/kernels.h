@@ -30,6 +30,7 @@ struct Rows {
     const uint64_t* mask = nullptr;
     int mask_words = 1;
     int n_region = 0;
+    bool shared_ctx = false;   // some sequence's context holds rows of another one of this launch (chunks of a prompt)
 };
 
 struct KVLayer {
@@ -149,6 +150,12 @@ size_t attention_workspace_bytes(int B, int n, int n_q_heads, int n_kv_heads, in
 hipError_t attention(hipStream_t s, int dtype, const Rows& rows, const KVLayer& kv, const void* qkv, void* out,
                      int n_q_heads, void* ws, size_t ws_bytes, int impl, bool reuse_plan = false,
                      unsigned int* status = nullptr);
+
+// The attention of rows whose projection qkv [B * n][(Hq + 2 Hkv) * d] has neither been rotated nor written to the cache: both are done on the way (see
+// rope_kv_write; of its table only the angles are kept).  Call only when attention_rope_supported().
+bool attention_rope_supported(int dtype, const Rows& rows, const KVLayer& kv, const void* qkv, const void* bias);
+hipError_t attention_rope(hipStream_t s, const Rows& rows, const KVLayer& kv, const void* qkv, void* out, int n_q_heads, float theta, const void* bias,
+                          const RopeTable& tab, bool from_table);
 
 // ---- sample.hip
 // (scratch, may be null: 8-byte aligned device memory the call may use, M * 256 bytes at most, to spread few rows over the chip)
