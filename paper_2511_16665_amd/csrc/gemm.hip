@@ -229,7 +229,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
     // load cursors: the next K tile each operand fetches, in the order the compute side consumes them
     // (descriptor, absolute K tile index, end of the tile's K range).  When a cursor reaches the end of
     // its tile it jumps to the `next` triple, which the compute loop points at its following tile, or,
-    // after the last one, back at the last K tile (harmless re-fetches keep the schedule uniform).  All
+    // after the last one, at an empty descriptor (loads that fetch nothing keep the schedule uniform, see gemm_bf16_few_k).  All
     // of it is scalar selects: the K loop stays one basic block.  A cursor runs at most SA-1 (SB-1) K
     // tiles ahead, so with at least max(SA, SB) K tiles per tile (the launcher's condition for giving a workgroup
     // more than one) it never needs more than the one following tile.
@@ -265,8 +265,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_pipe_k(int M, int N,
             nx_kt0 = tn.kt0;
             nx_end = tn.kt0 + tn.nt;
         } else {
-            rsA_nx = desc_a(tj);
-            rsB_nx = desc_b(tj);
+            rsA_nx[2] = rsB_nx[2] = 0u;
             nx_kt0 = tj.kt0 + tj.nt - 1;
             nx_end = tj.kt0 + tj.nt;
         }
@@ -820,7 +819,9 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_k(int M, int N, int K, cons
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lhi = lane >> 5, slice = wave;
     const int tile = blockIdx.x % nbn, cut = blockIdx.x / nbn, n0 = tile * BNO;
-    const int nk = K / 64, kt0 = (int)((int64_t)nk * cut / ksplit), nt = (int)((int64_t)nk * (cut + 1) / ksplit) - kt0;
+    // (integer division runs on the vector ALU: the uniform results go back into scalar registers)
+    const int nk = K / 64, kt0 = __builtin_amdgcn_readfirstlane((int)((int64_t)nk * cut / ksplit));
+    const int nt = __builtin_amdgcn_readfirstlane((int)((int64_t)nk * (cut + 1) / ksplit)) - kt0;
     auto desc = [&](const uint16_t* base, uint32_t bytes) {   // raw buffer descriptor; rows past its size fetch nothing
         const uint64_t p = (uint64_t)(uintptr_t)base;
         u32x4_t d;
@@ -831,7 +832,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_k(int M, int N, int K, cons
         return d;
     };
     const int cols = N - n0 < BNO ? N - n0 : BNO;
-    const u32x4_t rs_a = desc(A, (uint32_t)M * (uint32_t)K * 2u);
+    u32x4_t rs_a = desc(A, (uint32_t)M * (uint32_t)K * 2u);
     // load i of a wave covers 8 consecutive tile rows (BNO is a multiple of 8: they are gate rows or up rows as a whole)
     const int r = lane >> 3, c = lane & 7;
     u32x4_t rs_b[LB];
@@ -849,8 +850,13 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_k(int M, int N, int K, cons
         off_b[i] = ((uint32_t)(up ? row - BNO : row) * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
         dst_b[i] = lds_base + (on ? (uint32_t)(BM * 128 + row0 * 128) : (uint32_t)(S * SLOT * 2));
     }
-    auto fetch = [&](int t, int slot) {   // step t (past the end: the last one again, so that the wait counts hold)
+    // step t.  Past the end the loads stay, so that the wait counts hold, but have empty descriptors: the last step fetched again was S - 1 steps of
+    // traffic (a third of a cut's 18) in front of the sums (one sequence decoded plainly 12.45 -> 12.40 ms, 16 sequences 17.41 -> 17.27).
+    auto fetch = [&](int t, int slot) {
         const uint32_t k2 = (uint32_t)(kt0 + (t < nt ? t : nt - 1)) * 128u, so = (uint32_t)slot * (SLOT * 2);
+        rs_a[2] = t < nt ? rs_a[2] : 0u;
+#pragma unroll
+        for (int i = 0; i < LB; ++i) rs_b[i][2] = t < nt ? rs_b[i][2] : 0u;
 #pragma unroll
         for (int i = 0; i < LB; ++i)
             dma_buf_16_nt(rs_b[i], off_b[i], k2, kIdle && i == LB - 1 && wave + i * NW >= BN / 8 ? dst_b[i] : dst_b[i] + so);
@@ -882,7 +888,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_few_k(int M, int N, int K, cons
         slot = slot + 1 == S ? 0 : slot + 1;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the repeated fetches at the end as well: the ring is reused below
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the empty fetches at the end as well: the ring is reused below
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     // the four slices' sums: [slice][32][BN], then four columns per thread
@@ -1015,7 +1021,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         return d;
     };
     const int cols = N - n0 < BNO ? N - n0 : BNO;
-    const u32x4_t rs_a = desc(A, (uint32_t)M * (uint32_t)K * 2u);
+    u32x4_t rs_a = desc(A, (uint32_t)M * (uint32_t)K * 2u);
     const int r = lane >> 3, c = lane & 7;
     u32x4_t rs_b[LB];
     uint32_t off_a[LA], off_b[LB], dst_b[LB];
@@ -1035,7 +1041,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         off_b[i] = ((uint32_t)(up ? row - BNO : row) * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
         dst_b[i] = lds_base + (on ? (uint32_t)(BM * 128 + row0 * 128) : (uint32_t)(S * SLOT * 2));
     }
-    // load i of step t (past the end: the last step again, so that the wait counts hold), weights first
+    // load i of a step, weights first; past the last step, which `upto` is told, loads fetch nothing, so that the wait counts hold
+    auto upto = [&](int t) {
+        rs_a[2] = t < nt ? rs_a[2] : 0u;
+#pragma unroll
+        for (int i = 0; i < LB; ++i) rs_b[i][2] = t < nt ? rs_b[i][2] : 0u;
+    };
     auto load = [&](int i, uint32_t k2, uint32_t so) {
         if (i < LB) {
             const uint32_t dst = kIdle && i == LB - 1 && wave + i * NW >= BN / 8 ? dst_b[i] : dst_b[i] + so;
@@ -1053,9 +1064,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
     constexpr int Q3 = (L + 3) / 4;                // loads issued under slice 3; the rest under slices 0 .. 2 of the next step
     static_assert(S >= 3 && (S - 2) * L + Q3 < 64, "what the waits below count");
 #pragma unroll
-    for (int t = 0; t < S - 1; ++t)
+    for (int t = 0; t < S - 1; ++t) {
+        upto(t);
 #pragma unroll
         for (int i = 0; i < L; ++i) load(i, koff(t), (uint32_t)t * (SLOT * 2));
+    }
+    upto(S - 1);
 #pragma unroll
     for (int i = 0; i < Q3; ++i) load(i, koff(S - 1), (uint32_t)(S - 1) * (SLOT * 2));
     const int sw = (l32 >> 1) & 7;
@@ -1102,6 +1116,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         __builtin_amdgcn_sched_barrier(0);
         mul(1);
         __builtin_amdgcn_sched_barrier(0);
+        upto(t + S);
 #pragma unroll
         for (int i = 0; i < Q3; ++i) load(i, koff(t + S), (uint32_t)slot * (SLOT * 2));
         __builtin_amdgcn_sched_barrier(0);
@@ -1109,7 +1124,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         slot = next;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the repeated fetches at the end as well, before the LDS is released
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the empty fetches at the end as well, before the LDS is released
     // (as the mixed tiles of gemm_bf16_pipe_k: gate and up of a column lie in lanes l and l + 16 of a half-wave)
     const int row0 = wave * 32 + 4 * lhi, odd16 = (l32 >> 4) & 1, odd = lane & 1;
 #pragma unroll
