@@ -998,19 +998,26 @@ static int few_split_plan(int N, int K, int general_cuts, int max_cuts, int* cut
 // about 57 GB/s at 2.4 GHz (a load-only kernel with these loads: 40.7 us at 32 rows, 44.8 at 96, 49.6 at 192, 52.2 at 256 for N 18944, K 3584), and the
 // chip holds 1.6 to 2 GHz here under its power limit: what is saved is padding (128- and 256-row tiles) and the sums of four slices in
 // LDS (gemm_bf16_few_k).  Dispatch and measurements: mid_glu_width.
-template <int NW, int WTN, int S>
+// Products kept as partial sums (GLU off) have whole tiles of 32 * WTN columns and one of ksplit cuts of K per workgroup.  CH: how many chains of
+// products a cut is summed in (its 16-wide slices in turns, added pairwise at the end), in registers that are idle otherwise, so that
+// few long cuts round no worse than many short ones (mid_split_plan).
+template <int NW, int WTN, int S, bool GLU, int CH>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-                                                           const uint16_t* __restrict__ W2, bf16* __restrict__ C, int per_xcd) {
-    constexpr int BM = 32 * NW, BN = 32 * WTN, BNO = BN / 2;
+                                                           const uint16_t* __restrict__ W2, void* __restrict__ C, int per_xcd, int nbn, int ksplit) {
+    constexpr int BM = 32 * NW, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
     constexpr int SLOT = (BM + BN) * 64;           // elements per slot: activation rows, then weight rows
     constexpr int LA = 4, LB = (BN / 8 + NW - 1) / NW, L = LA + LB;   // 1 KB loads per wave and step (a wave's last weight load may be idle)
     constexpr bool kIdle = (BN / 8) % NW != 0;
     extern __shared__ __align__(16) uint16_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
-    // (an XCD's workgroups own neighbouring columns: the lines that two tiles share are completed in its L2)
-    const int n0 = ((blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3)) * BNO, nt = K / 64;
-    if (n0 >= N) return;
+    // (an XCD's workgroups own neighbouring columns: the lines that two tiles share are completed in its L2; of a product cut along K they
+    // own the same cut, whose activations each XCD then fetches once)
+    const int at = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const int cut = GLU ? 0 : __builtin_amdgcn_readfirstlane(at / nbn), n0 = (GLU ? at : at - cut * nbn) * BNO;
+    if (GLU ? n0 >= N : cut >= ksplit) return;
+    const int kt0 = GLU ? 0 : __builtin_amdgcn_readfirstlane((int)((int64_t)(K / 64) * cut / ksplit));
+    const int nt = GLU ? K / 64 : __builtin_amdgcn_readfirstlane((int)((int64_t)(K / 64) * (cut + 1) / ksplit)) - kt0;
     auto desc = [&](const uint16_t* base, uint32_t bytes) {   // raw buffer descriptor; rows past its size fetch nothing
         const uint64_t p = (uint64_t)(uintptr_t)base;
         u32x4_t d;
@@ -1036,7 +1043,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
     for (int i = 0; i < LB; ++i) {
         // (an idle load has an empty descriptor, fetches nothing and aims at a kilobyte behind the ring)
         const int row0 = (i * NW + wave) * 8, row = row0 + r;
-        const bool on = !kIdle || row0 < BN, up = row0 >= BNO;
+        const bool on = !kIdle || row0 < BN, up = GLU && row0 >= BNO;
         rs_b[i] = desc((up ? W2 : W) + (int64_t)n0 * K, on ? (uint32_t)cols * (uint32_t)K * 2u : 0u);
         off_b[i] = ((uint32_t)(up ? row - BNO : row) * (uint32_t)K + (c ^ ((row >> 1) & 7)) * 8) * 2u;
         dst_b[i] = lds_base + (on ? (uint32_t)(BM * 128 + row0 * 128) : (uint32_t)(S * SLOT * 2));
@@ -1055,12 +1062,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
             dma_buf_16(rs_a, off_a[i - LB], k2, lds_a + so + (i - LB) * 1024u);
         }
     };
-    auto koff = [&](int t) { return (uint32_t)(t < nt ? t : nt - 1) * 128u; };
-    f32x16_t acc[WTN];
+    auto koff = [&](int t) { return (uint32_t)(kt0 + (t < nt ? t : nt - 1)) * 128u; };
+    f32x16_t acc[CH][WTN];
 #pragma unroll
-    for (int j = 0; j < WTN; ++j)
+    for (int h = 0; h < CH; ++h)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        for (int j = 0; j < WTN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[h][j][v] = 0.f;
     constexpr int Q3 = (L + 3) / 4;                // loads issued under slice 3; the rest under slices 0 .. 2 of the next step
     static_assert(S >= 3 && (S - 2) * L + Q3 < 64, "what the waits below count");
 #pragma unroll
@@ -1074,18 +1083,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
     for (int i = 0; i < Q3; ++i) load(i, koff(S - 1), (uint32_t)(S - 1) * (SLOT * 2));
     const int sw = (l32 >> 1) & 7;
     const int fragA = (wave * 32 + l32) * 64;
-    const int fragB = ((l32 & 15) + (l32 >> 4) * BNO) * 64;   // 16 gate rows and the 16 up rows that belong to them
+    const int fragB = (GLU ? (l32 & 15) + (l32 >> 4) * BNO : l32) * 64;   // 16 gate rows and the 16 up rows that belong to them
     bf16x8_t fa[2], fb[2][WTN];
     auto read = [&](int buf, const uint16_t* p, int kk) {
         const int ch = ((2 * kk + lhi) ^ sw) * 8;
         fa[buf] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + fragA + ch));
 #pragma unroll
         for (int j = 0; j < WTN; ++j)
-            fb[buf][j] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + BM * 64 + fragB + j * 16 * 64 + ch));
+            fb[buf][j] = __builtin_bit_cast(bf16x8_t, *(const u32x4_t*)(p + BM * 64 + fragB + j * (GLU ? 16 : 32) * 64 + ch));
     };
-    auto mul = [&](int buf) {
+    auto mul = [&](int kk) {
 #pragma unroll
-        for (int j = 0; j < WTN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf], fb[buf][j], acc[j], 0, 0, 0);
+        for (int j = 0; j < WTN; ++j)
+            acc[kk % CH][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk & 1], fb[kk & 1][j], acc[kk % CH][j], 0, 0, 0);
     };
     __builtin_amdgcn_s_waitcnt(vmcnt_imm((S - 2) * L + Q3));   // step 0 has landed
     __builtin_amdgcn_s_barrier();
@@ -1102,7 +1112,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
             __builtin_amdgcn_sched_barrier(0);
             read((kk + 1) & 1, p, kk + 1);
             __builtin_amdgcn_sched_barrier(0);
-            mul(kk & 1);
+            mul(kk);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = Q3 + kk * (L - Q3) / 3; i < Q3 + (kk + 1) * (L - Q3) / 3; ++i) load(i, k2, so);
@@ -1114,7 +1124,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         __builtin_amdgcn_sched_barrier(0);
         read(0, lds + next * SLOT, 0);
         __builtin_amdgcn_sched_barrier(0);
-        mul(1);
+        mul(3);
         __builtin_amdgcn_sched_barrier(0);
         upto(t + S);
 #pragma unroll
@@ -1125,6 +1135,23 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the empty fetches at the end as well, before the LDS is released
+    if constexpr (!GLU) {                          // a lane's column of every block, 128 bytes of a row per half-wave
+        float* out = (float*)C + (int64_t)cut * M * N + n0 + l32;
+#pragma unroll
+        for (int h = CH / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int i = 0; i < h; ++i)
+#pragma unroll
+                for (int j = 0; j < WTN; ++j) acc[i][j] += acc[i + h][j];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = wave * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3);
+#pragma unroll
+            for (int j = 0; j < WTN; ++j)
+                if (row < M) out[(int64_t)row * N + j * 32] = acc[0][j][v];
+        }
+        return;
+    }
     // (as the mixed tiles of gemm_bf16_pipe_k: gate and up of a column lie in lanes l and l + 16 of a half-wave)
     const int row0 = wave * 32 + 4 * lhi, odd16 = (l32 >> 4) & 1, odd = lane & 1;
 #pragma unroll
@@ -1134,30 +1161,33 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
             float x[2];
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[j][4 * vq + 2 * e]), __float_as_uint(acc[j][4 * vq + 2 * e + 1]), false, false);
+                const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[0][j][4 * vq + 2 * e]), __float_as_uint(acc[0][j][4 * vq + 2 * e + 1]), false, false);
                 const float g = __uint_as_float(q[0]), u = __uint_as_float(q[1]);
                 x[e] = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;
             }
             const float other = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(odd ? x[0] : x[1]), 0xB1, 0xF, 0xF, false));
             const uint32_t out = odd ? pack_bf16x2(other, x[1]) : pack_bf16x2(x[0], other);
             const int row = row0 + 8 * vq + 2 * odd + odd16, col0 = j * 16;
-            if (row < M && col0 < cols) *(uint32_t*)(C + (int64_t)row * N + n0 + col0 + (l32 & 14)) = out;
+            if (row < M && col0 < cols) *(uint32_t*)((bf16*)C + (int64_t)row * N + n0 + col0 + (l32 & 14)) = out;
         }
 }
 
-template <int NW, int WTN>
-static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
-    constexpr int kSlot = (32 * NW + 32 * WTN) * 128, kFit = 159 * 1024 / kSlot, S = kFit < 6 ? kFit : 6;
-    constexpr size_t lds = (size_t)S * kSlot + 1024;
-    auto kern = gemm_bf16_mid_k<NW, WTN, S>;
+template <int NW, int WTN, bool GLU>
+static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, const void* W, const void* W2, void* C, int ksplit = 1) {
+    constexpr bool kIdle = (4 * WTN) % NW != 0;
+    constexpr int kSlot = (32 * NW + 32 * WTN) * 128, kFit = (GLU ? 159 * 1024 : 160 * 1024 - (kIdle ? 1024 : 0)) / kSlot, S = kFit < 6 ? kFit : 6;
+    constexpr size_t lds = (size_t)S * kSlot + (kIdle ? 1024 : 0);
+    constexpr int BNO = GLU ? 16 * WTN : 32 * WTN;
+    auto kern = gemm_bf16_mid_k<NW, WTN, S, GLU, GLU ? 1 : WTN <= 3 ? 4 : 2>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int per_xcd = ((N + 16 * WTN - 1) / (16 * WTN) + 7) / 8;
-    hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(64 * NW), lds, s, M, N, K, (const uint16_t*)A, (const uint16_t*)Wg, (const uint16_t*)Wu, (bf16*)act, per_xcd);
+    const int nbn = (N + BNO - 1) / BNO, per_xcd = (nbn * ksplit + 7) / 8;
+    hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(64 * NW), lds, s, M, N, K, (const uint16_t*)A, (const uint16_t*)W, (const uint16_t*)W2, C, per_xcd,
+                       nbn, ksplit);
     return hipGetLastError();
 }
 
@@ -1182,7 +1212,7 @@ static int mid_glu_width(int M, int N, int K) {
     return wtn <= 7 && M > 32 && M <= rows && K >= k_min ? wtn : 0;
 }
 static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
-#define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n>(s, M, N, K, A, Wg, Wu, act);
+#define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n, true>(s, M, N, K, A, Wg, Wu, act);
     TLT_MID(2, 2) TLT_MID(2, 3) TLT_MID(2, 4) TLT_MID(2, 5) TLT_MID(2, 6) TLT_MID(2, 7)
     TLT_MID(3, 2) TLT_MID(3, 3) TLT_MID(3, 4) TLT_MID(3, 5) TLT_MID(3, 6) TLT_MID(3, 7)
     TLT_MID(4, 2) TLT_MID(4, 3) TLT_MID(4, 4) TLT_MID(4, 5) TLT_MID(4, 6) TLT_MID(4, 7)
@@ -1191,6 +1221,53 @@ static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, co
     TLT_MID(7, 3) TLT_MID(7, 4) TLT_MID(7, 5) TLT_MID(7, 6)
     TLT_MID(8, 3) TLT_MID(8, 4)
 #undef TLT_MID
+    return hipErrorInvalidValue;
+}
+
+// Products kept as partial sums at 33 to 256 rows: gemm_bf16_mid_k with a workgroup per (64 columns up to 128 rows, 128 above; cut), the cuts as many as
+// leave at most one workgroup per CU.  Returns whether it takes the product; elsewhere the general plan is the better one.
+// - Up to 128 rows, K up to 4096: the general plan's 128x128 tiles come out even only with twice the cuts (and slices to write and read back).  Longer cuts
+//   pay for narrow tiles, which re-read the activation rows more often (K 7168: -2 to +2 %, K 8192 -4 to -9 %).  Us per call on cold weights, a graph of 40
+//   calls, slices read back at 4 TB/s included, the general plan and this kernel:
+//     rows           40           72           96           128
+//     3584 x 3584    9.8/9.1      12.0/10.8    13.2/11.8    14.5/13.2   (9 and 4 cuts)
+//     4608 x 3584    10.6/10.3    13.0/12.4    14.2/13.5    15.9/15.1   (7 and 3)
+//     4096 x 4096    10.6/10.0    13.1/11.5    14.3/13.0    16.0/14.1   (8 and 4)
+//     8192 x 2048    10.6/10.3    13.0/11.6    14.2/12.7    16.1/14.1   (4 and 2)
+//   Not with the cuts' first columns an odd multiple of 2048 apart (see few_split_plan; 8192 x 4096: 15.3/18.0, 21.4/22.3), nor uncut (14336 x 3584: 28.9/31.9).
+// - From 129 rows on, where the general plan too fills the chip by cutting (its 256-row tiles pad 130 rows to 256, two rows of 128-row tiles
+//   read the weights twice):
+//     rows           136          160          192          224          256
+//     3584 x 18944   39.3/37.5    41.2/39.2    43.3/40.7    45.8/44.2    47.8/49.4   (9 cuts)
+//     5120 x 27648   77.9/64.7    80.8/68.8    79.2/70.9    82.9/76      86.9/82.6   (12 or 6, and 6)
+//     7168 x 5120    27.8/26.7    29.4/27.8    31.2/28.6    32.6/31.1    34.5/33.9   (4)
+//     8192 x 8192    42.4/39.2    43.8/40.7    45.7/42.1    48.1/45.4    50.5/49.6   (4)
+//     14336 x 5120   44.4/41.1    47.1/43.8    48.9/45.0    51.6/48.0    53.9/50.7   (2)
+//   (above 224 rows nothing is padding, and in less than 5120 columns the gain is -4 to +1 %.)  Where the general plan prefers fewer, longer cuts of wide tiles (3584 x
+//   3584: 4) it is ahead by 1 to 6 %.
+// The kernel's two or four chains per cut keep the serial sums no longer than before in either case; error to float64 (slices added in fp32) 1.24e-7 ->
+// 0.98e-7 at 3584 x 3584, 2.8e-7 -> 2.0e-7 at 3584 x 18944, even where this kernel has half of the cuts.
+static bool mid_split_plan(int M, int N, int K, int general_cuts, int max_cuts, int* cuts) {
+    if (M <= 32 || M > 256) return false;
+    const int cols = M <= 128 ? 64 : 128, nbn = N / cols;
+    int ks = 256 / nbn;
+    if (ks > K / 64 / 6) ks = K / 64 / 6;
+    if (ks > max_cuts) ks = max_cuts;
+    if (ks < 2 || nbn * ks < 200) return false;
+    *cuts = ks;
+    if (M <= 128) return K <= 4096 && general_cuts <= 4 * ks && !(N > 2048 && K % (2048 * ks) == 0 && K / (2048 * ks) % 2 != 0);
+    return (M <= 224 || N >= 5120) && general_cuts >= ks && general_cuts <= 2 * ks;
+}
+static hipError_t launch_mid_parts(hipStream_t s, int M, int N, int K, const void* A, const void* W, float* parts, int cuts) {
+    switch ((M + 31) / 32) {
+        case 2: return launch_mid<2, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 3: return launch_mid<3, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 4: return launch_mid<4, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 5: return launch_mid<5, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 6: return launch_mid<6, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 7: return launch_mid<7, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 8: return launch_mid<8, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+    }
     return hipErrorInvalidValue;
 }
 
@@ -1489,6 +1566,11 @@ hipError_t gemm_parts(hipStream_t s, int dtype, int M, int N, int K, const void*
             if (wtn == 2) return launch_few<2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
             if (wtn == 3) return launch_few<3, false>(s, M, N, K, A, W, nullptr, parts, cuts);
             if (wtn == 4) return launch_few<4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        }
+        int mid_cuts = 0;
+        if (mid_split_plan(M, N, K, sp.ks, room > 12 ? 12 : (int)room, &mid_cuts)) {
+            *n_parts = mid_cuts;
+            return launch_mid_parts(s, M, N, K, A, W, parts, mid_cuts);
         }
         if (sp.kind != 0 && (size_t)sp.ks * M * N * 4 <= parts_bytes) {
             *n_parts = sp.ks;

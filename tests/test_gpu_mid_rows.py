@@ -1,4 +1,4 @@
-"""Products of 33 to 256 activation rows at the edges of their tiles: 32 rows per wave, two to eight waves, tiles of every width."""
+"""Products of 33 to 256 activation rows at the edges of their tiles: 32 rows per wave, two to eight waves, tiles of every width, cuts along K."""
 import pytest
 import torch
 
@@ -34,3 +34,28 @@ def test_bf16_gate_up(M, N, K):
         gate, up = (A[:M].double() @ x.double().T for x in (W, U))
         err = (K + 2) * 2.0 ** -24 * (A[:M].double().abs() @ (W.double().abs() + U.double().abs()).T) * (1.1 * up.abs() + gate.abs() + 1)
         assert bool(((act[:M].double() - want[:M].double()).abs() <= 2 * err + 2.0 ** -7 * want[:M].double().abs() + 1e-30).all())
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (33, 3584, 1536), (64, 4608, 2048), (65, 2560, 2112), (96, 3584, 3584), (97, 7168, 1024), (128, 4096, 4096), (127, 8192, 2048),   # 64 columns, even and uneven cuts
+    (40, 1536, 4096), (128, 2048, 3072),                                                                                              # ... ten and eight of them
+    (129, 5120, 8192), (160, 10240, 1536), (161, 8192, 5120), (192, 14336, 2048), (193, 6144, 3584), (224, 3584, 8192),               # 128 columns
+    (225, 5120, 8192), (256, 10240, 2048),
+    (80, 8192, 4096), (225, 3584, 18944), (129, 3584, 3584), (72, 14336, 1024),                                                       # beside the ranges
+])
+def test_bf16_parts(M, N, K):
+    """The slices' sum against float64, bounded by one rounding of 2^-24 per product and slice; nothing behind the slices, the same bits again."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    W = (torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16()
+    buf = torch.full((13 * M * N,), float("nan"), device="cuda")
+    print(f"slices M={M} N={N} K={K}", flush=True)
+    parts = tlt.gemm_parts(A, W, buf[:12 * M * N])
+    torch.cuda.synchronize()
+    n = parts.shape[0]
+    assert 1 <= n <= 12 and bool(torch.isnan(buf[n * M * N:]).all())
+    got = parts.double().sum(0)
+    err = (K + 2) * 2.0 ** -24 * (A.double().abs() @ W.double().abs().T)
+    assert bool(((got - A.double() @ W.double().T).abs() <= err).all())
+    again = tlt.gemm_parts(A, W, torch.empty_like(buf))
+    assert torch.equal(parts, again)
