@@ -1003,7 +1003,7 @@ static int few_split_plan(int N, int K, int general_cuts, int max_cuts, int* cut
 // few long cuts round no worse than many short ones (mid_split_plan).
 template <int NW, int WTN, int S, bool GLU, int CH>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-                                                           const uint16_t* __restrict__ W2, void* __restrict__ C, int per_xcd, int nbn, int ksplit) {
+                                                           const uint16_t* __restrict__ W2, void* __restrict__ C, int per_xcd, int nbn, int ksplit, int ldc) {
     constexpr int BM = 32 * NW, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
     constexpr int SLOT = (BM + BN) * 64;           // elements per slot: activation rows, then weight rows
     constexpr int LA = 4, LB = (BN / 8 + NW - 1) / NW, L = LA + LB;   // 1 KB loads per wave and step (a wave's last weight load may be idle)
@@ -1136,7 +1136,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the empty fetches at the end as well, before the LDS is released
     if constexpr (!GLU) {                          // a lane's column of every block, 128 bytes of a row per half-wave
-        float* out = (float*)C + (int64_t)cut * M * N + n0 + l32;
+        float* out = (float*)C + (int64_t)cut * M * ldc + n0 + l32;
 #pragma unroll
         for (int h = CH / 2; h > 0; h /= 2)
 #pragma unroll
@@ -1148,7 +1148,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
             const int row = wave * 32 + 8 * (v >> 2) + 4 * lhi + (v & 3);
 #pragma unroll
             for (int j = 0; j < WTN; ++j)
-                if (row < M) out[(int64_t)row * N + j * 32] = acc[0][j][v];
+                if (row < M && j * 32 < cols) out[(int64_t)row * ldc + j * 32] = acc[0][j][v];
         }
         return;
     }
@@ -1172,13 +1172,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         }
 }
 
-template <int NW, int WTN, bool GLU>
-static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, const void* W, const void* W2, void* C, int ksplit = 1) {
+template <int NW, int WTN, bool GLU, int CH>
+static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, const void* W, const void* W2, void* C, int ksplit = 1, int ldc = 0) {
     constexpr bool kIdle = (4 * WTN) % NW != 0;
     constexpr int kSlot = (32 * NW + 32 * WTN) * 128, kFit = (GLU ? 159 * 1024 : 160 * 1024 - (kIdle ? 1024 : 0)) / kSlot, S = kFit < 6 ? kFit : 6;
     constexpr size_t lds = (size_t)S * kSlot + (kIdle ? 1024 : 0);
     constexpr int BNO = GLU ? 16 * WTN : 32 * WTN;
-    auto kern = gemm_bf16_mid_k<NW, WTN, S, GLU, GLU ? 1 : WTN <= 3 ? 4 : 2>;
+    auto kern = gemm_bf16_mid_k<NW, WTN, S, GLU, CH>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1187,7 +1187,7 @@ static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, 
     }
     const int nbn = (N + BNO - 1) / BNO, per_xcd = (nbn * ksplit + 7) / 8;
     hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(64 * NW), lds, s, M, N, K, (const uint16_t*)A, (const uint16_t*)W, (const uint16_t*)W2, C, per_xcd,
-                       nbn, ksplit);
+                       nbn, ksplit, ldc ? ldc : N);
     return hipGetLastError();
 }
 
@@ -1212,7 +1212,7 @@ static int mid_glu_width(int M, int N, int K) {
     return wtn <= 7 && M > 32 && M <= rows && K >= k_min ? wtn : 0;
 }
 static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
-#define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n, true>(s, M, N, K, A, Wg, Wu, act);
+#define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n, true, 1>(s, M, N, K, A, Wg, Wu, act);
     TLT_MID(2, 2) TLT_MID(2, 3) TLT_MID(2, 4) TLT_MID(2, 5) TLT_MID(2, 6) TLT_MID(2, 7)
     TLT_MID(3, 2) TLT_MID(3, 3) TLT_MID(3, 4) TLT_MID(3, 5) TLT_MID(3, 6) TLT_MID(3, 7)
     TLT_MID(4, 2) TLT_MID(4, 3) TLT_MID(4, 4) TLT_MID(4, 5) TLT_MID(4, 6) TLT_MID(4, 7)
@@ -1260,14 +1260,27 @@ static bool mid_split_plan(int M, int N, int K, int general_cuts, int max_cuts, 
 }
 static hipError_t launch_mid_parts(hipStream_t s, int M, int N, int K, const void* A, const void* W, float* parts, int cuts) {
     switch ((M + 31) / 32) {
-        case 2: return launch_mid<2, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-        case 3: return launch_mid<3, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-        case 4: return launch_mid<4, 2, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-        case 5: return launch_mid<5, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-        case 6: return launch_mid<6, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-        case 7: return launch_mid<7, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
-        case 8: return launch_mid<8, 4, false>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 2: return launch_mid<2, 2, false, 4>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 3: return launch_mid<3, 2, false, 4>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 4: return launch_mid<4, 2, false, 4>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 5: return launch_mid<5, 4, false, 2>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 6: return launch_mid<6, 4, false, 2>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 7: return launch_mid<7, 4, false, 2>(s, M, N, K, A, W, nullptr, parts, cuts);
+        case 8: return launch_mid<8, 4, false, 2>(s, M, N, K, A, W, nullptr, parts, cuts);
     }
+    return hipErrorInvalidValue;
+}
+
+// What whole rounds of 256-column tiles leave of a product of 33 to 128 rows, up to 96 columns per CU: the narrowest tiles that come out at one per CU, K
+// summed in the one order of all tiles (so the bits are those of 128x128 tiles, whose 164 workgroups held a third less of the weights in flight).
+// Whole product on cold weights, us: N 152064, K 3584 40 rows 201 -> 195, 96 206 -> 202, 128 216 -> 213; K 5120 281 -> 269, 305 -> 298, 316 -> 311; N
+// 90112, K 4096 164 -> 160, 173 -> 169, 179 -> 173.
+static hipError_t launch_mid_rest(hipStream_t s, int M, int N, int K, const void* A, const void* W, void* C, int ldc) {
+#define TLT_MID(nw, n) if ((M + 31) / 32 == nw && (N + 32 * n - 1) / (32 * n) <= 256) return launch_mid<nw, n, false, 1>(s, M, N, K, A, W, nullptr, C, 1, ldc);
+    TLT_MID(2, 2) TLT_MID(2, 3)
+    TLT_MID(3, 2) TLT_MID(3, 3)
+    TLT_MID(4, 2) TLT_MID(4, 3)
+#undef TLT_MID
     return hipErrorInvalidValue;
 }
 
@@ -1429,6 +1442,7 @@ static hipError_t launch_tiled(hipStream_t s, int out_mode, int M, int N, int K,
             if (e != hipSuccess) return e;
             const void* w = (const uint16_t*)W + (int64_t)main_tiles * 256 * K;
             void* c = (char*)C + (size_t)main_tiles * 256 * c_elt;
+            if (out_mode == OUT_F32 && N - main_tiles * 256 <= 96 * 256) return launch_mid_rest(s, M, N - main_tiles * 256, K, A, w, c, N);
             return launch_pipe<2, 2, 2, 2, 3, 3, false, true>(s, out_mode, M, N - main_tiles * 256, K, A, w, c, nullptr, 1, N);
         }
         return launch_pipe<2, 2, 2, 4, 3, 3, false, true>(s, out_mode, M, N, K, A, W, C, nullptr, 1, N);

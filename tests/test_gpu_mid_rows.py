@@ -59,3 +59,21 @@ def test_bf16_parts(M, N, K):
     assert bool(((got - A.double() @ W.double().T).abs() <= err).all())
     again = tlt.gemm_parts(A, W, torch.empty_like(buf))
     assert torch.equal(parts, again)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (33, 65792, 2048), (65, 81920, 192), (128, 81920, 128), (96, 82176, 64), (100, 90112, 320), (128, 90112, 512),   # 64 and 96 columns, partial last tiles
+    (97, 90368, 64),                                                                                                # beside the range
+])
+def test_bf16_whole_rounds_and_rest(M, N, K):
+    """The same bits as the first rows of a product of 300 rows (all tiles add up K in one order), nothing behind the last row."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((300, K), generator=g, device="cuda").bfloat16()
+    W = (torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16()
+    out = torch.full((M + 1, N), float("nan"), device="cuda")
+    want = torch.empty((300, N), device="cuda")
+    print(f"stored M={M} N={N} K={K} and 300 rows", flush=True)
+    tlt.gemm(tlt.TLT_BF16, 1, A[:M].contiguous(), W, out[:M])
+    tlt.gemm(tlt.TLT_BF16, 1, A, W, want)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(out[M]).all()) and torch.equal(out[:M], want[:M])
