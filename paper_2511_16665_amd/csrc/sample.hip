@@ -338,22 +338,29 @@ __global__ __launch_bounds__(1024) void draft_level_k(int K, int level, int n_se
         par_mask[c][0] = st.pool_mask[2 * ((int64_t)b * st.P + pp)];
         par_mask[c][1] = st.pool_mask[2 * ((int64_t)b * st.P + pp) + 1];
     }
+    // Log-probability of a candidate, never a NaN, which a row with a NaN or an infinity among its logits makes of all of its: the ranks below and those of the
+    // pruning are counts of better scores, and only a total order makes them different from each other and fewer than the nodes.
+    auto log_prob = [](float v, float lse) { return v - lse == v - lse ? v - lse : -INFINITY; };
+    const int64_t o = ((int64_t)b * (level == 0 ? 1 : K) + wave) * n_seg;
+    const int n_cand = n_seg * K;
+    float rv[MR > 0 ? MR : 1];
+    int rj[MR > 0 ? MR : 1];
+    float lse;
+    bool sorted = false;
     if constexpr (ROW > 0) {
         __shared__ float s_stat[16][2];
-        topk_segment<ROW == 1, false>(logits + ((int64_t)b * (level == 0 ? 1 : K) + wave) * V, V, K, 0, s_stat[wave], s_logp[wave], s_tok[wave]);
+        topk_segment<ROW == 1, false>(logits + o * V, V, K, 0, s_stat[wave], s_logp[wave], s_tok[wave]);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // (read back by the same wave only)
         __builtin_amdgcn_wave_barrier();
-        const float lse = s_stat[wave][0] + logf(s_stat[wave][1]);
-        if (lane < K) {
-            const int t = s_tok[wave][lane];
-            s_tok[wave][lane] = t != 0x7fffffff ? t : -1;
-            s_logp[wave][lane] = t != 0x7fffffff ? s_logp[wave][lane] - lse : -INFINITY;
+        lse = s_stat[wave][0] + logf(s_stat[wave][1]);
+        rv[0] = lane < K ? s_logp[wave][lane] : -INFINITY;
+        rj[0] = lane < K ? s_tok[wave][lane] : 0x7fffffff;
+        sorted = !__any(rv[0] != rv[0]);   // (a NaN may stand anywhere in the segment's list: the rounds below leave it out)
+        if (sorted && lane < K) {
+            s_tok[wave][lane] = rj[0] != 0x7fffffff ? rj[0] : -1;
+            s_logp[wave][lane] = rj[0] != 0x7fffffff ? log_prob(rv[0], lse) : -INFINITY;
         }
     } else {
-        const int64_t o = ((int64_t)b * (level == 0 ? 1 : K) + wave) * n_seg;
-        const int n_cand = n_seg * K;
-        float rv[MR > 0 ? MR : 1];
-        int rj[MR > 0 ? MR : 1];
 #pragma unroll
         for (int r = 0; r < MR; ++r) {
             const int i = lane + 64 * r;
@@ -375,7 +382,9 @@ __global__ __launch_bounds__(1024) void draft_level_k(int K, int level, int n_se
             if (lane + 64 * u < n_seg) se += stat[u].y * expf(stat[u].x - mx);
         for (int sgm = lane + 128; sgm < n_seg; sgm += 64) se += seg_stat[2 * (o + sgm) + 1] * expf(seg_stat[2 * (o + sgm)] - mx);
         se = wave_sum(se);
-        const float lse = mx + logf(se);
+        lse = mx + logf(se);
+    }
+    if (!sorted) {
         float pv = INFINITY;
         int pi = -1;
         for (int k = 0; k < K; ++k) {
@@ -400,7 +409,7 @@ __global__ __launch_bounds__(1024) void draft_level_k(int K, int level, int n_se
             if (lane == 0) {
                 const bool have = ci != 0x7fffffff;
                 s_tok[wave][k] = have ? ci : -1;
-                s_logp[wave][k] = have ? cv - lse : -INFINITY;
+                s_logp[wave][k] = have ? log_prob(cv, lse) : -INFINITY;
             }
         }
     }
@@ -1393,8 +1402,8 @@ hipError_t draft_level(hipStream_t s, int B, int K, int level, int V, const floa
     const dim3 grid((n_seg + 3) / 4, M), block(64 * (level == 0 ? 1 : K));
     const bool vec = V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
     if (n_seg == 1) {
-        if (vec) hipLaunchKernelGGL((draft_level_k<0, 1>), dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st, logits, V);
-        else hipLaunchKernelGGL((draft_level_k<0, 2>), dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st, logits, V);
+        if (vec) hipLaunchKernelGGL((draft_level_k<1, 1>), dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st, logits, V);
+        else hipLaunchKernelGGL((draft_level_k<1, 2>), dim3(B), block, 0, s, K, level, n_seg, seg_stat, seg_val, seg_idx, st, logits, V);
         return hipGetLastError();
     }
     if (vec)

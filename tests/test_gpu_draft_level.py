@@ -87,6 +87,43 @@ def test_levels_hold_the_best_candidates_and_their_scores(V, K, D, B):
     e.ctx.close()
 
 
+@pytest.mark.parametrize("V,K", [(50, 5), (1024, 4), (2048, 16), (4099, 4)])     # one segment, in 16-byte pieces or not; several
+@pytest.mark.parametrize("bad", ["all NaN", "one NaN", "one infinite", "all infinite"])
+def test_logits_without_an_order_leave_scores_and_a_tree_that_have_one(bad, V, K):
+    """What is no number is no candidate, scores are numbers or -inf, and the tree has its n nodes, each behind its parent, and nothing behind them."""
+    cfg = dataclasses.replace(TINY, n_layers=1, hidden=64, mlp=64, vocab=V)
+    tw, dw, _, _ = make_models(cfg, 5, "fp32", std=0.2)
+    if bad == "all NaN":
+        tw["lm_head"].fill_(float("nan"))
+    elif bad == "one NaN":
+        tw["lm_head"][V // 2] = float("nan")
+    else:       # (one column: plus or minus infinity, as the drafter's output has it)
+        rows = slice(None) if bad == "all infinite" else V // 2
+        tw["lm_head"][rows] = 0
+        tw["lm_head"][rows, 0] = float("inf")
+    B, D, n = 2, 3, 6
+    e, _, _ = make_engine(cfg, "fp32", tw, dw, B, 8, D, K, 128, seed=3, seq_len=np.array([9, 40], np.int32))
+    e.dkv.k_pool.normal_(generator=torch.Generator(device="cuda").manual_seed(1))
+    e.dkv.v_pool.normal_(generator=torch.Generator(device="cuda").manual_seed(2))
+    wide = e.tree(n).empty(B + 1, n)
+    for x in vars(wide).values():
+        x.fill_(77)
+    t = type(wide)(**{k: x[:B] for k, x in vars(wide).items()})
+    print(f"draft levels without an order: {bad} V={V} K={K}", flush=True)
+    e.ctx.draft_expand(B, D, K, n, *_inputs(cfg, B, 2, [1, 2], 1), None, e.dkv, t)
+    tok, par, sc = (x.cpu().numpy() for x in e.ctx.draft_pool(B, D, K))
+    assert not np.isnan(sc).any() and (sc < 1e-5).all()
+    assert (tok >= -1).all() and (tok < V).all()
+    if bad == "all NaN":
+        assert (tok == -1).all() and np.isneginf(sc).all()
+    parent = t.parent.cpu().numpy()
+    assert (parent[:, 0] == -1).all() and (parent[:, 1:] >= 0).all() and (parent < np.arange(n)).all()
+    assert not torch.isnan(t.score).any()
+    for k, x in vars(wide).items():
+        assert (x[B] == 77).all(), k
+    e.ctx.close()
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_sequences_without_new_entries_keep_their_row_and_cache(dtype):
     cfg = dataclasses.replace(TINY, n_layers=1, hidden=256, head_dim=128 if dtype == "bf16" else 64, vocab=4096)
