@@ -1000,14 +1000,16 @@ static int few_split_plan(int N, int K, int general_cuts, int max_cuts, int* cut
 // LDS (gemm_bf16_few_k).  Dispatch and measurements: mid_glu_width.
 // Products kept as partial sums (GLU off) have whole tiles of 32 * WTN columns and one of ksplit cuts of K per workgroup.  CH: how many chains of
 // products a cut is summed in (its 16-wide slices in turns, added pairwise at the end), in registers that are idle otherwise, so that
-// few long cuts round no worse than many short ones (mid_split_plan).
-template <int NW, int WTN, int S, bool GLU, int CH>
+// few long cuts round no worse than many short ones (mid_split_plan).  SEG: in how many pieces of K one after the other, where chains side by side do not fit
+// the registers (mid_glu_four).
+template <int NW, int WTN, int S, bool GLU, int CH, int SEG>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                                                            const uint16_t* __restrict__ W2, void* __restrict__ C, int per_xcd, int nbn, int ksplit, int ldc) {
     constexpr int BM = 32 * NW, BN = 32 * WTN, BNO = GLU ? BN / 2 : BN;
     constexpr int SLOT = (BM + BN) * 64;           // elements per slot: activation rows, then weight rows
     constexpr int LA = 4, LB = (BN / 8 + NW - 1) / NW, L = LA + LB;   // 1 KB loads per wave and step (a wave's last weight load may be idle)
     constexpr bool kIdle = (BN / 8) % NW != 0;
+    static_assert(SEG == 1 || CH == 1, "one or the other");
     extern __shared__ __align__(16) uint16_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31, lhi = lane >> 5;
@@ -1063,13 +1065,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         }
     };
     auto koff = [&](int t) { return (uint32_t)(kt0 + (t < nt ? t : nt - 1)) * 128u; };
-    f32x16_t acc[CH][WTN];
+    f32x16_t acc[CH][WTN], done[SEG > 1 ? WTN : 1];   // (done: the finished pieces of K)
 #pragma unroll
     for (int h = 0; h < CH; ++h)
 #pragma unroll
         for (int j = 0; j < WTN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[h][j][v] = 0.f;
+    if constexpr (SEG > 1)
+#pragma unroll
+        for (int j = 0; j < WTN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) done[j][v] = 0.f;
+    int seg = 1;
     constexpr int Q3 = (L + 3) / 4;                // loads issued under slice 3; the rest under slices 0 .. 2 of the next step
     static_assert(S >= 3 && (S - 2) * L + Q3 < 64, "what the waits below count");
 #pragma unroll
@@ -1130,12 +1138,32 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
 #pragma unroll
         for (int i = 0; i < Q3; ++i) load(i, koff(t + S), (uint32_t)slot * (SLOT * 2));
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (SEG > 1) {
+            if (seg < SEG && (t + 1) * SEG >= nt * seg) {   // (the end of a piece of K)
+                ++seg;
+#pragma unroll
+                for (int j = 0; j < WTN; ++j) {
+                    done[j] += acc[0][j];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[0][j][v] = 0.f;
+                }
+            }
+        }
         before = slot;
         slot = next;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));      // the empty fetches at the end as well, before the LDS is released
-    if constexpr (!GLU) {                          // a lane's column of every block, 128 bytes of a row per half-wave
+    if constexpr (SEG > 1) {
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) acc[0][j] += done[j];
+    }
+    if constexpr (GLU) {                           // chain after chain, as gemm_bf16_few_k adds its four waves' sums
+#pragma unroll
+        for (int h = 1; h < CH; ++h)
+#pragma unroll
+            for (int j = 0; j < WTN; ++j) acc[0][j] += acc[h][j];
+    } else {                                       // a lane's column of every block, 128 bytes of a row per half-wave
         float* out = (float*)C + (int64_t)cut * M * ldc + n0 + l32;
 #pragma unroll
         for (int h = CH / 2; h > 0; h /= 2)
@@ -1172,13 +1200,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_mid_k(int M, int N, int K, 
         }
 }
 
-template <int NW, int WTN, bool GLU, int CH>
+template <int NW, int WTN, bool GLU, int CH, int SEG = 1>
 static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, const void* W, const void* W2, void* C, int ksplit = 1, int ldc = 0) {
     constexpr bool kIdle = (4 * WTN) % NW != 0;
     constexpr int kSlot = (32 * NW + 32 * WTN) * 128, kFit = (GLU ? 159 * 1024 : 160 * 1024 - (kIdle ? 1024 : 0)) / kSlot, S = kFit < 6 ? kFit : 6;
     constexpr size_t lds = (size_t)S * kSlot + (kIdle ? 1024 : 0);
     constexpr int BNO = GLU ? 16 * WTN : 32 * WTN;
-    auto kern = gemm_bf16_mid_k<NW, WTN, S, GLU, CH>;
+    auto kern = gemm_bf16_mid_k<NW, WTN, S, GLU, CH, SEG>;
     static bool attr_set = false;
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1211,9 +1239,33 @@ static int mid_glu_width(int M, int N, int K) {
     const int k_min = wtn >= 5 || (wtn == 2 && M <= 64) ? 64 : (wtn == 4 && M > 64) || M > 128 ? 512 : 1024;
     return wtn <= 7 && M > 32 && M <= rows && K >= k_min ? wtn : 0;
 }
+// Whether the tile's sums over K are four (long K up to 128 rows; gemm_bf16_few_k has four at up to 32): one chain errs twice as far.  Rms error of an up sum
+// to float64, four and one: K 1024 1.0e-7 and 1.8e-7, 3584 1.8e-7 and 3.7e-7.  Two blocks of columns hold four chains side by side, with the few-row
+// kernel's bits; wider ones add up K in quarters (four chains of 5 blocks are 320 registers that the compiler copies between its two files: 18944 x 3584, 64
+// rows 61.5 us; of 6 and 7 they do not fit).  The adds between quarters cost 0.3 to 1 us: us per call on cold weights, one chain and four sums,
+//   rows            48           64           72           128
+//   4864 x 896      8.9/9.4      9.0/9.7      -            -           (2 blocks)
+//   11008 x 4096    38.5/39.0    38.8/39.3    -            -           (3)
+//   14336 x 4096    -            -            49.5/50.1    51.5/52.1   (4)
+//   18944 x 3584    45.5/46.0    45.8/46.5    46.5/47.0    51.1/51.9   (5)
+//   24576 x 6144    112/113      113/114      115/115      120/121     (6)
+//   27648 x 5120    89.6/90.5    90.4/91.4    -            -           (7)
+// Shorter K and the other widths stay in one chain, with the bits of all tiles; above 128 rows the registers are taken.
+static bool mid_glu_four(int M, int wtn, int K) {
+    if (M <= 64) return wtn == 2 || (wtn != 4 && K >= (wtn < 7 ? 1024 : 2560));
+    return M <= 128 && (wtn == 4 ? K >= 512 : (wtn == 5 || wtn == 6) && K >= 2560);
+}
 static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
+    if (mid_glu_four(M, wtn, K)) {
+#define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n, true, n == 2 ? 4 : 1, n == 2 ? 1 : 4>(s, M, N, K, A, Wg, Wu, act);
+        TLT_MID(2, 2) TLT_MID(2, 3) TLT_MID(2, 5) TLT_MID(2, 6) TLT_MID(2, 7)
+        TLT_MID(3, 4) TLT_MID(3, 5) TLT_MID(3, 6)
+        TLT_MID(4, 4) TLT_MID(4, 5) TLT_MID(4, 6)
+#undef TLT_MID
+        return hipErrorInvalidValue;
+    }
 #define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n, true, 1>(s, M, N, K, A, Wg, Wu, act);
-    TLT_MID(2, 2) TLT_MID(2, 3) TLT_MID(2, 4) TLT_MID(2, 5) TLT_MID(2, 6) TLT_MID(2, 7)
+    TLT_MID(2, 3) TLT_MID(2, 4) TLT_MID(2, 5) TLT_MID(2, 6) TLT_MID(2, 7)
     TLT_MID(3, 2) TLT_MID(3, 3) TLT_MID(3, 4) TLT_MID(3, 5) TLT_MID(3, 6) TLT_MID(3, 7)
     TLT_MID(4, 2) TLT_MID(4, 3) TLT_MID(4, 4) TLT_MID(4, 5) TLT_MID(4, 6) TLT_MID(4, 7)
     TLT_MID(5, 3) TLT_MID(5, 4) TLT_MID(5, 5) TLT_MID(5, 6) TLT_MID(5, 7)
