@@ -1220,24 +1220,39 @@ static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, 
 }
 
 // Width of gemm_bf16_mid_k's tiles in blocks of 16 gate and 16 up rows: the fewest that leave at most one workgroup per CU; 0: another kernel.
-// Limits measured against the kernels that ran before (us per call, p10 of 40 calls, cold weights, activations rewritten before every call,
-// about 4 us of event overhead in both figures):
-//   rows            40         64         72         128        160        192        224        256
-//   18944 x 3584    -          -          52.7/49.4  59.6/54.8  66.4/59.4  69.3/65.0  72.3/68.4  74.0/73.3   (5 blocks)
-//   27648 x 5120    -          -          96.0/91.7  104/101    127/110    128/124    133/154    138/157     (7)
-//   24576 x 6144    96.3/96.0  98.8/97.5  101/98     108/105    141/111    142/119    145/126    145/165     (6)
-//   13824 x 5120    -          -          61.8/58.2  72.2/66.4  84.0/74.2  84.2/74.5  86.7/79.5  87.4/81.6   (4)
-//   11008 x 4096    -          -          42.0/36.9  47.9/43.3  64.9/50.0  68.2/53.2  73.6/55.8  79.0/59.3   (3)
-//   8192 x 4096     29.0/26.0  30.3/28.7  41.6/29.1  45.8/35.4  41.3/40.7  42.6/45.3  44.1/48.0  46.5/49.0   (2)
-// Wide tiles with many rows have two slots only and lose; two blocks leave half of the chip idle.  At five blocks 256 rows are even alone and 2 %
-// slower in a step (eight waves draw more power than four of 64 rows).  With K below 1024 the wide ones still gain (18944 x 512, 128 rows: 16.8 ->
-// 15.3), the narrow ones above 128 rows (11008 x 512: 160 rows 16.0 -> 13.6) and up to 64 rows two blocks (4864 x 896: 15.9 -> 15.0).
+// From 65 rows on, measured against the tiled kernels and a few-row kernel with two groups of waves (us per call, p10 of 40 calls, cold weights, activations
+// rewritten before every call, about 4 us of event overhead in both figures, sums in one chain; *: rings of two slots, which lose and are not built):
+//   rows            72         128        160        192        224        256
+//   18944 x 3584    52.7/49.4  59.6/54.8  66.4/59.4  69.3/65.0  72.3/68.4  74.0/73.3    (5 blocks)
+//   27648 x 5120    96.0/91.7  104/101    127/110    128/124    133/154*   138/157*     (7)
+//   24576 x 6144    101/98     108/105    141/111    142/119    145/126    145/165*     (6)
+//   13824 x 5120    61.8/58.2  72.2/66.4  84.0/74.2  84.2/74.5  86.7/79.5  87.4/81.6    (4)
+//   11008 x 4096    42.0/36.9  47.9/43.3  64.9/50.0  68.2/53.2  73.6/55.8  79.0/59.3    (3)
+//   8192 x 4096     41.6/29.1  45.8/35.4  41.3/40.7  42.6/45.3  44.1/48.0  46.5/49.0    (2)
+// Two blocks leave half of the chip idle.  At five blocks 256 rows are even alone and 2 % slower in a step (eight waves draw more power than four of 64 rows).
+// With K below 1024 the wide ones still gain (18944 x 512, 128 rows: 16.8 -> 15.3), and the narrow ones above 128 rows (11008 x 512: 160 rows 16.0 -> 13.6).
+// At 33 to 64 rows against the 64-row tiles (short K, four blocks) and the few-row kernel with 64 rows (the others), a graph of calls on cold weights, no
+// event between them, four sums where there are four:
+//   rows            33         48         64
+//   4864 x 768      7.8/7.6    8.4/7.8    9.0/8.3      (2 blocks)
+//   8192 x 3584     22.2/21.8  23.3/22.6  24.9/23.9
+//   11008 x 1024    11.8/11.9  12.2/12.1  12.9/12.4    (3)
+//   11008 x 3584    28.9/28.4  30.2/29.3  32.1/30.6
+//   18944 x 512     13.2/11.0  13.3/11.1  13.7/11.3    (5)
+//   18944 x 1536    24.6/24.5  25.4/24.7  26.8/25.2
+//   18944 x 3584    45.6/45.3  47.0/46.1  48.4/46.8
+//   24576 x 512     13.7/12.7  13.8/12.8  14.3/12.9    (6)
+//   24576 x 3584    56.5/56.6  57.3/57.0  58.5/57.4
+//   27648 x 5120    90.2/90.1  92.2/91.2  92.1/91.9    (7)
+// Not at four blocks, where the tiles come out at one per CU too and the ring is shorter (14336 x 1024 12.9/13.5 at 33 rows, x 2560 29.4/31.4 at 64, x 5120
+// 53.1/55.9; x 3584 38.0/37.8), nor at seven with K below 2560 (28672 x 128 7.7/8.6 at 33 rows, x 512 14.2/14.6, x 2048 51.1/52.3; x 1536 33.9/33.4).
 static int mid_glu_width(int M, int N, int K) {
     int wtn = 2;
     while ((N + 16 * wtn - 1) / (16 * wtn) > 256) ++wtn;
+    if (M <= 32 || wtn > 7 || (wtn == 4 && M <= 64)) return 0;
     const int rows = wtn == 2 ? 128 : wtn <= 4 ? 256 : wtn <= 6 ? 224 : 192;
-    const int k_min = wtn >= 5 || (wtn == 2 && M <= 64) ? 64 : (wtn == 4 && M > 64) || M > 128 ? 512 : 1024;
-    return wtn <= 7 && M > 32 && M <= rows && K >= k_min ? wtn : 0;
+    const int k_min = wtn == 7 && M <= 64 ? 2560 : wtn >= 5 || (wtn == 2 && M <= 64) ? 64 : wtn == 4 || M > 128 ? 512 : 1024;
+    return M <= rows && K >= k_min ? wtn : 0;
 }
 // Whether the tile's sums over K are four (long K up to 128 rows; gemm_bf16_few_k has four at up to 32): one chain errs twice as far.  Rms error of an up sum
 // to float64, four and one: K 1024 1.0e-7 and 1.8e-7, 3584 1.8e-7 and 3.7e-7.  Two blocks of columns hold four chains side by side, with the few-row
@@ -1252,8 +1267,8 @@ static int mid_glu_width(int M, int N, int K) {
 //   27648 x 5120    89.6/90.5    90.4/91.4    -            -           (7)
 // Shorter K and the other widths stay in one chain, with the bits of all tiles; above 128 rows the registers are taken.
 static bool mid_glu_four(int M, int wtn, int K) {
-    if (M <= 64) return wtn == 2 || (wtn != 4 && K >= (wtn < 7 ? 1024 : 2560));
-    return M <= 128 && (wtn == 4 ? K >= 512 : (wtn == 5 || wtn == 6) && K >= 2560);
+    if (M <= 64) return wtn == 2 || K >= 1024;
+    return M <= 128 && (wtn == 4 || ((wtn == 5 || wtn == 6) && K >= 2560));
 }
 static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, const void* A, const void* Wg, const void* Wu, void* act) {
     if (mid_glu_four(M, wtn, K)) {
@@ -1265,9 +1280,9 @@ static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, co
         return hipErrorInvalidValue;
     }
 #define TLT_MID(nw, n) if ((M + 31) / 32 == nw && wtn == n) return launch_mid<nw, n, true, 1>(s, M, N, K, A, Wg, Wu, act);
-    TLT_MID(2, 3) TLT_MID(2, 4) TLT_MID(2, 5) TLT_MID(2, 6) TLT_MID(2, 7)
-    TLT_MID(3, 2) TLT_MID(3, 3) TLT_MID(3, 4) TLT_MID(3, 5) TLT_MID(3, 6) TLT_MID(3, 7)
-    TLT_MID(4, 2) TLT_MID(4, 3) TLT_MID(4, 4) TLT_MID(4, 5) TLT_MID(4, 6) TLT_MID(4, 7)
+    TLT_MID(2, 5) TLT_MID(2, 6)
+    TLT_MID(3, 2) TLT_MID(3, 3) TLT_MID(3, 5) TLT_MID(3, 6) TLT_MID(3, 7)
+    TLT_MID(4, 2) TLT_MID(4, 3) TLT_MID(4, 5) TLT_MID(4, 6) TLT_MID(4, 7)
     TLT_MID(5, 3) TLT_MID(5, 4) TLT_MID(5, 5) TLT_MID(5, 6) TLT_MID(5, 7)
     TLT_MID(6, 3) TLT_MID(6, 4) TLT_MID(6, 5) TLT_MID(6, 6) TLT_MID(6, 7)
     TLT_MID(7, 3) TLT_MID(7, 4) TLT_MID(7, 5) TLT_MID(7, 6)
