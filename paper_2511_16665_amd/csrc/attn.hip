@@ -295,8 +295,13 @@ __global__ __launch_bounds__(64 * kRowWaves) void attn_rope_rows_k(Rows rows, KV
     o[threadIdx.x] = ll > 0.f ? a / ll : 0.f;
 }
 
+// Up to 512 keys, by the bound that the host knows: a key's pointer may be the LDS's or the memory's, and loads through such are slower than the row
+// attention's global ones, which shows where the keys are the time.  Us per block of a forward, rotary kernel and row attention against this one, heads of 64,
+// one sequence of 8 rows and 32 of them: 20 keys 24.5/22.6 and 34.6/33.4, 130 24.8/23.5 and 38.3/37.3, 500 29.4/28.4 and 53.2/53.2, 1000 37.4/38.2 and
+// 73.7/78.4, 4000 77.3/89.2 and 207/228; heads of 128, 4 rows: 500 36.6/36.3 and 63.2/61.6, 1000 48.8/49.3 and 98.6/98.0, 12000 301/317 (one sequence).
+constexpr int kRopeMaxKeys = 512;
 bool attention_rope_supported(int dtype, const Rows& rows, const KVLayer& kv, const void* qkv, const void* bias) {
-    return dtype == F32 && !rows.shared_ctx && kv.d % 64 == 0 && kv.d <= 256 && rows.n * (kv.d / 2) <= 64 * kRowWaves &&
+    return dtype == F32 && !rows.shared_ctx && (int64_t)kv.seq_len_bound + rows.n_region <= kRopeMaxKeys && kv.d % 64 == 0 && kv.d <= 256 && rows.n * (kv.d / 2) <= 64 * kRowWaves &&
            rows.n_region == rows.slot_base + rows.n && (((uintptr_t)qkv | (uintptr_t)kv.k | (uintptr_t)kv.v | (uintptr_t)bias) & 15) == 0;
 }
 
