@@ -1360,14 +1360,15 @@ __global__ void seq_len_advance_k(int B, int32_t* seq_len, const int32_t* accept
 }
 
 // ------------------------------------------------------------------------------------------------
-constexpr int kArgmaxShort = 4096;
 hipError_t row_argmax(hipStream_t s, int M, int V, const float* logits, int32_t* out, void* scratch, size_t scratch_bytes) {
     if (M <= 0) return hipSuccess;
-    // few rows: a row's scan over several workgroups (a single one pulls the 600 KB row through one CU's load path: 45 us); a short row is one load per
-    // thread and not worth a second kernel (1024 logits, 10 rows: 2.4 + 2.2 us -> 2.3)
+    // few rows: a row's scan over several workgroups (a single one pulls the 600 KB row through one CU's load path: 45 us); a short row is one to four
+    // 16-byte loads per thread, or up to eight of 4 bytes, and not worth a second kernel.  Us of a forward of one small block with two kernels and with one, 1, 10 and
+    // 64 rows: 1024 logits 30.8/26.6, 35.2/30.4 and 36.2/33.9; 2048 30.7/27.0, 35.1/30.7 and 36.4/34.4; 4096 31.1/28.0, 35.2/31.4 and 37.2/35.9; element by element
+    // 2047 31.1/28.8, 35.0/32.7 and 36.9/36.5, but 2501 31.2/29.9, 35.4/33.7 and 37.7/37.8, 4095 30.8/31.1, 35.3/35.1 and 38.1/39.4.
     int S = M < 128 ? 256 / M : 1;
     S = S > 32 ? 32 : S;
-    if (V <= kArgmaxShort) S = 1;
+    if (V <= (V % 4 == 0 && ((uintptr_t)logits & 15) == 0 ? 4096 : 2048)) S = 1;
     if (S >= 2 && scratch && ((uintptr_t)scratch & 7) == 0 && (size_t)M * S * 8 <= scratch_bytes) {
         const int seg = ((V + S - 1) / S + 3) / 4 * 4;
         float* pv = (float*)scratch;

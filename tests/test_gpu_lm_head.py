@@ -1,9 +1,14 @@
 """Wide products of up to 256 rows: tiles of 64 rows, launches cut into whole rounds and a rest, K shorter than the load ring."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2511_16665_amd import binding as tlt
+from synth import TINY
+
+from gpu_util import make_engine, make_models
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +66,24 @@ def test_row_argmax_over_whole_rounds_and_rest(M, N, K, ties):
     else:
         best = want.max(axis=1)
         assert np.all(want[np.arange(M), got] >= best - 2.0 ** -24 * K * np.abs(want).max())
+
+
+@pytest.mark.parametrize("V", [63, 2047, 2048, 2049, 4095, 4096, 4097, 4100])   # one kernel up to 2048 logits, or 4096 in 16-byte pieces; two
+def test_argmax_of_short_rows(V):
+    """The first of the largest logits, with ties, at one row and at several."""
+    cfg = dataclasses.replace(TINY, name=f"tiny-v{V}", n_layers=1, hidden=64, mlp=64, vocab=V)
+    tw, dw, _, _ = make_models(cfg, 5, "fp32", std=0.2)
+    rng = np.random.default_rng(V)
+    for j in rng.permutation(V)[: 3 * V // 4]:                      # most rows twice or more
+        tw["lm_head"][j] = tw["lm_head"][rng.integers(V)]
+    for B, n in ((1, 1), (2, 5), (4, 16), (3, 64)):
+        e, _, _ = make_engine(cfg, "fp32", tw, dw, B, 64, 2, 2, 128, seed=3, seq_len=np.full(B, 20, np.int32))
+        t = e.tree(n)
+        t.parent.copy_(torch.from_numpy(np.tile(np.arange(-1, n - 1, dtype=np.int32), (B, 1))))
+        t.token.copy_(torch.from_numpy(rng.integers(V, size=(B, n)).astype(np.int32)))
+        e.ctx.tree_finalize(B, t)
+        logits, am = torch.empty((B, n, V), device="cuda"), torch.full((B, n), -7, dtype=torch.int32, device="cuda")
+        print(f"argmax of short rows V={V} rows={B * n}", flush=True)
+        e.ctx.verify_forward(B, t, e.kv, out_logits=logits, out_argmax=am)
+        np.testing.assert_array_equal(am.cpu().numpy(), logits.cpu().numpy().argmax(-1))
+        e.ctx.close()
