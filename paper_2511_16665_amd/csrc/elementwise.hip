@@ -508,10 +508,11 @@ static void rmsnorm_launch_t(hipStream_t s, int M, int h, float* x, const void* 
         // flight at once.  (Few rows and up to four slices, against 256 threads, us per norm inside a forward of 1-32 rows: widths
         // 3584 and 4096 1.4 less, 1536 0.4 less, 256 to 1024 and 2048 the same within 0.3, though most waves are idle at 256.)
         plain ? launch(rmsnorm_vec_k<T, 1, TA, true, 12, 1024>, 1024) : launch(rmsnorm_vec_k<T, 1, TA, false, 12, 1024>, 1024);
-    else if (vec_ok && h > 4096 && h <= 8192 && add && sizeof(TA) == 4)
+    else if (vec_ok && h > 4096 && h <= 8192 && M <= 512 && add && sizeof(TA) == 4)
         // (wider rows: two positions per thread and up to eight slices of each in flight; with 256 threads eight positions waited for their slices one
         // after the other.  Width 5120, us per norm inside a step, 256 threads and 1024: 25 rows 5.8 and 4.4, 112 rows 8.3 and 5.3, 150 rows 7.3 and 5.8, 512 rows
-        // 12.9 and 12.4, where the slices' bytes count.)
+        // 12.9 and 12.4.  With more rows the chip is full of either and the bytes count: medians over widths 4608 to 8192, 512 rows 10.0 and 10.0, 1024 16.8 and 18.5,
+        // 2048 30.1 and 33.1, 4096 54.4 and 62.3.)
         plain ? launch(rmsnorm_vec_k<T, 2, TA, true, 8, 1024>, 1024) : launch(rmsnorm_vec_k<T, 2, TA, false, 8, 1024>, 1024);
     else if (vec_ok && h <= 4096)
         plain ? launch(rmsnorm_vec_k<T, 4, TA, true>, 256) : launch(rmsnorm_vec_k<T, 4, TA, false>, 256);

@@ -147,6 +147,12 @@ def test_bf16_forward_few_rows(hidden, heads, n):
     _verify_matches_oracle(cfg, "bf16", 2e-2, n, [70], 0.02, -1)
 
 
+def test_bf16_forward_of_576_rows_of_4608_elements():
+    """More than 512 rows wider than 4096: the norms with 256 threads."""
+    cfg = dataclasses.replace(MID, name="mid-h4608", hidden=4608, n_q_heads=36, n_kv_heads=4, mlp=1024, vocab=256, n_layers=1)
+    _verify_matches_oracle(cfg, "bf16", 2e-2, 64, [3, 70, 0, 1, 16, 5, 9, 33, 2], 0.02, -1)
+
+
 @pytest.mark.parametrize("dtype,d", [("fp32", 64), ("fp32", 192), ("fp32", 256), ("bf16", 64), ("bf16", 192)])
 def test_row_attention_head_dims(dtype, d):
     """Value rows spread over the lanes: 4, 1 (with idle lanes), 1, 8 and 2 rows (with idle lanes) at a time."""
