@@ -44,15 +44,16 @@ def _check_row(tokens, logp, a, K, slack):
 
 
 # segments of 2048 logits and K of them per lane of a merging wave: 5, 10 and 20 in registers, or none; more than 128 segments; rows whose
-# last segment is short, whose length is not a multiple of four, shorter than a wave
+# last segment is short, whose length is not a multiple of four, shorter than a wave; rows of one segment, whole and in part, in 16-byte pieces
 @pytest.mark.parametrize("V,K,D,B", [(4099, 2, 3, 3), (50, 5, 3, 2), (152064, 4, 2, 2), (152064, 8, 3, 1), (152064, 10, 3, 2), (152063, 16, 2, 1),
-                                     (200001, 16, 3, 1), (270336, 2, 3, 2), (270339, 10, 2, 2), (6144, 16, 3, 2)])
+                                     (200001, 16, 3, 1), (270336, 2, 3, 2), (270339, 10, 2, 2), (6144, 16, 3, 2),
+                                     (1024, 4, 4, 2), (1024, 16, 3, 3), (2048, 16, 3, 2), (2044, 8, 3, 2), (2047, 10, 3, 2)])
 def test_levels_hold_the_best_candidates_and_their_scores(V, K, D, B):
     cfg = dataclasses.replace(TINY, n_layers=1, hidden=64, mlp=64, vocab=V)
     tw, dw, _, _ = make_models(cfg, 5, "fp32", std=0.2)
     rng = np.random.default_rng(V)
     a = rng.integers(-3 << 17, (3 << 17) + 1, size=V) * 2.0 ** -20   # in [-0.375, 0.375]
-    if V > 4096:
+    if V > 1000:
         a[rng.integers(0, V, size=V // 8)] = 0.375                   # many equal ones near the top, on both sides
         a[rng.integers(0, V, size=V // 8)] = -0.375
     ends = rng.permutation(V - 1)[:3]

@@ -1,6 +1,6 @@
 """The few-row kernels at the edges of their tiles: fp32 products (16 weight rows x 16, 32 or 64 activation rows per
 workgroup, K in pieces of 16 dealt over four waves), bf16 gate/up products (tiles of 32 to 112 columns, K steps through a
-ring of slots), bf16 products kept as partial sums, and the paths of the decoder block that use them."""
+ring of slots; from 33 rows on a wave per 32 rows), bf16 products kept as partial sums, and the paths of the decoder block that use them."""
 import dataclasses
 
 import numpy as np
@@ -70,12 +70,13 @@ def test_fp32_forward(n, ctxs, mlp):
     (32, 16512, 64), (64, 20480, 1024),         # 80 columns
     (5, 20608, 128), (40, 24576, 1024),         # 96 columns
     (31, 24704, 512), (64, 28672, 2560),        # 112 columns
-    (65, 12416, 512), (128, 16384, 576),        # above 64 rows: two groups of waves, 64 columns
+    (65, 12416, 512), (128, 16384, 576),        # above 64 rows: three and four waves, 64 columns
     (97, 16512, 2560), (128, 20608, 2624),      # 80 and 96 columns, partial last tiles
-    (33, 12288, 576), (64, 20480, 448), (40, 24576, 64), (31, 24704, 128), (64, 28672, 192),   # K too short for it: the tiled kernel
-    (65, 12416, 384), (128, 16384, 64), (97, 16512, 320), (128, 20608, 128),
-    (64, 14336, 128), (66, 640, 128), (100, 24704, 64),       # beside the ranges: the tiled kernel
-    (129, 16512, 64), (200, 12800, 448), (256, 20480, 192),   # 256 rows x 80 columns, gate and up rows in turns of 16
+    (33, 12288, 576), (64, 20480, 448), (40, 24576, 64), (31, 24704, 128), (64, 28672, 192),   # K too short for four sums: one chain, in the tiled
+    (65, 12416, 384), (128, 16384, 64), (97, 16512, 320), (128, 20608, 128),                   # kernel or with a wave per 32 rows
+    (64, 14336, 128), (66, 640, 128), (100, 24704, 64),       # beside the ranges: one chain
+    (129, 16512, 64),                                         # five waves, the last one with a row
+    (200, 12800, 448), (256, 20480, 192),                     # 256 rows x 80 columns, gate and up rows in turns of 16
     (250, 20608, 192),                                        # one more column tile: 256x256 tiles
 ])
 def test_bf16_gate_up(M, N, K):
@@ -97,9 +98,9 @@ def test_bf16_gate_up(M, N, K):
 
 
 @pytest.mark.parametrize("M,N,K", [(33, 8320, 960), (64, 24576, 960), (32, 28672, 448), (64, 28672, 2496), (65, 13824, 448), (128, 18944, 2496)])
-def test_bf16_gate_up_with_short_k_takes_the_tiled_kernel(M, N, K):
-    """One K step less than the few-row kernel asks for: the same bits as the first rows of a product of 300 rows (the tiled kernels
-    all add up K in one order, the few-row kernel in four)."""
+def test_bf16_gate_up_with_short_k_takes_one_chain(M, N, K):
+    """One K step less than four sums over K ask for: the same bits as the first rows of a product of 300 rows (one chain over K, in the tiled kernels and
+    with a wave per 32 rows)."""
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     A = torch.randn((300, K), generator=g, device="cuda").bfloat16()
     W, U = ((torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16() for _ in range(2))

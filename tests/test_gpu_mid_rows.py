@@ -7,7 +7,7 @@ from paper_2511_16665_amd import binding as tlt
 pytestmark = pytest.mark.gpu
 
 
-FOUR_SUMS = [(33, 8192, 64), (64, 640, 1024), (63, 8320, 1024), (96, 16384, 512)]   # of the cases below: not in one chain over K
+FOUR_SUMS = [(33, 8192, 64), (64, 640, 1024), (63, 8320, 1024), (96, 16384, 512), (96, 18944, 2560), (72, 24576, 2560)]   # of the cases below: not in one chain
 
 
 @pytest.mark.parametrize("M,N,K", [
@@ -18,6 +18,9 @@ FOUR_SUMS = [(33, 8192, 64), (64, 640, 1024), (63, 8320, 1024), (96, 16384, 512)
     (224, 20480, 192), (65, 20608, 64), (192, 24576, 128), (224, 20608, 448),   # five, six
     (64, 24704, 64), (127, 28672, 192), (130, 24704, 128), (192, 28672, 64),    # seven
     (257, 16512, 128), (225, 16512, 128), (193, 28672, 64), (32, 16512, 64),    # beside the ranges
+    (66, 12288, 1088), (161, 11008, 576), (200, 12288, 576), (130, 16384, 576), (224, 13824, 576), (96, 18944, 2560),   # with these every pair of waves and blocks
+    (66, 18944, 64), (192, 18944, 192), (64, 24576, 64), (96, 24576, 64), (72, 24576, 2560), (150, 22016, 128),
+    (96, 27648, 192),
 ])
 def test_bf16_gate_up(M, N, K):
     """The same bits as the first rows of a product of 300 rows (one chain over K in all tiles), but for long K up to 128 rows and for 32 rows, which
@@ -96,6 +99,29 @@ def test_bf16_parts(M, N, K):
     assert bool(((got - A.double() @ W.double().T).abs() <= err).all())
     again = tlt.gemm_parts(A, W, torch.empty_like(buf))
     assert torch.equal(parts, again)
+
+
+@pytest.mark.parametrize("M,N,K,slices,chains", [
+    (33, 3584, 1536, 4, 4), (64, 4608, 2048, 3, 4), (65, 2560, 2112, 5, 4), (96, 3584, 3584, 4, 4), (97, 7168, 1024, 2, 4), (128, 4096, 4096, 4, 4),
+    (127, 8192, 2048, 2, 4), (40, 1536, 4096, 10, 4), (128, 2048, 3072, 8, 4),
+    (129, 5120, 8192, 6, 2), (160, 10240, 1536, 3, 2), (161, 8192, 5120, 4, 2), (192, 14336, 2048, 2, 2), (193, 6144, 3584, 5, 2), (224, 3584, 8192, 9, 2),
+    (225, 5120, 8192, 6, 2), (256, 10240, 2048, 3, 2),
+    (80, 8192, 4096, 4, 1), (225, 3584, 18944, 9, 1), (129, 3584, 3584, 4, 1), (72, 14336, 1024, 2, 1),          # beside the ranges: the tiled kernel's cuts, in one chain each
+])
+def test_bf16_parts_cuts_and_their_error(M, N, K, slices, chains):
+    """How many slices, and their error to float64 in the root of the mean square, against that of a random walk.  A chain of m matrix instructions of 16
+    products, m = K / 16 / (slices * chains), rounds its partial sum twice in each; a rounding errs by 0.43 * 2^-24 of the value in the mean (uniform within half a
+    unit, mantissas spread over their logarithm), and the squares of the growing sums are m / 2 of a result's for all chains of an element together.
+    The chains of a slice meet in at most as many additions; the slices are added in float64 here.  0.5 for 0.43: one chain in the place of several is outside."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    W = (torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16()
+    print(f"slices M={M} N={N} K={K}", flush=True)
+    parts = tlt.gemm_parts(A, W, torch.empty(12 * M * N, device="cuda"))
+    want = A.double() @ W.double().T
+    err, bound = float((parts.double().sum(0) - want).norm() / want.norm()), 0.5 * 2.0 ** -24 * (K / 16 / (slices * chains) + chains) ** 0.5
+    print(f"  {parts.shape[0]} slices, error {err:.2e}, bound {bound:.2e}", flush=True)
+    assert parts.shape[0] == slices and err <= bound
 
 
 @pytest.mark.parametrize("M,N,K", [

@@ -79,3 +79,23 @@ def test_cuts_along_k_fit_the_chip_the_buffer_and_the_ring(rules):
                         tiles = N // (64 if M <= 128 else 128)
                         assert 32 < M <= 256 and 2 <= cuts.value <= room and 200 <= tiles * cuts.value <= 256 and K // 64 // cuts.value >= 6
     assert taken > 1000
+
+
+def test_every_gate_up_instance_is_run_by_the_product_tests(rules):
+    """By the cases that compare products of random operands, from their parameters."""
+    test_gpu_mid_rows, test_gpu_few_rows = (pytest.importorskip(m) for m in ("test_gpu_mid_rows", "test_gpu_few_rows"))
+    run = set()
+    for f in (test_gpu_mid_rows.test_bf16_gate_up, test_gpu_few_rows.test_bf16_gate_up):
+        for M, N, K in f.pytestmark[0].args[1]:
+            wtn = rules.x_mid_glu_width(M, N, K)
+            if wtn:
+                run.add((bool(rules.x_mid_glu_four(M, wtn, K)), (M + 31) // 32, wtn))
+    assert run == _glu_instances()
+
+
+def test_the_gate_up_cases_are_told_apart_by_their_sums(rules):
+    """The cases that are compared bit for bit with one chain are those that have one."""
+    m = pytest.importorskip("test_gpu_mid_rows")
+    for M, N, K in m.test_bf16_gate_up.pytestmark[0].args[1]:
+        wtn = rules.x_mid_glu_width(M, N, K)
+        assert ((M, N, K) in m.FOUR_SUMS) == bool(wtn and rules.x_mid_glu_four(M, wtn, K)), (M, N, K)
