@@ -322,7 +322,8 @@ __global__ __launch_bounds__(256) void row_topk_seg_k(int V, int K, int n_seg, c
 // all MR: with 5 instead of 10 an expansion of five levels takes 247 instead of 262 us (32000 tokens, K = 8, one sequence; 16 of them 350 and
 // 362; 152064 tokens, K = 4, 257 and 272).
 // ROW: rows of a single segment come straight from the logits (1; 2: not in 16-byte pieces) and each wave selects its own row's K best first, with
-// the same result: a launch less per level (a step of a tiny decoder's four levels, vocabulary 1024, 7.8 -> 3.6 us a level).
+// the same result: a launch less per level (a step of a tiny decoder's four levels, vocabulary 1024, 7.8 -> 3.6 us a level).  An expansion of four levels, us, K =
+// 8, with two kernels a level and with one: vocabulary 1024, 1 sequence 166/137, 32 205/180, 128 639/638; 2048, 157/137, 202/189, 630/638 (K = 16: 898/876).
 template <int MR, int ROW = 0>
 __global__ __launch_bounds__(1024) void draft_level_k(int K, int level, int n_seg, const float* __restrict__ seg_stat,
                                                       const float* __restrict__ seg_val, const int32_t* __restrict__ seg_idx,
