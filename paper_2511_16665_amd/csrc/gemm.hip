@@ -1242,8 +1242,10 @@ static hipError_t launch_mid(hipStream_t s, int M, int N, int K, const void* A, 
 //   18944 x 1536    24.6/24.5  25.4/24.7  26.8/25.2
 //   18944 x 3584    45.6/45.3  47.0/46.1  48.4/46.8
 //   24576 x 512     13.7/12.7  13.8/12.8  14.3/12.9    (6)
+//   22016 x 1024    19.0/19.9  19.8/20.1  20.6/20.2
 //   24576 x 3584    56.5/56.6  57.3/57.0  58.5/57.4
 //   27648 x 5120    90.2/90.1  92.2/91.2  92.1/91.9    (7)
+// (K 1024 at 33 to 40 rows is where the adds between quarters show, 0.1 to 0.9 us; a K from 1536 on hides them.)
 // Not at four blocks, where the tiles come out at one per CU too and the ring is shorter (14336 x 1024 12.9/13.5 at 33 rows, x 2560 29.4/31.4 at 64, x 5120
 // 53.1/55.9; x 3584 38.0/37.8), nor at seven with K below 2560 (28672 x 128 7.7/8.6 at 33 rows, x 512 14.2/14.6, x 2048 51.1/52.3; x 1536 33.9/33.4).
 static int mid_glu_width(int M, int N, int K) {
