@@ -1314,8 +1314,7 @@ static hipError_t launch_mid_glu(hipStream_t s, int wtn, int M, int N, int K, co
 //     14336 x 5120   44.4/41.1    47.1/43.8    48.9/45.0    51.6/48.0    53.9/50.7   (2)
 //   (above 224 rows nothing is padding, and in less than 5120 columns the gain is -4 to +2 %; with long K it is -3 % at 4608 x 18944 and 3584 x 18944, +6 and +7 % at
 //   4608 x 14336 and 4096 x 28672, which stay where they were.)  Where the general plan prefers fewer, longer cuts of wide tiles (3584 x 3584: 4) it is ahead by 1
-//   to 6 %.  The gain is the card's too: from 193 rows on two cards showed 0 to +13 % over this range, a third -4 to +5 %, and at 2560 columns from 129 rows on +3 to
-//   +9 % and -2 to -9 %.
+//   to 6 %.  The gain is the card's too: from 193 rows on two cards showed 0 to +13 % over this range, two others -4 to +6 %.
 // The kernel's two or four chains per cut keep the serial sums no longer than the general plan's in either case; error to float64 (slices added in fp32) 1.24e-7 ->
 // 0.98e-7 at 3584 x 3584, 2.8e-7 -> 2.0e-7 at 3584 x 18944, even where this kernel has half of the cuts (14336 x 8192 at 136 rows: 2.73e-7 either way).
 static bool mid_split_plan(int M, int N, int K, int general_cuts, int max_cuts, int* cuts) {
