@@ -356,12 +356,12 @@ constexpr int kAhead = 2;                   // tiles of K/V in flight; one more 
 constexpr int kStageElems = 2 * kKT * kD;   // one stage: K tile then V tile, 16 KB each
 constexpr float kNegBig = -1e30f;
 constexpr int kMaxRows = 128;    // rows per sequence whose visibility bits are kept in LDS
-constexpr int kMaxChunk = 4096;  // keys per chunk: bounds the page-id table kept in LDS
+constexpr int kMaxChunk = 16384; // keys per chunk: bounds the page-id table kept in LDS
 
 // Work decomposition.  A work item is (sequence, key range); each item is run by n_kv * row_groups
 // workgroups.  The key ranges are cut ON THE DEVICE from the actual sequence lengths (the host only
 // knows an upper bound): a one-workgroup planning kernel picks the item length so that the chip
-// gets whole rounds of items (kMinTiles .. 64 tiles of 64 keys), gives every sequence equally long chunks,
+// gets whole rounds of items (kMinTiles .. 256 tiles of 64 keys), gives every sequence equally long chunks,
 // and lists the items longest first.  Workgroups are dispatched in list order, so the long items
 // start first and the short ones fill the tail (longest-processing-time-first list scheduling).
 struct AttnItem {
@@ -392,8 +392,8 @@ static AttnPlan plan_attention(int B, int n, int G, int n_kv, int bound_total) {
     const int per_wave = (per_group + 7) / 8;
     p.tpw = per_wave <= 1 ? 1 : (per_wave <= 2 ? 2 : 3);
     p.heads = n_kv * p.row_groups;
-    // items <= sum_b ceil(tiles_b / T) <= total_tiles / T + B, and the planner picks T so that they fill
-    // whole rounds of 256 workgroups with T <= 64: items * heads <= 256 * ceil((total_tiles / 64 + B) * heads / 256)
+    // items <= sum_b ceil(tiles_b / T) <= total_tiles / T + B, and the planner picks no more rounds of 256 workgroups than
+    // T = 64 needs: items * heads <= 256 * ceil((total_tiles / 64 + B) * heads / 256)
     const int64_t tiles_bound = (int64_t)B * ((bound_total + kKT - 1) / kKT);
     const int64_t a = (256 + p.heads - 1) / p.heads, c = (tiles_bound + 63) / 64;
     p.max_items = 2 * B + (int)(a + c);
@@ -408,6 +408,7 @@ static size_t attn_work_bytes(int B, int max_items) {
 // result to the merge (one sequence of 8192, main + merging kernel: 8 tiles 11.1 + 4.8 us, 4 tiles 8.5 + 6.0, 3 and 2 tiles 8.4
 // + 6.5; three of 5000, 161 query rows: 22.1 + 5.9, 4 tiles 19.9 + 7.4).
 constexpr int kMinTiles = 4;
+constexpr int kRoundTiles = 4;      // what a round of items costs besides its tiles (attn_plan_k)
 constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the planning kernel keeps in LDS
 
 // One workgroup, so a chain of latencies: lengths are read once, and the counting, the search for the chunk size, the running
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
                                                    unsigned int* __restrict__ status, const int32_t* __restrict__ block_table,
                                                    int max_pages, int64_t n_pages, const int32_t* __restrict__ n_valid) {
     extern __shared__ int s_len[];   // [min(B, kPlanCached)] keys of a sequence, then as many first slots
-    __shared__ int s_total, s_items, s_hist[66], s_pos[66], s_count[65];
+    __shared__ int s_total, s_items, s_hist[66], s_pos[66], s_count[2][65];
     int* slot0 = (int*)(work + 1);
     int* nch = slot0 + B;
     AttnItem* items = (AttnItem*)(nch + B);
@@ -432,7 +433,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     auto tiles_of = [&](int b) { return (total_of(b) + kKT - 1) / kKT; };
     auto slot_of = [&](int b) { return b < kPlanCached ? s_slot[b] : slot0[b]; };
     if (tid < 66) s_hist[tid] = 0;
-    if (tid < 65) s_count[tid] = 0;
+    if (tid < 130) ((int*)s_count)[tid] = 0;
     if (tid == 0) s_total = 0;
     __syncthreads();
     int mine = 0;
@@ -446,27 +447,40 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     }
     if (mine) atomicAdd(&s_total, mine);
     __syncthreads();
-    // A workgroup takes a whole CU (248 VGPRs per wave, 128 KB of LDS), so the work items run in rounds of
+    // A workgroup takes a whole CU (248 VGPRs per wave, 134 KB of LDS), so the work items run in rounds of
     // 256.  Measured at the 7B benchmark shape (attention ms per step): one round of 256 items 4.02, two
     // rounds 4.33, four 4.20, and 4.6-4.8 when the count falls between whole rounds (384, 768 items): the
-    // fewest whole rounds that the 64-tile cap on a chunk allows are the target, and of the chunk sizes that
-    // fit them the smallest (items closest to filling the rounds).  Thread (t, part) counts the items of chunk size t.
+    // fewest whole rounds that chunks of 64 tiles allow are the target, and of the chunk sizes that
+    // fit them the smallest (items closest to filling the rounds).  Longer chunks are taken where they save rounds: a round costs
+    // its first fetches and its stores besides its tiles, 4.9 us or kRoundTiles tile periods (64 sequences of 8192, one query row each: three rounds of
+    // 43 tiles 175 us, one of 129 165), against longest chunks that are longer than all the rounds' together where sequences differ (16 of 8192 on
+    // average, lognormal, 8 kv heads: two rounds of 37 tiles are shorter than one of 84).  Thread (t, part) counts the items of a chunk size.
     {
         const int t = (tid & 63) + 1;
         int64_t items_t = 0;
         if (t >= kMinTiles)
             for (int b = wave; b < B; b += 4) items_t += (tiles_of(b) + t - 1) / t;
-        atomicAdd(&s_count[t], (int)(items_t < 0x7fffffff / 256 ? items_t : 0x7fffffff / 256));
+        atomicAdd(&s_count[0][t], (int)(items_t < 0x7fffffff / 256 ? items_t : 0x7fffffff / 256));
     }
     __syncthreads();
-    int T;
+    int T, r;
     {
         const int t = lane + 1;
         const int rounds0 = (int)max(((int64_t)s_total * heads + 256 * 64 - 1) / (256 * 64), (int64_t)1);
-        const int rounds_t = t >= kMinTiles ? (int)(((int64_t)s_count[t] * heads + 255) / 256) : 0x7fffffff;
+        const int rounds_t = t >= kMinTiles ? (int)(((int64_t)s_count[0][t] * heads + 255) / 256) : 0x7fffffff;
         // (longer chunks never make more items: the fewest rounds are those of the longest)
-        const int r = max(__builtin_amdgcn_readlane(rounds_t, 63), rounds0);
+        r = max(__builtin_amdgcn_readlane(rounds_t, 63), rounds0);
         T = __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(rounds_t <= r));   // lane t - 1 stands for t
+    }
+    if (r > 1) {   // (uniform.  The counts are in floating point: a round more or less in an estimate, and never more items than with 64 tiles)
+        const int t = (tid & 63) + 1, size = 64 + 3 * t;   // 67 .. 256
+        const float inv = 1.0f / (float)size;
+        float items_l = 0.f;
+        for (int b = wave; b < B; b += 4) items_l += ceilf((float)tiles_of(b) * inv);
+        atomicAdd(&s_count[1][t], (int)fminf(items_l, (float)(0x7fffffff / 256)));
+        __syncthreads();
+        const float cost = ceilf((float)s_count[1][t] * (float)heads * (1.0f / 256.0f)) * (float)(size + kRoundTiles), best = -wave_max(-cost);
+        if (best < (float)r * (float)(T + kRoundTiles)) T = 64 + 3 * __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(cost == best));
     }
     // chunks of every sequence and the slots they take: running sums, 64 sequences at a time
     if (wave == 0) {
@@ -500,13 +514,14 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         const int tiles = tiles_of(lo), k = (tiles + T - 1) / T, per = (tiles + k - 1) / k, first = (i - slot_of(lo)) * per;
         return Chunk{lo, first * kKT, max(min(per, tiles - first), 0)};
     };
+    auto bin_of = [&](int tiles) { return T <= 64 ? tiles : (tiles * 64 + T - 1) / T; };   // 0 .. 64
     const int n_items = s_items;
-    for (int i = tid; i < n_items; i += 256) atomicAdd(&s_hist[chunk_of(i).tiles], 1);
+    for (int i = tid; i < n_items; i += 256) atomicAdd(&s_hist[bin_of(chunk_of(i).tiles)], 1);
     __syncthreads();
     if (wave == 0) {   // s_pos[t] = items longer than t
         const int h = s_hist[64 - lane];
         int sum = h;
-        for (int o = 1; o < T; o <<= 1) {   // (no chunk is longer than T: the lanes before T's hold zeros)
+        for (int o = 1; o < min(T, 64); o <<= 1) {   // (no bin is beyond min(T, 64): the lanes before hold zeros)
             const int up = __shfl_up(sum, o, 64);
             if (lane >= o) sum += up;
         }
@@ -524,7 +539,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
             const int pg = lp < max_pages && lp * 16 < it.k_end ? block_table[(int64_t)c.b * max_pages + lp] : -1;
             it.page[q] = pg >= 0 && pg < n_pages ? pg : -1;
         }
-        items[atomicAdd(&s_pos[c.tiles], 1)] = it;
+        items[atomicAdd(&s_pos[bin_of(c.tiles)], 1)] = it;
     }
 }
 

@@ -1,0 +1,47 @@
+"""The cut of the cached keys into chunks, at sizes where chunks beyond 64 tiles are taken (few long rounds instead of several short ones)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2511_16665_amd import binding as tlt  # noqa: E402
+from synth import random_block_table  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(Hq, Hkv, n, ctxs, check):
+    d, page, B = 128, 16, len(ctxs)
+    lens = np.array(ctxs, dtype=np.int32)
+    table, n_pages = random_block_table(lens + n + 8, page, seed=5, extra_pages=3)
+    gen = torch.Generator(device="cuda").manual_seed(n + B)
+    k, v = (torch.empty((n_pages, Hkv, page, d), dtype=torch.bfloat16, device="cuda").normal_(0.0, 1.0, generator=gen) for _ in range(2))
+    qkv = (1.5 * torch.randn((B, n, (Hq + 2 * Hkv) * d), generator=gen, device="cuda")).bfloat16()
+    mask = torch.tensor([(1 << (i + 1)) - 1 for i in range(n)], dtype=torch.int64, device="cuda").repeat(B, 1)   # a chain
+    table = torch.from_numpy(table.astype(np.int32)).cuda()
+    kv = tlt.KV(k, v, table, torch.from_numpy(lens).cuda(), int(lens.max()))
+    out = torch.full((B, n, Hq * d), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = tlt.attention_workspace(B, n, Hq, Hkv, d, int(lens.max()) + n + 8)
+    print(f"attention chunks Hq={Hq} Hkv={Hkv} n={n} B={B} longest={lens.max()}", flush=True)
+    assert tlt.attention(tlt.TLT_BF16, Hq, page, qkv, mask, kv, out, ws, 1) == 0
+    torch.cuda.synchronize()
+    for b in check:
+        c, G = int(lens[b]), Hq // Hkv
+        pages = table[b, :(c + n + page - 1) // page].long()
+        K, V = (x[pages].permute(1, 0, 2, 3).reshape(Hkv, -1, d)[:, :c + n].float() for x in (k, v))
+        q = qkv[b, :, :Hq * d].float().view(n, Hkv, G, d)
+        visible = torch.arange(c + n, device="cuda")[None, :] <= c + torch.arange(n, device="cuda")[:, None]
+        for h in range(Hkv):
+            s = (q[:, h].reshape(n * G, d) @ K[h].T) / d ** 0.5
+            s = s.view(n, G, -1).masked_fill(~visible[:, None, :], float("-inf")).view(n * G, -1)
+            want = (torch.softmax(s, -1) @ V[h]).view(n, G, d)
+            got = out[b].float().view(n, Hkv, G, d)[:, h]
+            # (P and the output are rounded to bf16: 2^-8 of the largest output)
+            assert ((got - want).abs().max() <= 1e-2 * want.abs().max()).item(), (b, h)
+
+
+# one round of 130-tile chunks instead of three of 43; one of 103 instead of two of 51, with two short sequences; one of the longest size (256 tiles) instead of
+# four of 64, with one sequence a tile longer than that and two short ones
+@pytest.mark.parametrize("heads,ctxs", [(32, [8200] * 8), (6, [6500] * 38 + [1, 700]), (16, [16383] * 12 + [16400, 5000, 64])])
+def test_chunks_longer_than_64_tiles(heads, ctxs):
+    _run(heads, heads, 1, ctxs, [0, len(ctxs) - 3, len(ctxs) - 2, len(ctxs) - 1])
