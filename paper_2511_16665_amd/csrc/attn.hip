@@ -11,6 +11,8 @@
 //   over the lanes, 16 rows of every lane group together (4 heads of 64, 130 keys: 40 us with one wave and 4-byte loads, one
 //   after the other; 13.7 with four waves, 16-byte key loads and 16 keys' values at a time; 7.6 this way).
 // impl 1 ("MFMA split-KV"): the bf16 / head_dim 128 production kernel, described further down.
+#include <algorithm>
+
 #include "dev_common.h"
 #include "kernels.h"
 
@@ -992,13 +994,17 @@ __global__ __launch_bounds__(512) void attn_mfma_k(const AttnWork* __restrict__ 
 // row), four rows per workgroup; the lanes read a chunk's maximum and sum each, and the outputs of 16 chunks are requested together (on the 17
 // chunks that one sequence of 8192 had at 8 tiles each: 12 us one after the other, 6.3 four at a time, 4.8 this way; on its 33 at 4 tiles
 // 6.1; 3 sequences x 23 nodes 7.3).
+// WPR: waves per row.  With four, a row's chunks are dealt over the waves of a workgroup in blocks of 16, so that up to 64 of them are one trip to memory
+// instead of four (attn_merge_wide); their sums meet in LDS.
+template <int WPR>
 __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __restrict__ work, const float* __restrict__ part_o,
                                                      const float* __restrict__ part_ml, uint16_t* __restrict__ out, int n_seq, int n,
                                                      int n_q_heads, int n_kv, int max_items, int r_pad, float scale_log2,
                                                      const int32_t* __restrict__ n_valid) {
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6), kh = blockIdx.y, b = blockIdx.z, lane = threadIdx.x & 63;
+    static_assert(WPR == 1 || WPR == 4, "a wave or a workgroup per row");
+    const int wave = threadIdx.x >> 6, r = WPR == 1 ? blockIdx.x * 4 + wave : blockIdx.x, kh = blockIdx.y, b = blockIdx.z, lane = threadIdx.x & 63;
     const int G = n_q_heads / n_kv;
-    if (r >= n * G) return;  // wave-uniform
+    if (r >= n * G) return;  // wave-uniform (with four waves per row there are as many workgroups as rows)
     const int i = r / G, gq = r - i * G;
     const int nv = n_valid ? min(n_valid[b], n) : n;
     uint32_t* o = (uint32_t*)(out + ((int64_t)(b * n + i) * n_q_heads + kh * G + gq) * kD);
@@ -1006,8 +1012,8 @@ __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __rest
     const int first = slot0[b];
     int used = slot0[n_seq + b];
     if (first + used > max_items) used = max(max_items - first, 0);
-    if (i >= nv || used <= 0) {
-        o[lane] = 0u;
+    if (i >= nv || used <= 0) {   // (uniform over a row's waves)
+        if (WPR == 1 || wave == 0) o[lane] = 0u;
         return;
     }
     const int64_t pbase = ((int64_t)first * n_kv + kh) * r_pad + r;
@@ -1016,6 +1022,7 @@ __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __rest
     float a0 = 0.f, a1 = 0.f, L = 0.f;
     {
         constexpr int U = 16;
+        const int c_first = WPR == 1 ? 0 : U * __builtin_amdgcn_readfirstlane(wave);
         float2 ml = make_float2(kNegBig, 0.f), v[U];   // lane c: chunk c's (maximum, sum)
         auto fetch = [&](int c0) {
 #pragma unroll
@@ -1023,15 +1030,16 @@ __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __rest
                 v[u] = c0 + u < used ? *(const float2*)(part_o + (pbase + (c0 + u) * pstride) * kD + lane * 2) : make_float2(0.f, 0.f);
         };
         if (lane < used) ml = *(const float2*)(part_ml + (pbase + lane * pstride) * 2);
-        fetch(0);
+        fetch(c_first);
         M = ml.x;
         for (int c = lane + 64; c < used; c += 64) M = fmaxf(M, part_ml[(pbase + c * pstride) * 2]);
         M = wave_max(M);
         float w_lane = exp2f((ml.x - M) * scale_log2);
-        for (int c0 = 0; c0 < used; c0 += U) {
-            if (c0 > 0) fetch(c0);
-            if (c0 > 0 && (c0 & 63) == 0) {
-                ml = c0 + lane < used ? *(const float2*)(part_ml + (pbase + (c0 + lane) * pstride) * 2) : make_float2(kNegBig, 0.f);
+        for (int c0 = c_first; c0 < used; c0 += U * WPR) {
+            if (c0 > c_first) fetch(c0);
+            if (c0 > c_first && (WPR > 1 || (c0 & 63) == 0)) {   // the next 64 chunks' maxima and sums
+                const int m0 = c0 & ~63;
+                ml = m0 + lane < used ? *(const float2*)(part_ml + (pbase + (m0 + lane) * pstride) * 2) : make_float2(kNegBig, 0.f);
                 w_lane = exp2f((ml.x - M) * scale_log2);
             }
 #pragma unroll
@@ -1045,8 +1053,32 @@ __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __rest
             }
         }
     }
+    if constexpr (WPR > 1) {   // the waves' sums, in their order
+        __shared__ float2 s_a[WPR][64];
+        __shared__ float s_l[WPR];
+        s_a[wave][lane] = make_float2(a0, a1);
+        if (lane == 0) s_l[wave] = L;
+        __syncthreads();
+        if (wave != 0) return;
+#pragma unroll
+        for (int w = 1; w < WPR; ++w) {
+            a0 += s_a[w][lane].x;
+            a1 += s_a[w][lane].y;
+            L += s_l[w];
+        }
+    }
     const float inv = L > 0.f ? 1.0f / L : 0.f;
     o[lane] = pack_bf16x2(a0 * inv, a1 * inv);
+}
+// Four waves per row from 17 chunks on (a second batch of 16), as long as the rows' workgroups are at most two per CU: behind that the waves that wait at the
+// barrier are missed elsewhere.  Whole attention call, us, one wave and four, 28 query and 4 kv heads: one sequence of 8192, 1 node 17.4/16.2, 8 nodes 20.1/18.4, 16 nodes
+// 23.9/22.6, 24 nodes (672 rows) 27.3/27.3, 64 nodes 35.7/36.7; of 30000, 8 nodes 27.6/24.4; 2 sequences, 8 nodes 21.7/21.4; 3 of 5000, 4 nodes 19.4/19.2, 23 nodes
+// (1932 rows) 31.6/33.0.  In a forward of one sequence the merge takes 4.4 us instead of 6.0.
+constexpr int kMergeChunks = 17, kMergeRows = 512;
+static bool attn_merge_wide(const AttnPlan& p, int B, int rows, int bound_total) {
+    // chunks that a sequence has on average: a round of items, fewer where they would be shorter than kMinTiles
+    const int per_round = (256 + p.heads - 1) / p.heads, tiles = (bound_total + kKT - 1) / kKT;
+    return rows <= kMergeRows && std::min((per_round + B - 1) / B, (tiles + kMinTiles - 1) / kMinTiles) >= kMergeChunks;
 }
 
 // With the chip full of waves, several rounds of them, a wave's load latency counts once per round: half a wave per row, 16 bytes per lane and
@@ -1150,14 +1182,18 @@ static hipError_t launch_attn_mfma(hipStream_t s, const Rows& rows, const KVLaye
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int R = rows.n * (n_q_heads / kv.n_kv);
-    if ((int64_t)R * kv.n_kv * rows.B <= 4096)   // (waves: half of what the chip holds at once)
-        hipLaunchKernelGGL(attn_combine_few_k, dim3((R + 3) / 4, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
-                           (const float*)part_o, (const float*)part_ml, (uint16_t*)out, rows.B, rows.n, n_q_heads, kv.n_kv, p.max_items, p.r_pad,
-                           scale_log2, rows.n_valid);
-    else
+    if ((int64_t)R * kv.n_kv * rows.B <= 4096) {   // (waves: half of what the chip holds at once)
+        auto few = [&](auto merge, int blocks) {
+            hipLaunchKernelGGL(merge, dim3(blocks, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work, (const float*)part_o, (const float*)part_ml,
+                               (uint16_t*)out, rows.B, rows.n, n_q_heads, kv.n_kv, p.max_items, p.r_pad, scale_log2, rows.n_valid);
+        };
+        if (attn_merge_wide(p, rows.B, R * kv.n_kv * rows.B, kv.seq_len_bound + rows.n_region)) few(attn_combine_few_k<4>, R);
+        else few(attn_combine_few_k<1>, (R + 3) / 4);
+    } else {
         hipLaunchKernelGGL(attn_combine_k, dim3((R + 7) / 8, kv.n_kv, rows.B), dim3(256), 0, s, (const AttnWork*)work,
                            (const float*)part_o, (const float*)part_ml, (uint16_t*)out, rows.B, rows.n, n_q_heads, kv.n_kv, p.max_items, p.r_pad,
                            scale_log2, rows.n_valid);
+    }
     return hipGetLastError();
 }
 

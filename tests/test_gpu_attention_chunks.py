@@ -1,4 +1,5 @@
-"""The cut of the cached keys into chunks, at sizes where chunks beyond 64 tiles are taken (few long rounds instead of several short ones)."""
+"""The cut of the cached keys into chunks, at sizes where a round of the chip decides: chunks beyond 64 tiles (few long rounds instead of several short ones),
+and the merge with four waves per row (17 chunks on, up to 512 rows)."""
 import numpy as np
 import pytest
 
@@ -45,3 +46,10 @@ def _run(Hq, Hkv, n, ctxs, check):
 @pytest.mark.parametrize("heads,ctxs", [(32, [8200] * 8), (6, [6500] * 38 + [1, 700]), (16, [16383] * 12 + [16400, 5000, 64])])
 def test_chunks_longer_than_64_tiles(heads, ctxs):
     _run(heads, heads, 1, ctxs, [0, len(ctxs) - 3, len(ctxs) - 2, len(ctxs) - 1])
+
+
+# sequences of 16, 17 and 65 chunks of the shortest length and one of two; 512 and 513 rows (one row beyond the limit)
+@pytest.mark.parametrize("Hq,Hkv,n,ctxs", [(4, 4, 1, [64 * 64 - 1]), (4, 4, 1, [64 * 64]), (2, 1, 3, [64 * 260 - 3]), (4, 1, 2, [9000, 500]),
+                                           (16, 2, 32, [8000]), (27, 1, 19, [8000])])
+def test_merge_of_many_chunks(Hq, Hkv, n, ctxs):
+    _run(Hq, Hkv, n, ctxs, range(len(ctxs)))
