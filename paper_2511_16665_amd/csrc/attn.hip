@@ -415,7 +415,7 @@ constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the pla
 
 // One workgroup, so a chain of latencies: lengths are read once, and the counting, the search for the chunk size, the running
 // sums and the sort are spread over its threads (once per forward and drafter level; against one thread walking the sequences, in
-// a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.0, 64 sequences 20.9 -> 9.4; called by itself again and again,
+// a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.0, 64 sequences 20.9 -> 9.4, 11.6 with the counts of longer chunks; called by itself again and again,
 // everything warm, 1 to 6 sequences of 30 to 250 the same within 0.3 us).  A step of a scan is a trip through the LDS crossbar:
 // no scan has more of them than its length needs (0.5 us).
 __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ seq_len, int B, int n_region, int heads,
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     // fewest whole rounds that chunks of 64 tiles allow are the target, and of the chunk sizes that
     // fit them the smallest (items closest to filling the rounds).  Longer chunks are taken where they save rounds: a round costs
     // its first fetches and its stores besides its tiles, 4.9 us or kRoundTiles tile periods (64 sequences of 8192, one query row each: three rounds of
-    // 43 tiles 175 us, one of 129 165), against longest chunks that are longer than all the rounds' together where sequences differ (16 of 8192 on
+    // 43 tiles 175 us, one of 129 166), against longest chunks that are longer than all the rounds' together where sequences differ (16 of 8192 on
     // average, lognormal, 8 kv heads: two rounds of 37 tiles are shorter than one of 84).  Thread (t, part) counts the items of a chunk size.
     {
         const int t = (tid & 63) + 1;
