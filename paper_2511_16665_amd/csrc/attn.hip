@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
                                                    unsigned int* __restrict__ status, const int32_t* __restrict__ block_table,
                                                    int max_pages, int64_t n_pages, const int32_t* __restrict__ n_valid) {
     extern __shared__ int s_len[];   // [min(B, kPlanCached)] keys of a sequence, then as many first slots
-    __shared__ int s_total, s_items, s_hist[66], s_pos[66], s_count[2][65];
+    __shared__ int s_total, s_items, s_shortest, s_long, s_hist[66], s_pos[66], s_count[2][65];
     int* slot0 = (int*)(work + 1);
     int* nch = slot0 + B;
     AttnItem* items = (AttnItem*)(nch + B);
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     auto slot_of = [&](int b) { return b < kPlanCached ? s_slot[b] : slot0[b]; };
     if (tid < 66) s_hist[tid] = 0;
     if (tid < 130) ((int*)s_count)[tid] = 0;
-    if (tid == 0) s_total = 0;
+    if (tid == 0) s_total = s_long = 0, s_shortest = 0x7fffffff;
     __syncthreads();
     int mine = 0;
     for (int b = tid; b < B; b += 256) {
@@ -453,10 +453,14 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     // 256.  Measured at the 7B benchmark shape (attention ms per step): one round of 256 items 4.02, two
     // rounds 4.33, four 4.20, and 4.6-4.8 when the count falls between whole rounds (384, 768 items): the
     // fewest whole rounds that chunks of 64 tiles allow are the target, and of the chunk sizes that
-    // fit them the smallest (items closest to filling the rounds).  Longer chunks are taken where they save rounds: a round costs
-    // its first fetches and its stores besides its tiles, 4.9 us or kRoundTiles tile periods (64 sequences of 8192, one query row each: three rounds of
-    // 43 tiles 175 us, one of 129 166), against longest chunks that are longer than all the rounds' together where sequences differ (16 of 8192 on
-    // average, lognormal, 8 kv heads: two rounds of 37 tiles are shorter than one of 84).  Thread (t, part) counts the items of a chunk size.
+    // fit them the smallest (items closest to filling the rounds).  Longer chunks are taken where they are sure to end sooner.  A round
+    // costs its first fetches and its stores besides its tiles: 4.9 us of the attention kernel, 4 tile periods, with one query row per key; of the whole call
+    // 3.5 / 7.8 / 15 us with one / two / three row tiles per wave, whose periods are 1.25 / 1.8 / 2.6 us: with kRoundTiles for all of them the rule
+    // errs towards short chunks.  Long chunks take at most their rounds' number times the longest.  The short plan takes at least what it is for all CUs
+    // together, and what a CU takes that has to run one of its chunks of at least T / 2 in every round.  64 sequences of 8192 with 1 / 23 / 48
+    // query rows (4 kv heads), the whole call: three rounds of 43 tiles 188 / 267 / 392 us, one of 129 181 / 251 / 362.  Lengths that differ much keep the
+    // short chunks, which fill their last round: 15 of 3846 on average, lognormal with 0.2, 16 kv heads, 82.2 us in two rounds of up to 35 tiles, 88.6
+    // in one of 73.  Thread (t, part) counts the items of a chunk size.
     {
         const int t = (tid & 63) + 1;
         int64_t items_t = 0;
@@ -476,13 +480,25 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     }
     if (r > 1) {   // (uniform.  The counts are in floating point: a round more or less in an estimate, and never more items than with 64 tiles)
         const int t = (tid & 63) + 1, size = 64 + 3 * t;   // 67 .. 256
-        const float inv = 1.0f / (float)size;
+        const float inv = 1.0f / (float)size, per_cu = (float)heads * (1.0f / 256.0f);
         float items_l = 0.f;
         for (int b = wave; b < B; b += 4) items_l += ceilf((float)tiles_of(b) * inv);
         atomicAdd(&s_count[1][t], (int)fminf(items_l, (float)(0x7fffffff / 256)));
+        float n_long = 0.f, shortest = 1e9f;   // chunks of at least T / 2 and the shortest of them
+        const float inv_T = __builtin_amdgcn_rcpf((float)T), half_T = 0.5f * (float)T;
+        for (int b = tid; b < B; b += 256) {
+            const float tiles = (float)tiles_of(b), k = ceilf((tiles - 0.5f) * inv_T), per = ceilf((tiles - 0.5f) * __builtin_amdgcn_rcpf(k));
+            const float full = floorf((tiles + 0.5f) * __builtin_amdgcn_rcpf(per)), rest = tiles - full * per;
+            if (tiles > 0.f && per >= half_T) n_long += full, shortest = fminf(shortest, per);
+            if (tiles > 0.f && rest >= half_T) n_long += 1.f, shortest = fminf(shortest, rest);
+        }
+        n_long = wave_sum(n_long), shortest = -wave_max(-shortest);
+        if (lane == 0 && n_long > 0.f) atomicAdd(&s_long, (int)n_long), atomicMin(&s_shortest, (int)shortest);
         __syncthreads();
-        const float cost = ceilf((float)s_count[1][t] * (float)heads * (1.0f / 256.0f)) * (float)(size + kRoundTiles), best = -wave_max(-cost);
-        if (best < (float)r * (float)(T + kRoundTiles)) T = 64 + 3 * __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(cost == best));
+        // (no sequence leaves none: the longest chunk is T long)
+        const float least = fmaxf(((float)s_total + (float)s_count[0][T] * kRoundTiles) * per_cu, ceilf((float)s_long * per_cu) * ((float)s_shortest + kRoundTiles));
+        const float most = ceilf((float)s_count[1][t] * per_cu) * (float)(size + kRoundTiles), best = -wave_max(-most);
+        if (best < least) T = 64 + 3 * __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(most == best));
     }
     // chunks of every sequence and the slots they take: running sums, 64 sequences at a time
     if (wave == 0) {

@@ -5,8 +5,9 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+import attention_plan_model as model  # noqa: E402
 from paper_2511_16665_amd import binding as tlt  # noqa: E402
-from synth import random_block_table  # noqa: E402
+from synth import lognormal_contexts, random_block_table  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -26,6 +27,7 @@ def _run(Hq, Hkv, n, ctxs, check):
     print(f"attention chunks Hq={Hq} Hkv={Hkv} n={n} B={B} longest={lens.max()}", flush=True)
     assert tlt.attention(tlt.TLT_BF16, Hq, page, qkv, mask, kv, out, ws, 1) == 0
     torch.cuda.synchronize()
+    planned = ws[:16 + 8 * B].view(torch.int32).cpu().numpy()   # items, three words of padding, first slots, chunks of each sequence
     for b in check:
         c, G = int(lens[b]), Hq // Hkv
         pages = table[b, :(c + n + page - 1) // page].long()
@@ -39,6 +41,8 @@ def _run(Hq, Hkv, n, ctxs, check):
             got = out[b].float().view(n, Hkv, G, d)[:, h]
             # (P and the output are rounded to bf16: 2^-8 of the largest output)
             assert ((got - want).abs().max() <= 1e-2 * want.abs().max()).item(), (b, h)
+    assert planned[0] == planned[4 + B:].sum()
+    return planned[4 + B:]
 
 
 # one round of 130-tile chunks instead of three of 43; one of 103 instead of two of 51, with two short sequences; one of the longest size (256 tiles) instead of
@@ -53,3 +57,15 @@ def test_chunks_longer_than_64_tiles(heads, ctxs):
                                            (16, 2, 32, [8000]), (27, 1, 19, [8000])])
 def test_merge_of_many_chunks(Hq, Hkv, n, ctxs):
     _run(Hq, Hkv, n, ctxs, range(len(ctxs)))
+
+
+# lengths that differ (short chunks: the long ones would end later), alike ones (long chunks, of up to 256 tiles), a short sequence among alike ones
+@pytest.mark.parametrize("heads,ctxs,longer", [
+    (16, lognormal_contexts(15, 3846, 0.2, 15384, 256, 0), False), (8, lognormal_contexts(14, 8200, 0.8, 32768, 256, 0), False),
+    (4, [8191] * 64, True), (32, [8200] * 8, True), (6, [6500] * 38 + [1, 700], True), (16, [16383] * 15 + [64], True)])
+def test_planned_chunks(heads, ctxs, longer):
+    got = _run(heads, heads, 1, ctxs, [0])
+    tiles = model.tiles_of(ctxs, 1)
+    size = model.chunk_size(tiles, heads)
+    assert (size > 64) == longer
+    assert got.tolist() == model.counts(tiles, size).tolist()
