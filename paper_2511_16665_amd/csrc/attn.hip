@@ -415,8 +415,9 @@ constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the pla
 
 // One workgroup, so a chain of latencies: lengths are read once, and the counting, the search for the chunk size, the running
 // sums and the sort are spread over its threads (once per forward and drafter level; against one thread walking the sequences, in
-// a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.0, 64 sequences 20.9 -> 9.4, 11.6 with the counts of longer chunks; called by itself again and again,
-// everything warm, 1 to 6 sequences of 30 to 250 the same within 0.3 us).  A step of a scan is a trip through the LDS crossbar:
+// a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.0, 64 sequences 20.9 -> 9.4; called by itself again and again,
+// everything warm, 1 to 6 sequences of 30 to 250 the same within 0.3 us).  Lengths reach the counting 64 in one read and by lane from there, chunks are counted
+// by reciprocals, and sums meet in a wave before they are added up in LDS: 64 sequences 9.8 -> 7.8 us, 200 16.6 -> 14.2, with two sizes counted per thread.  A step of a scan is a trip through the LDS crossbar:
 // no scan has more of them than its length needs (0.5 us).
 __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ seq_len, int B, int n_region, int heads,
                                                    int max_items, AttnWork* __restrict__ work, int len_bound,
@@ -434,6 +435,8 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     auto total_of = [&](int b) { return b < kPlanCached ? s_len[b] : keys_of(b, seq_len[b]); };
     auto tiles_of = [&](int b) { return (total_of(b) + kKT - 1) / kKT; };
     auto slot_of = [&](int b) { return b < kPlanCached ? s_slot[b] : slot0[b]; };
+    // ceil(tiles / t) by the reciprocal: (tiles - 1/2) / t is 1 / 2t or more from a whole number, its error below 2^21 tiles less than that
+    auto chunks_of = [](int tiles, int t, float inv) { return tiles < 1 << 21 ? (int)ceilf(((float)tiles - 0.5f) * inv) : (tiles - 1) / t + 1; };
     if (tid < 66) s_hist[tid] = 0;
     if (tid < 130) ((int*)s_count)[tid] = 0;
     if (tid == 0) s_total = s_long = 0, s_shortest = 0x7fffffff;
@@ -447,7 +450,8 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         // part of its context, which only the device can see
         if (status && len > len_bound) atomicOr(status, 1u);
     }
-    if (mine) atomicAdd(&s_total, mine);
+    mine = __float_as_int(wave_all(__int_as_float(mine), [](float x, float y) { return __int_as_float(__float_as_int(x) + __float_as_int(y)); }));
+    if (lane == 0 && mine) atomicAdd(&s_total, mine);   // (an atomic of differing values is taken lane by lane)
     __syncthreads();
     // A workgroup takes a whole CU (248 VGPRs per wave, 134 KB of LDS), so the work items run in rounds of
     // 256.  Measured at the 7B benchmark shape (attention ms per step): one round of 256 items 4.02, two
@@ -460,13 +464,21 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     // together, and what a CU takes that has to run one of its chunks of at least T / 2 in every round.  64 sequences of 8192 with 1 / 23 / 48
     // query rows (4 kv heads), the whole call: three rounds of 43 tiles 188 / 267 / 392 us, one of 129 181 / 251 / 362.  Lengths that differ much keep the
     // short chunks, which fill their last round: 15 of 3846 on average, lognormal with 0.2, 16 kv heads, 82.2 us in two rounds of up to 35 tiles, 88.6
-    // in one of 73.  Thread (t, part) counts the items of a chunk size.
+    // in one of 73.  Thread (t, part) counts the items of two chunk sizes.
     {
-        const int t = (tid & 63) + 1;
-        int64_t items_t = 0;
-        if (t >= kMinTiles)
-            for (int b = wave; b < B; b += 4) items_t += (tiles_of(b) + t - 1) / t;
+        const int t = lane + 1, size = 64 + 3 * t;   // 1 .. 64 and 67 .. 256
+        const float inv_t = 1.0f / (float)t, inv_size = 1.0f / (float)size;
+        int64_t items_t = 0, items_l = 0;
+        for (int b0 = 0; b0 < B; b0 += 64) {
+            const int many = min(B - b0, 64), tiles_l = lane < many ? tiles_of(b0 + lane) : 0;   // 64 lengths in one read
+            for (int i = wave; i < many; i += 4) {
+                const int tiles = __builtin_amdgcn_readlane(tiles_l, i);
+                items_t += chunks_of(tiles, t, inv_t);
+                items_l += chunks_of(tiles, size, inv_size);
+            }
+        }
         atomicAdd(&s_count[0][t], (int)(items_t < 0x7fffffff / 256 ? items_t : 0x7fffffff / 256));
+        atomicAdd(&s_count[1][t], (int)(items_l < 0x7fffffff / 256 ? items_l : 0x7fffffff / 256));
     }
     __syncthreads();
     int T, r;
@@ -478,12 +490,9 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         r = max(__builtin_amdgcn_readlane(rounds_t, 63), rounds0);
         T = __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(rounds_t <= r));   // lane t - 1 stands for t
     }
-    if (r > 1) {   // (uniform.  The counts are in floating point: a round more or less in an estimate, and never more items than with 64 tiles)
-        const int t = (tid & 63) + 1, size = 64 + 3 * t;   // 67 .. 256
-        const float inv = 1.0f / (float)size, per_cu = (float)heads * (1.0f / 256.0f);
-        float items_l = 0.f;
-        for (int b = wave; b < B; b += 4) items_l += ceilf((float)tiles_of(b) * inv);
-        atomicAdd(&s_count[1][t], (int)fminf(items_l, (float)(0x7fffffff / 256)));
+    if (r > 1) {   // (uniform)
+        const int t = lane + 1, size = 64 + 3 * t;
+        const float per_cu = (float)heads * (1.0f / 256.0f);
         float n_long = 0.f, shortest = 1e9f;   // chunks of at least T / 2 and the shortest of them
         const float inv_T = __builtin_amdgcn_rcpf((float)T), half_T = 0.5f * (float)T;
         for (int b = tid; b < B; b += 256) {

@@ -21,3 +21,13 @@ def test_longer_chunks_never_end_later(spread):
             for cost in (3, 4, 6):   # what an item costs besides its tiles, with one to three row tiles per wave
                 assert model.span(tiles, size, heads, cost) <= model.span(tiles, short, heads, cost), (lens.tolist(), heads, cost)
     assert switched
+
+
+def test_counts_by_reciprocal():
+    """The planner's chunk counts, ceil((tiles - 1/2) * (1 / size)) in fp32, are exact: all small counts, and next to multiples of the sizes up to 2^21 tiles."""
+    for size in list(range(4, 65)) + list(range(67, 257, 3)):
+        inv = np.float32(1) / np.float32(size)
+        multiples = np.arange(size, 1 << 21, size, dtype=np.int64)
+        for tiles in (np.arange(5000), multiples - 1, multiples, np.minimum(multiples + 1, (1 << 21) - 1)):
+            got = np.ceil((tiles.astype(np.float32) - np.float32(0.5)) * inv)
+            assert got.dtype == np.float32 and (got.astype(np.int64) == model.counts(tiles, size)).all(), size

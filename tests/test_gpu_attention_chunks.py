@@ -59,10 +59,12 @@ def test_merge_of_many_chunks(Hq, Hkv, n, ctxs):
     _run(Hq, Hkv, n, ctxs, range(len(ctxs)))
 
 
-# lengths that differ (short chunks: the long ones would end later), alike ones (long chunks, of up to 256 tiles), a short sequence among alike ones
+# lengths that differ (short chunks: the long ones would end later), alike ones (long chunks, of up to 256 tiles), a short sequence among alike ones; 1267 tiles
+# are seven chunks of 181, an eighth would cost a round
 @pytest.mark.parametrize("heads,ctxs,longer", [
     (16, lognormal_contexts(15, 3846, 0.2, 15384, 256, 0), False), (8, lognormal_contexts(14, 8200, 0.8, 32768, 256, 0), False),
-    (4, [8191] * 64, True), (32, [8200] * 8, True), (6, [6500] * 38 + [1, 700], True), (16, [16383] * 15 + [64], True)])
+    (4, [8191] * 64, True), (32, [8200] * 8, True), (6, [6500] * 38 + [1, 700], True), (16, [16383] * 15 + [64], True),
+    (1, [1267 * 64 - 1] * 35 + [367 * 64 - 1], True)])
 def test_planned_chunks(heads, ctxs, longer):
     got = _run(heads, heads, 1, ctxs, [0])
     tiles = model.tiles_of(ctxs, 1)
