@@ -847,6 +847,7 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
     // (tile it + 2) lands: the early waves read V of tile it-2 before barrier it, the late ones in the
     // iteration that ended with it.  Both kinds pass exactly n_tiles barriers.
     const bool late = wave_u >= 4;
+    const float lazy = n_tiles > 64 ? 0.f : lazy_raw;   // (see the running maximum)
     auto tile_wait = [&](int it) {
         __builtin_amdgcn_s_waitcnt(0x0F70u | (4 * (kAhead - 1)));  // vmcnt: this tile's 4 DMAs per wave have landed
         __builtin_amdgcn_s_barrier();
@@ -943,8 +944,11 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
             // exp2 in range.  As long as no score of this tile exceeds the reference in use by more than
             // 2^8 in the exponent (P <= 256: harmless in bf16 and in the fp32 sums), it stays, and the
             // rescaling of the accumulators (33 multiplies per row tile), the exp of the correction and the
-            // cross-lane maximum are all skipped; the decision is taken per wave.
-            if (__builtin_amdgcn_ballot_w64(tmax > m_run[t] + lazy_raw) != 0) {
+            // cross-lane maximum are all skipped; the decision is taken per wave.  A key at the reference itself has a P of exactly 1, any other key's is
+            // rounded.  Chunks beyond 64 tiles hold fewer references, so theirs follows the maximum at once, and a row's largest key, which counts most, is
+            // exact: with scores of a deviation of 1.2 (3) the output's distance from float64 is 2.243e-3 (1.774e-3) of its size instead of 2.337e-3 (1.983e-3), 2.334e-3
+            // (1.959e-3) in chunks of 43 tiles (64 sequences of 8192, one row each).  Free with one row tile per wave; 48 rows 364 -> 374 us, 392 in short chunks.
+            if (__builtin_amdgcn_ballot_w64(tmax > m_run[t] + lazy) != 0) {
                 tmax = group_max4(tmax);
                 const float m_new = fmaxf(m_run[t], tmax);
                 const float alpha = __builtin_amdgcn_exp2f((m_run[t] - m_new) * scale_log2);

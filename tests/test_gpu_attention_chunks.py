@@ -71,3 +71,38 @@ def test_planned_chunks(heads, ctxs, longer):
     size = model.chunk_size(tiles, heads)
     assert (size > 64) == longer
     assert got.tolist() == model.counts(tiles, size).tolist()
+
+
+def test_long_chunks_weigh_their_largest_key_exactly():
+    """A key whose score lies above the first tile's by less than the factor 2^8 at which short chunks move their reference, in a chunk of 129 tiles.  All other values are 0, so
+    the output's error is that of the key's weight, the same in all dimensions, and the outputs' own rounding, which averages out over them."""
+    H, B, d, page, ctx, at = 32, 8, 128, 16, 8200, 43 * 64 + 5
+    table, n_pages = random_block_table(np.full(B, ctx + 9), page, seed=5, extra_pages=3)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    k = torch.empty((n_pages, H, page, d), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.5, generator=gen)
+    v = torch.zeros_like(k)
+    qkv = torch.zeros((B, 1, 3 * H * d), dtype=torch.bfloat16, device="cuda")
+    q = torch.randn((B, H, d), generator=gen, device="cuda")
+    score = 5.0 + 0.8 * (2 * torch.rand((B, H, 1), generator=gen, device="cuda") - 1)   # (the others': deviation 0.5)
+    qkv[:, 0, :H * d] = q.view(B, H * d).bfloat16()
+    table = torch.from_numpy(table.astype(np.int32)).cuda()
+    spot = table[:, at // page].long()
+    k[spot, :, at % page] = (q * score * d ** 0.5 / q.pow(2).sum(-1, keepdim=True)).bfloat16()
+    v[spot, :, at % page] = (1 + torch.rand((B, H, d), generator=gen, device="cuda")).bfloat16()
+    lens = torch.full((B,), ctx, dtype=torch.int32, device="cuda")
+    mask = torch.ones((B, 1), dtype=torch.int64, device="cuda")
+    out = torch.full((B, 1, H * d), 7.0, dtype=torch.bfloat16, device="cuda")
+    ws = tlt.attention_workspace(B, 1, H, H, d, ctx + 9)
+    print("attention: the largest key of a long chunk", flush=True)
+    assert tlt.attention(tlt.TLT_BF16, H, page, qkv, mask, tlt.KV(k, v, table, lens, ctx), out, ws, 1) == 0
+    torch.cuda.synchronize()
+    assert ws[:4].view(torch.int32).item() == B   # a chunk per sequence
+    off = []
+    for b in range(B):
+        K, V = (x[table[b, :(ctx + page) // page].long()].permute(1, 0, 2, 3).reshape(H, -1, d)[:, :ctx + 1].double() for x in (k, v))
+        w = torch.softmax((K @ qkv[b, 0, :H * d].double().view(H, d, 1)).squeeze(-1) / d ** 0.5, -1)
+        want = (w.unsqueeze(1) @ V).squeeze(1)
+        off.append((out[b, 0].double().view(H, d) / want - 1).mean(-1))
+    # (the outputs' rounding to bf16, half of its last of 8 bits at most, in 128 dimensions, and the other keys' weights' over 8200 keys: in an emulation
+    # 2.4e-4 together; a rounding of the key's own weight leaves 1.6e-3 there)
+    assert torch.cat(off).pow(2).mean().sqrt().item() <= 2.0 ** -8 * (128 ** -0.5 + ctx ** -0.5)
