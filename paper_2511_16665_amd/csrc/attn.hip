@@ -529,7 +529,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         if (lane == 0) work->n_items = s_items = acc;   // cannot exceed the bound when seq_len respects the host's
     }
     __syncthreads();
-    // counting sort by tile count, longest first, a thread per item: the sequence is the last one whose slots start at or
+    // counting sort by tile count (beyond T = 64 by 64ths of T, up to four counts in a bin), longest first, a thread per item: the sequence is the last one whose slots start at or
     // before it (one without chunks starts where the next one does)
     struct Chunk { int b, kb, tiles; };
     auto chunk_of = [&](int i) {
@@ -545,7 +545,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     const int n_items = s_items;
     for (int i = tid; i < n_items; i += 256) atomicAdd(&s_hist[bin_of(chunk_of(i).tiles)], 1);
     __syncthreads();
-    if (wave == 0) {   // s_pos[t] = items longer than t
+    if (wave == 0) {   // s_pos[t] = items in bins above t
         const int h = s_hist[64 - lane];
         int sum = h;
         for (int o = 1; o < min(T, 64); o <<= 1) {   // (no bin is beyond min(T, 64): the lanes before hold zeros)
@@ -1018,20 +1018,24 @@ __global__ __launch_bounds__(512) void attn_mfma_k(const AttnWork* __restrict__ 
 #undef TLT_BODY
 }
 
-// The chunks' partial outputs merged (running max in raw score units), in chunk order, by one of two kernels.
+// The chunks' partial outputs merged (running max in raw score units), added up in chunk order, by one of two kernels.
 // With few rows in all (plain decoding, small batches) a wave's chunks, one load latency each, are the whole kernel: one wave per (b, kv head,
 // row), four rows per workgroup; the lanes read a chunk's maximum and sum each, and the outputs of 16 chunks are requested together (on the 17
 // chunks that one sequence of 8192 had at 8 tiles each: 12 us one after the other, 6.3 four at a time, 4.8 this way; on its 33 at 4 tiles
 // 6.1; 3 sequences x 23 nodes 7.3).
-// WPR: waves per row.  With four, a row's chunks are dealt over the waves of a workgroup in blocks of 16, so that up to 64 of them are one trip to memory
-// instead of four (attn_merge_wide); their sums meet in LDS.
+// WPR: waves per row.  With four, the waves of a workgroup fetch and weigh 16 chunks of a row each, so that 64 of them are one trip to memory instead of
+// four (attn_merge_wide); the first wave adds all of them up from LDS, in the same order as by itself: the same bits either way.  (Each wave adding up its own
+// and the four sums added instead: other bits, and 2 % longer or shorter for the whole call, 1 node of 8192 15.4 us, 8 nodes of 30000 25.3.)
 template <int WPR>
 __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __restrict__ work, const float* __restrict__ part_o,
                                                      const float* __restrict__ part_ml, uint16_t* __restrict__ out, int n_seq, int n,
                                                      int n_q_heads, int n_kv, int max_items, int r_pad, float scale_log2,
                                                      const int32_t* __restrict__ n_valid) {
     static_assert(WPR == 1 || WPR == 4, "a wave or a workgroup per row");
-    const int wave = threadIdx.x >> 6, r = WPR == 1 ? blockIdx.x * 4 + wave : blockIdx.x, kh = blockIdx.y, b = blockIdx.z, lane = threadIdx.x & 63;
+    constexpr int U = 16;
+    __shared__ float2 s_v[WPR > 1 ? U * (WPR - 1) : 1][64];   // the other waves' weighted outputs
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), part = WPR == 1 ? 0 : wave, lane = threadIdx.x & 63;
+    const int r = WPR == 1 ? blockIdx.x * 4 + wave : blockIdx.x, kh = blockIdx.y, b = blockIdx.z;
     const int G = n_q_heads / n_kv;
     if (r >= n * G) return;  // wave-uniform (with four waves per row there are as many workgroups as rows)
     const int i = r / G, gq = r - i * G;
@@ -1042,67 +1046,71 @@ __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __rest
     int used = slot0[n_seq + b];
     if (first + used > max_items) used = max(max_items - first, 0);
     if (i >= nv || used <= 0) {   // (uniform over a row's waves)
-        if (WPR == 1 || wave == 0) o[lane] = 0u;
+        if (part == 0) o[lane] = 0u;
         return;
     }
+    if (part > 0 && used <= U) return;   // (the first wave alone: it meets no barrier below either)
     const int64_t pbase = ((int64_t)first * n_kv + kh) * r_pad + r;
     const int64_t pstride = (int64_t)n_kv * r_pad;
-    float M = kNegBig;
+    float2 ml = make_float2(kNegBig, 0.f), v[U];   // lane c: chunk c's (maximum, sum)
+    auto fetch = [&](int c) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            v[u] = c + u < used ? *(const float2*)(part_o + (pbase + (c + u) * pstride) * kD + lane * 2) : make_float2(0.f, 0.f);
+    };
+    if (lane < used) ml = *(const float2*)(part_ml + (pbase + lane * pstride) * 2);
+    fetch(U * part);
+    float M = ml.x;
+    for (int c = lane + 64; c < used; c += 64) M = fmaxf(M, part_ml[(pbase + c * pstride) * 2]);
+    M = wave_max(M);
+    float w_lane = exp2f((ml.x - M) * scale_log2), l_lane = ml.y * w_lane;
     float a0 = 0.f, a1 = 0.f, L = 0.f;
-    {
-        constexpr int U = 16;
-        const int c_first = WPR == 1 ? 0 : U * __builtin_amdgcn_readfirstlane(wave);
-        float2 ml = make_float2(kNegBig, 0.f), v[U];   // lane c: chunk c's (maximum, sum)
-        auto fetch = [&](int c0) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                v[u] = c0 + u < used ? *(const float2*)(part_o + (pbase + (c0 + u) * pstride) * kD + lane * 2) : make_float2(0.f, 0.f);
-        };
-        if (lane < used) ml = *(const float2*)(part_ml + (pbase + lane * pstride) * 2);
-        fetch(c_first);
-        M = ml.x;
-        for (int c = lane + 64; c < used; c += 64) M = fmaxf(M, part_ml[(pbase + c * pstride) * 2]);
-        M = wave_max(M);
-        float w_lane = exp2f((ml.x - M) * scale_log2);
-        for (int c0 = c_first; c0 < used; c0 += U * WPR) {
-            if (c0 > c_first) fetch(c0);
-            if (c0 > c_first && (WPR > 1 || (c0 & 63) == 0)) {   // the next 64 chunks' maxima and sums
-                const int m0 = c0 & ~63;
-                ml = m0 + lane < used ? *(const float2*)(part_ml + (pbase + (m0 + lane) * pstride) * 2) : make_float2(kNegBig, 0.f);
-                w_lane = exp2f((ml.x - M) * scale_log2);
+    auto add = [&](int c, float2 x) {
+        L += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l_lane), c & 63));
+        a0 += x.x;
+        a1 += x.y;
+    };
+    for (int c0 = 0; c0 < used; c0 += U * WPR) {   // (uniform over a row's waves)
+        const int c = c0 + U * part;
+        if (c0 > 0) {
+            if (WPR > 1) __syncthreads();   // (s_v has been read)
+            fetch(c);
+            if ((c0 & 63) == 0) {
+                ml = c0 + lane < used ? *(const float2*)(part_ml + (pbase + (c0 + lane) * pstride) * 2) : make_float2(kNegBig, 0.f);
+                w_lane = exp2f((ml.x - M) * scale_log2), l_lane = ml.y * w_lane;
             }
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (c0 + u < used) {   // wave-uniform
-                    const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_lane), (c0 + u) & 63));
-                    L += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ml.y), (c0 + u) & 63)) * w;
-                    a0 += v[u].x * w;
-                    a1 += v[u].y * w;
+        for (int u = 0; u < U; ++u)
+            if (c + u < used) {   // wave-uniform
+                const float w = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w_lane), (c + u) & 63));
+                v[u] = make_float2(v[u].x * w, v[u].y * w);
+                if (part == 0) add(c + u, v[u]);
+            }
+        if (WPR > 1 && used > U) {
+            if (part > 0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) s_v[U * (part - 1) + u][lane] = v[u];
+            }
+            __syncthreads();
+            if (part == 0)
+                for (int g = U; g < min(U * WPR, used - c0); g += U) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) v[u] = s_v[g - U + u][lane];
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (c0 + g + u < used) add(c0 + g + u, v[u]);
                 }
-            }
         }
     }
-    if constexpr (WPR > 1) {   // the waves' sums, in their order
-        __shared__ float2 s_a[WPR][64];
-        __shared__ float s_l[WPR];
-        s_a[wave][lane] = make_float2(a0, a1);
-        if (lane == 0) s_l[wave] = L;
-        __syncthreads();
-        if (wave != 0) return;
-#pragma unroll
-        for (int w = 1; w < WPR; ++w) {
-            a0 += s_a[w][lane].x;
-            a1 += s_a[w][lane].y;
-            L += s_l[w];
-        }
-    }
+    if (part > 0) return;
     const float inv = L > 0.f ? 1.0f / L : 0.f;
     o[lane] = pack_bf16x2(a0 * inv, a1 * inv);
 }
 // Four waves per row from 17 chunks on (a second batch of 16), as long as the rows' workgroups are at most two per CU: behind that the waves that wait at the
-// barrier are missed elsewhere.  Whole attention call, us, one wave and four, 28 query and 4 kv heads: one sequence of 8192, 1 node 17.4/16.2, 8 nodes 20.1/18.4, 16 nodes
-// 23.9/22.6, 24 nodes (672 rows) 27.3/27.3, 64 nodes 35.7/36.7; of 30000, 8 nodes 27.6/24.4; 2 sequences, 8 nodes 21.7/21.4; 3 of 5000, 4 nodes 19.4/19.2, 23 nodes
-// (1932 rows) 31.6/33.0.  In a forward of one sequence the merge takes 4.4 us instead of 6.0.
+// barrier are missed elsewhere.  Whole attention call, us, one wave and four, 28 query and 4 kv heads: one sequence of 8192, 1 node 16.7/15.3, 8 nodes 19.5/17.9, 16 nodes
+// 23.6/22.4, 24 nodes (672 rows) 27.7/27.1, 48 nodes 37.6/38.3; of 30000, 8 nodes 27.6/25.8; 2 sequences, 8 nodes 22.1/21.1; 3 of 5000, 4 nodes 19.5/18.6, 23 nodes
+// (1932 rows) 31.9/33.0.
 constexpr int kMergeChunks = 17, kMergeRows = 512;
 static bool attn_merge_wide(const AttnPlan& p, int B, int rows, int bound_total) {
     // chunks that a sequence has on average: a round of items, fewer where they would be shorter than kMinTiles

@@ -59,6 +59,30 @@ def test_merge_of_many_chunks(Hq, Hkv, n, ctxs):
     _run(Hq, Hkv, n, ctxs, range(len(ctxs)))
 
 
+@pytest.mark.parametrize("ctxs", [[8192], [30000]])
+def test_one_and_four_waves_per_row_give_the_same_bits(ctxs):
+    """18 nodes of 28 heads are 504 rows, which four waves merge, 19 are 532.  Of a kv head's 7 rows per node, the first 16 nodes' fill seven row tiles, which hold
+    the same rows either way."""
+    Hq, Hkv, d, page, outs = 28, 4, 128, 16, []
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    lens = np.array(ctxs, dtype=np.int32)
+    table, n_pages = random_block_table(lens + 27, page, seed=5, extra_pages=3)
+    table = torch.from_numpy(table.astype(np.int32)).cuda()
+    k, v = (torch.empty((n_pages, Hkv, page, d), dtype=torch.bfloat16, device="cuda").normal_(0.0, 1.0, generator=gen) for _ in range(2))
+    qkv = (1.5 * torch.randn((1, 19, (Hq + 2 * Hkv) * d), generator=gen, device="cuda")).bfloat16()
+    mask = torch.tensor([[(2 << i) - 1 for i in range(19)]], dtype=torch.int64, device="cuda")
+    kv = tlt.KV(k, v, table, torch.from_numpy(lens).cuda(), int(lens.max()))
+    for n in (18, 19):
+        out = torch.full((1, n, Hq * d), 7.0, dtype=torch.bfloat16, device="cuda")
+        ws = tlt.attention_workspace(1, n, Hq, Hkv, d, int(lens.max()) + 27)
+        print(f"attention chunks merged, n={n} of {ctxs}", flush=True)
+        assert tlt.attention(tlt.TLT_BF16, Hq, page, qkv[:, :n].contiguous(), mask[:, :n].contiguous(), kv, out, ws, 1) == 0
+        torch.cuda.synchronize()
+        outs.append((out[:, :16], ws[20:24].view(torch.int32).item()))   # (the chunks)
+    assert outs[0][1] == outs[1][1] > 16
+    assert torch.equal(outs[0][0].view(torch.int16), outs[1][0].view(torch.int16))
+
+
 # lengths that differ (short chunks: the long ones would end later), alike ones (long chunks, of up to 256 tiles), a short sequence among alike ones; 1267 tiles
 # are seven chunks of 181, an eighth would cost a round
 @pytest.mark.parametrize("heads,ctxs,longer", [
