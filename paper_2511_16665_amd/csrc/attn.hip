@@ -1107,15 +1107,16 @@ __global__ __launch_bounds__(256) void attn_combine_few_k(const AttnWork* __rest
     const float inv = L > 0.f ? 1.0f / L : 0.f;
     o[lane] = pack_bf16x2(a0 * inv, a1 * inv);
 }
-// Four waves per row from 17 chunks on (a second batch of 16), as long as the rows' workgroups are at most two per CU: behind that the waves that wait at the
-// barrier are missed elsewhere.  Whole attention call, us, one wave and four, 28 query and 4 kv heads: one sequence of 8192, 1 node 16.7/15.3, 8 nodes 19.5/17.9, 16 nodes
-// 23.6/22.4, 24 nodes (672 rows) 27.7/27.1, 48 nodes 37.6/38.3; of 30000, 8 nodes 27.6/25.8; 2 sequences, 8 nodes 22.1/21.1; 3 of 5000, 4 nodes 19.5/18.6, 23 nodes
-// (1932 rows) 31.9/33.0.
+// Four waves per row where a sequence can have 17 chunks (a second batch of 16), as long as the rows' workgroups are at most two per CU: behind that the waves
+// that wait at the barrier are missed elsewhere.  It is the longest sequence that counts: its rows end last, and those of shorter ones are left to their first
+// wave.  Whole attention call, us, one wave and four, 28 query and 4 kv heads: one sequence of 8192, 1 node 16.7/15.3, 8 nodes 19.5/17.9, 16 nodes 23.6/22.4, 24 nodes
+// (672 rows) 27.7/27.1, 48 nodes 37.6/38.3; of 30000, 8 nodes 27.6/25.8; 2 sequences, 8 nodes 22.1/21.1; 3 of 5000, 4 nodes 19.5/18.6, 23 nodes (1932 rows) 31.9/33.0;
+// one of 30000 beside three of 1500, 1 node 25.7/23.5, beside fifteen of 600 28.3/26.1; where no sequence has 17, 4 of 8192, 1 node 21.1/21.2, 16 of 8192 52.3/51.8.
 constexpr int kMergeChunks = 17, kMergeRows = 512;
 static bool attn_merge_wide(const AttnPlan& p, int B, int rows, int bound_total) {
-    // chunks that a sequence has on average: a round of items, fewer where they would be shorter than kMinTiles
+    // chunks that the longest sequence has at most in one round of items: all of them, fewer where they would be shorter than kMinTiles
     const int per_round = (256 + p.heads - 1) / p.heads, tiles = (bound_total + kKT - 1) / kKT;
-    return rows <= kMergeRows && std::min((per_round + B - 1) / B, (tiles + kMinTiles - 1) / kMinTiles) >= kMergeChunks;
+    return rows <= kMergeRows && std::min(per_round, (tiles + kMinTiles - 1) / kMinTiles) >= kMergeChunks;
 }
 
 // With the chip full of waves, several rounds of them, a wave's load latency counts once per round: half a wave per row, 16 bytes per lane and

@@ -1,5 +1,5 @@
 """The cut of the cached keys into chunks, at sizes where a round of the chip decides: chunks beyond 64 tiles (few long rounds instead of several short ones),
-and the merge with four waves per row (17 chunks on, up to 512 rows)."""
+and the merge with four waves per row (where a sequence can have 17 chunks or more, up to 512 rows)."""
 import numpy as np
 import pytest
 
@@ -52,11 +52,12 @@ def test_chunks_longer_than_64_tiles(heads, ctxs):
     _run(heads, heads, 1, ctxs, [0, len(ctxs) - 3, len(ctxs) - 2, len(ctxs) - 1])
 
 
-# sequences of 16, 17 and 65 chunks of the shortest length and one of two; 512 and 513 rows (one row beyond the limit)
-@pytest.mark.parametrize("Hq,Hkv,n,ctxs", [(4, 4, 1, [64 * 64 - 1]), (4, 4, 1, [64 * 64]), (2, 1, 3, [64 * 260 - 3]), (4, 1, 2, [9000, 500]),
-                                           (16, 2, 32, [8000]), (27, 1, 19, [8000])])
-def test_merge_of_many_chunks(Hq, Hkv, n, ctxs):
-    _run(Hq, Hkv, n, ctxs, range(len(ctxs)))
+# sequences of 16, 17, 65 and 129 chunks of the shortest length, one of two, one long sequence among short ones; 512 and 513 rows (one row beyond the limit)
+@pytest.mark.parametrize("Hq,Hkv,n,ctxs,chunks", [
+    (4, 4, 1, [64 * 64 - 1], [16]), (4, 4, 1, [64 * 64], [17]), (2, 1, 3, [64 * 260 - 3], [65]), (1, 1, 1, [64 * 513 - 1], [129]), (4, 1, 2, [9000, 500], [36, 2]),
+    (28, 4, 1, [30000, 1500, 700, 0], [53, 3, 2, 1]), (16, 2, 32, [8000], [32]), (27, 1, 19, [8000], [32])])
+def test_merge_of_many_chunks(Hq, Hkv, n, ctxs, chunks):
+    assert _run(Hq, Hkv, n, ctxs, range(len(ctxs))).tolist() == chunks
 
 
 @pytest.mark.parametrize("ctxs", [[8192], [30000]])
