@@ -1,13 +1,18 @@
 """The cut of the cached keys into chunks, at sizes where a round of the chip decides: chunks beyond 64 tiles (few long rounds instead of several short ones),
 and the merge with four waves per row (where a sequence can have 17 chunks or more, up to 512 rows)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
 import attention_plan_model as model  # noqa: E402
+from gpu_util import check_draft_tree_against_forced_oracle, dense_cache, make_engine, make_models  # noqa: E402
+from oracle import decoder as dec  # noqa: E402
+from oracle import sd  # noqa: E402
 from paper_2511_16665_amd import binding as tlt  # noqa: E402
-from synth import lognormal_contexts, random_block_table  # noqa: E402
+from synth import MID, fill_kv_pool, lognormal_contexts, random_block_table  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -82,6 +87,49 @@ def test_one_and_four_waves_per_row_give_the_same_bits(ctxs):
         outs.append((out[:, :16], ws[20:24].view(torch.int32).item()))   # (the chunks)
     assert outs[0][1] == outs[1][1] > 16
     assert torch.equal(outs[0][0].view(torch.int16), outs[1][0].view(torch.int16))
+
+
+def test_four_waves_per_row_with_inactive_rows():
+    """The drafter's catch-up, whose rows beyond a sequence's new entries are inactive, all of them in a sequence without any, behind caches of 20 chunks: the trees
+    that come of it, against the oracle's drafter."""
+    cfg = dataclasses.replace(MID, name="mid-g7", n_q_heads=14, n_layers=1)
+    B, K, D, N, stride = 2, 3, 3, 8, 4
+    ctxs = np.array([5000, 3000], dtype=np.int32)
+    assert model.short_size(model.tiles_of(ctxs, 1), cfg.n_kv_heads)[0] == 4 and B * stride * cfg.n_q_heads <= 512
+    tw_dev, dw_dev, tw, dw = make_models(cfg, 5, "bf16", std=0.05)
+    cap = int(ctxs.max()) + 60
+    e, _, dtable = make_engine(cfg, "bf16", tw_dev, dw_dev, B, N, D, K, cap, seed=3, seq_len=ctxs)
+    dk, dv = fill_kv_pool(1, e.dkv.k_pool.shape[1], cfg.n_kv_heads, cfg.page_size, cfg.head_dim, 6, dtype=torch.bfloat16)
+    e.dkv.k_pool.copy_(dk)
+    e.dkv.v_pool.copy_(dv)
+    e.ctx.set_attention_impl(1)
+    e.dkv.seq_len_bound = int(ctxs.max())
+    rng = np.random.default_rng(1)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    states, last, lens = [], [0] * B, ctxs.copy()
+    for b, c in enumerate(ctxs):
+        st = sd.SeqState(cfg, cap, dec.round_to_bf16)
+        st.draft.k[:c], st.draft.v[:c] = dense_cache(dk, dtable, b, c, cfg.page_size)[0], dense_cache(dv, dtable, b, c, cfg.page_size)[0]
+        st.draft_len = int(c)
+        states.append(st)
+    for n_new in ([3, 1], [0, 2]):
+        n_new = np.array(n_new, dtype=np.int32)
+        tok, src = rng.integers(0, cfg.vocab, size=(B, stride)).astype(np.int32), rng.integers(0, 5, size=(B, stride)).astype(np.int32)
+        hidden, tree = rng.normal(size=(B, 5, cfg.hidden)).astype(np.float32), e.tree(N)
+        print(f"drafter behind long caches, new entries {n_new.tolist()}", flush=True)
+        e.ctx.draft_expand(B, D, K, N, dev(tok), dev(src), dev(n_new), dev(hidden), None, e.dkv, tree)
+        pool = [x.cpu().numpy() for x in e.ctx.draft_pool(B, D, K)]
+        e.dkv.seq_len_bound += stride
+        lens += n_new
+        np.testing.assert_array_equal(e.dkv.seq_len.cpu().numpy(), lens)
+        g_tree = [x.cpu().numpy() for x in (tree.token, tree.parent, tree.depth, tree.score)]
+        for b in range(B):
+            if n_new[b]:
+                toks = [int(t) for t in tok[b, :n_new[b]]]
+                sd.draft_extend(cfg, tw, dw, states[b], toks, hidden[b][src[b, :n_new[b]]].astype(np.float64))
+                last[b] = toks[-1]
+                check_draft_tree_against_forced_oracle(sd, cfg, tw, dw, states[b], last[b], K, D, N, tuple(x[b] for x in pool), tuple(x[b] for x in g_tree), 2e-2)
+    e.ctx.close()
 
 
 # lengths that differ (short chunks: the long ones would end later), alike ones (long chunks, of up to 256 tiles), a short sequence among alike ones; 1267 tiles
