@@ -358,12 +358,12 @@ constexpr int kAhead = 2;                   // tiles of K/V in flight; one more 
 constexpr int kStageElems = 2 * kKT * kD;   // one stage: K tile then V tile, 16 KB each
 constexpr float kNegBig = -1e30f;
 constexpr int kMaxRows = 128;    // rows per sequence whose visibility bits are kept in LDS
-constexpr int kMaxChunk = 16384; // keys per chunk: bounds the page-id table kept in LDS
+constexpr int kMaxChunk = 4096;  // keys per chunk: bounds the page-id table kept in LDS
 
 // Work decomposition.  A work item is (sequence, key range); each item is run by n_kv * row_groups
 // workgroups.  The key ranges are cut ON THE DEVICE from the actual sequence lengths (the host only
 // knows an upper bound): a one-workgroup planning kernel picks the item length so that the chip
-// gets whole rounds of items (kMinTiles .. 256 tiles of 64 keys), gives every sequence equally long chunks,
+// gets whole rounds of items (kMinTiles .. 64 tiles of 64 keys), gives every sequence equally long chunks,
 // and lists the items longest first.  Workgroups are dispatched in list order, so the long items
 // start first and the short ones fill the tail (longest-processing-time-first list scheduling).
 struct AttnItem {
@@ -394,8 +394,8 @@ static AttnPlan plan_attention(int B, int n, int G, int n_kv, int bound_total) {
     const int per_wave = (per_group + 7) / 8;
     p.tpw = per_wave <= 1 ? 1 : (per_wave <= 2 ? 2 : 3);
     p.heads = n_kv * p.row_groups;
-    // items <= sum_b ceil(tiles_b / T) <= total_tiles / T + B, and the planner picks no more rounds of 256 workgroups than
-    // T = 64 needs: items * heads <= 256 * ceil((total_tiles / 64 + B) * heads / 256)
+    // items <= sum_b ceil(tiles_b / T) <= total_tiles / T + B, and the planner picks T so that they fill
+    // whole rounds of 256 workgroups with T <= 64: items * heads <= 256 * ceil((total_tiles / 64 + B) * heads / 256)
     const int64_t tiles_bound = (int64_t)B * ((bound_total + kKT - 1) / kKT);
     const int64_t a = (256 + p.heads - 1) / p.heads, c = (tiles_bound + 63) / 64;
     p.max_items = 2 * B + (int)(a + c);
@@ -410,21 +410,19 @@ static size_t attn_work_bytes(int B, int max_items) {
 // result to the merge (one sequence of 8192, main + merging kernel: 8 tiles 11.1 + 4.8 us, 4 tiles 8.5 + 6.0, 3 and 2 tiles 8.4
 // + 6.5; three of 5000, 161 query rows: 22.1 + 5.9, 4 tiles 19.9 + 7.4).
 constexpr int kMinTiles = 4;
-constexpr int kRoundTiles = 4;      // what a round of items costs besides its tiles (attn_plan_k)
 constexpr int kPlanCached = 4096;   // sequences whose lengths and slots the planning kernel keeps in LDS
 
 // One workgroup, so a chain of latencies: lengths are read once, and the counting, the search for the chunk size, the running
 // sums and the sort are spread over its threads (once per forward and drafter level; against one thread walking the sequences, in
 // a forward: 1 sequence of 8192 7.2 -> 4.6 us, 16 sequences 9.1 -> 6.0, 64 sequences 20.9 -> 9.4; called by itself again and again,
-// everything warm, 1 to 6 sequences of 30 to 250 the same within 0.3 us).  Lengths reach the counting 64 in one read and by lane from there, chunks are counted
-// by reciprocals, and sums meet in a wave before they are added up in LDS: 64 sequences 9.8 -> 7.8 us, 200 16.6 -> 14.2, with two sizes counted per thread.  A step of a scan is a trip through the LDS crossbar:
+// everything warm, 1 to 6 sequences of 30 to 250 the same within 0.3 us).  A step of a scan is a trip through the LDS crossbar:
 // no scan has more of them than its length needs (0.5 us).
 __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ seq_len, int B, int n_region, int heads,
                                                    int max_items, AttnWork* __restrict__ work, int len_bound,
                                                    unsigned int* __restrict__ status, const int32_t* __restrict__ block_table,
                                                    int max_pages, int64_t n_pages, const int32_t* __restrict__ n_valid) {
     extern __shared__ int s_len[];   // [min(B, kPlanCached)] keys of a sequence, then as many first slots
-    __shared__ int s_total, s_items, s_shortest, s_long, s_hist[66], s_pos[66], s_count[2][65];
+    __shared__ int s_total, s_items, s_hist[66], s_pos[66], s_count[65];
     int* slot0 = (int*)(work + 1);
     int* nch = slot0 + B;
     AttnItem* items = (AttnItem*)(nch + B);
@@ -435,11 +433,9 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
     auto total_of = [&](int b) { return b < kPlanCached ? s_len[b] : keys_of(b, seq_len[b]); };
     auto tiles_of = [&](int b) { return (total_of(b) + kKT - 1) / kKT; };
     auto slot_of = [&](int b) { return b < kPlanCached ? s_slot[b] : slot0[b]; };
-    // ceil(tiles / t) by the reciprocal: (tiles - 1/2) / t is 1 / 2t or more from a whole number, its error below 2^21 tiles less than that
-    auto chunks_of = [](int tiles, int t, float inv) { return tiles < 1 << 21 ? (int)ceilf(((float)tiles - 0.5f) * inv) : (tiles - 1) / t + 1; };
     if (tid < 66) s_hist[tid] = 0;
-    if (tid < 130) ((int*)s_count)[tid] = 0;
-    if (tid == 0) s_total = s_long = 0, s_shortest = 0x7fffffff;
+    if (tid < 65) s_count[tid] = 0;
+    if (tid == 0) s_total = 0;
     __syncthreads();
     int mine = 0;
     for (int b = tid; b < B; b += 256) {
@@ -450,64 +446,29 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         // part of its context, which only the device can see
         if (status && len > len_bound) atomicOr(status, 1u);
     }
-    mine = __float_as_int(wave_all(__int_as_float(mine), [](float x, float y) { return __int_as_float(__float_as_int(x) + __float_as_int(y)); }));
-    if (lane == 0 && mine) atomicAdd(&s_total, mine);   // (an atomic of differing values is taken lane by lane)
+    if (mine) atomicAdd(&s_total, mine);
     __syncthreads();
-    // A workgroup takes a whole CU (248 VGPRs per wave, 134 KB of LDS), so the work items run in rounds of
+    // A workgroup takes a whole CU (248 VGPRs per wave, 131 KB of LDS), so the work items run in rounds of
     // 256.  Measured at the 7B benchmark shape (attention ms per step): one round of 256 items 4.02, two
     // rounds 4.33, four 4.20, and 4.6-4.8 when the count falls between whole rounds (384, 768 items): the
-    // fewest whole rounds that chunks of 64 tiles allow are the target, and of the chunk sizes that
-    // fit them the smallest (items closest to filling the rounds).  Longer chunks are taken where they are sure to end sooner.  A round
-    // costs its first fetches and its stores besides its tiles: 4.9 us of the attention kernel, 4 tile periods, with one query row per key; of the whole call
-    // 3.5 / 7.8 / 15 us with one / two / three row tiles per wave, whose periods are 1.25 / 1.8 / 2.6 us: with kRoundTiles for all of them the rule
-    // errs towards short chunks.  Long chunks take at most their rounds' number times the longest.  The short plan takes at least what it is for all CUs
-    // together, and what a CU takes that has to run one of its chunks of at least T / 2 in every round.  64 sequences of 8192 with 1 / 23 / 48
-    // query rows (4 kv heads), the whole call: three rounds of 43 tiles 188 / 267 / 392 us, one of 129 181 / 251 / 362.  Lengths that differ much keep the
-    // short chunks, which fill their last round: 15 of 3846 on average, lognormal with 0.2, 16 kv heads, 82.2 us in two rounds of up to 35 tiles, 88.6
-    // in one of 73.  Thread (t, part) counts the items of two chunk sizes.
+    // fewest whole rounds that the 64-tile cap on a chunk allows are the target, and of the chunk sizes that
+    // fit them the smallest (items closest to filling the rounds).  Thread (t, part) counts the items of chunk size t.
     {
-        const int t = lane + 1, size = 64 + 3 * t;   // 1 .. 64 and 67 .. 256
-        const float inv_t = 1.0f / (float)t, inv_size = 1.0f / (float)size;
-        int64_t items_t = 0, items_l = 0;
-        for (int b0 = 0; b0 < B; b0 += 64) {
-            const int many = min(B - b0, 64), tiles_l = lane < many ? tiles_of(b0 + lane) : 0;   // 64 lengths in one read
-            for (int i = wave; i < many; i += 4) {
-                const int tiles = __builtin_amdgcn_readlane(tiles_l, i);
-                items_t += chunks_of(tiles, t, inv_t);
-                items_l += chunks_of(tiles, size, inv_size);
-            }
-        }
-        atomicAdd(&s_count[0][t], (int)(items_t < 0x7fffffff / 256 ? items_t : 0x7fffffff / 256));
-        atomicAdd(&s_count[1][t], (int)(items_l < 0x7fffffff / 256 ? items_l : 0x7fffffff / 256));
+        const int t = (tid & 63) + 1;
+        int64_t items_t = 0;
+        if (t >= kMinTiles)
+            for (int b = wave; b < B; b += 4) items_t += (tiles_of(b) + t - 1) / t;
+        atomicAdd(&s_count[t], (int)(items_t < 0x7fffffff / 256 ? items_t : 0x7fffffff / 256));
     }
     __syncthreads();
-    int T, r;
+    int T;
     {
         const int t = lane + 1;
         const int rounds0 = (int)max(((int64_t)s_total * heads + 256 * 64 - 1) / (256 * 64), (int64_t)1);
-        const int rounds_t = t >= kMinTiles ? (int)(((int64_t)s_count[0][t] * heads + 255) / 256) : 0x7fffffff;
+        const int rounds_t = t >= kMinTiles ? (int)(((int64_t)s_count[t] * heads + 255) / 256) : 0x7fffffff;
         // (longer chunks never make more items: the fewest rounds are those of the longest)
-        r = max(__builtin_amdgcn_readlane(rounds_t, 63), rounds0);
+        const int r = max(__builtin_amdgcn_readlane(rounds_t, 63), rounds0);
         T = __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(rounds_t <= r));   // lane t - 1 stands for t
-    }
-    if (r > 1) {   // (uniform)
-        const int t = lane + 1, size = 64 + 3 * t;
-        const float per_cu = (float)heads * (1.0f / 256.0f);
-        float n_long = 0.f, shortest = 1e9f;   // chunks of at least T / 2 and the shortest of them
-        const float inv_T = __builtin_amdgcn_rcpf((float)T), half_T = 0.5f * (float)T;
-        for (int b = tid; b < B; b += 256) {
-            const float tiles = (float)tiles_of(b), k = ceilf((tiles - 0.5f) * inv_T), per = ceilf((tiles - 0.5f) * __builtin_amdgcn_rcpf(k));
-            const float full = floorf((tiles + 0.5f) * __builtin_amdgcn_rcpf(per)), rest = tiles - full * per;
-            if (tiles > 0.f && per >= half_T) n_long += full, shortest = fminf(shortest, per);
-            if (tiles > 0.f && rest >= half_T) n_long += 1.f, shortest = fminf(shortest, rest);
-        }
-        n_long = wave_sum(n_long), shortest = -wave_max(-shortest);
-        if (lane == 0 && n_long > 0.f) atomicAdd(&s_long, (int)n_long), atomicMin(&s_shortest, (int)shortest);
-        __syncthreads();
-        // (no sequence leaves none: the longest chunk is T long)
-        const float least = fmaxf(((float)s_total + (float)s_count[0][T] * kRoundTiles) * per_cu, ceilf((float)s_long * per_cu) * ((float)s_shortest + kRoundTiles));
-        const float most = ceilf((float)s_count[1][t] * per_cu) * (float)(size + kRoundTiles), best = -wave_max(-most);
-        if (best < least) T = 64 + 3 * __ffsll((unsigned long long)__builtin_amdgcn_ballot_w64(most == best));
     }
     // chunks of every sequence and the slots they take: running sums, 64 sequences at a time
     if (wave == 0) {
@@ -529,7 +490,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         if (lane == 0) work->n_items = s_items = acc;   // cannot exceed the bound when seq_len respects the host's
     }
     __syncthreads();
-    // counting sort by tile count (beyond T = 64 by 64ths of T, up to four counts in a bin), longest first, a thread per item: the sequence is the last one whose slots start at or
+    // counting sort by tile count, longest first, a thread per item: the sequence is the last one whose slots start at or
     // before it (one without chunks starts where the next one does)
     struct Chunk { int b, kb, tiles; };
     auto chunk_of = [&](int i) {
@@ -541,14 +502,13 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
         const int tiles = tiles_of(lo), k = (tiles + T - 1) / T, per = (tiles + k - 1) / k, first = (i - slot_of(lo)) * per;
         return Chunk{lo, first * kKT, max(min(per, tiles - first), 0)};
     };
-    auto bin_of = [&](int tiles) { return T <= 64 ? tiles : (tiles * 64 + T - 1) / T; };   // 0 .. 64
     const int n_items = s_items;
-    for (int i = tid; i < n_items; i += 256) atomicAdd(&s_hist[bin_of(chunk_of(i).tiles)], 1);
+    for (int i = tid; i < n_items; i += 256) atomicAdd(&s_hist[chunk_of(i).tiles], 1);
     __syncthreads();
-    if (wave == 0) {   // s_pos[t] = items in bins above t
+    if (wave == 0) {   // s_pos[t] = items longer than t
         const int h = s_hist[64 - lane];
         int sum = h;
-        for (int o = 1; o < min(T, 64); o <<= 1) {   // (no bin is beyond min(T, 64): the lanes before hold zeros)
+        for (int o = 1; o < T; o <<= 1) {   // (no chunk is longer than T: the lanes before T's hold zeros)
             const int up = __shfl_up(sum, o, 64);
             if (lane >= o) sum += up;
         }
@@ -566,7 +526,7 @@ __global__ __launch_bounds__(256) void attn_plan_k(const int32_t* __restrict__ s
             const int pg = lp < max_pages && lp * 16 < it.k_end ? block_table[(int64_t)c.b * max_pages + lp] : -1;
             it.page[q] = pg >= 0 && pg < n_pages ? pg : -1;
         }
-        items[atomicAdd(&s_pos[bin_of(c.tiles)], 1)] = it;
+        items[atomicAdd(&s_pos[c.tiles], 1)] = it;
     }
 }
 
@@ -847,7 +807,6 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
     // (tile it + 2) lands: the early waves read V of tile it-2 before barrier it, the late ones in the
     // iteration that ended with it.  Both kinds pass exactly n_tiles barriers.
     const bool late = wave_u >= 4;
-    const float lazy = n_tiles > 64 ? 0.f : lazy_raw;   // (see the running maximum)
     auto tile_wait = [&](int it) {
         __builtin_amdgcn_s_waitcnt(0x0F70u | (4 * (kAhead - 1)));  // vmcnt: this tile's 4 DMAs per wave have landed
         __builtin_amdgcn_s_barrier();
@@ -944,11 +903,8 @@ __device__ __forceinline__ void attn_body(const Rows& rows, const KVLayer& kv, c
             // exp2 in range.  As long as no score of this tile exceeds the reference in use by more than
             // 2^8 in the exponent (P <= 256: harmless in bf16 and in the fp32 sums), it stays, and the
             // rescaling of the accumulators (33 multiplies per row tile), the exp of the correction and the
-            // cross-lane maximum are all skipped; the decision is taken per wave.  A key at the reference itself has a P of exactly 1, any other key's is
-            // rounded.  Chunks beyond 64 tiles hold fewer references, so theirs follows the maximum at once, and a row's largest key, which counts most, is
-            // exact: with scores of a deviation of 1.2 (3) the output's distance from float64 is 2.243e-3 (1.774e-3) of its size instead of 2.337e-3 (1.983e-3), 2.334e-3
-            // (1.959e-3) in chunks of 43 tiles (64 sequences of 8192, one row each).  Free with one row tile per wave; 48 rows 364 -> 374 us, 392 in short chunks.
-            if (__builtin_amdgcn_ballot_w64(tmax > m_run[t] + lazy) != 0) {
+            // cross-lane maximum are all skipped; the decision is taken per wave.
+            if (__builtin_amdgcn_ballot_w64(tmax > m_run[t] + lazy_raw) != 0) {
                 tmax = group_max4(tmax);
                 const float m_new = fmaxf(m_run[t], tmax);
                 const float alpha = __builtin_amdgcn_exp2f((m_run[t] - m_new) * scale_log2);

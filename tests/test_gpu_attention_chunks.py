@@ -1,4 +1,4 @@
-"""The cut of the cached keys into chunks, at sizes where a round of the chip decides: chunks beyond 64 tiles (few long rounds instead of several short ones),
+"""The cut of the cached keys into chunks, at sizes where a round of the chip decides: the planner's lists against its rule,
 and the merge with four waves per row (where a sequence can have 17 chunks or more, up to 512 rows)."""
 import dataclasses
 
@@ -50,11 +50,14 @@ def _run(Hq, Hkv, n, ctxs, check):
     return planned[4 + B:]
 
 
-# one round of 130-tile chunks instead of three of 43; one of 103 instead of two of 51, with two short sequences; one of the longest size (256 tiles) instead of
-# four of 64, with one sequence a tile longer than that and two short ones
-@pytest.mark.parametrize("heads,ctxs", [(32, [8200] * 8), (6, [6500] * 38 + [1, 700]), (16, [16383] * 12 + [16400, 5000, 64])])
-def test_chunks_longer_than_64_tiles(heads, ctxs):
-    _run(heads, heads, 1, ctxs, [0, len(ctxs) - 3, len(ctxs) - 2, len(ctxs) - 1])
+# several rounds of items and one: equal lengths, single tiles and short sequences among them, lognormal ones, lengths at multiples of the chunk length
+@pytest.mark.parametrize("heads,ctxs", [
+    (32, [8200] * 8), (6, [6500] * 38 + [1, 700]), (16, [16383] * 12 + [16400, 5000, 64]), (16, lognormal_contexts(15, 3846, 0.2, 15384, 256, 0)),
+    (8, lognormal_contexts(14, 8200, 0.8, 32768, 256, 0)), (4, [8191] * 64), (16, [16383] * 15 + [64]), (1, [1267 * 64 - 1] * 35 + [367 * 64 - 1])])
+def test_planned_chunks(heads, ctxs):
+    tiles = model.tiles_of(ctxs, 1)
+    got = _run(heads, heads, 1, ctxs, [0, len(ctxs) - 3, len(ctxs) - 2, len(ctxs) - 1])
+    assert got.tolist() == model.counts(tiles, model.chunk_size(tiles, heads)).tolist()
 
 
 # sequences of 16, 17, 65 and 129 chunks of the shortest length, one of two, one long sequence among short ones; 512 and 513 rows (one row beyond the limit)
@@ -95,7 +98,7 @@ def test_four_waves_per_row_with_inactive_rows():
     cfg = dataclasses.replace(MID, name="mid-g7", n_q_heads=14, n_layers=1)
     B, K, D, N, stride = 2, 3, 3, 8, 4
     ctxs = np.array([5000, 3000], dtype=np.int32)
-    assert model.short_size(model.tiles_of(ctxs, 1), cfg.n_kv_heads)[0] == 4 and B * stride * cfg.n_q_heads <= 512
+    assert model.chunk_size(model.tiles_of(ctxs, 1), cfg.n_kv_heads) == 4 and B * stride * cfg.n_q_heads <= 512
     tw_dev, dw_dev, tw, dw = make_models(cfg, 5, "bf16", std=0.05)
     cap = int(ctxs.max()) + 60
     e, _, dtable = make_engine(cfg, "bf16", tw_dev, dw_dev, B, N, D, K, cap, seed=3, seq_len=ctxs)
@@ -130,52 +133,3 @@ def test_four_waves_per_row_with_inactive_rows():
                 last[b] = toks[-1]
                 check_draft_tree_against_forced_oracle(sd, cfg, tw, dw, states[b], last[b], K, D, N, tuple(x[b] for x in pool), tuple(x[b] for x in g_tree), 2e-2)
     e.ctx.close()
-
-
-# lengths that differ (short chunks: the long ones would end later), alike ones (long chunks, of up to 256 tiles), a short sequence among alike ones; 1267 tiles
-# are seven chunks of 181, an eighth would cost a round
-@pytest.mark.parametrize("heads,ctxs,longer", [
-    (16, lognormal_contexts(15, 3846, 0.2, 15384, 256, 0), False), (8, lognormal_contexts(14, 8200, 0.8, 32768, 256, 0), False),
-    (4, [8191] * 64, True), (32, [8200] * 8, True), (6, [6500] * 38 + [1, 700], True), (16, [16383] * 15 + [64], True),
-    (1, [1267 * 64 - 1] * 35 + [367 * 64 - 1], True)])
-def test_planned_chunks(heads, ctxs, longer):
-    got = _run(heads, heads, 1, ctxs, [0])
-    tiles = model.tiles_of(ctxs, 1)
-    size = model.chunk_size(tiles, heads)
-    assert (size > 64) == longer
-    assert got.tolist() == model.counts(tiles, size).tolist()
-
-
-def test_long_chunks_weigh_their_largest_key_exactly():
-    """A key whose score lies above the first tile's by less than the factor 2^8 at which short chunks move their reference, in a chunk of 129 tiles.  All other values are 0, so
-    the output's error is that of the key's weight, the same in all dimensions, and the outputs' own rounding, which averages out over them."""
-    H, B, d, page, ctx, at = 32, 8, 128, 16, 8200, 43 * 64 + 5
-    table, n_pages = random_block_table(np.full(B, ctx + 9), page, seed=5, extra_pages=3)
-    gen = torch.Generator(device="cuda").manual_seed(2)
-    k = torch.empty((n_pages, H, page, d), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.5, generator=gen)
-    v = torch.zeros_like(k)
-    qkv = torch.zeros((B, 1, 3 * H * d), dtype=torch.bfloat16, device="cuda")
-    q = torch.randn((B, H, d), generator=gen, device="cuda")
-    score = 5.0 + 0.8 * (2 * torch.rand((B, H, 1), generator=gen, device="cuda") - 1)   # (the others': deviation 0.5)
-    qkv[:, 0, :H * d] = q.view(B, H * d).bfloat16()
-    table = torch.from_numpy(table.astype(np.int32)).cuda()
-    spot = table[:, at // page].long()
-    k[spot, :, at % page] = (q * score * d ** 0.5 / q.pow(2).sum(-1, keepdim=True)).bfloat16()
-    v[spot, :, at % page] = (1 + torch.rand((B, H, d), generator=gen, device="cuda")).bfloat16()
-    lens = torch.full((B,), ctx, dtype=torch.int32, device="cuda")
-    mask = torch.ones((B, 1), dtype=torch.int64, device="cuda")
-    out = torch.full((B, 1, H * d), 7.0, dtype=torch.bfloat16, device="cuda")
-    ws = tlt.attention_workspace(B, 1, H, H, d, ctx + 9)
-    print("attention: the largest key of a long chunk", flush=True)
-    assert tlt.attention(tlt.TLT_BF16, H, page, qkv, mask, tlt.KV(k, v, table, lens, ctx), out, ws, 1) == 0
-    torch.cuda.synchronize()
-    assert ws[:4].view(torch.int32).item() == B   # a chunk per sequence
-    off = []
-    for b in range(B):
-        K, V = (x[table[b, :(ctx + page) // page].long()].permute(1, 0, 2, 3).reshape(H, -1, d)[:, :ctx + 1].double() for x in (k, v))
-        w = torch.softmax((K @ qkv[b, 0, :H * d].double().view(H, d, 1)).squeeze(-1) / d ** 0.5, -1)
-        want = (w.unsqueeze(1) @ V).squeeze(1)
-        off.append((out[b, 0].double().view(H, d) / want - 1).mean(-1))
-    # (the outputs' rounding to bf16, half of its last of 8 bits at most, in 128 dimensions, and the other keys' weights' over 8200 keys: in an emulation
-    # 2.4e-4 together; a rounding of the key's own weight leaves 1.6e-3 there)
-    assert torch.cat(off).pow(2).mean().sqrt().item() <= 2.0 ** -8 * (128 ** -0.5 + ctx ** -0.5)
